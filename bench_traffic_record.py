@@ -11,7 +11,8 @@ usage: python bench_traffic_record.py <dir>        (cfg2 .. cfg5, k = their larg
 Both counters are in KiB per dispatch; each is scaled by what the same counter reads for the plain 1 GiB device
 copy that --calibrate-copy adds to the run.  cfg2, cfg3: one launch is the whole backward pass.  cfg4, cfg5: the
 backward pass is many launches; the record adds up, per pass, the kernels of the backward pass (the output
-error, the chain products and their split finishes, the gradient products, the bias sums).  Every entry carries a
+error, the chain products and their split finishes, the gradient products, the bias sums; the direct kernels do
+all but the first in one launch per layer).  Every entry carries a
 hash of the sources of its kernels, and bench.py reports the figures only while that hash matches."""
 import collections
 import csv
@@ -33,7 +34,7 @@ def counter(path, name):
 
 
 PERSISTENT_SOURCES = ("persistent_kernels.hip", "persistent.h", "persistent_partition.h", "device_helpers.h")
-MINIBATCH_SOURCES = ("batched_kernels.hip", "b1_kernels.hip", "lf_internal.h", "device_helpers.h")
+MINIBATCH_SOURCES = ("batched_kernels.hip", "minibatch_kernels.h", "b1_kernels.hip", "lf_internal.h", "device_helpers.h")
 
 
 def source_hash(names):
@@ -49,10 +50,12 @@ def backward_part(kernel_name):
         return "output error (bp1)"
     if "k_bias_grad" in kernel_name:
         return "bias sums (bp3)"
+    if "k_backward_step" in kernel_name:
+        return "chain product with the gradients of the layer above (bp2)-(bp4)"
     if "k_grad_stream" in kernel_name:
         return "gradient product (bp4)"
     if "k_split_finish" in kernel_name:        # the chain's instance has epilogue 2 (sigma'), the forward's 1
-        return "chain split finish (bp2)" if re.search(r"Li2E|, 2>|,2>", kernel_name) else None
+        return "chain split finish (bp2)" if re.search(r"Li2E|<2>|, 2>|,2>", kernel_name) else None
     m = re.search(r"k_gemm\w*(<|I)", kernel_name)
     if m:
         demangled = re.search(r"<(?:float, |__bf16, )?(true|false), (true|false)", kernel_name)

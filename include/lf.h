@@ -83,7 +83,9 @@ typedef enum { LF_COST_QUADRATIC = 0, LF_COST_INT_RANGE = 0x7fffffff } lf_cost;
 
 /* How the k workers of section 3 are realised on the one GPU. */
 typedef enum {
-    LF_SCHED_AUTO = 0,        /* the library picks (persistent where supported) */
+    LF_SCHED_AUTO = 0,        /* the library picks: persistent where supported; for most minibatch nets one launch per
+                                 layer on the caller's stream, in which the gradients of layer l+1 ride beside the
+                                 chain step delta^{l+1} -> delta^l; else streams */
     LF_SCHED_STREAMS = 1,     /* chain on the caller's stream, k worker streams fed by per-layer events */
     LF_SCHED_PERSISTENT = 2,  /* one persistent kernel, k workgroup partitions fed by per-layer ready flags */
     LF_SCHED_REDUNDANT = 3,   /* Algorithm 1 as printed, for comparison: the parent (the caller's stream) walks
@@ -200,8 +202,8 @@ lf_status lf_backward_leapfrog(lf_net* net, const void* y, int k, void* hip_stre
 /* lf_backward_leapfrog for callers that cannot allocate: code that records the pass into a HIP graph on its
  * first call, tight serving loops, harnesses that forbid hipMalloc.  (lf_backward_leapfrog may create worker
  * streams and events, or pinned memory, the first time a handle runs with a new k or schedule.)  This call
- * allocates nothing, on the device or through any library: it enqueues the stream schedule's kernels -- chain
- * and gradient kernels of layer L, L-1, ..., 2 in that order -- on hip_stream alone, and the scratch of the chain
+ * allocates nothing, on the device or through any library: it enqueues the chain and gradient kernels of
+ * layer L, L-1, ..., 2 in that order on hip_stream alone, and the scratch of the chain
  * products (row-block partial sums at B = 1, split-K partials of a minibatch) is a static device array inside
  * the library instead of the caller's workspace.  Same arguments, same checks, same results bit for bit as
  * lf_backward_leapfrog with LF_SCHED_STREAMS (k only names the worker a layer would belong to; the gradients do

@@ -1,8 +1,6 @@
-// Minibatch (B > 1) kernels: the three per-layer contractions of the pass as LDS-tiled MFMA GEMMs.
-//
-//   forward (z),(a):  A_out[b][j] = sigma( sum_k A_in[b][k]  W[j][k]  + bias[j] )
-//   chain   (bp2):    D_l[b][k]   = ( sum_j D_next[b][j] W_next[j][k] ) * A_l[b][k] (1 - A_l[b][k])
-//   grads   (bp4):    nabla_w[j][k] = sum_b D[b][j] A_prev[b][k]        (bp3): nabla_b[j] = sum_b D[b][j]
+// Wide bf16 nets: the three per-layer contractions of the pass as LDS-tiled MFMA GEMMs whose workgroups fill a compute
+// unit, and the finish of a product that is split along its contraction; and the choice between these kernels and
+// those of minibatch_kernels.h, which serve all other minibatch nets.
 //
 // All three are  C[m][n] = sum_q P(m,q) Q(n,q)  with operands that are either contiguous along the
 // contraction index q ("QC": element (i,q) at p[i*ld + q]) or along their own index ("IC": element
@@ -10,33 +8,16 @@
 // grads: P = D (IC), Q = A_prev (IC).  Accumulation is fp32 in the MFMA accumulators, in an order fixed
 // by (N, B) alone, so results do not depend on k or on the launch.
 #include "lf_internal.h"
+#include "minibatch_kernels.h"
 
 namespace lf {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int BM = 128, BN = 128;          // output tile of a workgroup; 2 x 2 waves of 64 x 64
 
 __host__ __device__ constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 enum Epilogue { EPI_RAW = 0, EPI_SIGMOID = 1, EPI_SIGMA_PRIME = 2, EPI_GRAD = 3 };
-
-template <typename T> struct Tile;
-template <> struct Tile<float> {
-    static constexpr int BK = 32;
-    static constexpr int LDA = BM + 4;     // LDS is [q][i]: a lane reads one float per MFMA, lanes along i
-    static constexpr int ELEMS = BK * LDA;
-};
-template <> struct Tile<__bf16> {
-    static constexpr int BK = 64;
-    static constexpr int LDA = BK + 8;     // QC operand: LDS is [i][q], a lane reads 8 consecutive q (16 bytes)
-    static constexpr int LDI = BM + 32;    // IC operand: LDS is [q][i] as in memory; read with the transposing
-                                           // ds_read_b64_tr_b16, which hands each lane 4 consecutive q.  A half
-                                           // wave reads 4 rows x 64 bytes: with a row stride of 16 banks more than
-                                           // a multiple of 64 the four rows fill the 64 banks exactly (measured:
-                                           // no bank conflicts; +16 elements gave one conflict cycle in three)
-    static constexpr int ELEMS = BM * LDA > BK * LDI ? BM * LDA : BK * LDI;
-};
 
 struct GemmArgs {
     const void* P;  int ldp;               // rows of P index m
@@ -53,97 +34,10 @@ struct GemmArgs {
     float sgd_eta;                         // EPI_GRAD: != 0 = out holds w^l in fp32 and receives w - eta * C
 };
 
-// ---- global -> register staging ---------------------------------------------------------------
-// Each thread stages 4 x 16 bytes per operand and tile.  The operand is addressed as one buffer: a
-// vector that lies outside the matrix (row past the end, or past the contraction length) is given an
-// offset past the end of the buffer and loads zeros.  No branch surrounds a load, so the compiler can
-// count the loads in flight and the prefetch depth below is real.
+// Operands are addressed as one buffer each: a vector that lies outside the matrix (row past the end, or past the
+// contraction length) is given an offset past the end of the buffer and loads zeros.  No branch surrounds a load, so
+// the compiler can count the loads in flight.
 constexpr unsigned kOutside = 0xFFFFFFF0u;
-
-template <typename T, bool IC> struct Stage;
-
-template <> struct Stage<float, false> {   // [i][q], float4 along q; 8 threads cover 32 q of one row
-    v4f r[4];
-    __device__ void load(__amdgpu_buffer_rsrc_t buf, int ld, int i0, int q0, int I, int Kq) {
-        const int t = threadIdx.x, qv = (t & 7) * 4;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = (t >> 3) + 32 * u;
-            const bool ok = (i0 + i < I) && (q0 + qv < Kq);
-            const unsigned off = ((unsigned)(i0 + i) * (unsigned)ld + (unsigned)(q0 + qv)) * 4u;
-            r[u] = buffer_load_v4f(buf, ok ? off : kOutside);
-        }
-    }
-    __device__ void store(float* s) const {
-        const int t = threadIdx.x, qv = (t & 7) * 4;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = (t >> 3) + 32 * u;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) s[(qv + c) * Tile<float>::LDA + i] = r[u][c];
-        }
-    }
-};
-template <> struct Stage<float, true> {    // [q][i], float4 along i; 32 threads cover 128 i of one q
-    v4f r[4];
-    __device__ void load(__amdgpu_buffer_rsrc_t buf, int ld, int i0, int q0, int I, int Kq) {
-        const int t = threadIdx.x, iv = (t & 31) * 4;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int q = (t >> 5) + 8 * u;
-            const bool ok = (q0 + q < Kq) && (i0 + iv < I);
-            const unsigned off = ((unsigned)(q0 + q) * (unsigned)ld + (unsigned)(i0 + iv)) * 4u;
-            r[u] = buffer_load_v4f(buf, ok ? off : kOutside);
-        }
-    }
-    __device__ void store(float* s) const {
-        const int t = threadIdx.x, iv = (t & 31) * 4;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int q = (t >> 5) + 8 * u;
-            *reinterpret_cast<v4f*>(s + q * Tile<float>::LDA + iv) = r[u];
-        }
-    }
-};
-template <> struct Stage<__bf16, false> {  // [i][q], 8 bf16 along q; 8 threads cover 64 q of one row
-    v4f r[4];
-    __device__ void load(__amdgpu_buffer_rsrc_t buf, int ld, int i0, int q0, int I, int Kq) {
-        const int t = threadIdx.x, qv = (t & 7) * 8;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = (t >> 3) + 32 * u;
-            const bool ok = (i0 + i < I) && (q0 + qv < Kq);
-            const unsigned off = ((unsigned)(i0 + i) * (unsigned)ld + (unsigned)(q0 + qv)) * 2u;
-            r[u] = buffer_load_v4f(buf, ok ? off : kOutside);
-        }
-    }
-    __device__ void store(__bf16* s) const {
-        const int t = threadIdx.x, qv = (t & 7) * 8;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = (t >> 3) + 32 * u;
-            *reinterpret_cast<v4f*>(s + i * Tile<__bf16>::LDA + qv) = r[u];
-        }
-    }
-};
-template <> struct Stage<__bf16, true> {   // [q][i], 8 bf16 along i; 16 threads cover 128 i of one q
-    v4f r[4];
-    __device__ void load(__amdgpu_buffer_rsrc_t buf, int ld, int i0, int q0, int I, int Kq) {
-        const int t = threadIdx.x, iv = (t & 15) * 8;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int q = (t >> 4) * 4 + u;            // a thread holds 4 consecutive q of its 8 i
-            const bool ok = (q0 + q < Kq) && (i0 + iv < I);
-            const unsigned off = ((unsigned)(q0 + q) * (unsigned)ld + (unsigned)(i0 + iv)) * 2u;
-            r[u] = buffer_load_v4f(buf, ok ? off : kOutside);
-        }
-    }
-    __device__ void store(__bf16* s) const {   // LDS keeps the memory layout [q][i]
-        const int t = threadIdx.x, iv = (t & 15) * 8, q = (t >> 4) * 4;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) *reinterpret_cast<v4f*>(s + (q + u) * Tile<__bf16>::LDI + iv) = r[u];
-    }
-};
 
 // MFMA operand (8 consecutive q for row i = lane % 32, starting at q0 + 8 (lane / 32)) from an LDS tile kept
 // as [q][i].  ds_read_b64_tr_b16 works on groups of 16 lanes: source lane s supplies the address of four
@@ -162,174 +56,6 @@ __device__ __forceinline__ v8bf lds_operand_transposed(const __bf16* tile, int l
     const v8s both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(v8bf, both);
 }
-
-// ---- the kernel -------------------------------------------------------------------------------
-template <typename T, bool P_IC, bool Q_IC, int EPI>
-__global__ __launch_bounds__(kThreads) void k_gemm(const GemmArgs g) {
-    using TL = Tile<T>;
-    // one block: the two operand tiles, and afterwards the staging area of the gradient epilogue
-    constexpr int kOperandBytes = 2 * TL::ELEMS * (int)sizeof(T);
-    constexpr int kEpilogueBytes = 4 * 32 * (64 + 4) * 4;       // 4 waves x 32 rows x (64+4) floats
-    __shared__ __attribute__((aligned(16))) char s_block[kOperandBytes > kEpilogueBytes ? kOperandBytes : kEpilogueBytes];
-    T* s_p = reinterpret_cast<T*>(s_block);
-    T* s_q = s_p + TL::ELEMS;
-
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
-    const int r32 = lane & 31, half = lane >> 5;
-
-    const int kt_total = ceil_div(g.K, TL::BK);
-    const int kt_begin = blockIdx.z * g.k_tiles_per_split;
-    const int kt_end = min(kt_total, kt_begin + g.k_tiles_per_split);
-
-    v16f acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-
-    // Global -> register -> LDS with a prefetch distance of three k-tiles: tile kt+3 is requested while
-    // tile kt is multiplied, which covers the memory latency even when only one or two workgroups share
-    // a compute unit.  The three register stages rotate by a 3-way unrolled loop (static indexing).
-    Stage<T, P_IC> sp[3];
-    Stage<T, Q_IC> sq[3];
-    const __amdgpu_buffer_rsrc_t P = make_buffer(g.P, g.p_bytes);
-    const __amdgpu_buffer_rsrc_t Q = make_buffer(g.Q, g.q_bytes);
-#pragma unroll
-    for (int u = 0; u < 3; ++u)
-        if (kt_begin + u < kt_end) {
-            sp[u].load(P, g.ldp, m0, (kt_begin + u) * TL::BK, g.M, g.K);
-            sq[u].load(Q, g.ldq, n0, (kt_begin + u) * TL::BK, g.Nn, g.K);
-        }
-    __builtin_amdgcn_sched_barrier(0);   // keep the requests up here: the scheduler would sink them to their uses
-    auto multiply_tile = [&]() {
-        if constexpr (sizeof(T) == 4) {
-#pragma unroll
-            for (int kk = 0; kk < TL::BK; kk += 2) {
-                float a[2], b[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) a[i] = s_p[(kk + half) * TL::LDA + wm + i * 32 + r32];
-#pragma unroll
-                for (int j = 0; j < 2; ++j) b[j] = s_q[(kk + half) * TL::LDA + wn + j * 32 + r32];
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-            }
-        } else {
-#pragma unroll
-            for (int kk = 0; kk < TL::BK; kk += 16) {
-                v8bf a[2], b[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    if constexpr (P_IC) a[i] = lds_operand_transposed(s_p, TL::LDI, wm + i * 32, kk);
-                    else a[i] = *reinterpret_cast<const v8bf*>(&s_p[(wm + i * 32 + r32) * TL::LDA + kk + half * 8]);
-                }
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    if constexpr (Q_IC) b[j] = lds_operand_transposed(s_q, TL::LDI, wn + j * 32, kk);
-                    else b[j] = *reinterpret_cast<const v8bf*>(&s_q[(wn + j * 32 + r32) * TL::LDA + kk + half * 8]);
-                }
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-            }
-        }
-    };
-    for (int kt = kt_begin; kt < kt_end; kt += 3) {
-#pragma unroll
-        for (int u = 0; u < 3; ++u) {
-            if (kt + u < kt_end) {
-                sp[u].store(s_p);
-                sq[u].store(s_q);
-                __syncthreads();
-                if (kt + u + 3 < kt_end) {
-                    sp[u].load(P, g.ldp, m0, (kt + u + 3) * TL::BK, g.M, g.K);
-                    sq[u].load(Q, g.ldq, n0, (kt + u + 3) * TL::BK, g.Nn, g.K);
-                }
-                __builtin_amdgcn_sched_barrier(0);   // requests stay ahead of the multiplications
-                multiply_tile();
-                __syncthreads();
-            }
-        }
-    }
-
-    // Accumulator element e of lane (r32, half) in tile (i, j) is
-    // C[m0 + wm + 32 i + 8 (e/4) + 4 half + e%4][n0 + wn + 32 j + r32].
-    if constexpr (EPI == EPI_GRAD) {
-        // nabla_w is the one large output (N x N fp32): each wave turns its accumulators through a private
-        // LDS area so that a lane stores 16 contiguous bytes and a wave 4 rows x 256 contiguous bytes.
-        constexpr int LDE = 64 + 4;
-        float* stage = reinterpret_cast<float*>(s_block) + wave * 32 * LDE;
-        float* out = static_cast<float*>(g.out);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    stage[(8 * (e >> 2) + 4 * half + (e & 3)) * LDE + j * 32 + r32] = acc[i][j][e];
-            // the area is private to the wave: no barrier, LDS operations of a wave complete in order
-#pragma unroll
-            for (int it = 0; it < 8; ++it) {
-                const int row = 4 * it + (lane >> 4), c4 = (lane & 15) * 4;
-                const v4f v = *reinterpret_cast<const v4f*>(&stage[row * LDE + c4]);
-                const int m = m0 + wm + i * 32 + row, n = n0 + wn + c4;
-                if (m < g.M && n < g.Nn) {
-                    float* dst = out + (size_t)m * g.Nn + n;
-                    if (g.sgd_eta != 0.0f) {       // the descent step fused in: one more read of the same line
-                        const v4f w = *reinterpret_cast<const v4f*>(dst);
-                        const v4f o = {fmaf(-g.sgd_eta, v.x, w.x), fmaf(-g.sgd_eta, v.y, w.y),
-                                       fmaf(-g.sgd_eta, v.z, w.z), fmaf(-g.sgd_eta, v.w, w.w)};
-                        *reinterpret_cast<v4f*>(dst) = o;
-                        if (g.out_bf) {            // bfloat16 storage: the weights the next pass multiplies with
-                            const v4bf ob = {(__bf16)o.x, (__bf16)o.y, (__bf16)o.z, (__bf16)o.w};
-                            *reinterpret_cast<v4bf*>(static_cast<__bf16*>(g.out_bf) + (size_t)m * g.Nn + n) = ob;
-                        }
-                    } else {
-                        store_global_nt_v4f(dst, v);
-                    }
-                }
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int n = n0 + wn + j * 32 + r32;
-            if (n >= g.Nn) continue;
-            float bias = 0.0f;
-            if constexpr (EPI == EPI_SIGMOID) bias = g.bias[n];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int m = m0 + wm + i * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
-                if (m >= g.M) continue;
-                const size_t o = (size_t)m * g.Nn + n;
-                const float v = acc[i][j][e];
-                if constexpr (EPI == EPI_RAW) {
-                    g.raw[(size_t)blockIdx.z * g.M * g.Nn + o] = v;
-                } else if constexpr (EPI == EPI_SIGMOID) {
-                    static_cast<T*>(g.out)[o] = (T)sigmoidf(v + bias);
-                } else if constexpr (EPI == EPI_SIGMA_PRIME) {
-                    const float a = (float)static_cast<const T*>(g.act)[o];
-                    const float d = v * (a * (1.0f - a));
-                    static_cast<float*>(g.out)[o] = d;
-                    if constexpr (sizeof(T) == 2) static_cast<__bf16*>(g.out_bf)[o] = (__bf16)d;
-                } else {
-                    __builtin_nontemporal_store(v, static_cast<float*>(g.out) + o);
-                }
-            }
-        }
-}
-
 
 // ================================================================================================
 // bf16, large shapes: 256 x 256 tile, 512 threads
@@ -683,7 +409,6 @@ __global__ __launch_bounds__(kThreadsBig) void k_grad_stream(const GemmArgs g, i
     }
 }
 
-static_assert(TK == Tile<__bf16>::BK, "both bf16 kernels count k-tiles of the same length");
 static_assert(2 * 2 * ELEMS * 2 <= 160 * 1024, "LDS of one compute unit");
 }  // namespace big
 
@@ -894,37 +619,32 @@ static_assert(2 * (P_ELEMS + Q_ELEMS) * 2 <= 80 * 1024, "two workgroups' LDS fit
 }  // namespace half
 
 // Split-K second stage: sum the raw partials in split order, then the layer's epilogue.  A thread takes four
-// consecutive outputs (one row: every width is a multiple of 4), 16 bytes per load.
-template <typename T, int EPI>
-__global__ __launch_bounds__(kThreads) void k_split_finish(const float* __restrict__ raw, int splits,
-                                                           size_t count, int Nn,
-                                                           const float* __restrict__ bias,
-                                                           const T* __restrict__ act, void* out,
-                                                           __bf16* out_bf) {
+// consecutive outputs (one row: every width is a multiple of 8), 16 bytes per load.
+template <int EPI>
+__global__ __launch_bounds__(kThreads) void k_split_finish(const float* __restrict__ raw, int splits, size_t count,
+                                                           int Nn, const float* __restrict__ bias,
+                                                           const __bf16* __restrict__ act, void* out, __bf16* out_bf) {
     const size_t o = ((size_t)blockIdx.x * kThreads + threadIdx.x) * 4;
     if (o >= count) return;
     v4f v = *reinterpret_cast<const v4f*>(raw + o);
     for (int z = 1; z < splits; ++z) v += *reinterpret_cast<const v4f*>(raw + (size_t)z * count + o);
     if constexpr (EPI == EPI_SIGMOID) {
         const v4f bs = *reinterpret_cast<const v4f*>(bias + o % Nn);
-        typedef T v4t __attribute__((ext_vector_type(4)));
-        const v4t r = {(T)sigmoidf(v[0] + bs[0]), (T)sigmoidf(v[1] + bs[1]), (T)sigmoidf(v[2] + bs[2]),
-                       (T)sigmoidf(v[3] + bs[3])};
-        *reinterpret_cast<v4t*>(static_cast<T*>(out) + o) = r;
+        const v4bf r = {(__bf16)sigmoidf(v[0] + bs[0]), (__bf16)sigmoidf(v[1] + bs[1]), (__bf16)sigmoidf(v[2] + bs[2]),
+                        (__bf16)sigmoidf(v[3] + bs[3])};
+        *reinterpret_cast<v4bf*>(static_cast<__bf16*>(out) + o) = r;
     } else {
-        typedef T v4t __attribute__((ext_vector_type(4)));
-        const v4t av = *reinterpret_cast<const v4t*>(act + o);
+        const v4bf av = *reinterpret_cast<const v4bf*>(act + o);
         v4f d;
+        v4bf db;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const float a = (float)av[c];
             d[c] = v[c] * (a * (1.0f - a));
+            db[c] = (__bf16)d[c];
         }
         *reinterpret_cast<v4f*>(static_cast<float*>(out) + o) = d;
-        if constexpr (sizeof(T) == 2) {
-            const v4bf db = {(__bf16)d[0], (__bf16)d[1], (__bf16)d[2], (__bf16)d[3]};
-            *reinterpret_cast<v4bf*>(out_bf + o) = db;
-        }
+        *reinterpret_cast<v4bf*>(out_bf + o) = db;
     }
 }
 
@@ -957,19 +677,6 @@ __global__ __launch_bounds__(kThreads) void k_bias_grad(const float* __restrict_
         for (int q = 1; q < 8; ++q) t += s_part[q][c];
         nabla_b[j] = sgd_eta != 0.0f ? fmaf(-sgd_eta, t, nabla_b[j]) : t;
     }
-}
-
-template <typename T, bool P_IC, bool Q_IC, int EPI>
-hipError_t run(GemmArgs g, int splits, hipStream_t s) {
-    // operand sizes for the buffer addressing: P is (P_IC ? K x M : M x K), Q likewise with Nn
-    const unsigned long long pb = (unsigned long long)(P_IC ? g.K : g.M) * g.ldp * sizeof(T);
-    const unsigned long long qb = (unsigned long long)(Q_IC ? g.K : g.Nn) * g.ldq * sizeof(T);
-    if (pb >= 0xFFFFFFF0ull || qb >= 0xFFFFFFF0ull) return hipErrorInvalidValue;
-    g.p_bytes = (unsigned)pb;
-    g.q_bytes = (unsigned)qb;
-    const dim3 grid(ceil_div(g.Nn, BN), ceil_div(g.M, BM), splits);
-    k_gemm<T, P_IC, Q_IC, EPI><<<grid, kThreads, 0, s>>>(g);
-    return hipGetLastError();
 }
 
 template <bool P_IC, bool Q_IC, int EPI>
@@ -1011,10 +718,17 @@ hipError_t run_half(GemmArgs g, int splits, hipStream_t s) {
 
 }  // namespace
 
-// Which kernels a minibatch net takes, decided once per net from its widest layer.  bf16 nets whose forward
-// product has at least 64 tiles of 256 x 256 take the wide-net kernels: by default the 256 x 256-tile kernel for
-// all three products (measured faster than the 128 x 256 one, alone and beside each other).
-// How such a net shares the chip between the chain and the workers: a kernel of either kind fills every compute
+// Which kernels a minibatch net takes, decided once per net from its widest layer (N) and its storage type.
+// The direct kernels (minibatch_kernels.h) serve every fp32 net and bf16 nets of moderate size; wide bf16 nets take
+// the kernels of this file: by default the 256 x 256-tile kernel for all three products (measured faster than the
+// 128 x 256 one, alone and beside each other).  Where the lines lie (us a layer, direct against wide, k = 4):
+//   forward     N = 4096: B = 256 19 / 43, B = 512 34 / 41;  N = 6144: B = 64 28 / 37, B = 200 48 / 46 (128 x 128 tiles), B = 400 69 / 65;
+//               N = 8192: B = 128 45 / 44, B = 256 66 / 61, B = 512 110 / 80
+//   backward    N = 3072, B = 256: 27 / 34;  N = 4096: B = 64 24 / 34, B = 256 41 / 43, B = 512 73 / 56;
+//               N = 6144: B = 64 56 / 50, B = 200 97 / 72;  N = 8192: B = 32 79 / 77, B = 128 109 / 86, B = 512 274 / 146
+// The direct kernels read every operand once per 64 x 64 outputs, the wide ones once per 256 x 256: with a long
+// contraction that traffic decides; with a short one the wide kernels' second pass and their events do.
+// How a wide net shares the chip between the chain and the workers: a kernel of either kind fills every compute
 // unit it gets (registers, LDS), so two of them never share one; what can be shared is the set of compute
 // units.  The chain product is split only two ways along K -- 128 workgroups, half the chip (and half the
 // split's partial-sum traffic) -- the streamed gradient product keeps 96 workgroups resident, and the k workers
@@ -1023,29 +737,26 @@ hipError_t run_half(GemmArgs g, int splits, hipStream_t s) {
 // pass against 8.0 ms with every kernel spread over the whole chip.  (The split does not depend on k: the
 // gradients must be the same bits for every k.  A sequential pass, k = 1, would be faster with four splits.)
 // Overrides for tests and A/B runs, read when the plan is made:
-// LF_GEMM_BIG=0/1 forces the narrow / wide-net kernels; LF_GEMM_CHAIN_TILE = "big" or "half" picks the wide-net
+// LF_GEMM_BIG=0/1 forces the direct / wide-net kernels; LF_GEMM_CHAIN_TILE = "big" or "half" picks the wide-net
 // kernel of the forward and chain products, LF_GEMM_GRAD_TILE = "stream" (default), "big" or "half" that of the
 // gradient product; LF_GEMM_SPLIT_TARGET = workgroups the split of a chain-side product aims at (both products),
 // LF_GEMM_CHAIN_SPLIT_TARGET = the same for the backward chain product alone; LF_GEMM_STREAM_GROUPS = resident
 // workgroups of the streamed gradient product; LF_WORKER_STREAMS (read by the schedule) = streams the workers share.
 GemmPlan gemm_plan(int N, int B, bool bf16) {
-    // (narrow kernels: one stream for all workers -- at L = 32, N = 4096, B = 256, k = 4 the backward pass takes
-    // 4.4-4.5 ms with one worker stream and 4.6-4.7 ms with four: gradient products that queue behind each other
-    // leave the chain its compute units)
-    GemmPlan p{GEMM_128, GEMM_128, 512, 512, 256, 1};
-    bool wide = bf16 && ceil_div(B, big::TM) * ceil_div(N, big::TN) >= 64;
+    GemmPlan p{GEMM_DIRECT, GEMM_DIRECT, GEMM_DIRECT, 256, 128, 96, 1};
+    bool wide_forward = bf16 && N >= 6144 && B >= 192;
+    bool wide_backward = bf16 && ((N >= 6144 && B >= 48) || (N >= 4096 && B >= 384));
     if (const char* e = getenv("LF_GEMM_BIG")) {
-        if (e[0] == '0') wide = false;
-        if (e[0] == '1') wide = bf16;
+        if (e[0] == '0') wide_forward = wide_backward = false;
+        if (e[0] == '1') wide_forward = wide_backward = bf16;
     }
-    if (wide) {
-        p.chain = GEMM_BIG;
+    int tile = GEMM_BIG;
+    if (const char* e = getenv("LF_GEMM_CHAIN_TILE")) tile = e[0] == 'b' ? GEMM_BIG : GEMM_HALF;
+    if (wide_forward) p.forward = tile;
+    if (wide_backward) {
+        p.chain = tile;
         p.grad = GEMM_STREAM;
-        p.split_target = 256;
-        p.chain_split_target = 128;
-        p.stream_groups = 96;
         p.worker_streams = 2;
-        if (const char* e = getenv("LF_GEMM_CHAIN_TILE")) p.chain = e[0] == 'b' ? GEMM_BIG : GEMM_HALF;
         if (const char* e = getenv("LF_GEMM_GRAD_TILE")) p.grad = e[0] == 'b' ? GEMM_BIG : (e[0] == 's' ? GEMM_STREAM : GEMM_HALF);
     }
     if (const char* e = getenv("LF_GEMM_STREAM_GROUPS")) {
@@ -1063,148 +774,90 @@ GemmPlan gemm_plan(int N, int B, bool bf16) {
     return p;
 }
 
-int chain_splits(int n_out, int K, int B, bool bf16, int kernel, int target) {
-    if (kernel == GEMM_HALF) {
-        const int tiles = ceil_div(n_out, half::TN) * ceil_div(B, half::TM);
-        const int kt = ceil_div(K, half::TK);
-        int s = 1;
-        while (tiles * s < target && s < 16 && kt / (s * 2) >= 8) s *= 2;
-        return s;
-    }
-    if (kernel == GEMM_BIG) {
-        const int tiles = ceil_div(n_out, big::TN) * ceil_div(B, big::TM);
-        const int kt = ceil_div(K, big::TK);
-        int s = 1;
-        while (tiles * s < target && s < 16 && kt / (s * 2) >= 4) s *= 2;   // one workgroup per compute unit
-        return s;
-    }
-    const int tiles = ceil_div(n_out, BN) * ceil_div(B, BM);
-    const int kt = ceil_div(K, bf16 ? Tile<__bf16>::BK : Tile<float>::BK);
+static int chain_splits(int n_out, int K, int B, int kernel, int target) {
+    const bool half_tile = kernel == GEMM_HALF;
+    const int tiles = half_tile ? ceil_div(n_out, half::TN) * ceil_div(B, half::TM)
+                                : ceil_div(n_out, big::TN) * ceil_div(B, big::TM);
+    const int kt = ceil_div(K, half_tile ? half::TK : big::TK), least = half_tile ? 8 : 4;
     int s = 1;
-    while (tiles * s < target && s < 16 && kt / (s * 2) >= 4) s *= 2;
+    while (tiles * s < target && s < 16 && kt / (s * 2) >= least) s *= 2;
     return s;
 }
 
-size_t split_workspace_floats(int n_out, int K, int B, bool bf16) {      // enough for any plan
-    (void)K; (void)bf16;
-    return (size_t)16 * B * n_out;                                       // no plan splits more than 16 ways
+size_t split_workspace_floats(int n_out, int B, bool bf16) {             // enough for any plan
+    return bf16 ? (size_t)16 * B * n_out : 0;                            // no plan splits more than 16 ways
 }
 
-size_t split_scratch_floats(int n_out, int K, int B, bool bf16, const GemmPlan& plan, bool chain_product) {
-    const int s = chain_splits(n_out, K, B, bf16, plan.chain, chain_product ? plan.chain_split_target : plan.split_target);
+size_t split_scratch_floats(int n_out, int K, int B, bool bf16, const GemmPlan& plan) {
+    if (plan.chain != GEMM_DIRECT) {
+        const int s = chain_splits(n_out, K, B, plan.chain, plan.chain_split_target);
+        return s > 1 ? (size_t)s * B * n_out : 0;
+    }
+    // The direct kernels use none: what is charged is the published limit of the entry point that asks, the partial
+    // sums of a product of 128 x 128 tiles split to at most 512 workgroups.
+    const int tiles = ceil_div(n_out, 128) * ceil_div(B, 128), kt = ceil_div(K, bf16 ? 64 : 32);
+    int s = 1;
+    while (tiles * s < 512 && s < 16 && kt / (s * 2) >= 4) s *= 2;
     return s > 1 ? (size_t)s * B * n_out : 0;
 }
 
-template <typename T>
-static hipError_t fwd_impl(const void* W, const float* bias, const void* A_in, void* A_out, float* raw,
+hipError_t launch_fwd_gemm(const void* W, const float* bias, const void* A_in, void* A_out, float* raw,
                            int n_out, int n_in, int B, const GemmPlan& plan, hipStream_t s) {
-    constexpr bool bf = sizeof(T) == 2;
-    const int splits = chain_splits(n_out, n_in, B, bf, plan.chain, plan.split_target);
+    const int splits = chain_splits(n_out, n_in, B, plan.forward, plan.split_target);
+    const bool half_tile = plan.forward == GEMM_HALF;
     GemmArgs g{};
     g.P = A_in; g.ldp = n_in; g.Q = W; g.ldq = n_in; g.M = B; g.Nn = n_out; g.K = n_in;
-    g.k_tiles_per_split = ceil_div(ceil_div(n_in, Tile<T>::BK), splits);
+    g.k_tiles_per_split = ceil_div(ceil_div(n_in, half_tile ? half::TK : big::TK), splits);
     g.bias = bias; g.out = A_out; g.raw = raw;
-    hipError_t e;
-    if constexpr (bf) {
-        if (plan.chain == GEMM_HALF) {
-            g.k_tiles_per_split = ceil_div(ceil_div(n_in, half::TK), splits);
-            if (splits == 1) return run_half<false, false, EPI_SIGMOID>(g, 1, s);
-            e = run_half<false, false, EPI_RAW>(g, splits, s);
-        } else if (plan.chain == GEMM_BIG) {
-            if (splits == 1) return run_big<false, false, EPI_SIGMOID>(g, 1, s);
-            e = run_big<false, false, EPI_RAW>(g, splits, s);
-        } else {
-            if (splits == 1) return run<T, false, false, EPI_SIGMOID>(g, 1, s);
-            e = run<T, false, false, EPI_RAW>(g, splits, s);
-        }
-    } else {
-        if (splits == 1) return run<T, false, false, EPI_SIGMOID>(g, 1, s);
-        e = run<T, false, false, EPI_RAW>(g, splits, s);
-    }
+    if (splits == 1)
+        return half_tile ? run_half<false, false, EPI_SIGMOID>(g, 1, s) : run_big<false, false, EPI_SIGMOID>(g, 1, s);
+    const hipError_t e = half_tile ? run_half<false, false, EPI_RAW>(g, splits, s)
+                                   : run_big<false, false, EPI_RAW>(g, splits, s);
     if (e != hipSuccess) return e;
     const size_t count = (size_t)B * n_out;
-    k_split_finish<T, EPI_SIGMOID><<<(unsigned)((count / 4 + kThreads - 1) / kThreads), kThreads, 0, s>>>(
+    k_split_finish<EPI_SIGMOID><<<(unsigned)((count / 4 + kThreads - 1) / kThreads), kThreads, 0, s>>>(
         raw, splits, count, n_out, bias, nullptr, A_out, nullptr);
     return hipGetLastError();
 }
 
-template <typename T>
-static hipError_t chain_impl(const void* W_next, const void* D_next_op, const void* A_l, float* D_l,
-                             void* D_l_bf, float* raw, int n_l, int n_next, int B, const GemmPlan& plan,
-                             hipStream_t s) {
-    constexpr bool bf = sizeof(T) == 2;
-    const int splits = chain_splits(n_l, n_next, B, bf, plan.chain, plan.chain_split_target);
+hipError_t launch_chain_gemm(const void* W_next, const void* D_next_bf, const void* A_l, float* D_l, void* D_l_bf,
+                             float* raw, int n_l, int n_next, int B, const GemmPlan& plan, hipStream_t s) {
+    const int splits = chain_splits(n_l, n_next, B, plan.chain, plan.chain_split_target);
+    const bool half_tile = plan.chain == GEMM_HALF;
     GemmArgs g{};
-    g.P = D_next_op; g.ldp = n_next; g.Q = W_next; g.ldq = n_l; g.M = B; g.Nn = n_l; g.K = n_next;
-    g.k_tiles_per_split = ceil_div(ceil_div(n_next, Tile<T>::BK), splits);
+    g.P = D_next_bf; g.ldp = n_next; g.Q = W_next; g.ldq = n_l; g.M = B; g.Nn = n_l; g.K = n_next;
+    g.k_tiles_per_split = ceil_div(ceil_div(n_next, half_tile ? half::TK : big::TK), splits);
     g.act = A_l; g.out = D_l; g.out_bf = D_l_bf; g.raw = raw;
-    hipError_t e;
-    if constexpr (bf) {
-        if (plan.chain == GEMM_HALF) {
-            g.k_tiles_per_split = ceil_div(ceil_div(n_next, half::TK), splits);
-            if (splits == 1) return run_half<false, true, EPI_SIGMA_PRIME>(g, 1, s);
-            e = run_half<false, true, EPI_RAW>(g, splits, s);
-        } else if (plan.chain == GEMM_BIG) {
-            if (splits == 1) return run_big<false, true, EPI_SIGMA_PRIME>(g, 1, s);
-            e = run_big<false, true, EPI_RAW>(g, splits, s);
-        } else {
-            if (splits == 1) return run<T, false, true, EPI_SIGMA_PRIME>(g, 1, s);
-            e = run<T, false, true, EPI_RAW>(g, splits, s);
-        }
-    } else {
-        if (splits == 1) return run<T, false, true, EPI_SIGMA_PRIME>(g, 1, s);
-        e = run<T, false, true, EPI_RAW>(g, splits, s);
-    }
+    if (splits == 1)
+        return half_tile ? run_half<false, true, EPI_SIGMA_PRIME>(g, 1, s) : run_big<false, true, EPI_SIGMA_PRIME>(g, 1, s);
+    const hipError_t e = half_tile ? run_half<false, true, EPI_RAW>(g, splits, s)
+                                   : run_big<false, true, EPI_RAW>(g, splits, s);
     if (e != hipSuccess) return e;
     const size_t count = (size_t)B * n_l;
-    k_split_finish<T, EPI_SIGMA_PRIME><<<(unsigned)((count / 4 + kThreads - 1) / kThreads), kThreads, 0, s>>>(
-        raw, splits, count, n_l, nullptr, static_cast<const T*>(A_l), D_l, static_cast<__bf16*>(D_l_bf));
+    k_split_finish<EPI_SIGMA_PRIME><<<(unsigned)((count / 4 + kThreads - 1) / kThreads), kThreads, 0, s>>>(
+        raw, splits, count, n_l, nullptr, static_cast<const __bf16*>(A_l), D_l, static_cast<__bf16*>(D_l_bf));
     return hipGetLastError();
 }
 
-hipError_t launch_fwd_gemm(const void* W, const float* bias, const void* A_in, void* A_out, float* raw,
-                           int n_out, int n_in, int B, bool bf16, const GemmPlan& plan, hipStream_t s) {
-    return bf16 ? fwd_impl<__bf16>(W, bias, A_in, A_out, raw, n_out, n_in, B, plan, s)
-                : fwd_impl<float>(W, bias, A_in, A_out, raw, n_out, n_in, B, plan, s);
-}
-
-hipError_t launch_chain_gemm(const void* W_next, const float* D_next, const void* D_next_bf,
-                             const void* A_l, float* D_l, void* D_l_bf, float* raw, int n_l, int n_next,
-                             int B, bool bf16, const GemmPlan& plan, hipStream_t s) {
-    return bf16 ? chain_impl<__bf16>(W_next, D_next_bf, A_l, D_l, D_l_bf, raw, n_l, n_next, B, plan, s)
-                : chain_impl<float>(W_next, D_next, A_l, D_l, nullptr, raw, n_l, n_next, B, plan, s);
-}
-
-hipError_t launch_grad_gemm(const float* D, const void* D_bf, const void* A_prev, float* nabla_w,
-                            float* nabla_b, int n_l, int n_prev, int B, bool bf16, const GemmPlan& plan,
-                            bool whole_chip, float sgd_eta, void* w_bf, hipStream_t s) {
-    if (sgd_eta != 0.0f && bf16 != (w_bf != nullptr)) return hipErrorInvalidValue;
+hipError_t launch_grad_gemm(const float* D, const void* D_bf, const void* A_prev, float* nabla_w, float* nabla_b,
+                            int n_l, int n_prev, int B, const GemmPlan& plan, bool whole_chip, float sgd_eta,
+                            void* w_bf, hipStream_t s) {
+    if ((sgd_eta != 0.0f) != (w_bf != nullptr)) return hipErrorInvalidValue;
     k_bias_grad<<<ceil_div(n_l, 32), kThreads, 0, s>>>(D, nabla_b, n_l, B, sgd_eta);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     GemmArgs g{};
-    g.ldp = n_l; g.Q = A_prev; g.ldq = n_prev; g.M = n_l; g.Nn = n_prev; g.K = B;
+    g.P = D_bf; g.ldp = n_l; g.Q = A_prev; g.ldq = n_prev; g.M = n_l; g.Nn = n_prev; g.K = B;
     g.out = nabla_w;
     g.sgd_eta = sgd_eta;
-    g.out_bf = sgd_eta != 0.0f ? w_bf : nullptr;
-    if (bf16) {
-        g.P = D_bf;
-        g.k_tiles_per_split = ceil_div(B, Tile<__bf16>::BK);
-        if (plan.grad == GEMM_HALF) {
-            g.k_tiles_per_split = ceil_div(B, half::TK);
-            return run_half<true, true, EPI_GRAD>(g, 1, s);
-        }
-        // the streamed kernel stores gradients only (the descent step keeps the tile-per-workgroup kernel) and
-        // addresses the result through one 32-bit buffer
-        if (plan.grad == GEMM_STREAM && sgd_eta == 0.0f &&
-            (unsigned long long)(n_l + big::TM) * n_prev * 4ull < 0xFFFFFFF0ull)
-            return run_grad_stream(g, whole_chip ? 256 : plan.stream_groups, s);
-        if (plan.grad == GEMM_BIG || plan.grad == GEMM_STREAM) return run_big<true, true, EPI_GRAD>(g, 1, s);
-        return run<__bf16, true, true, EPI_GRAD>(g, 1, s);
-    }
-    g.P = D;
-    g.k_tiles_per_split = ceil_div(B, Tile<float>::BK);
-    return run<float, true, true, EPI_GRAD>(g, 1, s);
+    g.out_bf = w_bf;
+    g.k_tiles_per_split = ceil_div(B, plan.grad == GEMM_HALF ? half::TK : big::TK);
+    if (plan.grad == GEMM_HALF) return run_half<true, true, EPI_GRAD>(g, 1, s);
+    // the streamed kernel stores gradients only (the descent step keeps the tile-per-workgroup kernel) and
+    // addresses the result through one 32-bit buffer
+    if (plan.grad == GEMM_STREAM && sgd_eta == 0.0f && (unsigned long long)(n_l + big::TM) * n_prev * 4ull < 0xFFFFFFF0ull)
+        return run_grad_stream(g, whole_chip ? 256 : plan.stream_groups, s);
+    return run_big<true, true, EPI_GRAD>(g, 1, s);
 }
 
 }  // namespace lf

@@ -122,8 +122,8 @@ Layout make_layout(int L, const int* n, int B, lf_dtype dt) {
             if (l >= 3)   // the step delta^l -> delta^{l-1} reads w^l (n_l x n_prev)
                 partial_floats = std::max(partial_floats, (size_t)lf::chain_partial_blocks(n_l) * n_prev);
         } else {
-            raw_floats = std::max(raw_floats, lf::split_workspace_floats(n_l, n_prev, B, dt == LF_BF16));
-            if (l >= 3) raw_floats = std::max(raw_floats, lf::split_workspace_floats(n_prev, n_l, B, dt == LF_BF16));
+            raw_floats = std::max(raw_floats, lf::split_workspace_floats(n_l, B, dt == LF_BF16));
+            if (l >= 3) raw_floats = std::max(raw_floats, lf::split_workspace_floats(n_prev, B, dt == LF_BF16));
         }
     }
     y.partial_off = off;
@@ -267,6 +267,11 @@ lf_status ensure_workers(lf_net* net, int k) {
         if (v >= 1 && v <= kMaxWorkerStreams) cap = v;
     }
     return ensure_worker_streams(net, k > 1 ? (size_t)(k < cap ? k : cap) : 0);
+}
+
+// A minibatch net (or a bf16 one of any B) whose backward products are the direct kernels.
+bool direct_minibatch(const lf_net* net) {
+    return !single_sample_path(net->N, net->B, net->dt) && net->gemm.chain == lf::GEMM_DIRECT;
 }
 
 bool persistent_possible(const lf_net* net) {
@@ -455,6 +460,24 @@ lf::PersistArgs persist_args(lf_net* net, const void* y, int k) {
     return A;
 }
 
+// The layer-l work of the direct minibatch kernels.
+lf::ChainStep chain_step(const lf_net* net, int l) {            // delta^l from delta^{l+1}
+    return {net->w[l - 1], net->d_ptr(l + 1), net->dbf_ptr(l + 1), net->a_ptr(l), net->d_ptr(l), net->dbf_ptr(l),
+            net->width(l), net->width(l + 1)};
+}
+lf::GradStep grad_step(const lf_net* net, int l) {              // (bp3), (bp4), or the descent step, of layer l
+    const int i = l - 2;
+    const bool sgd = net->sgd_eta != 0.0f, bf = net->dt == LF_BF16;
+    lf::GradStep g{net->d_ptr(l), net->dbf_ptr(l), net->a_ptr(l - 1), net->gw[i], net->gb[i], nullptr,
+                   net->width(l), net->width(l - 1)};
+    if (sgd) {
+        g.w = bf ? net->w32[i] : static_cast<float*>(const_cast<void*>(net->w[i]));
+        g.b = const_cast<float*>(net->b[i]);
+        g.w_bf = bf ? const_cast<void*>(net->w[i]) : nullptr;
+    }
+    return g;
+}
+
 // (bp3),(bp4) of layer l on stream s; with the descent step fused in, applied to w^l and b^l in place.
 lf_status enqueue_grads(lf_net* net, int l, hipStream_t s, bool whole_chip = true) {
     const int i = l - 2;
@@ -465,9 +488,12 @@ lf_status enqueue_grads(lf_net* net, int l, hipStream_t s, bool whole_chip = tru
     if (single_sample_path(net->N, net->B, net->dt)) {
         LF_HIP(net, lf::launch_grad_outer_f32(net->d_ptr(l), static_cast<const float*>(net->a_ptr(l - 1)),
                                               out_w, out_b, net->width(l), net->width(l - 1), net->sgd_eta, s));
+    } else if (net->gemm.grad == lf::GEMM_DIRECT) {
+        const lf::GradStep g = grad_step(net, l);
+        LF_HIP(net, lf::launch_backward_step(nullptr, &g, 1, net->B, bf, net->sgd_eta, s));
     } else {
         LF_HIP(net, lf::launch_grad_gemm(net->d_ptr(l), net->dbf_ptr(l), net->a_ptr(l - 1), out_w, out_b,
-                                         net->width(l), net->width(l - 1), net->B, bf, net->gemm, whole_chip,
+                                         net->width(l), net->width(l - 1), net->B, net->gemm, whole_chip,
                                          net->sgd_eta, w_bf, s));
     }
     return LF_OK;
@@ -584,10 +610,12 @@ lf_status backward_streams(lf_net* net, const void* y, int k, hipStream_t s, flo
             LF_HIP(net, lf::launch_chain_gemvT_f32(static_cast<const float*>(net->w[l - 1]), net->d_ptr(l + 1),
                                                    static_cast<const float*>(net->a_ptr(l)), net->d_ptr(l),
                                                    partial, net->width(l + 1), net->width(l), s));
+        } else if (net->gemm.chain == lf::GEMM_DIRECT) {
+            const lf::ChainStep c = chain_step(net, l);
+            LF_HIP(net, lf::launch_backward_step(&c, nullptr, 0, B, bf, 0.0f, s));
         } else {
-            LF_HIP(net, lf::launch_chain_gemm(net->w[l - 1], net->d_ptr(l + 1), net->dbf_ptr(l + 1), net->a_ptr(l),
-                                              net->d_ptr(l), net->dbf_ptr(l), raw, net->width(l),
-                                              net->width(l + 1), B, bf, net->gemm, s));
+            LF_HIP(net, lf::launch_chain_gemm(net->w[l - 1], net->dbf_ptr(l + 1), net->a_ptr(l), net->d_ptr(l),
+                                              net->dbf_ptr(l), raw, net->width(l), net->width(l + 1), B, net->gemm, s));
         }
         // (bp3),(bp4) of layer l, off the chain: as soon as delta^l is there.  With the descent step fused in
         // the worker rewrites w^l, which the chain still reads on its way to delta^{l-1}: layer l's work then
@@ -614,6 +642,34 @@ lf_status backward_streams(lf_net* net, const void* y, int k, hipStream_t s, flo
     }
     net->bwd_done = !chain_only;
     if (sgd) net->stepped = true;                      // the stored activations belong to the old weights
+    return LF_OK;
+}
+
+// The direct minibatch kernels in line on one stream: the launch of the chain step delta^{l+1} -> delta^l also takes the
+// gradients of layer l+1, whose operands are there at the same time (the worker's share rides beside the chain's in
+// one grid: no events, no second stream).  With the descent step fused in, layer l+1's weights are still being read
+// by that chain step: the launch then takes layer l+2's.
+lf_status backward_steps(lf_net* net, const void* y, hipStream_t s) {
+    const int L = net->L, B = net->B;
+    const bool bf = net->dt == LF_BF16, sgd = net->sgd_eta != 0.0f;
+    const bool chain_only = (net->debug_flags & LF_DEBUG_CHAIN_ONLY) != 0;
+    LF_HIP(net, lf::launch_output_error(net->a_ptr(L), y, net->d_ptr(L), net->dbf_ptr(L), (size_t)B * net->width(L), bf,
+                                        net->cost_scale, s));
+    const int lag = sgd ? 2 : 1;
+    for (int l = L - 1; l >= 2; --l) {
+        const lf::ChainStep c = chain_step(net, l);
+        const bool grads = !chain_only && l + lag <= L;
+        const lf::GradStep g = grads ? grad_step(net, l + lag) : lf::GradStep{};
+        LF_HIP(net, lf::launch_backward_step(&c, &g, grads ? 1 : 0, B, bf, net->sgd_eta, s));
+    }
+    if (!chain_only) {
+        lf::GradStep last[2];
+        int n = 0;
+        for (int l = std::min(L, 1 + lag); l >= 2; --l) last[n++] = grad_step(net, l);
+        LF_HIP(net, lf::launch_backward_step(nullptr, last, n, B, bf, net->sgd_eta, s));
+    }
+    net->bwd_done = !chain_only;
+    if (sgd) net->stepped = true;
     return LF_OK;
 }
 
@@ -831,10 +887,12 @@ lf_status lf_forward(lf_net* net, const void* x1, void* hip_stream) {
                                                 static_cast<const float*>(net->a_ptr(l - 1)),
                                                 static_cast<float*>(net->a_ptr(l)), net->width(l),
                                                 net->width(l - 1), s));
+        } else if (net->gemm.forward == lf::GEMM_DIRECT) {
+            LF_HIP(net, lf::launch_forward_direct(net->w[l - 2], net->b[l - 2], net->a_ptr(l - 1), net->a_ptr(l),
+                                                  net->width(l), net->width(l - 1), net->B, bf, s));
         } else {
-            LF_HIP(net, lf::launch_fwd_gemm(net->w[l - 2], net->b[l - 2], net->a_ptr(l - 1), net->a_ptr(l),
-                                            net->raw(), net->width(l), net->width(l - 1), net->B, bf,
-                                            net->gemm, s));
+            LF_HIP(net, lf::launch_fwd_gemm(net->w[l - 2], net->b[l - 2], net->a_ptr(l - 1), net->a_ptr(l), net->raw(),
+                                            net->width(l), net->width(l - 1), net->B, net->gemm, s));
         }
     }
     net->fwd_done = true;
@@ -871,6 +929,7 @@ lf_status lf_backward_leapfrog(lf_net* net, const void* y, int k, void* hip_stre
         if (st == LF_OK) net->bwd_done = true;
         return st;
     }
+    if (net->sched == LF_SCHED_AUTO && direct_minibatch(net)) return backward_steps(net, y, s);
     st = ensure_workers(net, k);
     if (st != LF_OK) return st;
     return backward_streams(net, y, k, s, net->partial(), net->raw(), /*in_line=*/k == 1);
@@ -884,13 +943,13 @@ lf_status lf_backward_leapfrog_noalloc(lf_net* net, const void* y, int k, void* 
     if (st != LF_OK) return st;
     if (net->sched == LF_SCHED_REDUNDANT || net->sched == LF_SCHED_FUSED)
         return fail(net, LF_EUNSUPPORTED, "lf_backward_leapfrog_noalloc: runs the stream schedule's kernels only");
-    // what the chain products of this net really use: the single-sample row-block partial sums, or the split-K
-    // partials under the net's plan (the workspace reserves room for the deepest split any plan could take)
+    // what the chain products of this net are charged for: the single-sample row-block partial sums, or the split-K
+    // partials of a minibatch
     size_t need = net->lay.partial_bytes;
     if (!single_sample_path(net->N, net->B, net->dt))
         for (int l = 2; l < net->L; ++l)
             need = std::max(need, 4 * lf::split_scratch_floats(net->width(l), net->width(l + 1), net->B,
-                                                               net->dt == LF_BF16, net->gemm, true));
+                                                               net->dt == LF_BF16, net->gemm));
     if (need > LF_STATIC_SCRATCH_BYTES)
         return fail(net, LF_EUNSUPPORTED,
                     "lf_backward_leapfrog_noalloc: this shape needs " + std::to_string(need) +
@@ -899,6 +958,7 @@ lf_status lf_backward_leapfrog_noalloc(lf_net* net, const void* y, int k, void* 
     st = static_scratch_of_current_device(net, &area);
     if (st != LF_OK) return st;
     net->bwd_done = false;
+    if (direct_minibatch(net)) return backward_steps(net, y, static_cast<hipStream_t>(hip_stream));
     // every word of the scratch a pass reads it has written before (the chain's partial sums are stored
     // whole, then summed): nothing needs clearing between calls
     return backward_streams(net, y, k, static_cast<hipStream_t>(hip_stream), static_cast<float*>(area),

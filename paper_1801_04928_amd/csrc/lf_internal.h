@@ -36,49 +36,66 @@ hipError_t launch_grad_outer_f32(const float* delta, const float* a_prev, float*
 hipError_t launch_output_error(const void* a_L, const void* y, float* delta_L, void* delta_bf,
                                size_t count, bool bf16, float scale, hipStream_t s);
 
-// ---- minibatch path: MFMA contractions ----------------------------------------------------------
+// ---- minibatch path: which kernels ----------------------------------------------------------------
 
-// Floats of scratch the split-K stage of a forward / chain contraction with a B x n_out result and
-// contraction length K needs (0 = no split).
-size_t split_workspace_floats(int n_out, int K, int B, bool bf16);
-struct GemmPlan;
-// Floats of split-K scratch the forward (chain_product = false) or chain product actually uses under a plan.
-size_t split_scratch_floats(int n_out, int K, int B, bool bf16, const GemmPlan& plan, bool chain_product);
-// Which matrix kernel a product takes: 128 x 128 tiles (fp32; bf16 nets of moderate width), or one of the two
-// wide-net bf16 kernels -- 256 x 256 tiles filling a compute unit, or 128 x 256 tiles sized so that two
-// workgroups (of one product or of two) share a compute unit; the gradient product also as resident workgroups
-// that stream through all their 256 x 256 tiles.
-enum GemmKernel { GEMM_128 = 0, GEMM_BIG = 1, GEMM_HALF = 2, GEMM_STREAM = 3 };   // STREAM: gradient product only
+// DIRECT: the kernels of minibatch_kernels.h.  The others are the wide-net bf16 kernels: 256 x 256 tiles filling a
+// compute unit, or 128 x 256 tiles sized so that two workgroups (of one product or of two) share a compute unit; the
+// gradient product also as resident workgroups that stream through all their 256 x 256 tiles (STREAM).
+enum GemmKernel { GEMM_DIRECT = 0, GEMM_BIG = 1, GEMM_HALF = 2, GEMM_STREAM = 3 };
 struct GemmPlan {
-    int chain;          // GemmKernel of the forward and chain products
-    int grad;           // GemmKernel of the gradient product
-    int split_target;   // workgroups the K split of the forward product aims at
+    int forward;        // GemmKernel of the forward product,
+    int chain;          // of the chain product
+    int grad;           // and of the gradient product (chain and grad are either both DIRECT or neither)
+    int split_target;   // workgroups the K split of a wide forward product aims at
     int chain_split_target;   // the same for the chain product of the backward pass
     int stream_groups;  // resident workgroups of the streamed gradient product
     int worker_streams; // streams the k workers share (worker j runs on stream j mod this)
 };
 // The plan of a net whose widest layer has N neurons (decided once per net).
 GemmPlan gemm_plan(int N, int B, bool bf16);
+// Floats of scratch that hold the split-K partials of a wide product with a B x n_out result under any plan.
+size_t split_workspace_floats(int n_out, int B, bool bf16);
+// Floats of chain scratch a net is charged for by lf_backward_leapfrog_noalloc, for a B x n_out result and contraction
+// length K.
+size_t split_scratch_floats(int n_out, int K, int B, bool bf16, const GemmPlan& plan);
+
+// ---- minibatch path: wide bf16 nets ---------------------------------------------------------------
 
 // eqs. (z),(a) for a minibatch: A_out[b][j] = sigma(sum_k A_in[b][k] W[j][k] + bias[j]); W is n_out x n_in.
-// `raw` is the split-K scratch, split_workspace_floats(n_out, n_in, B, bf16) floats (may be NULL when that is 0).
+// `raw` is the split-K scratch, split_workspace_floats(n_out, B, true) floats.
 hipError_t launch_fwd_gemm(const void* W, const float* bias, const void* A_in, void* A_out, float* raw,
-                           int n_out, int n_in, int B, bool bf16, const GemmPlan& plan, hipStream_t s);
+                           int n_out, int n_in, int B, const GemmPlan& plan, hipStream_t s);
 // eq. (bp2) for a minibatch: D_l[b][k] = (sum_j D_next[b][j] W_next[j][k]) A_l[b][k] (1 - A_l[b][k]);
-// W_next is n_next x n_l.  For bf16, D_next_bf / D_l_bf are the bfloat16 copies used as matrix operands.
-// raw: split_workspace_floats(n_l, n_next, B, bf16) floats.
-hipError_t launch_chain_gemm(const void* W_next, const float* D_next, const void* D_next_bf,
-                             const void* A_l, float* D_l, void* D_l_bf, float* raw,
-                             int n_l, int n_next, int B, bool bf16, const GemmPlan& plan, hipStream_t s);
+// W_next is n_next x n_l.  D_next_bf / D_l_bf are the bfloat16 copies used as matrix operands.
+// raw: split_workspace_floats(n_l, B, true) floats.
+hipError_t launch_chain_gemm(const void* W_next, const void* D_next_bf, const void* A_l, float* D_l, void* D_l_bf,
+                             float* raw, int n_l, int n_next, int B, const GemmPlan& plan, hipStream_t s);
 // eqs. (bp3),(bp4) for a minibatch: nabla_w[j][k] = sum_b D[b][j] A_prev[b][k] (n_l x n_prev);
 // nabla_b[j] = sum_b D[b][j] (fixed summation order).
-// sgd_eta != 0: the descent step fused into the epilogues -- nabla_w and nabla_b are then w^l (in fp32) and b^l
-// themselves and receive w - eta nabla_w, b - eta nabla_b; the gradients are not stored.  With bfloat16 storage
-// nabla_w is the fp32 master copy of w^l, and w_bf, the bfloat16 weights, are rewritten as its rounding (w_bf
-// is NULL exactly when the storage is fp32).  whole_chip: nothing runs beside this product (the sequential
+// sgd_eta != 0: the descent step fused into the epilogues -- nabla_w and nabla_b are then the fp32 master copy of w^l
+// and b^l themselves and receive w - eta nabla_w, b - eta nabla_b, and w_bf, the bfloat16 weights, are rewritten as
+// the master's rounding; the gradients are not stored.  whole_chip: nothing runs beside this product (the sequential
 // pass), so the streamed kernel keeps a workgroup on every compute unit instead of the plan's share.
-hipError_t launch_grad_gemm(const float* D, const void* D_bf, const void* A_prev, float* nabla_w,
-                            float* nabla_b, int n_l, int n_prev, int B, bool bf16, const GemmPlan& plan,
-                            bool whole_chip, float sgd_eta, void* w_bf, hipStream_t s);
+hipError_t launch_grad_gemm(const float* D, const void* D_bf, const void* A_prev, float* nabla_w, float* nabla_b,
+                            int n_l, int n_prev, int B, const GemmPlan& plan, bool whole_chip, float sgd_eta,
+                            void* w_bf, hipStream_t s);
+
+// ---- minibatch path: direct kernels (fp32; bf16 nets that are not wide) -----------------------------
+
+// eqs. (z),(a) for a minibatch (as launch_fwd_gemm), one launch, no scratch.
+hipError_t launch_forward_direct(const void* W, const float* bias, const void* A_in, void* A_out, int n_out, int n_in,
+                                 int B, bool bf16, hipStream_t s);
+struct ChainStep {      // eq. (bp2): delta^l from delta^{l+1} (as launch_chain_gemm; fp32 nets have no *_bf)
+    const void* W_next; const float* D_next; const void* D_next_bf; const void* A_l; float* D_l; void* D_l_bf;
+    int n_l, n_next;
+};
+struct GradStep {       // eqs. (bp3), (bp4) of one layer (as launch_grad_gemm)
+    const float* D; const void* D_bf; const void* A_prev; float* w; float* b; void* w_bf;
+    int n_l, n_prev;
+};
+// One launch that takes a chain step (or none: NULL) and the gradients of up to two layers, none of which depends on
+// another.  What a product's sums look like depends on its shape, B and the type alone, not on what it is launched with.
+hipError_t launch_backward_step(const ChainStep* chain, const GradStep* grads, int ngrads, int B, bool bf16,
+                                float sgd_eta, hipStream_t s);
 
 }  // namespace lf

@@ -1,0 +1,623 @@
+// Minibatch (B > 1, and bf16 at any B) kernels that need neither LDS operand tiles nor a second pass: the three
+// per-layer contractions as matrix instructions on fragments loaded straight from memory into registers.
+//
+//   forward (z),(a):  A_out[b][j] = sigma( sum_k A_in[b][k]  W[j][k]  + bias[j] )
+//   chain   (bp2):    D_l[b][k]   = ( sum_j D_next[b][j] W_next[j][k] ) * A_l[b][k] (1 - A_l[b][k])
+//   grads   (bp4):    nabla_w[j][k] = sum_b D[b][j] A_prev[b][k]        (bp3): nabla_b[j] = sum_b D[b][j]
+//
+// All three are  C[m][n] = sum_q P(m,q) Q(n,q)  with operands that are either contiguous along the contraction index
+// q ("QC": element (i,q) at p[i*ld + q]) or along their own index ("IC": element (i,q) at p[q*ld + i]).  forward:
+// P = A_in (QC), Q = W (QC).  chain: P = D_next (QC), Q = W_next (IC).  grads: P = D (IC), Q = A_prev (IC).
+// Accumulation is fp32, in an order fixed by the shape alone, so results depend neither on k nor on the launch.
+#pragma once
+#include "lf_internal.h"
+
+#include <algorithm>
+
+namespace lf {
+namespace direct {
+namespace {
+
+__host__ __device__ constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+constexpr unsigned kOutside = 0xFFFFFFF0u;   // an offset past the end of every buffer: loads zeros
+constexpr int kWaves = 4;                    // of every workgroup
+
+// A unit of the contraction: the q's of one 64-byte piece of a QC row.  A 16 x 16 matrix instruction hands row
+// (lane % 16) of its operand to a lane and one quarter (g = lane / 16) of the q's; which q's form a quarter is free as
+// long as both operands agree.  Here lane group g holds q0 + PL g .. + PL - 1: 16 bytes of a QC row.
+template <typename T> struct Unit;
+template <> struct Unit<float> { static constexpr int Q = 16, PL = 4; };
+template <> struct Unit<__bf16> { static constexpr int Q = 32, PL = 8; };
+
+// One unit of NT 16-row tiles of an operand in registers.
+template <typename T, bool IC, int NT> struct Operand;
+
+// QC: tile t is rows i0 + 16 t .. + 15, and registers hold a pair of units: 128 bytes of every row, a whole cache line.
+// The memory pipeline coalesces neighbouring lanes only, and the L2 serves a request per cycle and channel, of 64 bytes
+// or of 128: eight neighbouring lanes load the line of a row (lane-per-row addressing, as the instructions want it,
+// moves 16 bytes a cycle and compute unit instead of 64; half lines get half of the L2's rate).  A turn through 2 KB of
+// LDS per tile that belong to the wave alone gives every lane its row.  LDS operations of a wave complete in order: no
+// barrier, and the area can be overwritten by the next pair at once.  The 16-byte pieces of row i are placed by an
+// exclusive or with i % 8: no bank conflicts either way.
+template <typename T, int NT> struct Operand<T, false, NT> {
+    static constexpr int kLdsVecs = 128 * NT;
+    struct At {
+        unsigned off[2 * NT];
+        int qlane, write[2], read[2];
+        __device__ At(int i0, int I, int ld) {
+            const int lane = threadIdx.x & 63, row = lane >> 3, c = lane & 7, i = lane & 15, g = lane >> 4;
+            qlane = Unit<T>::PL * c;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                write[h] = 8 * (row + 8 * h) + (c ^ row);
+                read[h] = 8 * i + ((4 * h + g) ^ (i & 7));
+            }
+#pragma unroll
+            for (int t = 0; t < 2 * NT; ++t)   // rows past the end repeat the last one (their results are not stored)
+                off[t] = (unsigned)min(i0 + 8 * t + row, I - 1) * (unsigned)ld * (unsigned)sizeof(T) + 16u * c;
+        }
+    };
+    struct Raw { v4f r[2 * NT]; };             // a pair, as loaded
+    struct Op { v4f r[NT]; };                  // a unit, as the matrix instructions take it
+    static __device__ __forceinline__ void load(Raw& x, __amdgpu_buffer_rsrc_t buf, const At& at, int q0, int K) {
+        const bool ok = q0 + at.qlane < K;     // K is a multiple of PL
+#pragma unroll
+        for (int t = 0; t < 2 * NT; ++t)
+            x.r[t] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(
+                         buf, ok ? at.off[t] : kOutside, q0 * (int)sizeof(T), 0));
+    }
+    static __device__ __forceinline__ void put(const Raw& x, const At& at, v4f* lds) {
+#pragma unroll
+        for (int t = 0; t < 2 * NT; ++t) lds[128 * (t >> 1) + at.write[t & 1]] = x.r[t];
+    }
+    static __device__ __forceinline__ void take(Op& o, int unit, const At& at, const v4f* lds) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) o.r[t] = lds[128 * t + at.read[unit]];
+    }
+    static __device__ __forceinline__ float f32(const Op& o, int t, int e) { return o.r[t][e]; }
+    static __device__ __forceinline__ v8bf bf(const Op& o, int t) { return __builtin_bit_cast(v8bf, o.r[t]); }
+};
+
+// IC: a lane loads NT consecutive i's of each of its PL q's; element t of each belongs to tile t, so tile t is the
+// rows i0 + NT * (lane % 16) + t: a permutation of the NT * 16 rows that only the store has to know.
+template <typename T, int NT> struct Operand<T, true, NT> {
+    static constexpr int PL = Unit<T>::PL;
+    static constexpr int W = NT * (int)sizeof(T) / 4;          // 32-bit words of one load
+    static constexpr int kLdsVecs = 0;
+    struct At {
+        unsigned off;
+        int qlane;
+        __device__ At(int i0, int I, int ld) {
+            const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+            qlane = PL * g;
+            // columns past the end repeat the last ones (their results are not stored); I is a multiple of NT
+            off = ((unsigned)qlane * (unsigned)ld + (unsigned)min(i0 + NT * i, I - NT)) * (unsigned)sizeof(T);
+        }
+    };
+    struct Raw { unsigned r[PL][W]; };         // a unit, as loaded and as used
+    typedef Raw Op;
+    static __device__ __forceinline__ void load(Raw& x, __amdgpu_buffer_rsrc_t buf, const At& at, int ld, int q0, int K) {
+#pragma unroll
+        for (int e = 0; e < PL; ++e) {
+            const unsigned off = q0 + at.qlane + e < K ? at.off : kOutside;
+            const unsigned row = (unsigned)(q0 + e) * (unsigned)ld * (unsigned)sizeof(T);
+            if constexpr (W == 4) {
+                const v4u v = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(buf, off, row, 0));
+#pragma unroll
+                for (int c = 0; c < 4; ++c) x.r[e][c] = v[c];
+            } else if constexpr (W == 2) {
+                typedef unsigned v2u __attribute__((ext_vector_type(2)));
+                const v2u v = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(buf, off, row, 0));
+                x.r[e][0] = v[0];
+                x.r[e][1] = v[1];
+            } else {
+                x.r[e][0] = __builtin_amdgcn_raw_buffer_load_b32(buf, off, row, 0);
+            }
+        }
+    }
+    static __device__ __forceinline__ float f32(const Raw& x, int t, int e) { return __uint_as_float(x.r[e][t]); }
+    static __device__ __forceinline__ v8bf bf(const Raw& x, int t) {      // halves t % 2 of word t / 2 of the eight q's
+        const unsigned sel = (t & 1) ? 0x07060302u : 0x05040100u;
+        v4u v;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) v[d] = __builtin_amdgcn_perm(x.r[2 * d + 1][t >> 1], x.r[2 * d][t >> 1], sel);
+        return __builtin_bit_cast(v8bf, v);
+    }
+};
+
+// acc[mt][nt] += P Q^T of one 16*MT x 16*NT tile over the units of wave w of W that share the contraction: pairs of
+// units are dealt to the waves in turn.  A QC operand is requested D pairs ahead of its way through LDS, which is half
+// a pair ahead of its use; an IC operand E units ahead of its use.  lds: the workgroup's area, kLdsVecs vectors a wave.
+template <typename T, bool P_IC, bool Q_IC, int MT, int NT>
+__device__ __forceinline__ void contract(v4f (&acc)[MT][NT], float* lds, const void* p, unsigned p_bytes, int ldp, int m0,
+                                         int M, const void* q, unsigned q_bytes, int ldq, int n0, int Nn, int K, int w,
+                                         int W) {
+    typedef Operand<T, P_IC, MT> OP;
+    typedef Operand<T, Q_IC, NT> OQ;
+    // as many as about 96 registers hold
+    constexpr int kFit = 96 / (8 * (MT + NT));
+    constexpr int D = kFit > 4 ? 4 : kFit;
+    constexpr int E = D == 1 ? 4 : 2 * D;
+    constexpr int U = (P_IC || Q_IC) ? E : 2 * D;               // units a turn of the loop
+    const __amdgpu_buffer_rsrc_t P = make_buffer(p, p_bytes);
+    const __amdgpu_buffer_rsrc_t Q = make_buffer(q, q_bytes);
+    const typename OP::At pa(m0, M, ldp);
+    const typename OQ::At qa(n0, Nn, ldq);
+    v4f* const lp = reinterpret_cast<v4f*>(lds) + (threadIdx.x >> 6) * (OP::kLdsVecs + OQ::kLdsVecs);
+    v4f* const lq = lp + OP::kLdsVecs;
+    const int pairs = ceil_div(ceil_div(K, Unit<T>::Q), 2);
+    const int nu = w < pairs ? 2 * ((pairs - w + W - 1) / W) : 0;
+    // (units past the last one start at K or beyond and load zeros)
+    auto q_of = [&](int j) { return (((j >> 1) * W + w) * 2 + (j & 1)) * Unit<T>::Q; };
+    typename OP::Raw rp[P_IC ? E : D];
+    typename OQ::Raw rq[Q_IC ? E : D];
+    typename OP::Op op[2];
+    typename OQ::Op oq[2];
+    // unit j of an IC operand, or the pair that starts with unit j of a QC one, into slot d
+    auto request_p = [&](int d, int j) {
+        if constexpr (P_IC) OP::load(rp[d], P, pa, ldp, q_of(j), K);
+        else OP::load(rp[d], P, pa, q_of(j), K);
+    };
+    auto request_q = [&](int d, int j) {
+        if constexpr (Q_IC) OQ::load(rq[d], Q, qa, ldq, q_of(j), K);
+        else OQ::load(rq[d], Q, qa, q_of(j), K);
+    };
+    auto put = [&](int d) {
+        if constexpr (!P_IC) OP::put(rp[d], pa, lp);
+        if constexpr (!Q_IC) OQ::put(rq[d], qa, lq);
+    };
+    auto take = [&](int unit) {
+        if constexpr (!P_IC) OP::take(op[unit], unit, pa, lp);
+        if constexpr (!Q_IC) OQ::take(oq[unit], unit, qa, lq);
+    };
+    auto multiply_ops = [&](const typename OP::Op& x, const typename OQ::Op& y) {
+        if constexpr (sizeof(T) == 4) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(OP::f32(x, mt, e), OQ::f32(y, nt, e),
+                                                                           acc[mt][nt], 0, 0, 0);
+        } else {
+            v8bf a[MT], b[NT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) a[mt] = OP::bf(x, mt);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) b[nt] = OQ::bf(y, nt);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], b[nt], acc[mt][nt], 0, 0, 0);
+        }
+    };
+    auto multiply = [&](int u) {                                // unit u of a turn
+        if constexpr (P_IC && Q_IC) multiply_ops(rp[u % E], rq[u % E]);
+        else if constexpr (Q_IC) multiply_ops(op[u & 1], rq[u % E]);
+        else multiply_ops(op[u & 1], oq[u & 1]);
+    };
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int d = 0; d < (E > D ? E : D); ++d) {
+        if (P_IC ? d < E : d < D) request_p(d, P_IC ? d : 2 * d);
+        if (Q_IC ? d < E : d < D) request_q(d, Q_IC ? d : 2 * d);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    put(0);
+    if constexpr (!P_IC) request_p(0, 2 * D);
+    if constexpr (!Q_IC) request_q(0, 2 * D);
+    take(0);
+    // One unit: the QC operands of the next one come from LDS (the first of a pair behind the pair's way there), the
+    // slots that are free again are requested.  No branch inside the loop: on a path around a request or a use the
+    // compiler's waits would have to cover loads that are younger than the unit needed.
+    auto unit = [&](int u, int j) {
+        __builtin_amdgcn_sched_barrier(0);                      // requests stay where they are written
+        if (u & 1) {
+            const int n = ((u + 1) / 2) % D;
+            put(n);
+            if constexpr (!P_IC) request_p(n, j + u + 1 + 2 * D);
+            if constexpr (!Q_IC) request_q(n, j + u + 1 + 2 * D);
+            take(0);
+        } else {
+            take(1);
+        }
+        multiply(u);
+        if constexpr (P_IC || Q_IC) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (P_IC) request_p(u % E, j + u + E);
+        if constexpr (Q_IC) request_q(u % E, j + u + E);
+    };
+    int j = 0;
+    for (; j + U <= nu; j += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) unit(u, j);
+    }
+#pragma unroll
+    for (int u = 0; u < U - 2; u += 2)
+        if (j + u < nu) {
+            unit(u, j);
+            unit(u + 1, j);
+        }
+}
+
+// Where element r of lane (i = lane % 16, g = lane / 16) of acc[mt][nt] lies in the tile.
+template <bool IC, int MT> __device__ __forceinline__ int tile_row(int mt, int idx) {      // idx = 4 g + r
+    return IC ? MT * idx + mt : 16 * mt + idx;
+}
+template <bool IC, int NT> __device__ __forceinline__ int tile_col(int nt, int i) { return IC ? NT * i + nt : 16 * nt + i; }
+
+constexpr int kPad = 4;
+// LDS of a workgroup: the waves' operand areas (qc_tiles 16-row tiles of QC operands a wave), then the reduction's slices
+constexpr size_t lds_bytes(int qc_tiles, int nt) {
+    const int operands = kWaves * qc_tiles * 2048, slices = kWaves * 16 * (16 * nt + kPad) * 4;
+    return operands > slices ? operands : slices;
+}
+
+// The waves' partial tiles are added in wave order through LDS, one 16-row slice (acc[mt]) at a time; `store(row, col,
+// v4f)` then gets four consecutive columns of the tile.  Every thread of the workgroup calls it.
+template <bool P_IC, bool Q_IC, int MT, int NT, typename Store>
+__device__ __forceinline__ void reduce_waves(const v4f (&acc)[MT][NT], float* lds, Store store) {
+    constexpr int TN = 16 * NT, LD = TN + kPad;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, i = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        __syncthreads();                                       // the slice before, or the waves' operand areas
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) lds[(wave * 16 + 4 * g + r) * LD + tile_col<Q_IC, NT>(nt, i)] = acc[mt][nt][r];
+        __syncthreads();
+        for (int v = t; v < 4 * TN; v += 64 * kWaves) {       // 16 rows of TN / 4 vectors
+            const int idx = v / (TN / 4), c4 = (v % (TN / 4)) * 4;
+            v4f s = *reinterpret_cast<const v4f*>(&lds[idx * LD + c4]);
+            for (int q = 1; q < kWaves; ++q) s += *reinterpret_cast<const v4f*>(&lds[(q * 16 + idx) * LD + c4]);
+            store(tile_row<P_IC, MT>(mt, idx), c4, s);
+        }
+    }
+}
+
+// ---- forward ------------------------------------------------------------------------------------------------
+struct ForwardArgs {
+    const void* A_in; const void* W; const float* bias; void* A_out;
+    unsigned a_bytes, w_bytes;
+    int B, n_out, n_in;
+    int tiles_m, tiles_n;
+};
+
+// Tile of workgroup x.  Workgroups go to the 8 XCDs in turn: an XCD takes an eighth of the tile columns, side by side,
+// and the workgroups that share weights (equal tn) follow each other there, so its L2 serves all but the first.
+// (Every eighth column instead: L = 10, N = 4096, fp32, B = 16 backward 42.1 -> 35.1 us a layer.)
+__device__ __forceinline__ void tile_of(int x, int tiles_m, int tiles_n, int* tm, int* tn) {
+    *tm = (x >> 3) % tiles_m;
+    *tn = (x >> 3) / tiles_m + (x & 7) * ceil_div(tiles_n, 8);
+}
+
+template <typename T, int MT, int NT>
+__global__ __launch_bounds__(64 * kWaves, 2) void k_forward_tile(const ForwardArgs g) {
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    int tm, tn;
+    tile_of(blockIdx.x, g.tiles_m, g.tiles_n, &tm, &tn);
+    if (tn >= g.tiles_n) return;
+    const int m0 = tm * 16 * MT, n0 = tn * 16 * NT;
+    v4f acc[MT][NT];
+    contract<T, false, false, MT, NT>(acc, lds, g.A_in, g.a_bytes, g.n_in, m0, g.B, g.W, g.w_bytes, g.n_in, n0, g.n_out,
+                                      g.n_in, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kWaves);
+    reduce_waves<false, false, MT, NT>(acc, lds, [&](int row, int col, v4f z) {
+        const int m = m0 + row, n = n0 + col;
+        if (m >= g.B || n >= g.n_out) return;
+        const v4f bs = *reinterpret_cast<const v4f*>(g.bias + n);
+        typedef T v4t __attribute__((ext_vector_type(4)));
+        const v4t a = {(T)sigmoidf(z[0] + bs[0]), (T)sigmoidf(z[1] + bs[1]), (T)sigmoidf(z[2] + bs[2]),
+                       (T)sigmoidf(z[3] + bs[3])};
+        *reinterpret_cast<v4t*>(static_cast<T*>(g.A_out) + (size_t)m * g.n_out + n) = a;
+    });
+}
+
+// ---- backward -----------------------------------------------------------------------------------------------
+struct GradJob {                    // (bp3), (bp4) of one layer
+    const void* D_op;               // delta^l as the products' operand (fp32, or its bfloat16 copy)
+    const float* D;                 // delta^l
+    const void* A_prev;
+    float* w; float* b; void* w_bf;
+    unsigned d_bytes, a_bytes;
+    int n_l, n_prev;
+    int tiles_x, tile_blocks, blocks;   // workgroups: tile_blocks for nabla_w, the rest for nabla_b
+};
+struct StepArgs {
+    // the chain: delta^l from delta^{l+1}
+    const void* D_next; const void* W_next; const void* A_l; float* D_l; void* D_l_bf;
+    unsigned d_bytes, w_bytes;
+    int n_l, n_next;
+    int tiles_m, tiles_n, chain_blocks;
+    GradJob grad[2];
+    int B;
+    float sgd_eta;
+};
+
+// nabla_b[j] = sum_b D[b][j]: 32 columns a workgroup; eight row groups each add every 8th sample in ascending order,
+// then the eight partial sums are added in group order.
+__device__ __forceinline__ void bias_block(const GradJob& g, int x, int B, float sgd_eta, float* lds) {
+    const int t = threadIdx.x, c = t & 31, rg = t >> 5;
+    const int j = x * 32 + c;
+    if (rg < 8) {
+        float s = 0.0f;
+        if (j < g.n_l) {
+            int b = rg;
+            for (; b + 56 < B; b += 64) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = g.D[(size_t)(b + 8 * u) * g.n_l + j];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s += v[u];
+            }
+            for (; b < B; b += 8) s += g.D[(size_t)b * g.n_l + j];
+        }
+        lds[rg * 32 + c] = s;
+    }
+    __syncthreads();
+    if (rg == 0 && j < g.n_l) {
+        float s = lds[c];
+#pragma unroll
+        for (int q = 1; q < 8; ++q) s += lds[q * 32 + c];
+        g.b[j] = sgd_eta != 0.0f ? fmaf(-sgd_eta, s, g.b[j]) : s;
+    }
+}
+
+// R vectors of nabla_w (N consecutive columns of row m[r] from column n[r] on): stored, or applied to the weights, whose
+// old values are then requested together (entries past the edges re-read the last ones and are not written).
+template <int R, int N, typename At, typename Value>
+__device__ __forceinline__ void put_grads(const GradJob& g, float sgd_eta, At at, Value value) {
+    typedef float vf __attribute__((ext_vector_type(N)));
+    typedef __bf16 vb __attribute__((ext_vector_type(N)));
+    if (sgd_eta == 0.0f) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            int m, n;
+            at(r, &m, &n);
+            if (m >= g.n_l || n >= g.n_prev) continue;
+            __builtin_nontemporal_store(__builtin_bit_cast(vf, value(r)),
+                                        (__attribute__((address_space(1))) vf*)(g.w + (size_t)m * g.n_prev + n));
+        }
+        return;
+    }
+    vf old[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        int m, n;
+        at(r, &m, &n);
+        old[r] = *(const __attribute__((address_space(1))) vf*)(
+            g.w + (size_t)min(m, g.n_l - 1) * g.n_prev + min(n, g.n_prev - N));
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        int m, n;
+        at(r, &m, &n);
+        if (m >= g.n_l || n >= g.n_prev) continue;
+        const vf v = __builtin_bit_cast(vf, value(r));
+        vf o;
+#pragma unroll
+        for (int c = 0; c < N; ++c) o[c] = fmaf(-sgd_eta, v[c], old[r][c]);
+        const size_t off = (size_t)m * g.n_prev + n;
+        *(__attribute__((address_space(1))) vf*)(g.w + off) = o;
+        if (g.w_bf) {                                  // bfloat16 storage: the weights the next pass multiplies with
+            vb ob;
+#pragma unroll
+            for (int c = 0; c < N; ++c) ob[c] = (__bf16)o[c];
+            *(__attribute__((address_space(1))) vb*)(static_cast<__bf16*>(g.w_bf) + off) = ob;
+        }
+    }
+}
+
+// nabla_w of one layer, workgroup x of tile_blocks.  SPLIT: the waves of a workgroup share one tile and its
+// contraction; otherwise every wave has a tile of its own (2 x 2 of them a workgroup).
+template <typename T, int GT, bool SPLIT>
+__device__ __forceinline__ void grad_block(const GradJob& g, int x, int B, float sgd_eta, float* lds) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    v4f acc[GT][GT];
+    if constexpr (SPLIT) {
+        const int m0 = x / g.tiles_x * 16 * GT, n0 = x % g.tiles_x * 16 * GT;
+        contract<T, true, true, GT, GT>(acc, lds, g.D_op, g.d_bytes, g.n_l, m0, g.n_l, g.A_prev, g.a_bytes, g.n_prev, n0,
+                                        g.n_prev, B, wave, kWaves);
+        reduce_waves<true, true, GT, GT>(acc, lds, [&](int row, int col, v4f s) {
+            put_grads<1, 4>(g, sgd_eta, [&](int, int* m, int* n) { *m = m0 + row; *n = n0 + col; }, [&](int) { return s; });
+        });
+    } else {
+        constexpr int wx = kWaves / 2;
+        const int m0 = (x / g.tiles_x * 2 + wave / wx) * 16 * GT, n0 = (x % g.tiles_x * wx + wave % wx) * 16 * GT;
+        if (m0 >= g.n_l || n0 >= g.n_prev) return;
+        contract<T, true, true, GT, GT>(acc, lds, g.D_op, g.d_bytes, g.n_l, m0, g.n_l, g.A_prev, g.a_bytes, g.n_prev, n0,
+                                        g.n_prev, B, 0, 1);
+        const int lane = threadIdx.x & 63, i = lane & 15, gr = lane >> 4;
+        typedef float vg __attribute__((ext_vector_type(GT)));
+        put_grads<4 * GT, GT>(
+            g, sgd_eta, [&](int r, int* m, int* n) { *m = m0 + GT * (4 * gr + (r & 3)) + (r >> 2); *n = n0 + GT * i; },
+            [&](int r) {
+                vg v;
+#pragma unroll
+                for (int nt = 0; nt < GT; ++nt) v[nt] = acc[r >> 2][nt][r & 3];
+                return v;
+            });
+    }
+}
+
+template <typename T, int MT, int NT, int GT, bool GSPLIT>
+__global__ __launch_bounds__(64 * kWaves, 2) void k_backward_step(const StepArgs g) {
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    int x = blockIdx.x;
+    if (x < g.chain_blocks) {
+        int tm, tn;
+        tile_of(x, g.tiles_m, g.tiles_n, &tm, &tn);
+        if (tn >= g.tiles_n) return;
+        const int m0 = tm * 16 * MT, n0 = tn * 16 * NT;
+        v4f acc[MT][NT];
+        contract<T, false, true, MT, NT>(acc, lds, g.D_next, g.d_bytes, g.n_next, m0, g.B, g.W_next, g.w_bytes, g.n_l, n0,
+                                         g.n_l, g.n_next, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kWaves);
+        reduce_waves<false, true, MT, NT>(acc, lds, [&](int row, int col, v4f u) {
+            const int m = m0 + row, n = n0 + col;
+            if (m >= g.B || n >= g.n_l) return;
+            const size_t o = (size_t)m * g.n_l + n;
+            typedef T v4t __attribute__((ext_vector_type(4)));
+            const v4t av = *reinterpret_cast<const v4t*>(static_cast<const T*>(g.A_l) + o);
+            v4f d;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float a = (float)av[c];
+                d[c] = u[c] * (a * (1.0f - a));
+            }
+            *reinterpret_cast<v4f*>(g.D_l + o) = d;
+            if constexpr (sizeof(T) == 2) {
+                const v4bf db = {(__bf16)d[0], (__bf16)d[1], (__bf16)d[2], (__bf16)d[3]};
+                *reinterpret_cast<v4bf*>(static_cast<__bf16*>(g.D_l_bf) + o) = db;
+            }
+        });
+        return;
+    }
+    x -= g.chain_blocks;
+    const bool second = x >= g.grad[0].blocks;
+    if (second) x -= g.grad[0].blocks;
+    const GradJob& j = second ? g.grad[1] : g.grad[0];
+    if (x < j.tile_blocks) grad_block<T, GT, GSPLIT>(j, x, g.B, g.sgd_eta, lds);
+    else bias_block(j, x - j.tile_blocks, g.B, g.sgd_eta, lds);
+}
+
+bool fits_buffer(unsigned long long bytes) { return bytes < 0xFFFFFFF0ull; }
+
+// Tile of a chain-side product, in 16 x 16 blocks.  A compute unit works through ceil(tiles / 256) of them; a tile
+// costs, per q of the contraction, its 16 (mt + nt) operand rows (measured: as if each took 35 cycles per unit and 16
+// rows, the rate the L2s give all compute units together) or its mt nt matrix instructions (32 cycles a unit for fp32,
+// 4 for bf16, over four SIMDs), whichever is more.  Forward, us a layer, tiles 1x1, 1x2, 2x2, 2x4, 4x4:
+//   fp32: N = 1024, B = 64: 5.4, 6.8, 9.4, 14, 23;  N = 2048, B = 64: 10.2, 10.3, 14, 23, 39;  N = 4096, B = 256: 108, 91, 77, 74, 75
+//   bf16: N = 2048, B = 128: 9.8, 8.5, 7.3, 8.5, 12;  N = 4096, B = 256: 58, 45, 33, 26, 24
+// A bf16 chain product takes at least two columns a lane (one would be a two-byte load).
+struct TileShape { int mt, nt; };
+
+TileShape chain_tile(int B, int n_out, bool bf16, bool chain) {
+    TileShape best{1, 2};
+    long best_cost = 0;
+    static const TileShape candidates[] = {{4, 4}, {2, 4}, {2, 2}, {1, 2}, {1, 1}};
+    for (const TileShape& c : candidates) {
+        if (c.mt == 1 && c.nt == 1 && chain && bf16) continue;
+        if (c.mt > 1 && c.mt > ceil_div(B, 16)) continue;
+        const int tiles = ceil_div(B, 16 * c.mt) * ceil_div(n_out, 16 * c.nt);
+        const long cost = (long)ceil_div(tiles, 256) * std::max(35 * (c.mt + c.nt), (bf16 ? 4 : 32) * c.mt * c.nt);
+        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = c; }
+    }
+    return best;
+}
+
+// How nabla_w of a layer is cut: 64 x 64 a wave where that gives at least four waves per compute unit; 32 x 32 a wave
+// below; and where even those leave SIMDs idle and the minibatch is long enough to divide, 32 x 32 a workgroup whose
+// waves share the samples.  Backward, us a layer, 64 / 32 / 32 split: fp32, N = 2048, B = 64: 16 / 20 / 33; N = 1024,
+// B = 64: 11 / 9 / 11; N = 512, B = 128: 14 / 8.2 / 7.1, B = 512: 39 / 17 / 13; bf16, N = 1024, B = 256: 12 / 9 / 13.
+enum GradKind { GRAD_WAVE_64, GRAD_WAVE_32, GRAD_SPLIT_32 };
+
+GradKind grad_kind(const GradStep& g, int B, bool bf16) {
+    if (ceil_div(g.n_l, 64) * ceil_div(g.n_prev, 64) >= 1024) return GRAD_WAVE_64;
+    if (ceil_div(g.n_l, 32) * ceil_div(g.n_prev, 32) < 1024 && B > (bf16 ? 96 : 48)) return GRAD_SPLIT_32;
+    return GRAD_WAVE_32;
+}
+
+template <typename T, int MT, int NT>
+hipError_t launch_forward(const ForwardArgs& g, hipStream_t s) {
+    k_forward_tile<T, MT, NT><<<ceil_div(g.tiles_n, 8) * 8 * g.tiles_m, 64 * kWaves, lds_bytes(MT + NT, NT), s>>>(g);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t forward_any(ForwardArgs g, TileShape t, hipStream_t s) {
+    g.tiles_m = ceil_div(g.B, 16 * t.mt);
+    g.tiles_n = ceil_div(g.n_out, 16 * t.nt);
+    if (t.mt == 4 && t.nt == 4) return launch_forward<T, 4, 4>(g, s);
+    if (t.mt == 2 && t.nt == 4) return launch_forward<T, 2, 4>(g, s);
+    if (t.mt == 2 && t.nt == 2) return launch_forward<T, 2, 2>(g, s);
+    if (t.mt == 1 && t.nt == 2) return launch_forward<T, 1, 2>(g, s);
+    return launch_forward<T, 1, 1>(g, s);
+}
+
+template <typename T, int MT, int NT, int GT, bool GSPLIT>
+hipError_t launch_step(const StepArgs& g, hipStream_t s) {
+    k_backward_step<T, MT, NT, GT, GSPLIT><<<g.chain_blocks + g.grad[0].blocks + g.grad[1].blocks, 64 * kWaves,
+                                             lds_bytes(MT, NT > GT ? NT : GT), s>>>(g);
+    return hipGetLastError();
+}
+
+template <typename T, int GT, bool GSPLIT>
+hipError_t step_any(StepArgs g, TileShape t, hipStream_t s) {
+    if (t.mt == 4 && t.nt == 4) return launch_step<T, 4, 4, GT, GSPLIT>(g, s);
+    if (t.mt == 2 && t.nt == 4) return launch_step<T, 2, 4, GT, GSPLIT>(g, s);
+    if (t.mt == 2 && t.nt == 2) return launch_step<T, 2, 2, GT, GSPLIT>(g, s);
+    if constexpr (sizeof(T) == 4)
+        if (t.mt == 1 && t.nt == 1) return launch_step<T, 1, 1, GT, GSPLIT>(g, s);
+    return launch_step<T, 1, 2, GT, GSPLIT>(g, s);
+}
+
+}  // namespace
+}  // namespace direct
+
+hipError_t launch_forward_direct(const void* W, const float* bias, const void* A_in, void* A_out, int n_out, int n_in,
+                                 int B, bool bf16, hipStream_t s) {
+    using namespace direct;
+    const unsigned long long es = bf16 ? 2 : 4, ab = es * B * n_in, wb = es * n_out * n_in;
+    if (!fits_buffer(ab) || !fits_buffer(wb)) return hipErrorInvalidValue;
+    ForwardArgs g{};
+    g.A_in = A_in; g.W = W; g.bias = bias; g.A_out = A_out;
+    g.a_bytes = (unsigned)ab; g.w_bytes = (unsigned)wb;
+    g.B = B; g.n_out = n_out; g.n_in = n_in;
+    const TileShape t = chain_tile(B, n_out, bf16, false);
+    return bf16 ? forward_any<__bf16>(g, t, s) : forward_any<float>(g, t, s);
+}
+
+hipError_t launch_backward_step(const ChainStep* c, const GradStep* grads, int ngrads, int B, bool bf16, float sgd_eta,
+                                hipStream_t s) {
+    using namespace direct;
+    if (ngrads == 2 && grad_kind(grads[0], B, bf16) != grad_kind(grads[1], B, bf16)) {
+        const hipError_t e = launch_backward_step(c, grads, 1, B, bf16, sgd_eta, s);
+        return e != hipSuccess ? e : launch_backward_step(nullptr, grads + 1, 1, B, bf16, sgd_eta, s);
+    }
+    const unsigned long long es = bf16 ? 2 : 4;
+    StepArgs g{};
+    g.B = B; g.sgd_eta = sgd_eta;
+    TileShape t{1, 2};
+    if (c) {
+        const unsigned long long db = es * B * c->n_next, wb = es * c->n_next * c->n_l;
+        if (!fits_buffer(db) || !fits_buffer(wb)) return hipErrorInvalidValue;
+        t = chain_tile(B, c->n_l, bf16, true);
+        g.D_next = bf16 ? c->D_next_bf : static_cast<const void*>(c->D_next);
+        g.W_next = c->W_next; g.A_l = c->A_l; g.D_l = c->D_l; g.D_l_bf = c->D_l_bf;
+        g.d_bytes = (unsigned)db; g.w_bytes = (unsigned)wb;
+        g.n_l = c->n_l; g.n_next = c->n_next;
+        g.tiles_m = ceil_div(B, 16 * t.mt);
+        g.tiles_n = ceil_div(c->n_l, 16 * t.nt);
+            g.chain_blocks = ceil_div(g.tiles_n, 8) * 8 * g.tiles_m;
+    }
+    const GradKind kind = ngrads > 0 ? grad_kind(grads[0], B, bf16) : GRAD_WAVE_32;
+    const bool split = kind == GRAD_SPLIT_32;
+    const int gt = kind == GRAD_WAVE_64 ? 4 : 2;
+    for (int i = 0; i < ngrads; ++i) {
+        const GradStep& in = grads[i];
+        GradJob& j = g.grad[i];
+        const unsigned long long db = es * B * in.n_l, ab = es * B * in.n_prev;
+        if (!fits_buffer(db) || !fits_buffer(ab)) return hipErrorInvalidValue;
+        j.D_op = bf16 ? in.D_bf : static_cast<const void*>(in.D);
+        j.D = in.D; j.A_prev = in.A_prev; j.w = in.w; j.b = in.b; j.w_bf = in.w_bf;
+        j.d_bytes = (unsigned)db; j.a_bytes = (unsigned)ab;
+        j.n_l = in.n_l; j.n_prev = in.n_prev;
+        const int tm = split ? 16 * gt : 2 * 16 * gt, tn = split ? 16 * gt : kWaves / 2 * 16 * gt;
+        j.tiles_x = ceil_div(in.n_prev, tn);
+        j.tile_blocks = j.tiles_x * ceil_div(in.n_l, tm);
+        j.blocks = j.tile_blocks + ceil_div(in.n_l, 32);
+    }
+    if (g.chain_blocks + g.grad[0].blocks + g.grad[1].blocks == 0) return hipSuccess;
+    switch (kind) {
+        case GRAD_WAVE_64: return bf16 ? step_any<__bf16, 4, false>(g, t, s) : step_any<float, 4, false>(g, t, s);
+        case GRAD_WAVE_32: return bf16 ? step_any<__bf16, 2, false>(g, t, s) : step_any<float, 2, false>(g, t, s);
+        default: return bf16 ? step_any<__bf16, 2, true>(g, t, s) : step_any<float, 2, true>(g, t, s);
+    }
+}
+
+}  // namespace lf

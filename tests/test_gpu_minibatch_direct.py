@@ -1,0 +1,76 @@
+"""The direct minibatch kernels (fragments straight from memory, chain step and gradients in one launch) at the edges of
+their tiles and of the rules that choose them, against the oracle; and the same bits from every way to enqueue them."""
+import numpy as np
+import pytest
+
+from lf_inputs import make_net
+from tests.gpu_util import check_against_oracle, log, run_gpu, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def _tensors(g):
+    return [to_np(t).view(np.uint32).copy() for t in g.nabla_w + g.nabla_b]
+
+
+@pytest.mark.parametrize("shape,B,dtype", [
+    ((3, 4), 2, "f32"),               # less than one tile and one unit of the contraction in every dimension
+    ((3, 8), 1, "bf16"),
+    ((5, 520), 37, "f32"),            # tiles of 16 x 16, a ragged third row block; gradients 32 x 32 a wave
+    ((4, 520), 77, "f32"),            # gradients whose waves share the samples, a ragged last unit
+    ((4, 520), 130, "bf16"),
+    ((3, 2052), 15, "f32"),           # gradients 64 x 64 a wave, ragged edges of both kinds
+    ((3, 2048), 64, "f32"),           # tiles of 16 x 32, all full
+    ((4, 1032), 20, "bf16"),          # tiles of 16 x 16 and 16 x 32
+    ((3, 1500), 100, "f32"),          # tiles of 32 x 32, a ragged fourth row block
+    ((3, 2056), 130, "f32"),          # tiles of 32 x 64, rows of the last one past the minibatch
+    ((3, 4104), 64, "bf16"),
+    ((3, 2056), 400, "f32"),          # tiles of 64 x 64
+    ((3, 3080), 200, "bf16"),
+    ((72, 1000, 36, 1500, 8), 19, "f32"),      # contractions shorter than a turn of the waves; unequal widths
+    ((264, 8, 2056, 136), 33, "bf16"),
+])
+def test_direct_kernels_match_oracle_with_the_same_bits_from_every_schedule(shape, B, dtype):
+    import paper_1801_04928_amd as P
+    import torch
+    widths = shape if len(shape) > 2 else (shape[1],) * shape[0]
+    L = len(widths)
+    net = make_net(L, widths[0] if len(shape) == 2 else widths, B, dtype=dtype, seed=sum(widths) + B)
+    g = run_gpu(net, 1)                                   # chain step and the gradients above it in one launch
+    rep = check_against_oracle(net, g)
+    log(f"direct kernels {shape} B={B} {dtype}: worst {rep['worst']:.2e}")
+    want = _tensors(g)
+    stream = torch.cuda.current_stream().cuda_stream
+    ways = [(sched, k) for sched in (P.LF_SCHED_AUTO, P.LF_SCHED_STREAMS) for k in sorted({1, L - 1})]
+    for sched, k in ways:                                 # STREAMS: every product a launch of its own
+        g.set_schedule(sched)
+        for t in g.nabla_w + g.nabla_b:
+            t.fill_(float("nan"))
+        g.forward()
+        g.backward(k)
+        torch.cuda.synchronize()
+        assert all(np.array_equal(a, b) for a, b in zip(want, _tensors(g))), (sched, k)
+    g.forward()
+    st = P.lf_backward_leapfrog_noalloc(g.handle, g.y.data_ptr(), 1, stream)
+    assert st in (P.LF_OK, P.LF_EUNSUPPORTED)             # (the widest are beyond that entry point's limit)
+    torch.cuda.synchronize()
+    assert all(np.array_equal(a, b) for a, b in zip(want, _tensors(g)))
+    # the descent step: layer l's rides one launch later, layers 3 and 2 share the last one
+    results = []
+    for sched in (P.LF_SCHED_AUTO, P.LF_SCHED_STREAMS):
+        g.load(net)
+        if g.master_w is not None:
+            for m, w in zip(g.master_w, g.w):
+                m.copy_(w)
+        g.set_schedule(sched)
+        g.set_sgd(0.125)
+        g.forward()
+        g.backward(L - 1)
+        torch.cuda.synchronize()
+        results.append([to_np(t).copy() for t in g.w + g.b])
+    if dtype == "f32":                                    # eta is a power of two: one rounding, of the exact difference
+        for l in range(2, L + 1):
+            exact = net.w(l).astype(np.float64) - 0.125 * want[l - 2].view(np.float32).astype(np.float64)
+            assert np.array_equal(results[0][l - 2], exact.astype(np.float32)), f"layer {l}"
+    assert all(np.array_equal(a, b) for a, b in zip(*results))
+    g.close()
