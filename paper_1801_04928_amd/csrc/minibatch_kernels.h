@@ -126,6 +126,37 @@ template <typename T, int NT> struct Operand<T, true, NT> {
     }
 };
 
+template <int W, int FROM, int TO>
+__device__ __forceinline__ void interleave_ops() {              // operations FROM .. TO - 1: W writes, then reads
+    if constexpr (FROM < TO) {
+        if constexpr (FROM < W) {
+            __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        } else {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        interleave_ops<W, FROM + 1, TO>();
+    }
+}
+// Issue order of one unit as scheduling groups (mask 0x008 matrix instruction, 0x020 memory read, 0x100 LDS read, 0x200
+// LDS write): after every matrix instruction its share of the W writes to LDS, each with the request that refills its
+// register, and of the R reads, all within the first WINDOW of the M matrix instructions; behind each quarter (the one
+// of four values of q) the IC requests that refill the registers it has read.  A SIMD often has a single wave, whose
+// matrix instructions (32 cycles each in fp32) stand still while it issues anything in a row; left alone, the compiler
+// puts a pair's 16 writes and 16 requests together, and the reads right in front of their use.  us per pass, before ->
+// after: L = 32, N = 4096, B = 256 6966 -> 6005; L = 16, N = 2048, B = 64 396 -> 376; unequal widths, B = 100, 100 -> 95.
+template <int M, int WINDOW, int W, int R, int IC, int I = 0>
+__device__ __forceinline__ void interleave() {
+    if constexpr (I < M) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        constexpr int ops = W + R, from = I < WINDOW ? I * ops / WINDOW : ops;
+        constexpr int to = I + 1 < WINDOW ? (I + 1) * ops / WINDOW : ops;
+        interleave_ops<W, from, to>();
+        if constexpr (IC > 0 && (I + 1) % (M / 4) == 0) __builtin_amdgcn_sched_group_barrier(0x020, IC, 0);
+        interleave<M, WINDOW, W, R, IC, I + 1>();
+    }
+}
+
 // acc[mt][nt] += P Q^T of one 16*MT x 16*NT tile over the units of wave w of W that share the contraction: pairs of
 // units are dealt to the waves in turn.  A QC operand is requested D pairs ahead of its way through LDS, which is half
 // a pair ahead of its use; an IC operand E units ahead of its use.  lds: the workgroup's area, kLdsVecs vectors a wave.
@@ -140,6 +171,9 @@ __device__ __forceinline__ void contract(v4f (&acc)[MT][NT], float* lds, const v
     constexpr int D = kFit > 4 ? 4 : kFit;
     constexpr int E = D == 1 ? 4 : 2 * D;
     constexpr int U = (P_IC || Q_IC) ? E : 2 * D;               // units a turn of the loop
+    constexpr int kMfmas = MT * NT * (sizeof(T) == 4 ? 4 : 1);  // matrix instructions a unit
+    // bfloat16's matrix instructions are too short to cover the requests (N = 2048, B = 128: 466 -> 471 us interleaved)
+    constexpr bool kInterleave = sizeof(T) == 4;
     const __amdgpu_buffer_rsrc_t P = make_buffer(p, p_bytes);
     const __amdgpu_buffer_rsrc_t Q = make_buffer(q, q_bytes);
     const typename OP::At pa(m0, M, ldp);
@@ -228,9 +262,15 @@ __device__ __forceinline__ void contract(v4f (&acc)[MT][NT], float* lds, const v
             take(1);
         }
         multiply(u);
-        if constexpr (P_IC || Q_IC) __builtin_amdgcn_sched_barrier(0);
+        if constexpr ((P_IC || Q_IC) && !kInterleave) __builtin_amdgcn_sched_barrier(0);
         if constexpr (P_IC) request_p(u % E, j + u + E);
         if constexpr (Q_IC) request_q(u % E, j + u + E);
+        if constexpr (kInterleave) {
+            constexpr int R = (P_IC ? 0 : MT) + (Q_IC ? 0 : NT), IC = (P_IC ? 1 : 0) + (Q_IC ? 1 : 0);
+            constexpr int window = IC ? kMfmas / 2 : 3 * kMfmas / 4;
+            if (u & 1) interleave<kMfmas, window, 2 * R, R, IC>();
+            else interleave<kMfmas, window, 0, R, IC>();
+        }
     };
     int j = 0;
     for (; j + U <= nu; j += U) {
