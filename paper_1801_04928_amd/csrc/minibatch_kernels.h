@@ -633,7 +633,7 @@ hipError_t launch_backward_step(const ChainStep* c, const GradStep* grads, int n
         g.n_l = c->n_l; g.n_next = c->n_next;
         g.tiles_m = ceil_div(B, 16 * t.mt);
         g.tiles_n = ceil_div(c->n_l, 16 * t.nt);
-            g.chain_blocks = ceil_div(g.tiles_n, 8) * 8 * g.tiles_m;
+        g.chain_blocks = ceil_div(g.tiles_n, 8) * 8 * g.tiles_m;
     }
     const GradKind kind = ngrads > 0 ? grad_kind(grads[0], B, bf16) : GRAD_WAVE_32;
     const bool split = kind == GRAD_SPLIT_32;
