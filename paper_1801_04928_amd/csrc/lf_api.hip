@@ -29,21 +29,6 @@ constexpr int kMaxDevices = 64;
 void* g_static_scratch[kMaxDevices];   // device address of `scratch` on each device; null = not asked yet
 std::mutex g_static_scratch_mutex;
 
-// Worker streams of a device, shared by all nets on it: worker j of every net enqueues on stream j.  The device has
-// four hardware queues per process, and the runtime deals streams to them in turn: with streams of their own, the
-// workers of a process's second net fall on the queue of the caller's stream and wait for the chain that feeds them.
-// L = 48, N = 8192, B = 512, k = 8, ms a pass: 10.84 where both workers have queues of their own, 12.84 where one shares
-// the caller's; two streams, or one, that some other part of the process holds decide which.  Events order the work of
-// each net, so sharing only makes the works of two nets follow each other on a stream.  A pass that is being captured
-// takes streams of the net's own instead (a capture claims the streams it passes through).  At most
-// kMaxWorkerStreams; destroyed with the last net that has used them.
-struct SharedStreams {
-    std::vector<hipStream_t> streams;
-    int nets = 0;
-};
-SharedStreams g_shared_streams[kMaxDevices];
-std::mutex g_shared_streams_mutex;
-
 constexpr size_t kAlign = 256;
 constexpr int kMaxL = 4096;
 constexpr int kMaxWorkerStreams = 32;   // workers beyond this share streams (worker j -> stream j mod 32)
@@ -197,9 +182,7 @@ struct lf_net {
     const void* x1;
     bool have_params, have_grads, fwd_done, bwd_done;
     bool stepped;                      // a fused descent step has changed the weights since the last forward pass
-    std::vector<hipStream_t> workers;      // of the pass being enqueued: the device's shared streams, or own_workers
-    std::vector<hipStream_t> own_workers;  // of captured passes
-    int shared_device = -1;                // the device whose shared streams this net counts as a user of
+    std::vector<hipStream_t> workers;
     std::vector<hipEvent_t> ev_delta;  // index l-2
     std::vector<hipEvent_t> ev_done;   // per worker stream
     std::string err;
@@ -254,69 +237,27 @@ lf_status fail_hip(lf_net* net, hipError_t e, const char* what) {
         if (e_ != hipSuccess) return fail_hip(net, e_, #call);    \
     } while (0)
 
-lf_status grow_streams(lf_net* net, std::vector<hipStream_t>& v, size_t want) {
-    while (v.size() < want) {
-        hipStream_t q;
-        LF_HIP(net, hipStreamCreateWithFlags(&q, hipStreamNonBlocking));
-        v.push_back(q);
-    }
-    return LF_OK;
-}
-
-bool is_capturing(hipStream_t s) {
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &status) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return status != hipStreamCaptureStatusNone;
-}
-
-// Per-layer events, and for this pass of the caller's stream s `want` worker streams, with an end-of-work event each.
-lf_status ensure_worker_streams(lf_net* net, size_t want, hipStream_t s) {
+// Per-layer events, and `want` worker streams with an end-of-work event each.
+lf_status ensure_worker_streams(lf_net* net, size_t want) {
     const size_t M = (size_t)net->L - 1;
     while (net->ev_delta.size() < M) {
         hipEvent_t e;
         LF_HIP(net, hipEventCreateWithFlags(&e, hipEventDisableTiming));
         net->ev_delta.push_back(e);
     }
-    while (net->ev_done.size() < want) {
+    while (net->workers.size() < want) {
+        hipStream_t s;
+        LF_HIP(net, hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
+        net->workers.push_back(s);
         hipEvent_t e;
         LF_HIP(net, hipEventCreateWithFlags(&e, hipEventDisableTiming));
         net->ev_done.push_back(e);
     }
-    net->workers.clear();
-    if (want == 0) return LF_OK;
-    int dev = -1;
-    LF_HIP(net, hipGetDevice(&dev));
-    if (dev >= kMaxDevices || (net->shared_device >= 0 && net->shared_device != dev) || is_capturing(s)) {
-        const lf_status st = grow_streams(net, net->own_workers, want);
-        if (st == LF_OK) net->workers.assign(net->own_workers.begin(), net->own_workers.begin() + want);
-        return st;
-    }
-    std::lock_guard<std::mutex> lock(g_shared_streams_mutex);
-    SharedStreams& shared = g_shared_streams[dev];
-    if (net->shared_device < 0) {
-        net->shared_device = dev;
-        ++shared.nets;
-    }
-    const lf_status st = grow_streams(net, shared.streams, want);
-    if (st == LF_OK) net->workers.assign(shared.streams.begin(), shared.streams.begin() + want);
-    return st;
-}
-
-void release_worker_streams(lf_net* net) {
-    for (hipStream_t q : net->own_workers) (void)hipStreamDestroy(q);
-    if (net->shared_device < 0) return;
-    std::lock_guard<std::mutex> lock(g_shared_streams_mutex);
-    SharedStreams& shared = g_shared_streams[net->shared_device];
-    if (--shared.nets > 0) return;
-    for (hipStream_t q : shared.streams) (void)hipStreamDestroy(q);
-    shared.streams.clear();
+    return LF_OK;
 }
 
 // The stream schedule's workers: k streams (none for the sequential pass, which runs on the caller's).
-lf_status ensure_workers(lf_net* net, int k, hipStream_t s) {
+lf_status ensure_workers(lf_net* net, int k) {
     // Workers beyond the plan's number of streams share them: worker j runs on stream j mod that number.
     // LF_WORKER_STREAMS overrides it (tuning).
     int cap = single_sample_path(net->N, net->B, net->dt) ? kMaxWorkerStreams
@@ -325,7 +266,7 @@ lf_status ensure_workers(lf_net* net, int k, hipStream_t s) {
         const int v = std::atoi(e);
         if (v >= 1 && v <= kMaxWorkerStreams) cap = v;
     }
-    return ensure_worker_streams(net, k > 1 ? (size_t)(k < cap ? k : cap) : 0, s);
+    return ensure_worker_streams(net, k > 1 ? (size_t)(k < cap ? k : cap) : 0);
 }
 
 // A minibatch net (or a bf16 one of any B) whose backward products are the direct kernels.
@@ -579,7 +520,7 @@ lf_status backward_redundant(lf_net* net, const void* y, int k, hipStream_t s) {
         return fail(net, LF_EUNSUPPORTED, "lf_backward_leapfrog: LF_SCHED_REDUNDANT has chains for at most 8 workers");
     if (net->sgd_eta != 0.0f)
         return fail(net, LF_EUNSUPPORTED, "lf_backward_leapfrog: LF_SCHED_REDUNDANT does not take the descent step");
-    lf_status st = ensure_worker_streams(net, (size_t)k, s);       // a stream per thread, also for k = 1
+    lf_status st = ensure_worker_streams(net, (size_t)k);       // a stream per thread, also for k = 1
     if (st != LF_OK) return st;
     auto chain = [&](int l, const float* d_next, float* d_l, float* partial, hipStream_t q) -> hipError_t {
         return lf::launch_chain_gemvT_f32(static_cast<const float*>(net->w[l - 1]), d_next,
@@ -989,7 +930,7 @@ lf_status lf_backward_leapfrog(lf_net* net, const void* y, int k, void* hip_stre
         return st;
     }
     if (net->sched == LF_SCHED_AUTO && direct_minibatch(net)) return backward_steps(net, y, s);
-    st = ensure_workers(net, k, s);
+    st = ensure_workers(net, k);
     if (st != LF_OK) return st;
     return backward_streams(net, y, k, s, net->partial(), net->raw(), /*in_line=*/k == 1);
 }
@@ -1060,7 +1001,7 @@ const char* lf_last_error(const lf_net* net) { return net ? net->err.c_str() : g
 
 void lf_destroy(lf_net* net) {
     if (!net) return;
-    release_worker_streams(net);
+    for (hipStream_t s : net->workers) (void)hipStreamDestroy(s);
     for (hipEvent_t e : net->ev_delta) (void)hipEventDestroy(e);
     for (hipEvent_t e : net->ev_done) (void)hipEventDestroy(e);
     if (net->p_abort_host) (void)hipHostFree(net->p_abort_host);

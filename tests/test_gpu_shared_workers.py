@@ -1,5 +1,5 @@
-"""Nets of one device share its worker streams: passes of several nets from several caller streams and threads, with one
-of them captured or destroyed meanwhile, give the bits of each net's sequential pass."""
+"""Several nets on one device: passes from several caller streams and threads, with one net captured or destroyed
+meanwhile, give the bits of each net's sequential pass."""
 import threading
 
 import numpy as np
@@ -24,7 +24,7 @@ def _same(g, want):
     return all(np.array_equal(a, b) for a, b in zip(want, _bits(g)))
 
 
-def test_nets_that_share_worker_streams_keep_their_bits():
+def test_nets_used_together_keep_their_bits():
     import paper_1801_04928_amd as P
     import torch
     shapes = [(6, 516, 1, "f32", 5), (5, 264, 37, "f32", 3), (4, 520, 40, "bf16", 2), (7, 260, 1, "f32", 2)]
@@ -55,7 +55,7 @@ def test_nets_that_share_worker_streams_keep_their_bits():
         t.join()
     torch.cuda.synchronize()
     assert all(_same(g, w) for g, w in zip(nets, want))
-    # captured passes leave the shared streams alone: another net's eager pass may be enqueued meanwhile
+    # another net's eager pass may be enqueued while a pass is being captured
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=streams[0], capture_error_mode="thread_local"):
         nets[0].forward()
@@ -72,7 +72,7 @@ def test_nets_that_share_worker_streams_keep_their_bits():
         passes(1, 1)
         torch.cuda.synchronize()
         assert _same(nets[0], want[0]) and _same(nets[1], want[1]), replay
-    # the streams outlive the net that brought them
+    # a destroyed net takes nothing from the others
     nets[0].close()
     for i in (1, 2, 3):
         _clear(nets[i])
@@ -81,7 +81,7 @@ def test_nets_that_share_worker_streams_keep_their_bits():
         torch.cuda.synchronize()
         assert _same(nets[i], want[i]), i
         nets[i].close()
-    g = run_gpu(make_net(6, 516, 1, seed=522), 1)               # and come anew after the last one
+    g = run_gpu(make_net(6, 516, 1, seed=522), 1)               # nor the last one from the next
     g.set_schedule(P.LF_SCHED_STREAMS)
     _clear(g)
     g.forward()
