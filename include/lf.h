@@ -208,9 +208,11 @@ lf_status lf_backward_leapfrog(lf_net* net, const void* y, int k, void* hip_stre
  * the library instead of the caller's workspace.  Same arguments, same checks, same results bit for bit as
  * lf_backward_leapfrog with LF_SCHED_STREAMS (k only names the worker a layer would belong to; the gradients do
  * not depend on it).  lf_forward must have run (with LF_SCHED_STREAMS it allocates nothing either).
- * Limits: the chain scratch of the net's shape (a part of lf_workspace_bytes) must fit
- * lf_noalloc_scratch_limit() bytes -- 8 MiB: every B = 1 net up to N = 8192, small minibatch nets -- else
- * LF_EUNSUPPORTED, with both sizes in lf_last_error(); the handle's schedule
+ * Limits: the chain scratch that the net's shape is charged for must fit lf_noalloc_scratch_limit() bytes -- 8 MiB:
+ * every B = 1 fp32 net up to N = 8192, small minibatch nets, minibatch nets with so many outputs that no product
+ * is split -- else LF_EUNSUPPORTED, with both sizes in lf_last_error().  The charge depends on the shape alone: the
+ * row-block partial sums at B = 1; for a minibatch the split-K partial sums of its widest product (a kernel that
+ * needs none is charged all the same).  The handle's schedule
  * must be LF_SCHED_AUTO, LF_SCHED_STREAMS or LF_SCHED_PERSISTENT (which only matter to the other calls).
  * Every call on one GPU uses that GPU's one array: calls that overlap in time on one GPU (two streams, two
  * handles, two threads) race on it; order them on one stream or with events.  The array is held from the

@@ -788,17 +788,23 @@ size_t split_workspace_floats(int n_out, int B, bool bf16) {             // enou
     return bf16 ? (size_t)16 * B * n_out : 0;                            // no plan splits more than 16 ways
 }
 
-size_t split_scratch_floats(int n_out, int K, int B, bool bf16, const GemmPlan& plan) {
-    if (plan.chain != GEMM_DIRECT) {
-        const int s = chain_splits(n_out, K, B, plan.chain, plan.chain_split_target);
-        return s > 1 ? (size_t)s * B * n_out : 0;
+size_t noalloc_scratch_floats(const int* n, int L, int B, bool bf16, const GemmPlan& plan) {
+    size_t used = 0, tiles_128 = 0, tiles_256 = 0;
+    auto add = [&](size_t& most, int splits, int n_out) {
+        if (splits > 1) most = std::max(most, (size_t)splits * B * n_out);
+    };
+    for (int l = 2; l < L; ++l) {
+        const int n_out = n[l - 1], K = n[l];
+        if (plan.chain != GEMM_DIRECT) add(used, chain_splits(n_out, K, B, plan.chain, plan.chain_split_target), n_out);
+        add(tiles_256, chain_splits(n_out, K, B, GEMM_BIG, 128), n_out);
+        const int tiles = ceil_div(n_out, 128) * ceil_div(B, 128), kt = ceil_div(K, bf16 ? 64 : 32);
+        int s = 1;
+        while (tiles * s < 512 && s < 16 && kt / (s * 2) >= 4) s *= 2;
+        add(tiles_128, s, n_out);
     }
-    // The direct kernels use none: what is charged is the published limit of the entry point that asks, the partial
-    // sums of a product of 128 x 128 tiles split to at most 512 workgroups.
-    const int tiles = ceil_div(n_out, 128) * ceil_div(B, 128), kt = ceil_div(K, bf16 ? 64 : 32);
-    int s = 1;
-    while (tiles * s < 512 && s < 16 && kt / (s * 2) >= 4) s *= 2;
-    return s > 1 ? (size_t)s * B * n_out : 0;
+    const int N = *std::max_element(n, n + L);
+    const bool wide = bf16 && (ceil_div(B, 256) * ceil_div(N, 256) >= 64 || (N >= 6144 && B >= 48) || (N >= 4096 && B >= 384));
+    return std::max(used, wide ? std::min(tiles_128, tiles_256) : tiles_128);
 }
 
 hipError_t launch_fwd_gemm(const void* W, const float* bias, const void* A_in, void* A_out, float* raw,

@@ -945,14 +945,12 @@ lf_status lf_backward_leapfrog_noalloc(lf_net* net, const void* y, int k, void* 
         return fail(net, LF_EUNSUPPORTED, "lf_backward_leapfrog_noalloc: runs the stream schedule's kernels only");
     // what the chain products of this net are charged for: the single-sample row-block partial sums, or the split-K
     // partials of a minibatch
-    size_t need = net->lay.partial_bytes;
-    if (!single_sample_path(net->N, net->B, net->dt))
-        for (int l = 2; l < net->L; ++l)
-            need = std::max(need, 4 * lf::split_scratch_floats(net->width(l), net->width(l + 1), net->B,
-                                                               net->dt == LF_BF16, net->gemm));
+    const size_t need = single_sample_path(net->N, net->B, net->dt)
+                            ? net->lay.partial_bytes
+                            : 4 * lf::noalloc_scratch_floats(net->n.data(), net->L, net->B, net->dt == LF_BF16, net->gemm);
     if (need > LF_STATIC_SCRATCH_BYTES)
         return fail(net, LF_EUNSUPPORTED,
-                    "lf_backward_leapfrog_noalloc: this shape needs " + std::to_string(need) +
+                    "lf_backward_leapfrog_noalloc: this shape is charged " + std::to_string(need) +
                         " bytes of chain scratch, the static scratch holds " + std::to_string(LF_STATIC_SCRATCH_BYTES));
     void* area = nullptr;
     st = static_scratch_of_current_device(net, &area);

@@ -55,9 +55,12 @@ struct GemmPlan {
 GemmPlan gemm_plan(int N, int B, bool bf16);
 // Floats of scratch that hold the split-K partials of a wide product with a B x n_out result under any plan.
 size_t split_workspace_floats(int n_out, int B, bool bf16);
-// Floats of chain scratch a net is charged for by lf_backward_leapfrog_noalloc, for a B x n_out result and contraction
-// length K.
-size_t split_scratch_floats(int n_out, int K, int B, bool bf16, const GemmPlan& plan);
+// Floats of chain scratch that lf_backward_leapfrog_noalloc charges a minibatch net of L layers of n[0 .. L-1] neurons for.
+// This is the published limit of that call and does not follow the choice of kernels, which may change from one version
+// to the next (the direct kernels use no scratch at all): the split-K partials of 128 x 128 tiles split to at most 512
+// workgroups, or, for wide bf16 nets, those of 256 x 256 tiles split to at most 128 where they are fewer; and never
+// less than what the plan's kernels do use.
+size_t noalloc_scratch_floats(const int* n, int L, int B, bool bf16, const GemmPlan& plan);
 
 // ---- minibatch path: wide bf16 nets ---------------------------------------------------------------
 
