@@ -533,6 +533,9 @@ bool fits_buffer(unsigned long long bytes) { return bytes < 0xFFFFFFF0ull; }
 // 4 for bf16, over four SIMDs), whichever is more.  Forward, us a layer, tiles 1x1, 1x2, 2x2, 2x4, 4x4:
 //   fp32: N = 1024, B = 64: 5.4, 6.8, 9.4, 14, 23;  N = 2048, B = 64: 10.2, 10.3, 14, 23, 39;  N = 4096, B = 256: 108, 91, 77, 74, 75
 //   bf16: N = 2048, B = 128: 9.8, 8.5, 7.3, 8.5, 12;  N = 4096, B = 256: 58, 45, 33, 26, 24
+// Rows past the minibatch may be part of a tile where that saves a turn: B = 33 .. 48 beyond N = 8192 takes one turn of
+// 4x4 tiles instead of two of 2x4 (bf16, N = 9216, B = 48: forward 65 -> 53, backward 94 -> 86; N = 10240, B = 40: 74 -> 62,
+// 111 -> 99; fp32 within 1 % there, N = 16384: 313 -> 281, 573 -> 548).
 // A bf16 chain product takes at least two columns a lane (one would be a two-byte load).
 struct TileShape { int mt, nt; };
 
@@ -542,7 +545,7 @@ TileShape chain_tile(int B, int n_out, bool bf16, bool chain) {
     static const TileShape candidates[] = {{4, 4}, {2, 4}, {2, 2}, {1, 2}, {1, 1}};
     for (const TileShape& c : candidates) {
         if (c.mt == 1 && c.nt == 1 && chain && bf16) continue;
-        if (c.mt > 1 && c.mt > ceil_div(B, 16)) continue;
+        if (c.mt > 1 && c.mt / 2 >= ceil_div(B, 16)) continue;         // half of its rows would do
         const int tiles = ceil_div(B, 16 * c.mt) * ceil_div(n_out, 16 * c.nt);
         const long cost = (long)ceil_div(tiles, 256) * std::max(35 * (c.mt + c.nt), (bf16 ? 4 : 32) * c.mt * c.nt);
         if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = c; }

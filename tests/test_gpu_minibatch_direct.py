@@ -74,3 +74,13 @@ def test_direct_kernels_match_oracle_with_the_same_bits_from_every_schedule(shap
             assert np.array_equal(results[0][l - 2], exact.astype(np.float32)), f"layer {l}"
     assert all(np.array_equal(a, b) for a, b in zip(*results))
     g.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tile_with_a_row_block_past_the_minibatch(dtype):
+    """64 x 64 tiles for three row blocks of 16 samples (wider nets than 8192 take them)."""
+    net = make_net(3, 8200, 41, dtype=dtype, seed=8241, cache=False)
+    g = run_gpu(net, 1)
+    rep = check_against_oracle(net, g, sample_tiles=(40, 64), rng=np.random.default_rng(5))
+    log(f"N=8200 B=41 {dtype}: worst {rep['worst']:.2e}")
+    g.close()

@@ -58,3 +58,15 @@ OK, UNSUPPORTED = 0, 5
 ])
 def test_nets_served_without_allocation(program, N, B, dtype, want):
     assert _routes(program, [N] * 4, B, dtype)[2] == want
+
+
+@pytest.mark.parametrize("N,B,dtype,mt,nt", [
+    (8192, 40, "bf16", 2, 4), (9216, 32, "bf16", 2, 4),        # one turn of the compute units
+    (8256, 33, "bf16", 4, 4), (9216, 48, "bf16", 4, 4),        # 4 x 4 blocks, one of them past the minibatch: still one turn
+    (16384, 48, "f32", 4, 4),
+])
+def test_tile_of_a_direct_product(program, N, B, dtype, mt, nt):
+    forward, backward, _ = _routes(program, [N] * 4, B, dtype, LF_GEMM_BIG="0")
+    type_ = {"f32": "f", "bf16": "DF16b"}[dtype]
+    assert len(forward) == 3 and all(f"k_forward_tileI{type_}Li{mt}ELi{nt}E" in name for name in forward)
+    assert sum(f"k_backward_stepI{type_}Li{mt}ELi{nt}E" in name for name in backward) == 2
