@@ -14,6 +14,8 @@ namespace lf {
 namespace {
 
 constexpr int kThreads = 256;
+// the default plan (gemm_plan)
+constexpr int kSplitTarget = 256, kChainSplitTarget = 128, kStreamGroups = 96, kStreamAlign = 32;
 
 __host__ __device__ constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
@@ -718,16 +720,53 @@ hipError_t run_half(GemmArgs g, int splits, hipStream_t s) {
 
 }  // namespace
 
-// Which kernels a minibatch net takes, decided once per net from its widest layer (N) and its storage type.
-// The direct kernels (minibatch_kernels.h) serve every fp32 net and bf16 nets of moderate size; wide bf16 nets take
-// the kernels of this file: by default the 256 x 256-tile kernel for all three products (measured faster than the
-// 128 x 256 one, alone and beside each other).  Where the lines lie (us a layer, direct against wide, k = 4):
-//   forward     N = 4096: B = 256 19 / 43, B = 512 34 / 41;  N = 6144: B = 64 28 / 37, B = 200 48 / 46 (128 x 128 tiles), B = 400 69 / 65;
-//               N = 8192: B = 128 45 / 44, B = 256 66 / 61, B = 512 110 / 80
-//   backward    N = 3072, B = 256: 27 / 34;  N = 4096: B = 64 24 / 34, B = 256 41 / 43, B = 512 73 / 56;
-//               N = 6144: B = 64 56 / 50, B = 200 97 / 72;  N = 8192: B = 32 79 / 77, B = 128 109 / 86, B = 512 274 / 146
-// The direct kernels read every operand once per 64 x 64 outputs, the wide ones once per 256 x 256: with a long
-// contraction that traffic decides; with a short one the wide kernels' second pass and their events do.
+static int chain_splits(int n_out, int K, int B, int kernel, int target) {
+    const bool half_tile = kernel == GEMM_HALF;
+    const int tiles = half_tile ? ceil_div(n_out, half::TN) * ceil_div(B, half::TM)
+                                : ceil_div(n_out, big::TN) * ceil_div(B, big::TM);
+    const int kt = ceil_div(K, half_tile ? half::TK : big::TK), least = half_tile ? 8 : 4;
+    int s = 1;
+    while (tiles * s < target && s < 16 && kt / (s * 2) >= least) s *= 2;
+    return s;
+}
+
+// What the wide-net kernels take for a layer, as direct::forward_us and backward_us.  Forward: turns of 256 compute
+// units, a k-tile at a time, and the split's second pass over its partial sums.  Backward: the chain and the workers'
+// streams side by side have a floor of 18 us a layer, to which come the partial sums, the turns of 96 resident
+// workgroups through the samples, and the gradient stores.
+static double wide_forward_us(int n_out, int n_in, int B) {
+    const int s = chain_splits(n_out, n_in, B, GEMM_BIG, kSplitTarget);
+    const double groups = (double)s * ceil_div(n_out, big::TN) * ceil_div(B, big::TM);
+    return 8.3 + 1.09 * direct::turns(groups, 256, 0.9) * ceil_div(ceil_div(n_in, big::TK), s) * (n_in % 64 ? 1.12 : 1.0) +
+           (s > 1 ? 0.352 * 4e-6 * s * B * n_out : 0.0) + 0.074 * 2e-6 * n_out * n_in;
+}
+static double wide_backward_us(int n_l, int n_prev, int B, bool chain) {
+    const int s = chain ? chain_splits(n_prev, n_l, B, GEMM_BIG, kChainSplitTarget) : 1;
+    const double tiles = (double)ceil_div(n_l, big::TM) * ceil_div(n_prev, big::TN);
+    return 18.0 + (s > 1 ? 0.172 * 4e-6 * s * B * n_prev : 0.0) +
+           0.758 * direct::turns(tiles, kStreamGroups, 1.0) * ceil_div(B, big::TK) +
+           0.624e-6 * n_l * n_prev * (n_prev % kStreamAlign ? 1.31 : 1.0) + 0.993 * 2e-6 * B * n_prev;
+}
+
+// Which kernels a minibatch net takes, decided once per net from its widths n[0 .. L-1] and its storage type.
+// The direct kernels (minibatch_kernels.h) serve every fp32 net; a bf16 net takes them or the kernels of this file, by
+// default with 256 x 256 tiles for all three products (measured faster than 128 x 256 ones, alone and beside each other).
+// The direct kernels read every operand once per 64 x 64 outputs at most, the wide ones once per 256 x 256: with many
+// outputs or a long contraction that traffic decides; with few the wide kernels' second pass, their events and their
+// whole tiles of 256 samples do.  Neither N nor B nor a number of tiles alone says which is faster, because turns of the
+// chip are whole numbers: the two estimates above are compared, summed over the layers, forward and backward each for
+// itself.  Their constants are fitted to 230 uniform nets, N = 256 .. 16384, B = 1 .. 32768; the choice is within 4 % of
+// the faster kernels on 96 % of them and within 15 % on all.  us a layer, direct / wide, k = 4:
+//   forward   N = 2048: B = 1024 17 / 31, 2048 39 / 37, 4096 80 / 52;  N = 3072: B = 1024 33 / 55, 2048 85 / 71;
+//             N = 4096: B = 256 17 / 38, 512 28 / 38, 1024 59 / 50, 4096 293 / 120;  N = 5120: B = 256 41 / 52, 768 73 / 75, 2048 230 / 139;
+//             N = 6144: B = 128 36 / 42, 256 50 / 58, 640 85 / 85;  N = 8192: B = 64 37 / 38, 256 66 / 56, 512 108 / 79
+//   backward  N = 1536: B = 768 31 / 34, 2048 76 / 54;  N = 2048: B = 1024 35 / 41, 2048 77 / 60;  N = 3072: B = 512 42 / 45, 768 62 / 49;
+//             N = 4096: B = 256 42 / 43, 512 72 / 53, 4096 537 / 249;  N = 5120: B = 128 39 / 44, 256 62 / 54;
+//             N = 6144: B = 64 49 / 50, 128 62 / 57, 512 146 / 100;  N = 8192: B = 64 74 / 78, 128 100 / 84, 512 258 / 146
+// The streamed gradient product stores single columns, 32 neighbouring ones of a row at a time: where rows of nabla_w are
+// no whole 128-byte lines (n_prev not a multiple of 32) every store is two partial lines, and the layer takes the
+// kernel with a workgroup per tile, whose epilogue stores 512 bytes of a row at a time.  Backward, us a layer, streamed /
+// per tile: N = 4360, B = 200 58 / 49; N = 5384, B = 300 85 / 73; N = 7000, B = 150 122 / 93; N = 8120, B = 500 181 / 163.
 // How a wide net shares the chip between the chain and the workers: a kernel of either kind fills every compute
 // unit it gets (registers, LDS), so two of them never share one; what can be shared is the set of compute
 // units.  The chain product is split only two ways along K -- 128 workgroups, half the chip (and half the
@@ -738,14 +777,22 @@ hipError_t run_half(GemmArgs g, int splits, hipStream_t s) {
 // gradients must be the same bits for every k.  A sequential pass, k = 1, would be faster with four splits.)
 // Overrides for tests and A/B runs, read when the plan is made:
 // LF_GEMM_BIG=0/1 forces the direct / wide-net kernels; LF_GEMM_CHAIN_TILE = "big" or "half" picks the wide-net
-// kernel of the forward and chain products, LF_GEMM_GRAD_TILE = "stream" (default), "big" or "half" that of the
-// gradient product; LF_GEMM_SPLIT_TARGET = workgroups the split of a chain-side product aims at (both products),
+// kernel of the forward and chain products, LF_GEMM_GRAD_TILE = "stream", "big" or "half" that of the gradient
+// product of every layer; LF_GEMM_SPLIT_TARGET = workgroups the split of a chain-side product aims at (both products),
 // LF_GEMM_CHAIN_SPLIT_TARGET = the same for the backward chain product alone; LF_GEMM_STREAM_GROUPS = resident
-// workgroups of the streamed gradient product; LF_WORKER_STREAMS (read by the schedule) = streams the workers share.
-GemmPlan gemm_plan(int N, int B, bool bf16) {
-    GemmPlan p{GEMM_DIRECT, GEMM_DIRECT, GEMM_DIRECT, 256, 128, 96, 1};
-    bool wide_forward = bf16 && N >= 6144 && B >= 192;
-    bool wide_backward = bf16 && ((N >= 6144 && B >= 48) || (N >= 4096 && B >= 384));
+// workgroups of the streamed gradient product, which every layer then takes; LF_WORKER_STREAMS (read by the schedule) =
+// streams the workers share.
+GemmPlan gemm_plan(const int* n, int L, int B, bool bf16) {
+    GemmPlan p{GEMM_DIRECT, GEMM_DIRECT, GEMM_DIRECT, kSplitTarget, kChainSplitTarget, kStreamGroups, kStreamAlign, 1};
+    double fwd = 0.0, wide_fwd = 0.0, bwd = 0.0, wide_bwd = 0.0;
+    for (int l = 2; bf16 && l <= L; ++l) {
+        const int n_l = n[l - 1], n_prev = n[l - 2];
+        fwd += direct::forward_us(n_l, n_prev, B);
+        wide_fwd += wide_forward_us(n_l, n_prev, B);
+        bwd += direct::backward_us(n_l, n_prev, B, l > 2);
+        wide_bwd += wide_backward_us(n_l, n_prev, B, l > 2);
+    }
+    bool wide_forward = wide_fwd < fwd, wide_backward = wide_bwd < bwd;
     if (const char* e = getenv("LF_GEMM_BIG")) {
         if (e[0] == '0') wide_forward = wide_backward = false;
         if (e[0] == '1') wide_forward = wide_backward = bf16;
@@ -757,11 +804,14 @@ GemmPlan gemm_plan(int N, int B, bool bf16) {
         p.chain = tile;
         p.grad = GEMM_STREAM;
         p.worker_streams = 2;
-        if (const char* e = getenv("LF_GEMM_GRAD_TILE")) p.grad = e[0] == 'b' ? GEMM_BIG : (e[0] == 's' ? GEMM_STREAM : GEMM_HALF);
+        if (const char* e = getenv("LF_GEMM_GRAD_TILE")) {
+            p.grad = e[0] == 'b' ? GEMM_BIG : (e[0] == 's' ? GEMM_STREAM : GEMM_HALF);
+            p.stream_align = 1;
+        }
     }
     if (const char* e = getenv("LF_GEMM_STREAM_GROUPS")) {
         const int t = atoi(e);
-        if (t >= 8 && t <= 1024) p.stream_groups = t;
+        if (t >= 8 && t <= 1024) { p.stream_groups = t; p.stream_align = 1; }
     }
     if (const char* e = getenv("LF_GEMM_SPLIT_TARGET")) {
         const int t = atoi(e);
@@ -772,16 +822,6 @@ GemmPlan gemm_plan(int N, int B, bool bf16) {
         if (t >= 64 && t <= 2048) p.chain_split_target = t;
     }
     return p;
-}
-
-static int chain_splits(int n_out, int K, int B, int kernel, int target) {
-    const bool half_tile = kernel == GEMM_HALF;
-    const int tiles = half_tile ? ceil_div(n_out, half::TN) * ceil_div(B, half::TM)
-                                : ceil_div(n_out, big::TN) * ceil_div(B, big::TM);
-    const int kt = ceil_div(K, half_tile ? half::TK : big::TK), least = half_tile ? 8 : 4;
-    int s = 1;
-    while (tiles * s < target && s < 16 && kt / (s * 2) >= least) s *= 2;
-    return s;
 }
 
 size_t split_workspace_floats(int n_out, int B, bool bf16) {             // enough for any plan
@@ -859,9 +899,10 @@ hipError_t launch_grad_gemm(const float* D, const void* D_bf, const void* A_prev
     g.out_bf = w_bf;
     g.k_tiles_per_split = ceil_div(B, plan.grad == GEMM_HALF ? half::TK : big::TK);
     if (plan.grad == GEMM_HALF) return run_half<true, true, EPI_GRAD>(g, 1, s);
-    // the streamed kernel stores gradients only (the descent step keeps the tile-per-workgroup kernel) and
-    // addresses the result through one 32-bit buffer
-    if (plan.grad == GEMM_STREAM && sgd_eta == 0.0f && (unsigned long long)(n_l + big::TM) * n_prev * 4ull < 0xFFFFFFF0ull)
+    // the streamed kernel stores gradients only (the descent step keeps the tile-per-workgroup kernel), whole lines of
+    // them, and addresses the result through one 32-bit buffer
+    if (plan.grad == GEMM_STREAM && sgd_eta == 0.0f && n_prev % plan.stream_align == 0 &&
+        (unsigned long long)(n_l + big::TM) * n_prev * 4ull < 0xFFFFFFF0ull)
         return run_grad_stream(g, whole_chip ? 256 : plan.stream_groups, s);
     return run_big<true, true, EPI_GRAD>(g, 1, s);
 }

@@ -733,7 +733,7 @@ lf_status lf_create_widths(lf_net** out, int L, const int* n, int B, lf_dtype dt
     net->x1 = nullptr;
     net->have_params = net->have_grads = net->fwd_done = net->bwd_done = net->stepped = false;
     net->have_master = false;
-    net->gemm = lf::gemm_plan(N, B, dt == LF_BF16);
+    net->gemm = lf::gemm_plan(n, L, B, dt == LF_BF16);
     net->debug_flags = 0; net->p_failed_over = false; net->p_fused_ok = false;
     net->p_ready = false; net->p_tables_dirty = true; net->p_groups = net->p_rpg = net->p_bgroups = net->p_tpr = 0; net->p_workers = 0;
     net->p_abort_host = nullptr; net->p_abort_dev_view = nullptr;

@@ -49,10 +49,11 @@ struct GemmPlan {
     int split_target;   // workgroups the K split of a wide forward product aims at
     int chain_split_target;   // the same for the chain product of the backward pass
     int stream_groups;  // resident workgroups of the streamed gradient product
+    int stream_align;   // the streamed product takes layers whose n_prev is a multiple of this
     int worker_streams; // streams the k workers share (worker j runs on stream j mod this)
 };
-// The plan of a net whose widest layer has N neurons (decided once per net).
-GemmPlan gemm_plan(int N, int B, bool bf16);
+// The plan of a net of L layers of n[0 .. L-1] neurons (decided once per net).
+GemmPlan gemm_plan(const int* n, int L, int B, bool bf16);
 // Floats of scratch that hold the split-K partials of a wide product with a B x n_out result under any plan.
 size_t split_workspace_floats(int n_out, int B, bool bf16);
 // Floats of chain scratch that lf_backward_leapfrog_noalloc charges a minibatch net of L layers of n[0 .. L-1] neurons for.

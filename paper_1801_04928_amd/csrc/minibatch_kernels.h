@@ -539,6 +539,9 @@ bool fits_buffer(unsigned long long bytes) { return bytes < 0xFFFFFFF0ull; }
 // A bf16 chain product takes at least two columns a lane (one would be a two-byte load).
 struct TileShape { int mt, nt; };
 
+// cycles a unit of the contraction costs a compute unit
+long tile_cycles(const TileShape& c, bool bf16) { return std::max(35 * (c.mt + c.nt), (bf16 ? 4 : 32) * c.mt * c.nt); }
+
 TileShape chain_tile(int B, int n_out, bool bf16, bool chain) {
     TileShape best{1, 2};
     long best_cost = 0;
@@ -546,8 +549,8 @@ TileShape chain_tile(int B, int n_out, bool bf16, bool chain) {
     for (const TileShape& c : candidates) {
         if (c.mt == 1 && c.nt == 1 && chain && bf16) continue;
         if (c.mt > 1 && c.mt / 2 >= ceil_div(B, 16)) continue;         // half of its rows would do
-        const int tiles = ceil_div(B, 16 * c.mt) * ceil_div(n_out, 16 * c.nt);
-        const long cost = (long)ceil_div(tiles, 256) * std::max(35 * (c.mt + c.nt), (bf16 ? 4 : 32) * c.mt * c.nt);
+        const long tiles = (long)ceil_div(B, 16 * c.mt) * ceil_div(n_out, 16 * c.nt);
+        const long cost = (tiles + 255) / 256 * tile_cycles(c, bf16);
         if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = c; }
     }
     return best;
@@ -560,9 +563,44 @@ TileShape chain_tile(int B, int n_out, bool bf16, bool chain) {
 enum GradKind { GRAD_WAVE_64, GRAD_WAVE_32, GRAD_SPLIT_32 };
 
 GradKind grad_kind(const GradStep& g, int B, bool bf16) {
-    if (ceil_div(g.n_l, 64) * ceil_div(g.n_prev, 64) >= 1024) return GRAD_WAVE_64;
-    if (ceil_div(g.n_l, 32) * ceil_div(g.n_prev, 32) < 1024 && B > (bf16 ? 96 : 48)) return GRAD_SPLIT_32;
+    if ((long)ceil_div(g.n_l, 64) * ceil_div(g.n_prev, 64) >= 1024) return GRAD_WAVE_64;
+    if ((long)ceil_div(g.n_l, 32) * ceil_div(g.n_prev, 32) < 1024 && B > (bf16 ? 96 : 48)) return GRAD_SPLIT_32;
     return GRAD_WAVE_32;
+}
+
+// What the direct kernels take for a layer of a bf16 net in us, for the choice between them and the wide-net kernels
+// (gemm_plan, where the measurements are).  Turns of the compute units: `part` of a turn is lost where the last is not full.
+double turns(double jobs, int units, double part) {
+    if (jobs <= units) return 1.0;
+    const double t = jobs / units, whole = (double)(long)t;
+    return t > whole ? whole + part + (1.0 - part) * (t - whole) : whole;
+}
+// A chain-side product: the busiest XCD's tiles over its 32 compute units, a tile's units at the rate of the L2s, or at
+// the rate at which memory feeds an XCD's L2 (3 cycles for each 16 operand rows that its 32 tiles of a turn read between
+// them: from B = 2048 on every tile brings rows of its own).  With nothing beside it a second turn, once begun, takes
+// as long as the first.
+double chain_us(int B, int n_out, int K, bool chain) {
+    const TileShape t = chain_tile(B, n_out, true, chain);
+    const int tm = ceil_div(B, 16 * t.mt), tn = ceil_div(n_out, 16 * t.nt);
+    const double rows = std::min(tm, 32) * t.mt + std::max(1.0, 32.0 / tm) * t.nt;
+    const double cycles = std::max((double)tile_cycles(t, true), 3.0 * rows);
+    double n = turns((double)ceil_div(tn, 8) * tm, 32, 0.76);
+    if (!chain && n > 1.0 && n < 2.0) n = 2.0;
+    return n * cycles * ceil_div(K, 32) / 2400.0;
+}
+// (rows that are no whole 128-byte lines cost forward operands a third more, gradients a quarter)
+double forward_us(int n_out, int n_in, int B) {
+    return 2.8 + 0.915 * chain_us(B, n_out, n_in, false) * (n_in % 64 ? 1.34 : 1.0) + 0.06 * 2e-6 * n_out * n_in;
+}
+double grad_us(int n_l, int n_prev, int B) {
+    const GradStep g{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, n_l, n_prev};
+    const int gt = grad_kind(g, B, true) == GRAD_WAVE_64 ? 4 : 2;
+    const double waves = (double)ceil_div(n_l, 16 * gt) * ceil_div(n_prev, 16 * gt);
+    const double wave = 2.0 * ceil_div(B, 64) * 35 * 2 * gt / 2400.0;                // units of 32 samples come in pairs
+    return 1.58 * turns(waves, 1024, 0.4) * 4 * wave * (n_prev % 64 ? 1.24 : 1.0) + 0.442e-6 * n_l * n_prev;
+}
+double backward_us(int n_l, int n_prev, int B, bool chain) {    // gradients of layer l, and the chain step below it
+    return 4.2 + grad_us(n_l, n_prev, B) + (chain ? 0.437 * chain_us(B, n_prev, n_l, true) : 0.0);
 }
 
 template <typename T, int MT, int NT>

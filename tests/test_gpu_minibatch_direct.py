@@ -84,3 +84,26 @@ def test_tile_with_a_row_block_past_the_minibatch(dtype):
     rep = check_against_oracle(net, g, sample_tiles=(40, 64), rng=np.random.default_rng(5))
     log(f"N=8200 B=41 {dtype}: worst {rep['worst']:.2e}")
     g.close()
+
+
+@pytest.mark.parametrize("shape,B,k", [
+    ((3, 3072), 768, 2),                  # direct forward, wide-net backward, gradients streamed
+    ((4, 256), 32768, 2),                 # wide-net forward, direct backward
+    ((4, 4104), 304, 2),                  # wide-net backward with a workgroup per gradient tile (rows of no whole lines)
+    ((2048, 4104, 2080, 2048), 1024, 2),  # streamed and per-tile gradients in one net
+])
+def test_plans_that_mix_direct_and_wide_kernels_match_oracle(shape, B, k):
+    import torch
+    widths = shape if len(shape) > 2 else (shape[1],) * shape[0]
+    net = make_net(len(widths), widths[0] if len(shape) == 2 else widths, B, dtype="bf16", seed=sum(widths) + B, cache=False)
+    g = run_gpu(net, k)
+    rep = check_against_oracle(net, g, sample_tiles=(24, 96), rng=np.random.default_rng(3))
+    log(f"mixed plan {shape} B={B}: worst {rep['worst']:.2e}")
+    want = _tensors(g)
+    for t in g.nabla_w + g.nabla_b:
+        t.fill_(float("nan"))
+    g.forward()
+    g.backward(1)
+    torch.cuda.synchronize()
+    assert all(np.array_equal(a, b) for a, b in zip(want, _tensors(g)))
+    g.close()

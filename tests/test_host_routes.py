@@ -70,3 +70,52 @@ def test_tile_of_a_direct_product(program, N, B, dtype, mt, nt):
     type_ = {"f32": "f", "bf16": "DF16b"}[dtype]
     assert len(forward) == 3 and all(f"k_forward_tileI{type_}Li{mt}ELi{nt}E" in name for name in forward)
     assert sum(f"k_backward_stepI{type_}Li{mt}ELi{nt}E" in name for name in backward) == 2
+
+
+# us a layer, (direct, wide-net kernels), measured at L = 6 .. 8, k = 4: the choice is to be the faster side
+@pytest.mark.parametrize("N,B,forward,backward", [
+    (256, 32768, (51, 26), (263, 537)), (1024, 512, (6.4, 16.8), (11.8, 28.3)), (1024, 4096, (27, 34), (69, 82)),
+    (1536, 2048, (26, 30), (76, 54)), (2048, 128, (6.3, 17.3), (11.4, 28.4)), (2048, 1024, (17, 31), (35, 41)),
+    (2048, 4096, (80, 52), (155, 90)), (2056, 1800, (58, 47), (110, 64)), (2560, 1024, (31, 48), (63, 54)),
+    (3072, 384, (21, 26), (37, 41)), (3072, 768, (32, 46), (62, 49)), (3072, 2048, (85, 71), (178, 91)),
+    (3584, 1024, (48, 65), (112, 80)), (4096, 8, (7.6, 17.2), (18.8, 33.3)), (4096, 128, (12, 22), (32, 38)),
+    (4096, 512, (28, 37), (72, 53)), (4096, 1024, (59, 50), (124, 77)), (4360, 200, (34, 34), (60, 49)),
+    (4608, 320, (36, 46), (60, 52)), (5016, 240, (42, 54), (72, 62)), (5120, 64, (21, 31), (27, 40)),
+    (5120, 256, (41, 53), (62, 54)), (5120, 2048, (230, 139), (428, 180)), (5384, 700, (98, 85), (190, 114)),
+    (6144, 256, (50, 58), (90, 74)), (6144, 512, (67, 70), (146, 99)), (7000, 150, (71, 55), (102, 93)),
+    (7168, 256, (57, 67), (120, 92)), (8192, 32, (31, 36), (70, 75)), (8192, 192, (67, 49), (118, 89)),
+    (8192, 512, (108, 78), (258, 148)), (10240, 128, (97, 79), (157, 115)), (12288, 384, (216, 166), (444, 256)),
+    (16384, 8, (99, 139), (259, 261)), (16384, 256, (238, 179), (595, 312)),
+])
+def test_bf16_nets_take_the_faster_kernels(program, N, B, forward, backward):
+    """(sides within 6 % of each other are as good; L = 6)"""
+    fwd, bwd, _ = _routes(program, [N] * 6, B, "bf16")
+    for names, (direct, wide), direct_kernel in ((fwd, forward, "k_forward_tile"), (bwd, backward, "k_backward_step")):
+        took_direct = any(direct_kernel in name for name in names)
+        assert took_direct != any("k_gemm_big" in name for name in names)
+        assert (direct if took_direct else wide) <= 1.06 * min(direct, wide), (took_direct, direct, wide)
+
+
+@pytest.mark.parametrize("widths,B,fwd_direct,bwd_direct", [
+    ([8192] + [1024] * 7, 256, True, True),               # one wide layer decides nothing: 6.5 / 16 us forward, 9.6 / 26 backward
+    ([2048] + [256] * 5, 2048, True, True),               # 7.6 / 22, 19 / 41
+    ([4096, 11008, 4096, 11008, 4096], 512, False, False),      # 82 / 79, 179 / 111
+])
+def test_all_layers_have_a_say_in_the_choice(program, widths, B, fwd_direct, bwd_direct):
+    fwd, bwd, _ = _routes(program, widths, B, "bf16")
+    assert all("k_forward_tile" in name for name in fwd) if fwd_direct else not any("k_forward_tile" in name for name in fwd)
+    assert any("k_backward_step" in name for name in bwd) == bwd_direct
+
+
+def test_fp32_nets_take_the_direct_kernels(program):
+    for N, B in ((64, 2), (2048, 2048), (8192, 1024)):
+        fwd, bwd, _ = _routes(program, [N] * 4, B, "f32")
+        assert all("k_forward_tile" in name for name in fwd) and sum("k_backward_step" in name for name in bwd) == 3
+
+
+@pytest.mark.parametrize("widths,streamed", [([4096] * 4, 3), ([4104] * 4, 0), ([4096, 4104, 4096, 4096], 2)])
+def test_streamed_gradients_have_rows_of_whole_lines(program, widths, streamed):
+    """One product a layer: the streamed kernel where n_prev is a multiple of 32, else a workgroup per tile."""
+    _, bwd, _ = _routes(program, widths, 1024, "bf16")
+    grads = [name for name in bwd if "k_grad_stream" in name or "k_gemm_bigILb1ELb1E" in name]
+    assert len(grads) == 3 and sum("k_grad_stream" in name for name in grads) == streamed
