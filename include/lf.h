@@ -34,7 +34,9 @@
  *     from and join hip_stream through events); a replay gives the same results as the recorded calls would.
  *   - Every function returns an lf_status; nothing throws, nothing aborts.
  *     After a non-OK status lf_last_error() describes it.  A handle is not
- *     thread-safe.  Different handles share nothing, with one restriction: the persistent
+ *     thread-safe.  Different handles share nothing that one could have to wait for because of the other
+ *     (handles whose passes run on one stream, and so follow each other, also share worker streams), with one
+ *     restriction: the persistent
  *     kernels (LF_SCHED_PERSISTENT, LF_SCHED_FUSED, and LF_SCHED_AUTO where it picks them: B = 1,
  *     fp32, layers 2..L-1 of one width N <= 4096, the first and last no wider) need every workgroup
  *     of a launch resident at once, because the

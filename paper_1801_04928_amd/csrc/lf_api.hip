@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <list>
 #include <mutex>
 #include <new>
 #include <string>
@@ -28,6 +29,23 @@ namespace {
 constexpr int kMaxDevices = 64;
 void* g_static_scratch[kMaxDevices];   // device address of `scratch` on each device; null = not asked yet
 std::mutex g_static_scratch_mutex;
+
+// Worker streams of the nets that are driven from one stream of the caller's.  The device has four hardware queues per
+// process, and the runtime deals streams to them in turn: with streams of their own alone, the workers of a process's
+// second net fall on the queue of the caller's stream and wait for the chain that feeds them.  L = 48, N = 8192, B = 512,
+// k = 8, ms a pass: 10.6 where both workers have queues of their own, 11.3 on average over three nets in turn, 12.8 for the
+// worst of them.  Passes on one stream follow each other there, and every event a worker waits for is recorded on that
+// stream: on shared worker streams no work waits for any that it would not follow anyway.  (Between nets on different
+// streams that would not hold: one whose stream is held up would hold up the other.)  A net joins the streams of
+// the stream of its first pass, its home; passes on other streams take streams of the net's own.
+struct SharedWorkers {
+    int device;
+    hipStream_t caller;
+    std::vector<hipStream_t> streams;      // at most kMaxWorkerStreams
+    int nets;                              // destroyed with the last of these
+};
+std::list<SharedWorkers> g_shared_workers;
+std::mutex g_shared_workers_mutex;
 
 constexpr size_t kAlign = 256;
 constexpr int kMaxL = 4096;
@@ -182,7 +200,9 @@ struct lf_net {
     const void* x1;
     bool have_params, have_grads, fwd_done, bwd_done;
     bool stepped;                      // a fused descent step has changed the weights since the last forward pass
-    std::vector<hipStream_t> workers;
+    std::vector<hipStream_t> workers;      // of the pass being enqueued: own_workers or home_workers
+    std::vector<hipStream_t> own_workers, home_workers;
+    SharedWorkers* home = nullptr;         // home_workers are the first of home->streams
     std::vector<hipEvent_t> ev_delta;  // index l-2
     std::vector<hipEvent_t> ev_done;   // per worker stream
     std::string err;
@@ -237,27 +257,86 @@ lf_status fail_hip(lf_net* net, hipError_t e, const char* what) {
         if (e_ != hipSuccess) return fail_hip(net, e_, #call);    \
     } while (0)
 
-// Per-layer events, and `want` worker streams with an end-of-work event each.
-lf_status ensure_worker_streams(lf_net* net, size_t want) {
+lf_status grow_streams(lf_net* net, std::vector<hipStream_t>& v, size_t want) {
+    while (v.size() < want) {
+        hipStream_t q;
+        LF_HIP(net, hipStreamCreateWithFlags(&q, hipStreamNonBlocking));
+        v.push_back(q);
+    }
+    return LF_OK;
+}
+
+bool is_capturing(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;                       // not known: as if
+    }
+    return status != hipStreamCaptureStatusNone;
+}
+
+// `want` worker streams in net->home_workers, shared with the other nets of this device and stream.
+lf_status grow_home(lf_net* net, size_t want, int device, hipStream_t s) {
+    std::lock_guard<std::mutex> lock(g_shared_workers_mutex);
+    if (!net->home) {
+        for (SharedWorkers& h : g_shared_workers)
+            if (h.device == device && h.caller == s) net->home = &h;
+        if (!net->home) {
+            g_shared_workers.push_back({device, s, {}, 0});
+            net->home = &g_shared_workers.back();
+        }
+        ++net->home->nets;
+    }
+    const lf_status st = grow_streams(net, net->home->streams, want);
+    if (st == LF_OK) net->home_workers.assign(net->home->streams.begin(), net->home->streams.begin() + want);
+    return st;
+}
+
+// For this pass on the caller's stream s: per-layer events, and `want` worker streams with an end-of-work event each.
+// Streams and events are created in the first pass that wants so many, and only there.
+lf_status ensure_worker_streams(lf_net* net, size_t want, hipStream_t s) {
     const size_t M = (size_t)net->L - 1;
     while (net->ev_delta.size() < M) {
         hipEvent_t e;
         LF_HIP(net, hipEventCreateWithFlags(&e, hipEventDisableTiming));
         net->ev_delta.push_back(e);
     }
-    while (net->workers.size() < want) {
-        hipStream_t s;
-        LF_HIP(net, hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
-        net->workers.push_back(s);
+    while (net->ev_done.size() < want) {
         hipEvent_t e;
         LF_HIP(net, hipEventCreateWithFlags(&e, hipEventDisableTiming));
         net->ev_done.push_back(e);
     }
+    if (want == 0) return LF_OK;
+    int device = -1;
+    LF_HIP(net, hipGetDevice(&device));
+    try {
+        // (hipStreamPerThread is one handle for a stream of every thread)
+        if (net->own_workers.size() < want && s != hipStreamPerThread && !is_capturing(s) &&
+            (!net->home || (net->home->device == device && net->home->caller == s))) {
+            const lf_status st = grow_home(net, want, device, s);
+            if (st != LF_OK) return st;
+        }
+        const lf_status st = grow_streams(net, net->own_workers, want);
+        if (st != LF_OK) return st;
+        const bool at_home = net->home && net->home->device == device && net->home->caller == s;
+        net->workers = at_home && net->home_workers.size() >= want ? net->home_workers : net->own_workers;
+    } catch (const std::bad_alloc&) {
+        return fail(net, LF_ENOMEM, "out of host memory");
+    }
     return LF_OK;
 }
 
+void release_worker_streams(lf_net* net) {
+    for (hipStream_t q : net->own_workers) (void)hipStreamDestroy(q);
+    if (!net->home) return;
+    std::lock_guard<std::mutex> lock(g_shared_workers_mutex);
+    if (--net->home->nets > 0) return;
+    for (hipStream_t q : net->home->streams) (void)hipStreamDestroy(q);
+    g_shared_workers.remove_if([&](const SharedWorkers& h) { return &h == net->home; });
+}
+
 // The stream schedule's workers: k streams (none for the sequential pass, which runs on the caller's).
-lf_status ensure_workers(lf_net* net, int k) {
+lf_status ensure_workers(lf_net* net, int k, hipStream_t s) {
     // Workers beyond the plan's number of streams share them: worker j runs on stream j mod that number.
     // LF_WORKER_STREAMS overrides it (tuning).
     int cap = single_sample_path(net->N, net->B, net->dt) ? kMaxWorkerStreams
@@ -266,7 +345,7 @@ lf_status ensure_workers(lf_net* net, int k) {
         const int v = std::atoi(e);
         if (v >= 1 && v <= kMaxWorkerStreams) cap = v;
     }
-    return ensure_worker_streams(net, k > 1 ? (size_t)(k < cap ? k : cap) : 0);
+    return ensure_worker_streams(net, k > 1 ? (size_t)(k < cap ? k : cap) : 0, s);
 }
 
 // A minibatch net (or a bf16 one of any B) whose backward products are the direct kernels.
@@ -520,7 +599,7 @@ lf_status backward_redundant(lf_net* net, const void* y, int k, hipStream_t s) {
         return fail(net, LF_EUNSUPPORTED, "lf_backward_leapfrog: LF_SCHED_REDUNDANT has chains for at most 8 workers");
     if (net->sgd_eta != 0.0f)
         return fail(net, LF_EUNSUPPORTED, "lf_backward_leapfrog: LF_SCHED_REDUNDANT does not take the descent step");
-    lf_status st = ensure_worker_streams(net, (size_t)k);       // a stream per thread, also for k = 1
+    lf_status st = ensure_worker_streams(net, (size_t)k, s);    // a stream per thread, also for k = 1
     if (st != LF_OK) return st;
     auto chain = [&](int l, const float* d_next, float* d_l, float* partial, hipStream_t q) -> hipError_t {
         return lf::launch_chain_gemvT_f32(static_cast<const float*>(net->w[l - 1]), d_next,
@@ -930,7 +1009,7 @@ lf_status lf_backward_leapfrog(lf_net* net, const void* y, int k, void* hip_stre
         return st;
     }
     if (net->sched == LF_SCHED_AUTO && direct_minibatch(net)) return backward_steps(net, y, s);
-    st = ensure_workers(net, k);
+    st = ensure_workers(net, k, s);
     if (st != LF_OK) return st;
     return backward_streams(net, y, k, s, net->partial(), net->raw(), /*in_line=*/k == 1);
 }
@@ -999,7 +1078,7 @@ const char* lf_last_error(const lf_net* net) { return net ? net->err.c_str() : g
 
 void lf_destroy(lf_net* net) {
     if (!net) return;
-    for (hipStream_t s : net->workers) (void)hipStreamDestroy(s);
+    release_worker_streams(net);
     for (hipEvent_t e : net->ev_delta) (void)hipEventDestroy(e);
     for (hipEvent_t e : net->ev_done) (void)hipEventDestroy(e);
     if (net->p_abort_host) (void)hipHostFree(net->p_abort_host);

@@ -21,7 +21,7 @@ static std::set<stream_t> used, live;
 static int created;                                  // streams, events and pinned blocks
 static bool capturing;
 static uintptr_t next_handle = 0x1000;
-static int caller_1, caller_2;
+static int caller_1, caller_2, caller_3;
 static stream_t launch_stream;
 static std::vector<std::string> launched;            // names of the kernels, in order
 static std::map<const void*, std::string>& kernels() { static std::map<const void*, std::string> m; return m; }
