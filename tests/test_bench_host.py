@@ -40,12 +40,15 @@ def test_descent_step_work_reads_and_rewrites_the_weights():
     ("void lf::(anonymous namespace)::big::k_gemm_big<false, false, 0>(lf::(anonymous namespace)::GemmArgs)", None),
     ("void lf::(anonymous namespace)::big::k_gemm_big<true, true, 3>(lf::(anonymous namespace)::GemmArgs)", "gradient product (bp4)"),
     ("void lf::(anonymous namespace)::big::k_grad_stream<0>(lf::(anonymous namespace)::GemmArgs, int, int)", "gradient product (bp4)"),
-    ("void lf::(anonymous namespace)::k_gemm<float, false, true, 0>(lf::(anonymous namespace)::GemmArgs)", "chain product (bp2)"),
-    ("void lf::(anonymous namespace)::k_gemm<float, true, true, 3>(lf::(anonymous namespace)::GemmArgs)", "gradient product (bp4)"),
-    ("void lf::(anonymous namespace)::k_gemm<__bf16, false, false, 1>(lf::(anonymous namespace)::GemmArgs)", None),
-    ("_ZN2lf12_GLOBAL__N_114k_split_finishIDF16bLi2EEEvPKfimiS3_PKT_PvPDF16b", "chain split finish (bp2)"),
-    ("_ZN2lf12_GLOBAL__N_114k_split_finishIDF16bLi1EEEvPKfimiS3_PKT_PvPDF16b", None),
-    ("void lf::(anonymous namespace)::k_split_finish<float, 2>(float const*, int, unsigned long, int)", "chain split finish (bp2)"),
+    ("void lf::(anonymous namespace)::half::k_gemm_half<true, true, 3>(lf::(anonymous namespace)::GemmArgs)", "gradient product (bp4)"),
+    ("void lf::direct::(anonymous namespace)::k_backward_step<float, 4, 4, 4, false>(lf::direct::(anonymous namespace)::StepArgs)",
+     "chain product with the gradients of the layer above (bp2)-(bp4)"),
+    ("_ZN2lf6direct12_GLOBAL__N_115k_backward_stepIDF16bLi1ELi2ELi4ELb0EEEvNS1_8StepArgsE",
+     "chain product with the gradients of the layer above (bp2)-(bp4)"),
+    ("void lf::direct::(anonymous namespace)::k_forward_tile<float, 4, 4>(lf::direct::(anonymous namespace)::ForwardArgs)", None),
+    ("_ZN2lf12_GLOBAL__N_114k_split_finishILi2EEEvPKfimiS3_PKDF16bPvPDF16b", "chain split finish (bp2)"),
+    ("_ZN2lf12_GLOBAL__N_114k_split_finishILi1EEEvPKfimiS3_PKDF16bPvPDF16b", None),
+    ("void lf::(anonymous namespace)::k_split_finish<2>(float const*, int, unsigned long, int)", "chain split finish (bp2)"),
     ("lf::(anonymous namespace)::k_bias_grad(float const*, float*, int, int, float)", "bias sums (bp3)"),
     ("_ZN2lf12_GLOBAL__N_114k_output_errorIDF16bEEvPKT_S4_PfPDF16bmf", "output error (bp1)"),
     ("void at::native::vectorized_elementwise_kernel<4, at::native::FillFunctor<float>>", None),

@@ -3,7 +3,7 @@ their tiles and of the rules that choose them, against the oracle; and the same 
 import numpy as np
 import pytest
 
-from lf_inputs import make_net
+from lf_inputs import make_net, round_to_bf16
 from tests.gpu_util import check_against_oracle, log, run_gpu, to_np
 
 pytestmark = pytest.mark.gpu
@@ -11,6 +11,10 @@ pytestmark = pytest.mark.gpu
 
 def _tensors(g):
     return [to_np(t).view(np.uint32).copy() for t in g.nabla_w + g.nabla_b]
+
+
+# of the nets below: those that lf_backward_leapfrog_noalloc is not published to serve
+BEYOND_NOALLOC = [((3, 2056), 130), ((3, 4104), 64), ((3, 2056), 400), ((3, 3080), 200)]
 
 
 @pytest.mark.parametrize("shape,B,dtype", [
@@ -29,10 +33,14 @@ def _tensors(g):
     ((3, 3080), 200, "bf16"),
     ((72, 1000, 36, 1500, 8), 19, "f32"),      # contractions shorter than a turn of the waves; unequal widths
     ((264, 8, 2056, 136), 33, "bf16"),
+    ((3, 2048), 128, "bf16"),         # tiles of 32 x 32, all full; gradients 64 x 64 a wave
+    ((520, 1000, 1500, 1500, 700, 264), 100, "f32"),   # layers whose gradients are cut in different ways, the last two too
+    ((520, 1000, 1504, 1504, 704, 264), 100, "bf16"),
 ])
-def test_direct_kernels_match_oracle_with_the_same_bits_from_every_schedule(shape, B, dtype):
+def test_direct_kernels_match_oracle_with_the_same_bits_from_every_schedule(monkeypatch, shape, B, dtype):
     import paper_1801_04928_amd as P
     import torch
+    monkeypatch.setenv("LF_GEMM_BIG", "0")
     widths = shape if len(shape) > 2 else (shape[1],) * shape[0]
     L = len(widths)
     net = make_net(L, widths[0] if len(shape) == 2 else widths, B, dtype=dtype, seed=sum(widths) + B)
@@ -50,11 +58,16 @@ def test_direct_kernels_match_oracle_with_the_same_bits_from_every_schedule(shap
         g.backward(k)
         torch.cuda.synchronize()
         assert all(np.array_equal(a, b) for a, b in zip(want, _tensors(g))), (sched, k)
+    for t in g.nabla_w + g.nabla_b:
+        t.fill_(float("nan"))
     g.forward()
     st = P.lf_backward_leapfrog_noalloc(g.handle, g.y.data_ptr(), 1, stream)
-    assert st in (P.LF_OK, P.LF_EUNSUPPORTED)             # (the widest are beyond that entry point's limit)
+    assert st == (P.LF_EUNSUPPORTED if (shape, B) in BEYOND_NOALLOC else P.LF_OK), P.lf_last_error(g.handle)
     torch.cuda.synchronize()
-    assert all(np.array_equal(a, b) for a, b in zip(want, _tensors(g)))
+    if st == P.LF_OK:
+        assert all(np.array_equal(a, b) for a, b in zip(want, _tensors(g)))
+    else:
+        assert all(bool(torch.isnan(t).all()) for t in g.nabla_w + g.nabla_b)
     # the descent step: layer l's rides one launch later, layers 3 and 2 share the last one
     results = []
     for sched in (P.LF_SCHED_AUTO, P.LF_SCHED_STREAMS):
@@ -67,11 +80,16 @@ def test_direct_kernels_match_oracle_with_the_same_bits_from_every_schedule(shap
         g.forward()
         g.backward(L - 1)
         torch.cuda.synchronize()
-        results.append([to_np(t).copy() for t in g.w + g.b])
-    if dtype == "f32":                                    # eta is a power of two: one rounding, of the exact difference
-        for l in range(2, L + 1):
-            exact = net.w(l).astype(np.float64) - 0.125 * want[l - 2].view(np.float32).astype(np.float64)
-            assert np.array_equal(results[0][l - 2], exact.astype(np.float32)), f"layer {l}"
+        results.append([to_np(t).copy() for t in g.w + g.b + (g.master_w or [])])
+    # eta is a power of two: one rounding, of the exact difference; the bf16 weights are the masters' rounding
+    old = [net.w(l) for l in range(2, L + 1)] + [net.b(l) for l in range(2, L + 1)]
+    new = results[0] if dtype == "f32" else results[0][2 * L - 2:] + results[0][L - 1:2 * L - 2]
+    for i, (o, n, grad) in enumerate(zip(old, new, want)):
+        exact = o.astype(np.float64) - 0.125 * grad.view(np.float32).astype(np.float64)
+        assert np.array_equal(n, exact.astype(np.float32).reshape(n.shape)), i
+    if dtype == "bf16":
+        for w, master in zip(results[0][:L - 1], new):
+            assert np.array_equal(w, round_to_bf16(master))
     assert all(np.array_equal(a, b) for a, b in zip(*results))
     g.close()
 
