@@ -166,7 +166,8 @@ __device__ __forceinline__ void contract(v4f (&acc)[MT][NT], float* lds, const v
                                          int W) {
     typedef Operand<T, P_IC, MT> OP;
     typedef Operand<T, Q_IC, NT> OQ;
-    // as many as about 96 registers hold
+    // requested ahead: as many pairs of QC units as about 96 registers hold, and at least four IC units (of 4 (MT + NT)
+    // registers each in fp32: 128 for the gradients' 4 x 4 tiles)
     constexpr int kFit = 96 / (8 * (MT + NT));
     constexpr int D = kFit > 4 ? 4 : kFit;
     constexpr int E = D == 1 ? 4 : 2 * D;
@@ -384,24 +385,22 @@ struct StepArgs {
 __device__ __forceinline__ void bias_block(const GradJob& g, int x, int B, float sgd_eta, float* lds) {
     const int t = threadIdx.x, c = t & 31, rg = t >> 5;
     const int j = x * 32 + c;
-    if (rg < 8) {
-        float s = 0.0f;
-        if (j < g.n_l) {
-            int b = rg;
-            for (; b + 56 < B; b += 64) {
-                float v[8];
+    float s = 0.0f;
+    if (j < g.n_l) {
+        int b = rg;
+        for (; b + 56 < B; b += 64) {
+            float v[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = g.D[(size_t)(b + 8 * u) * g.n_l + j];
+            for (int u = 0; u < 8; ++u) v[u] = g.D[(size_t)(b + 8 * u) * g.n_l + j];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) s += v[u];
-            }
-            for (; b < B; b += 8) s += g.D[(size_t)b * g.n_l + j];
+            for (int u = 0; u < 8; ++u) s += v[u];
         }
-        lds[rg * 32 + c] = s;
+        for (; b < B; b += 8) s += g.D[(size_t)b * g.n_l + j];
     }
+    lds[rg * 32 + c] = s;
     __syncthreads();
     if (rg == 0 && j < g.n_l) {
-        float s = lds[c];
+        s = lds[c];
 #pragma unroll
         for (int q = 1; q < 8; ++q) s += lds[q * 32 + c];
         g.b[j] = sgd_eta != 0.0f ? fmaf(-sgd_eta, s, g.b[j]) : s;
@@ -531,8 +530,8 @@ bool fits_buffer(unsigned long long bytes) { return bytes < 0xFFFFFFF0ull; }
 // costs, per q of the contraction, its 16 (mt + nt) operand rows (measured: as if each took 35 cycles per unit and 16
 // rows, the rate the L2s give all compute units together) or its mt nt matrix instructions (32 cycles a unit for fp32,
 // 4 for bf16, over four SIMDs), whichever is more.  Forward, us a layer, tiles 1x1, 1x2, 2x2, 2x4, 4x4:
-//   fp32: N = 1024, B = 64: 5.4, 6.8, 9.4, 14, 23;  N = 2048, B = 64: 10.2, 10.3, 14, 23, 39;  N = 4096, B = 256: 108, 91, 77, 74, 75
-//   bf16: N = 2048, B = 128: 9.8, 8.5, 7.3, 8.5, 12;  N = 4096, B = 256: 58, 45, 33, 26, 24
+//   fp32: N = 1024, B = 64: 4.4, 5.9, 7.9, 12, 20;  N = 2048, B = 64: 10.2, 9.3, 12.5, 20, 35;  N = 4096, B = 256: 108, 89, 73, 68, 64
+//   bf16: N = 2048, B = 128: 9.1, 7.7, 6.3, 7.8, 11;  N = 4096, B = 256: 59, 45, 33, 26, 23
 // Rows past the minibatch may be part of a tile where that saves a turn: B = 33 .. 48 beyond N = 8192 takes one turn of
 // 4x4 tiles instead of two of 2x4 (bf16, N = 9216, B = 48: forward 65 -> 53, backward 94 -> 86; N = 10240, B = 40: 74 -> 62,
 // 111 -> 99; fp32 within 1 % there, N = 16384: 313 -> 281, 573 -> 548).
@@ -558,8 +557,8 @@ TileShape chain_tile(int B, int n_out, bool bf16, bool chain) {
 
 // How nabla_w of a layer is cut: 64 x 64 a wave where that gives at least four waves per compute unit; 32 x 32 a wave
 // below; and where even those leave SIMDs idle and the minibatch is long enough to divide, 32 x 32 a workgroup whose
-// waves share the samples.  Backward, us a layer, 64 / 32 / 32 split: fp32, N = 2048, B = 64: 16 / 20 / 33; N = 1024,
-// B = 64: 11 / 9 / 11; N = 512, B = 128: 14 / 8.2 / 7.1, B = 512: 39 / 17 / 13; bf16, N = 1024, B = 256: 12 / 9 / 13.
+// waves share the samples.  Backward, us a layer, 64 / 32 / 32 split: fp32, N = 2048, B = 64: 14.3 / 18.5 / 31; N = 1024,
+// B = 64: 11.1 / 8.8 / 10.7; N = 512, B = 128: 14 / 7.3 / 6.2, B = 512: 39 / 17 / 10; bf16, N = 1024, B = 256: 10.9 / 8.4 / 12.
 enum GradKind { GRAD_WAVE_64, GRAD_WAVE_32, GRAD_SPLIT_32 };
 
 GradKind grad_kind(const GradStep& g, int B, bool bf16) {

@@ -510,7 +510,7 @@ def test_minibatch_bf16_half_tile_kernel_deeper_split(monkeypatch, target):
     ((8, 4), 1, "f32", 1, None),                         # one tiny weight layer
     ((264, 520, 136, 392), 70, "f32", 2, None),          # minibatch fp32 MFMA, ragged in every dimension
     ((136, 1032, 264), 300, "f32", 1, None),             # several row tiles
-    ((264, 520, 136, 392), 70, "bf16", 3, "0"),          # bf16, 128 x 128 tiles
+    ((264, 520, 136, 392), 70, "bf16", 3, "0"),          # bf16, the direct kernels
     ((520, 264, 1032, 264), 260, "bf16", 2, "1"),        # bf16, 256 x 256 tiles, split K of unequal lengths
 ])
 def test_unequal_layer_widths_match_oracle(monkeypatch, widths, B, dtype, k, big):

@@ -1,7 +1,7 @@
 """The backward entry point that allocates nothing (lf_backward_leapfrog_noalloc), called through the C ABI:
 its gradients against lf_backward_leapfrog's on the same handle, bit for bit (the same kernels in the same
-order) and hence within the parity tolerance, on two calls in a row, the second on a smaller net; then a
-minibatch net with split-K scratch, a shape beyond the static scratch, and the oracle."""
+order) and hence within the parity tolerance, on two calls in a row, the second on a smaller net; then
+minibatch nets, a shape beyond the published limit, and the oracle."""
 import numpy as np
 import pytest
 
@@ -75,7 +75,7 @@ def test_noalloc_backward_limits():
     import torch
     import paper_1801_04928_amd as P
     stream = torch.cuda.current_stream().cuda_stream
-    # a shape whose split-K scratch (8 x 256 x 4096 floats) is beyond the static 8 MiB
+    # a shape charged for more (8 x 256 x 4096 floats of split-K partials) than the static 8 MiB
     net = make_net(3, 4096, 256, seed=1, cache=False)
     g = P.LeapfrogNet(3, 4096, 256, "f32")
     g.load(net)
