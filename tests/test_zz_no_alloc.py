@@ -63,7 +63,8 @@ def test_noalloc_backward_twice_second_call_smaller():
     g2.close()
 
 
-@pytest.mark.parametrize("L,N,B,dtype,k", [(5, 512, 256, "f32", 4), (4, 264, 70, "bf16", 2)])
+@pytest.mark.parametrize("L,N,B,dtype,k", [(5, 512, 256, "f32", 4), (4, 264, 70, "bf16", 2),
+                                           (3, 1856, 4096, "bf16", 2)])      # (wide-net kernels, no product split)
 def test_noalloc_backward_minibatch(L, N, B, dtype, k):
     net, g, want, got = _run_pair(L, N, B, dtype, k, seed=N + B)
     _assert_same(want, got, TOL[dtype])
