@@ -206,7 +206,7 @@ lf_status lf_backward_leapfrog(lf_net* net, const void* y, int k, void* hip_stre
  * streams and events, or pinned memory, the first time a handle runs with a new k or schedule.)  This call
  * allocates nothing, on the device or through any library: it enqueues the chain and gradient kernels of
  * layer L, L-1, ..., 2 in that order on hip_stream alone, and the scratch of the chain
- * products (row-block partial sums at B = 1, split-K partials of a minibatch) is a static device array inside
+ * products (row-block partial sums at B = 1, split-K partials of a wide minibatch net) is a static device array inside
  * the library instead of the caller's workspace.  Same arguments, same checks, same results bit for bit as
  * lf_backward_leapfrog with LF_SCHED_STREAMS (k only names the worker a layer would belong to; the gradients do
  * not depend on it).  lf_forward must have run (with LF_SCHED_STREAMS it allocates nothing either).

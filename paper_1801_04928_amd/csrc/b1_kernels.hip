@@ -207,7 +207,9 @@ __global__ __launch_bounds__(kThreads) void k_output_error(const T* __restrict__
                                                            const T* __restrict__ y,
                                                            float* __restrict__ delta_L,
                                                            __bf16* __restrict__ delta_bf, size_t count,
-                                                           float scale) {
+                                                           float scale, unsigned* clear, int clear_words) {
+    if (clear && blockIdx.x == 0)
+        for (int c = threadIdx.x; c < clear_words; c += kThreads) clear[c] = 0;
     const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= count) return;
     const float a = (float)a_L[i];
@@ -266,14 +268,14 @@ hipError_t launch_grad_outer_f32(const float* delta, const float* a_prev, float*
 }
 
 hipError_t launch_output_error(const void* a_L, const void* y, float* delta_L, void* delta_bf,
-                               size_t count, bool bf16, float scale, hipStream_t s) {
+                               size_t count, bool bf16, float scale, unsigned* clear, int clear_words, hipStream_t s) {
     const unsigned grid = (unsigned)((count + kThreads - 1) / kThreads);
     if (bf16)
         k_output_error<__bf16><<<grid, kThreads, 0, s>>>((const __bf16*)a_L, (const __bf16*)y, delta_L,
-                                                         (__bf16*)delta_bf, count, scale);
+                                                         (__bf16*)delta_bf, count, scale, clear, clear_words);
     else
         k_output_error<float><<<grid, kThreads, 0, s>>>((const float*)a_L, (const float*)y, delta_L,
-                                                        (__bf16*)delta_bf, count, scale);
+                                                        (__bf16*)delta_bf, count, scale, clear, clear_words);
     return hipGetLastError();
 }
 

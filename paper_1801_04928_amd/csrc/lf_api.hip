@@ -65,6 +65,7 @@ struct Layout {
     // partial buffer of its own
     size_t red_off, red_vec_bytes, red_stride;
     size_t raw_off, raw_bytes;
+    bool direct_splits;              // the direct kernels split some chain step of this shape (should the net take them)
     // persistent single-sample path: tagged-word exchange buffers, pointer tables, abort word
     size_t dll_off, all_off, ll_words;   // [L-1][ll_layer] each
     size_t ll_layer; int ll_shift;       // words per layer; spacing of the eight-word groups
@@ -141,7 +142,12 @@ Layout make_layout(int L, const int* n, int B, lf_dtype dt) {
                 partial_floats = std::max(partial_floats, (size_t)lf::chain_partial_blocks(n_l) * n_prev);
         } else {
             raw_floats = std::max(raw_floats, lf::split_workspace_floats(n_l, B, dt == LF_BF16));
-            if (l >= 3) raw_floats = std::max(raw_floats, lf::split_workspace_floats(n_prev, B, dt == LF_BF16));
+            if (l >= 3) {     // the step delta^l -> delta^{l-1}, by the kernels of either kind
+                raw_floats = std::max(raw_floats, lf::split_workspace_floats(n_prev, B, dt == LF_BF16));
+                const size_t direct = lf::direct_chain_scratch_floats(n_prev, n_l, B, dt == LF_BF16);
+                raw_floats = std::max(raw_floats, direct);
+                if (direct > 0) y.direct_splits = true;
+            }
         }
     }
     y.partial_off = off;
@@ -542,7 +548,11 @@ lf::PersistArgs persist_args(lf_net* net, const void* y, int k) {
 // The layer-l work of the direct minibatch kernels.
 lf::ChainStep chain_step(const lf_net* net, int l) {            // delta^l from delta^{l+1}
     return {net->w[l - 1], net->d_ptr(l + 1), net->dbf_ptr(l + 1), net->a_ptr(l), net->d_ptr(l), net->dbf_ptr(l),
-            net->width(l), net->width(l + 1)};
+            net->width(l), net->width(l + 1), direct_minibatch(net) ? net->raw() : nullptr};
+}
+// The arrival counters of the direct chain products, which the pass's first kernel clears (none: no product is split).
+unsigned* chain_counters(const lf_net* net) {
+    return direct_minibatch(net) && net->lay.direct_splits ? reinterpret_cast<unsigned*>(net->raw()) : nullptr;
 }
 lf::GradStep grad_step(const lf_net* net, int l) {              // (bp3), (bp4), or the descent step, of layer l
     const int i = l - 2;
@@ -608,7 +618,7 @@ lf_status backward_redundant(lf_net* net, const void* y, int k, hipStream_t s) {
     };
     // parent
     LF_HIP(net, lf::launch_output_error(net->a_ptr(L), y, net->d_ptr(L), nullptr, (size_t)net->width(L), false,
-                                        net->cost_scale, s));
+                                        net->cost_scale, nullptr, 0, s));
     st = enqueue_grads(net, L, s);
     if (st != LF_OK) return st;
     const int parent_low = L - k + 1 > 2 ? L - k + 1 : 2;        // the parent's lowest layer
@@ -683,7 +693,8 @@ lf_status backward_streams(lf_net* net, const void* y, int k, hipStream_t s, flo
         // the chain: (bp1) at L, (bp2) below
         if (l == L) {
             LF_HIP(net, lf::launch_output_error(net->a_ptr(L), y, net->d_ptr(L), net->dbf_ptr(L),
-                                                (size_t)B * net->width(L), bf, net->cost_scale, s));
+                                                (size_t)B * net->width(L), bf, net->cost_scale, chain_counters(net),
+                                                lf::chain_counters(), s));
         } else if (b1) {
             // w^{l+1} has n_{l+1} rows and n_l columns
             LF_HIP(net, lf::launch_chain_gemvT_f32(static_cast<const float*>(net->w[l - 1]), net->d_ptr(l + 1),
@@ -733,7 +744,7 @@ lf_status backward_steps(lf_net* net, const void* y, hipStream_t s) {
     const bool bf = net->dt == LF_BF16, sgd = net->sgd_eta != 0.0f;
     const bool chain_only = (net->debug_flags & LF_DEBUG_CHAIN_ONLY) != 0;
     LF_HIP(net, lf::launch_output_error(net->a_ptr(L), y, net->d_ptr(L), net->dbf_ptr(L), (size_t)B * net->width(L), bf,
-                                        net->cost_scale, s));
+                                        net->cost_scale, chain_counters(net), lf::chain_counters(), s));
     const int lag = sgd ? 2 : 1;
     for (int l = L - 1; l >= 2; --l) {
         const lf::ChainStep c = chain_step(net, l);

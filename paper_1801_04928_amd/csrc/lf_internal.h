@@ -32,9 +32,9 @@ hipError_t launch_grad_outer_f32(const float* delta, const float* a_prev, float*
 
 // eq. (bp1): delta_L = scale * (a_L - y) (.) a_L (1 - a_L) over count = B*N elements (scale: a power
 // of two, see lf_set_cost_scale).  delta_bf (may be NULL) receives a bfloat16 copy of delta_L for the
-// bf16 matrix kernels.
+// bf16 matrix kernels.  clear (may be NULL) receives `clear_words` zeros: the arrival counters of a split chain product.
 hipError_t launch_output_error(const void* a_L, const void* y, float* delta_L, void* delta_bf,
-                               size_t count, bool bf16, float scale, hipStream_t s);
+                               size_t count, bool bf16, float scale, unsigned* clear, int clear_words, hipStream_t s);
 
 // ---- minibatch path: which kernels ----------------------------------------------------------------
 
@@ -86,13 +86,17 @@ hipError_t launch_grad_gemm(const float* D, const void* D_bf, const void* A_prev
 
 // ---- minibatch path: direct kernels (fp32; bf16 nets that are not wide) -----------------------------
 
-// eqs. (z),(a) for a minibatch (as launch_fwd_gemm), one launch, no scratch.
+// eqs. (z),(a) for a minibatch (as launch_fwd_gemm), one launch, no scratch (the chain step takes some where few samples
+// meet a wide layer).
 hipError_t launch_forward_direct(const void* W, const float* bias, const void* A_in, void* A_out, int n_out, int n_in,
                                  int B, bool bf16, hipStream_t s);
 struct ChainStep {      // eq. (bp2): delta^l from delta^{l+1} (as launch_chain_gemm; fp32 nets have no *_bf)
     const void* W_next; const float* D_next; const void* D_next_bf; const void* A_l; float* D_l; void* D_l_bf;
     int n_l, n_next;
-};
+    float* scratch;     // direct_chain_scratch_floats() floats (NULL where that is 0); its first chain_counters() words are 0
+};                      // when the first chain step of a pass starts, and again when a step has ended
+int chain_counters();
+size_t direct_chain_scratch_floats(int n_l, int n_next, int B, bool bf16);
 struct GradStep {       // eqs. (bp3), (bp4) of one layer (as launch_grad_gemm)
     const float* D; const void* D_bf; const void* A_prev; float* w; float* b; void* w_bf;
     int n_l, n_prev;

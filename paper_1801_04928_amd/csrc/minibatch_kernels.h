@@ -22,6 +22,7 @@ __host__ __device__ constexpr int ceil_div(int a, int b) { return (a + b - 1) / 
 
 constexpr unsigned kOutside = 0xFFFFFFF0u;   // an offset past the end of every buffer: loads zeros
 constexpr int kWaves = 4;                    // of every workgroup
+constexpr int kSplitWorkgroups = 256;        // of a split chain product, at most: also the number of its arrival counters
 
 // A unit of the contraction: the q's of one 64-byte piece of a QC row.  A 16 x 16 matrix instruction hands row
 // (lane % 16) of its operand to a lane and one quarter (g = lane / 16) of the q's; which q's form a quarter is free as
@@ -322,6 +323,41 @@ __device__ __forceinline__ void reduce_waves(const v4f (&acc)[MT][NT], float* ld
     }
 }
 
+// The same for a tile whose contraction is split over workgroups as well: each stores its sum, and the last one to do so
+// adds all of them, in the order of the splits, and stores the result.  No workgroup waits for another.  The sums pass
+// through memory at device scope (aux 16) on either side: written through and acknowledged before the split is counted.
+template <int MT, int NT, typename Store>
+__device__ __forceinline__ void meet(const v4f (&acc)[MT][NT], float* lds, float* scratch, int tile, int splits, int split,
+                                     Store store) {
+    constexpr int TM = 16 * MT, TN = 16 * NT, kDevice = 16;
+    unsigned* const arrived = reinterpret_cast<unsigned*>(scratch) + tile;
+    const __amdgpu_buffer_rsrc_t buf = make_buffer(scratch + kSplitWorkgroups + (size_t)tile * splits * TM * TN,
+                                                   (unsigned)splits * TM * TN * 4u);
+    reduce_waves<false, true, MT, NT>(acc, lds, [&](int row, int col, v4f u) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, u), buf, ((split * TM + row) * TN + col) * 4, 0, kDevice);
+    });
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0)
+        lds[0] = (float)__hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (lds[0] != (float)(splits - 1)) return;                 // (the same for every thread)
+    if (threadIdx.x == 0) __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int v = threadIdx.x; v < TM * TN / 4; v += 64 * kWaves) {
+        const int at = v * 16;
+        v4f s = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int z = 0; z < splits; z += 4) {                   // (past the last split: zeros from outside the buffer)
+            v4f x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                x[u] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(buf, at + (z + u) * TM * TN * 4, 0, kDevice));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s += x[u];
+        }
+        store(v / (TN / 4), v % (TN / 4) * 4, s);
+    }
+}
+
 // ---- forward ------------------------------------------------------------------------------------------------
 struct ForwardArgs {
     const void* A_in; const void* W; const float* bias; void* A_out;
@@ -374,7 +410,8 @@ struct StepArgs {
     const void* D_next; const void* W_next; const void* A_l; float* D_l; void* D_l_bf;
     unsigned d_bytes, w_bytes;
     int n_l, n_next;
-    int tiles_m, tiles_n, chain_blocks;
+    int tiles_m, tiles_n, splits, chain_blocks;
+    float* scratch;                     // splits > 1: how many of a tile's splits have arrived, and their partial tiles
     GradJob grad[2];
     int B;
     float sgd_eta;
@@ -484,19 +521,24 @@ __device__ __forceinline__ void grad_block(const GradJob& g, int x, int B, float
     }
 }
 
-template <typename T, int MT, int NT, int GT, bool GSPLIT>
+// MEET: the chain's tiles are split along the contraction (an instance of its own: the few instructions that this takes cost the
+// smallest nets 4 % where they stand beside the whole tiles').
+template <typename T, int MT, int NT, int GT, bool GSPLIT, bool MEET>
 __global__ __launch_bounds__(64 * kWaves, 2) void k_backward_step(const StepArgs g) {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     int x = blockIdx.x;
     if (x < g.chain_blocks) {
-        int tm, tn;
-        tile_of(x, g.tiles_m, g.tiles_n, &tm, &tn);
+        int tm, tn;                                             // (the splits of a tile follow each other on its XCD)
+        tile_of(x, MEET ? g.tiles_m * g.splits : g.tiles_m, g.tiles_n, &tm, &tn);
         if (tn >= g.tiles_n) return;
+        const int split = MEET ? tm / g.tiles_m : 0;
+        if constexpr (MEET) tm %= g.tiles_m;
         const int m0 = tm * 16 * MT, n0 = tn * 16 * NT;
         v4f acc[MT][NT];
         contract<T, false, true, MT, NT>(acc, lds, g.D_next, g.d_bytes, g.n_next, m0, g.B, g.W_next, g.w_bytes, g.n_l, n0,
-                                         g.n_l, g.n_next, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kWaves);
-        reduce_waves<false, true, MT, NT>(acc, lds, [&](int row, int col, v4f u) {
+                                         g.n_l, g.n_next, split * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
+                                         MEET ? g.splits * kWaves : kWaves);
+        auto finish = [&](int row, int col, v4f u) {
             const int m = m0 + row, n = n0 + col;
             if (m >= g.B || n >= g.n_l) return;
             const size_t o = (size_t)m * g.n_l + n;
@@ -513,7 +555,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_backward_step(const StepArgs
                 const v4bf db = {(__bf16)d[0], (__bf16)d[1], (__bf16)d[2], (__bf16)d[3]};
                 *reinterpret_cast<v4bf*>(static_cast<__bf16*>(g.D_l_bf) + o) = db;
             }
-        });
+        };
+        if constexpr (!MEET) reduce_waves<false, true, MT, NT>(acc, lds, finish);
+        else meet<MT, NT>(acc, lds, g.scratch, tn * g.tiles_m + tm, g.splits, split, finish);
         return;
     }
     x -= g.chain_blocks;
@@ -536,7 +580,7 @@ bool fits_buffer(unsigned long long bytes) { return bytes < 0xFFFFFFF0ull; }
 // 4x4 tiles instead of two of 2x4 (bf16, N = 9216, B = 48: forward 65 -> 53, backward 94 -> 86; N = 10240, B = 40: 74 -> 62,
 // 111 -> 99; fp32 within 1 % there, N = 16384: 313 -> 281, 573 -> 548).
 // A bf16 chain product takes at least two columns a lane (one would be a two-byte load).
-struct TileShape { int mt, nt; };
+struct TileShape { int mt, nt, splits = 1; };
 
 // cycles a unit of the contraction costs a compute unit
 long tile_cycles(const TileShape& c, bool bf16) { return std::max(35 * (c.mt + c.nt), (bf16 ? 4 : 32) * c.mt * c.nt); }
@@ -553,6 +597,44 @@ TileShape chain_tile(int B, int n_out, bool bf16, bool chain) {
         if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = c; }
     }
     return best;
+}
+
+// The chain product of a few samples is the reading of W_next, by columns: a tile's workgroup walks a strip of it, 32 nt (bf16)
+// or 64 nt (fp32) bytes wide, down all its rows.  Whole tiles alone make too few workgroups to keep memory busy (N = 4096,
+// B = 8, bf16: 128 of 64-byte strips, 2.1 TB/s), so their contraction is split over workgroups that meet in memory, which
+// costs about 2 us, and the strips become wider.  us a layer of a backward pass (weights and gradients from memory), unsplit
+// -> split (mt, nt, splits):
+//   bf16  B = 8: N = 1024 7.3 -> 6.9 (1, 2, 4);  2048 10.5 -> 8.4 (1, 2, 4);  3072 15.7 -> 13.1 (1, 4, 2);  4096 27.8 -> 23.4 (1, 4, 2);
+//         6144 52 -> 43, 8192 80 -> 71 (1, 4, 2);  B = 32: N = 1536 9.1 -> 7.8, 2048 10.6 -> 8.7 (2, 2, 4);  3072 15.0 -> 14.5,
+//         6144 57 -> 45 (2, 4, 2);  B = 64: N = 4096 30.8 -> 25.6 (4, 4, 4);  5200 55 -> 45, 8192 86 -> 78 (4, 4, 2)
+//   fp32  B = 8: N = 1024 7.7 -> 7.0 (1, 2, 4);  2048 12.1 -> 11.3, 3072 27 -> 21, 4096 37 -> 33 (1, 4, 4);  6144 73 -> 68 (1, 4, 2);
+//         B = 32: N = 3072 28 -> 24, 4096 41 -> 37 (2, 4, 4);  6144 79 -> 70 (2, 4, 2);  B = 64: N = 4096 53 -> 49 (2, 4, 2);
+//         5200 84 -> 79 (4, 4, 2)
+// Below 1024 rows or columns the meeting costs more than it brings (N = 512, 768: 20 to 30 % slower), in between (bf16 B = 24
+// at N = 2600, fp32 B = 32 at N = 2048) nothing is gained, and longer minibatches have tiles enough.
+TileShape chain_shape(int B, int n_l, int n_next, bool bf16) {
+    TileShape t{0, 0, 1};
+    const int rows = ceil_div(B, 16);
+    auto groups = [&](int mt, int nt) { return ceil_div(rows, mt) * ceil_div(n_l, 16 * nt); };
+    auto most = [&](int mt, int nt) { return groups(mt, nt) * 4 <= kSplitWorkgroups ? 4 : 2; };
+    if (std::min(n_l, n_next) >= 1024) {
+        if (bf16) {
+            if (rows <= 2 && n_l <= 2048) t = {rows, 2, 4};
+            else if (rows == 1 || (rows == 2 && n_l >= 3072)) t = {rows, 4, 2};
+            else if (rows > 2 && rows <= 4 && n_l >= 4096) t = {4, 4, most(4, 4)};
+        } else {
+            if (rows == 1) t = n_l < 2048 ? TileShape{1, 2, 4} : TileShape{1, 4, most(1, 4)};
+            else if (rows == 2 && n_l >= 3072) t = {2, 4, most(2, 4)};
+            else if (rows > 2 && rows <= 4 && n_l >= 3072) t = n_l <= 4096 ? TileShape{2, 4, 2} : TileShape{4, 4, 2};
+        }
+    }
+    if (t.splits == 1 || groups(t.mt, t.nt) * t.splits > kSplitWorkgroups) return chain_tile(B, n_l, bf16, true);
+    return t;
+}
+size_t chain_scratch(int B, int n_l, int n_next, bool bf16) {  // floats: arrival counters, then the partial tiles
+    const TileShape t = chain_shape(B, n_l, n_next, bf16);
+    if (t.splits == 1) return 0;
+    return kSplitWorkgroups + (size_t)ceil_div(B, 16 * t.mt) * ceil_div(n_l, 16 * t.nt) * t.splits * (16 * t.mt) * (16 * t.nt);
 }
 
 // How nabla_w of a layer is cut: 64 x 64 a wave where that gives at least four waves per compute unit; 32 x 32 a wave
@@ -619,15 +701,23 @@ hipError_t forward_any(ForwardArgs g, TileShape t, hipStream_t s) {
     return launch_forward<T, 1, 1>(g, s);
 }
 
-template <typename T, int MT, int NT, int GT, bool GSPLIT>
+template <typename T, int MT, int NT, int GT, bool GSPLIT, bool MEET = false>
 hipError_t launch_step(const StepArgs& g, hipStream_t s) {
-    k_backward_step<T, MT, NT, GT, GSPLIT><<<g.chain_blocks + g.grad[0].blocks + g.grad[1].blocks, 64 * kWaves,
-                                             lds_bytes(MT, NT > GT ? NT : GT), s>>>(g);
+    k_backward_step<T, MT, NT, GT, GSPLIT, MEET><<<g.chain_blocks + g.grad[0].blocks + g.grad[1].blocks, 64 * kWaves,
+                                                   lds_bytes(MT, NT > GT ? NT : GT), s>>>(g);
     return hipGetLastError();
 }
 
 template <typename T, int GT, bool GSPLIT>
 hipError_t step_any(StepArgs g, TileShape t, hipStream_t s) {
+    if (t.splits > 1) {                                                    // (the shapes of chain_shape)
+        if (t.mt == 4) return launch_step<T, 4, 4, GT, GSPLIT, true>(g, s);
+        if (t.mt == 2 && t.nt == 4) return launch_step<T, 2, 4, GT, GSPLIT, true>(g, s);
+        if (t.mt == 1 && t.nt == 4) return launch_step<T, 1, 4, GT, GSPLIT, true>(g, s);
+        if constexpr (sizeof(T) == 2)
+            if (t.mt == 2) return launch_step<T, 2, 2, GT, GSPLIT, true>(g, s);
+        return launch_step<T, 1, 2, GT, GSPLIT, true>(g, s);
+    }
     if (t.mt == 4 && t.nt == 4) return launch_step<T, 4, 4, GT, GSPLIT>(g, s);
     if (t.mt == 2 && t.nt == 4) return launch_step<T, 2, 4, GT, GSPLIT>(g, s);
     if (t.mt == 2 && t.nt == 2) return launch_step<T, 2, 2, GT, GSPLIT>(g, s);
@@ -638,6 +728,9 @@ hipError_t step_any(StepArgs g, TileShape t, hipStream_t s) {
 
 }  // namespace
 }  // namespace direct
+
+int chain_counters() { return direct::kSplitWorkgroups; }
+size_t direct_chain_scratch_floats(int n_l, int n_next, int B, bool bf16) { return direct::chain_scratch(B, n_l, n_next, bf16); }
 
 hipError_t launch_forward_direct(const void* W, const float* bias, const void* A_in, void* A_out, int n_out, int n_in,
                                  int B, bool bf16, hipStream_t s) {
@@ -666,14 +759,17 @@ hipError_t launch_backward_step(const ChainStep* c, const GradStep* grads, int n
     if (c) {
         const unsigned long long db = es * B * c->n_next, wb = es * c->n_next * c->n_l;
         if (!fits_buffer(db) || !fits_buffer(wb)) return hipErrorInvalidValue;
-        t = chain_tile(B, c->n_l, bf16, true);
+        t = chain_shape(B, c->n_l, c->n_next, bf16);
+        if (t.splits > 1 && !c->scratch) return hipErrorInvalidValue;
         g.D_next = bf16 ? c->D_next_bf : static_cast<const void*>(c->D_next);
         g.W_next = c->W_next; g.A_l = c->A_l; g.D_l = c->D_l; g.D_l_bf = c->D_l_bf;
         g.d_bytes = (unsigned)db; g.w_bytes = (unsigned)wb;
         g.n_l = c->n_l; g.n_next = c->n_next;
         g.tiles_m = ceil_div(B, 16 * t.mt);
         g.tiles_n = ceil_div(c->n_l, 16 * t.nt);
-        g.chain_blocks = ceil_div(g.tiles_n, 8) * 8 * g.tiles_m;
+        g.splits = t.splits;
+        g.scratch = c->scratch;
+        g.chain_blocks = ceil_div(g.tiles_n, 8) * 8 * g.tiles_m * g.splits;
     }
     const GradKind kind = ngrads > 0 ? grad_kind(grads[0], B, bf16) : GRAD_WAVE_32;
     const bool split = kind == GRAD_SPLIT_32;
