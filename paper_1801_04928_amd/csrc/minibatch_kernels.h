@@ -611,7 +611,8 @@ TileShape chain_tile(int B, int n_out, bool bf16, bool chain) {
 //         B = 32: N = 3072 28 -> 24, 4096 41 -> 37 (2, 4, 4);  6144 79 -> 70 (2, 4, 2);  B = 64: N = 4096 53 -> 49 (2, 4, 2);
 //         5200 84 -> 79 (4, 4, 2)
 // Below 1024 rows or columns the meeting costs more than it brings (N = 512, 768: 20 to 30 % slower), in between (bf16 B = 24
-// at N = 2600, fp32 B = 32 at N = 2048) nothing is gained, and longer minibatches have tiles enough.
+// at N = 2600, fp32 B = 32 at N = 2048) nothing is gained, and longer minibatches have tiles enough.  Three row blocks whose
+// 32 x 64 tiles are one a compute unit stay with those: a quarter of every 64 x 64 tile would be padding.
 TileShape chain_shape(int B, int n_l, int n_next, bool bf16) {
     TileShape t{0, 0, 1};
     const int rows = ceil_div(B, 16);
@@ -621,7 +622,7 @@ TileShape chain_shape(int B, int n_l, int n_next, bool bf16) {
         if (bf16) {
             if (rows <= 2 && n_l <= 2048) t = {rows, 2, 4};
             else if (rows == 1 || (rows == 2 && n_l >= 3072)) t = {rows, 4, 2};
-            else if (rows > 2 && rows <= 4 && n_l >= 4096) t = {4, 4, most(4, 4)};
+            else if (rows > 2 && rows <= 4 && n_l >= 4096 && !(rows == 3 && groups(2, 4) == 256)) t = {4, 4, most(4, 4)};
         } else {
             if (rows == 1) t = n_l < 2048 ? TileShape{1, 2, 4} : TileShape{1, 4, most(1, 4)};
             else if (rows == 2 && n_l >= 3072) t = {2, 4, most(2, 4)};
