@@ -182,8 +182,9 @@ __device__ __forceinline__ void contract(v4f (&acc)[MT][NT], float* lds, const v
     const typename OQ::At qa(n0, Nn, ldq);
     v4f* const lp = reinterpret_cast<v4f*>(lds) + (threadIdx.x >> 6) * (OP::kLdsVecs + OQ::kLdsVecs);
     v4f* const lq = lp + OP::kLdsVecs;
-    const int pairs = ceil_div(ceil_div(K, Unit<T>::Q), 2);
-    const int nu = w < pairs ? 2 * ((pairs - w + W - 1) / W) : 0;
+    const int units = ceil_div(K, Unit<T>::Q), pairs = ceil_div(units, 2);
+    // (a QC operand goes through LDS by pairs; without one, a wave that has the contraction to itself ends with its last unit)
+    const int nu = P_IC && W == 1 ? units : (w < pairs ? 2 * ((pairs - w + W - 1) / W) : 0);
     // (units past the last one start at K or beyond and load zeros)
     auto q_of = [&](int j) { return (((j >> 1) * W + w) * 2 + (j & 1)) * Unit<T>::Q; };
     typename OP::Raw rp[P_IC ? E : D];
@@ -279,12 +280,18 @@ __device__ __forceinline__ void contract(v4f (&acc)[MT][NT], float* lds, const v
 #pragma unroll
         for (int u = 0; u < U; ++u) unit(u, j);
     }
+    if constexpr (P_IC) {
 #pragma unroll
-    for (int u = 0; u < U - 2; u += 2)
-        if (j + u < nu) {
-            unit(u, j);
-            unit(u + 1, j);
-        }
+        for (int u = 0; u < U - 1; ++u)
+            if (j + u < nu) unit(u, j);
+    } else {
+#pragma unroll
+        for (int u = 0; u < U - 2; u += 2)
+            if (j + u < nu) {
+                unit(u, j);
+                unit(u + 1, j);
+            }
+    }
 }
 
 // Where element r of lane (i = lane % 16, g = lane / 16) of acc[mt][nt] lies in the tile.
