@@ -87,7 +87,8 @@ typedef enum { LF_COST_QUADRATIC = 0, LF_COST_INT_RANGE = 0x7fffffff } lf_cost;
 typedef enum {
     LF_SCHED_AUTO = 0,        /* the library picks: persistent where supported; for most minibatch nets one launch per
                                  layer on the caller's stream, in which the gradients of layer l+1 ride beside the
-                                 chain step delta^{l+1} -> delta^l; else streams */
+                                 chain step delta^{l+1} -> delta^l; for a single sample outside the persistent
+                                 kernels' shapes every kernel in line on the caller's stream; else streams */
     LF_SCHED_STREAMS = 1,     /* chain on the caller's stream, k worker streams fed by per-layer events */
     LF_SCHED_PERSISTENT = 2,  /* one persistent kernel, k workgroup partitions fed by per-layer ready flags */
     LF_SCHED_REDUNDANT = 3,   /* Algorithm 1 as printed, for comparison: the parent (the caller's stream) walks

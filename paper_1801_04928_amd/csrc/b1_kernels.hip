@@ -87,15 +87,13 @@ __global__ __launch_bounds__(kThreads) void k_fwd_gemv(const float* __restrict__
 // as one contiguous 1 KiB segment) and RPW rows per wave; the four waves' sums are added in wave
 // order through LDS.
 template <int RPW>
-__global__ __launch_bounds__(kThreads) void k_chain_partial(const float* __restrict__ W,
-                                                            const float* __restrict__ delta,
-                                                            float* __restrict__ partial, int rows,
-                                                            int cols) {
+__device__ __forceinline__ void chain_partial_block(const float* __restrict__ W, const float* __restrict__ delta,
+                                                    float* __restrict__ partial, int rows, int cols, int strip, int block) {
     __shared__ v4f s_acc[kWavesPerWg][kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
-    const int col = blockIdx.x * (kWave * 4) + lane * 4;
-    const int row_begin = (blockIdx.y * kWavesPerWg + wave) * RPW;
+    const int col = strip * (kWave * 4) + lane * 4;
+    const int row_begin = (block * kWavesPerWg + wave) * RPW;
     v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
     if (col < cols) {
         const float* wp = W + (size_t)row_begin * cols + col;
@@ -128,8 +126,13 @@ __global__ __launch_bounds__(kThreads) void k_chain_partial(const float* __restr
         v4f t = s_acc[0][lane];
 #pragma unroll
         for (int q = 1; q < kWavesPerWg; ++q) t += s_acc[q][lane];
-        *reinterpret_cast<v4f*>(partial + (size_t)blockIdx.y * cols + col) = t;
+        *reinterpret_cast<v4f*>(partial + (size_t)block * cols + col) = t;
     }
+}
+template <int RPW>
+__global__ __launch_bounds__(kThreads) void k_chain_partial(const float* __restrict__ W, const float* __restrict__ delta,
+                                                            float* __restrict__ partial, int rows, int cols) {
+    chain_partial_block<RPW>(W, delta, partial, rows, cols, blockIdx.x, blockIdx.y);
 }
 
 // eq. (bp2), stage 2: delta_l[k] = (sum_p partial[p][k]) * a_l[k] * (1 - a_l[k]), p in ascending order.
@@ -138,9 +141,17 @@ __global__ __launch_bounds__(kThreads) void k_chain_finish(const float* __restri
                                                            float* __restrict__ delta_l, int N, int P) {
     const int k = blockIdx.x * kThreads + threadIdx.x;
     if (k >= N) return;
-    float u = 0.0f;
-    for (int p = 0; p < P; ++p) u += partial[(size_t)p * N + k];
     const float a = a_l[k];
+    float u = 0.0f;
+    int p = 0;
+    for (; p + 8 <= P; p += 8) {            // eight requested at a time, added in ascending order
+        float v[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = partial[(size_t)(p + c) * N + k];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) u += v[c];
+    }
+    for (; p < P; ++p) u += partial[(size_t)p * N + k];
     delta_l[k] = u * (a * (1.0f - a));
 }
 
@@ -152,12 +163,11 @@ __global__ __launch_bounds__(kThreads) void k_chain_finish(const float* __restri
 // themselves and receive w - eta * nabla_w, b - eta * nabla_b (the gradient entry is rounded to fp32 exactly as
 // it would have been stored, then one fused multiply-add); the gradients are not stored.
 template <int RW, bool SGD>
-__global__ __launch_bounds__(kThreads) void k_grad_outer(const float* __restrict__ delta,
-                                                         const float* __restrict__ a_prev,
-                                                         float* nabla_w, float* nabla_b, int rows,
-                                                         int cols, int nstrips, float eta) {
+__device__ __forceinline__ void grad_outer_block(const float* __restrict__ delta, const float* __restrict__ a_prev,
+                                                 float* nabla_w, float* nabla_b, int rows, int cols, int nstrips, float eta,
+                                                 int block) {
     const int lane = threadIdx.x & (kWave - 1);
-    const int gw = blockIdx.x * kWavesPerWg + (threadIdx.x >> 6);   // global wave index
+    const int gw = block * kWavesPerWg + (threadIdx.x >> 6);   // global wave index
     const int strip = gw % nstrips;
     const int row0 = (gw / nstrips) * RW;
     if (row0 >= rows) return;
@@ -198,6 +208,27 @@ __global__ __launch_bounds__(kThreads) void k_grad_outer(const float* __restrict
             __builtin_nontemporal_store(g, reinterpret_cast<v4f*>(out + (size_t)r * cols));
         }
     }
+}
+template <int RW, bool SGD>
+__global__ __launch_bounds__(kThreads) void k_grad_outer(const float* __restrict__ delta, const float* __restrict__ a_prev,
+                                                         float* nabla_w, float* nabla_b, int rows, int cols, int nstrips,
+                                                         float eta) {
+    grad_outer_block<RW, SGD>(delta, a_prev, nabla_w, nabla_b, rows, cols, nstrips, eta, blockIdx.x);
+}
+
+// Both in one launch: stage 1 of the chain step delta^{l+1} -> delta^l, and beside it the gradients (or the descent step) of a
+// layer above, which do not wait for it.  A pass of a small net is a sequence of launches of about 3 us each, and this is
+// one for two: us a pass, in line without / with it: widths 72-100-64-200-128-80-64-400 83 / 67,
+// 84-996-6348-1364-1084-88 147 / 88;  N = 4100, L = 6 295 / 220;  N = 8192, L = 12 2021 / 1743 (the stores fill what the chain leaves of memory).
+struct OuterArgs { const float* delta; const float* a_prev; float* w; float* b; int rows, cols, nstrips; float eta; };
+template <int RPW, int RW, bool SGD>
+__global__ __launch_bounds__(kThreads) void k_chain_partial_beside_grads(const float* __restrict__ W,
+                                                                         const float* __restrict__ delta,
+                                                                         float* __restrict__ partial, int rows, int cols,
+                                                                         int strips, int chain_blocks, const OuterArgs g) {
+    const int x = blockIdx.x;
+    if (x < chain_blocks) chain_partial_block<RPW>(W, delta, partial, rows, cols, x % strips, x / strips);
+    else grad_outer_block<RW, SGD>(g.delta, g.a_prev, g.w, g.b, g.rows, g.cols, g.nstrips, g.eta, x - chain_blocks);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -249,6 +280,33 @@ hipError_t launch_chain_gemvT_f32(const float* W_next, const float* delta_next, 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_chain_finish<<<ceil_div(cols, kThreads), kThreads, 0, s>>>(partial, a_l, delta_l, cols, P);
+    return hipGetLastError();
+}
+
+template <bool SGD>
+static void chain_partial_beside_grads(const float* W_next, const float* delta_next, float* partial, int rows, int cols,
+                                       const OuterArgs& g, hipStream_t s) {
+    constexpr int RW = 16;
+    const int rpw = chain_rows_per_wave(rows), strips = ceil_div(cols, kWave * 4);
+    const int chain_blocks = strips * chain_partial_blocks(rows);
+    const int grid = chain_blocks + ceil_div(g.nstrips * ceil_div(g.rows, RW), kWavesPerWg);
+    if (rpw == 16)
+        k_chain_partial_beside_grads<16, RW, SGD><<<grid, kThreads, 0, s>>>(W_next, delta_next, partial, rows, cols, strips, chain_blocks, g);
+    else if (rpw == 8)
+        k_chain_partial_beside_grads<8, RW, SGD><<<grid, kThreads, 0, s>>>(W_next, delta_next, partial, rows, cols, strips, chain_blocks, g);
+    else
+        k_chain_partial_beside_grads<4, RW, SGD><<<grid, kThreads, 0, s>>>(W_next, delta_next, partial, rows, cols, strips, chain_blocks, g);
+}
+
+hipError_t launch_chain_gemvT_beside_grads_f32(const float* W_next, const float* delta_next, const float* a_l,
+                                               float* delta_l, float* partial, int rows, int cols, const OuterStep& o,
+                                               float sgd_eta, hipStream_t s) {
+    const OuterArgs g{o.delta, o.a_prev, o.w, o.b, o.rows, o.cols, ceil_div(o.cols, kWave * 4), sgd_eta};
+    if (sgd_eta != 0.0f) chain_partial_beside_grads<true>(W_next, delta_next, partial, rows, cols, g, s);
+    else chain_partial_beside_grads<false>(W_next, delta_next, partial, rows, cols, g, s);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_chain_finish<<<ceil_div(cols, kThreads), kThreads, 0, s>>>(partial, a_l, delta_l, cols, chain_partial_blocks(rows));
     return hipGetLastError();
 }
 

@@ -763,6 +763,36 @@ lf_status backward_steps(lf_net* net, const void* y, hipStream_t s) {
     return LF_OK;
 }
 
+// A single sample in line on one stream: as backward_steps, with the gradients beside the first of the chain step's kernels.
+lf_status backward_single(lf_net* net, const void* y, hipStream_t s) {
+    const int L = net->L;
+    const bool sgd = net->sgd_eta != 0.0f;
+    const bool chain_only = (net->debug_flags & LF_DEBUG_CHAIN_ONLY) != 0;
+    LF_HIP(net, lf::launch_output_error(net->a_ptr(L), y, net->d_ptr(L), nullptr, (size_t)net->width(L), false, net->cost_scale,
+                                        nullptr, 0, s));
+    const int lag = sgd ? 2 : 1;
+    for (int l = L - 1; l >= 2; --l) {
+        const float* const w = static_cast<const float*>(net->w[l - 1]);
+        const float* const a_l = static_cast<const float*>(net->a_ptr(l));
+        if (chain_only || l + lag > L) {
+            LF_HIP(net, lf::launch_chain_gemvT_f32(w, net->d_ptr(l + 1), a_l, net->d_ptr(l), net->partial(), net->width(l + 1),
+                                                   net->width(l), s));
+            continue;
+        }
+        const lf::GradStep g = grad_step(net, l + lag);
+        const lf::OuterStep o{g.D, static_cast<const float*>(g.A_prev), g.w, g.b, g.n_l, g.n_prev};
+        LF_HIP(net, lf::launch_chain_gemvT_beside_grads_f32(w, net->d_ptr(l + 1), a_l, net->d_ptr(l), net->partial(),
+                                                            net->width(l + 1), net->width(l), o, net->sgd_eta, s));
+    }
+    for (int l = std::min(L, 1 + lag); !chain_only && l >= 2; --l) {
+        const lf_status st = enqueue_grads(net, l, s);
+        if (st != LF_OK) return st;
+    }
+    net->bwd_done = !chain_only;
+    if (sgd) net->stepped = true;
+    return LF_OK;
+}
+
 // Address of this device's copy of `scratch` (asked once per device, with that device current).
 lf_status static_scratch_of_current_device(lf_net* net, void** out) {
     int dev = -1;
@@ -1020,6 +1050,12 @@ lf_status lf_backward_leapfrog(lf_net* net, const void* y, int k, void* hip_stre
         return st;
     }
     if (net->sched == LF_SCHED_AUTO && direct_minibatch(net)) return backward_steps(net, y, s);
+    // Left to the library, a single sample outside the persistent kernels' shapes has its gradients in line as well: its
+    // kernels are bound by memory or by their launches, and a worker's stream costs an event, a wait on another queue and a
+    // join.  us a pass, in line (gradients in launches of their own) / k = 2 / k = 5: widths 84-996-6348-1364-1084-88 147 / 187 /
+    // 201;  72-100-64-200-128-80-64-400 83 / 226 / 256;  N = 4100, L = 6 295 / 317 / 334;  N = 8192, L = 4 503 / 523 / 522, L = 12
+    // 2021 / 2040 / 2094;  N = 5000, L = 12 947 / 943 / 1001.
+    if (net->sched == LF_SCHED_AUTO && single_sample_path(net->N, net->B, net->dt)) return backward_single(net, y, s);
     st = ensure_workers(net, k, s);
     if (st != LF_OK) return st;
     return backward_streams(net, y, k, s, net->partial(), net->raw(), /*in_line=*/k == 1);

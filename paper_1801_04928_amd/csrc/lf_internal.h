@@ -28,6 +28,12 @@ hipError_t launch_chain_gemvT_f32(const float* W_next, const float* delta_next, 
 hipError_t launch_grad_outer_f32(const float* delta, const float* a_prev, float* nabla_w,
                                  float* nabla_b, int rows, int cols, float sgd_eta, hipStream_t s);
 
+// Both at once: the chain step, and beside its first kernel the gradients of a layer whose operands are there already.
+struct OuterStep { const float* delta; const float* a_prev; float* w; float* b; int rows, cols; };
+hipError_t launch_chain_gemvT_beside_grads_f32(const float* W_next, const float* delta_next, const float* a_l,
+                                               float* delta_l, float* partial, int rows, int cols, const OuterStep& grads,
+                                               float sgd_eta, hipStream_t s);
+
 // ---- any B, either storage type ----------------------------------------------------------------
 
 // eq. (bp1): delta_L = scale * (a_L - y) (.) a_L (1 - a_L) over count = B*N elements (scale: a power

@@ -1,0 +1,43 @@
+"""Single-sample nets outside the persistent kernels' shapes, schedule left to the library: the gradients ride beside the chain
+step of the layer below.  The same bits as the stream schedule's launches of their own, and the oracle's gradients."""
+import numpy as np
+import pytest
+
+from lf_inputs import make_net
+from tests.gpu_util import check_against_oracle, log, run_gpu, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("widths", [
+    (4, 8),                                    # no chain step
+    (260, 4, 516),                             # one chain step, less than a row block
+    (4100, 4100, 4100),                        # beyond the persistent kernels' width
+    (8, 2052, 260, 4096, 12, 1000, 4, 256),    # 4, 8 and 16 rows a wave in one net; strips and rows that end inside a block
+    (84, 996, 6348, 1364, 88),
+])
+def test_gradients_beside_the_chain_match_the_streams_and_the_oracle(widths):
+    import paper_1801_04928_amd as P
+    import torch
+    L = len(widths)
+    net = make_net(L, widths, 1, dtype="f32", seed=sum(widths), cache=False)
+    g = run_gpu(net, L - 1)
+    rep = check_against_oracle(net, g)
+    log(f"single sample in line {widths}: worst {rep['worst']:.2e}")
+
+    def run(sched, k, eta):
+        g.load(net)
+        g.set_schedule(sched)
+        g.set_sgd(eta)
+        for t in g.nabla_w + g.nabla_b:
+            t.fill_(float("nan"))
+        g.forward()
+        g.backward(k)
+        torch.cuda.synchronize()
+        return [to_np(t).view(np.uint32).copy() for t in (g.w + g.b if eta else g.nabla_w + g.nabla_b)]
+
+    for eta in (0.0, 0.125):
+        want = run(P.LF_SCHED_STREAMS, 1, eta)
+        for sched, k in ((P.LF_SCHED_AUTO, 1), (P.LF_SCHED_AUTO, L - 1), (P.LF_SCHED_STREAMS, L - 1)):
+            assert all(np.array_equal(a, b) for a, b in zip(want, run(sched, k, eta))), (sched, k, eta)
+    g.close()
