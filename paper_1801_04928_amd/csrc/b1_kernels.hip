@@ -18,7 +18,7 @@ __host__ __device__ constexpr int ceil_div(int a, int b) { return (a + b - 1) / 
 // One wave owns R consecutive rows.  a_in is staged once per workgroup in LDS; a lane walks the row
 // in float4 steps of stride 64 lanes, keeps one accumulator per row, and the 64 lane sums are
 // combined in a fixed order (row rotations, then the four rows of 16 lanes).
-template <int R>
+template <int R, bool NT>
 __global__ __launch_bounds__(kThreads) void k_fwd_gemv(const float* __restrict__ W,
                                                        const float* __restrict__ bias,
                                                        const float* __restrict__ a_in,
@@ -43,14 +43,14 @@ __global__ __launch_bounds__(kThreads) void k_fwd_gemv(const float* __restrict__
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] = 0.0f;
 
-    constexpr int U = (R >= 4) ? 2 : (R == 2 ? 4 : 8);   // float4 loads in flight per lane = R*U
+    constexpr int U = R == 2 ? 4 : 8;                    // float4 loads in flight per lane = R*U
     int v = lane;
     for (; v + (U - 1) * kWave < nvec; v += U * kWave) {
         v4f w[U][R];
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int r = 0; r < R; ++r) w[u][r] = wrow[r][v + u * kWave];
+            for (int r = 0; r < R; ++r) w[u][r] = NT ? __builtin_nontemporal_load(&wrow[r][v + u * kWave]) : wrow[r][v + u * kWave];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const v4f a = s_a[v + u * kWave];
@@ -255,17 +255,22 @@ int chain_rows_per_wave(int rows) { return rows >= 4096 ? 16 : (rows >= 2048 ? 8
 
 int chain_partial_blocks(int rows) { return ceil_div(rows, kWavesPerWg * chain_rows_per_wave(rows)); }
 
+// Rows a wave: one where the matrix is large or small, two in between (as few waves as fill the chip, as many bytes in flight).
+// Weights that exceed the cache are read with non-temporal loads.  Forward pass, us, four rows a wave / one / one, non-temporal:
+// N = 4100, L = 6 83 / 74 / 66;  N = 5000, L = 12 265 / 225 / 206;  N = 8192, L = 12 649 / 544 / 490 (6.0 TB/s).
+template <bool NT>
+static void fwd_gemv(const float* W, const float* b, const float* a_in, float* a_out, int rows, int cols, hipStream_t s) {
+    const size_t lds = (size_t)cols * sizeof(float), elems = (size_t)rows * cols;
+    if (elems >= (size_t)2048 * 2048 && elems < (size_t)4096 * 4096)
+        k_fwd_gemv<2, NT><<<ceil_div(rows, kWavesPerWg * 2), kThreads, lds, s>>>(W, b, a_in, a_out, rows, cols);
+    else
+        k_fwd_gemv<1, NT><<<ceil_div(rows, kWavesPerWg), kThreads, lds, s>>>(W, b, a_in, a_out, rows, cols);
+}
+
 hipError_t launch_fwd_gemv_f32(const float* W, const float* b, const float* a_in, float* a_out,
-                               int rows, int cols, hipStream_t s) {
-    const size_t lds = (size_t)cols * sizeof(float);
-    const size_t elems = (size_t)rows * cols;
-    if (elems >= (size_t)4096 * 4096) {
-        k_fwd_gemv<4><<<ceil_div(rows, kWavesPerWg * 4), kThreads, lds, s>>>(W, b, a_in, a_out, rows, cols);
-    } else if (elems >= (size_t)2048 * 2048) {
-        k_fwd_gemv<2><<<ceil_div(rows, kWavesPerWg * 2), kThreads, lds, s>>>(W, b, a_in, a_out, rows, cols);
-    } else {
-        k_fwd_gemv<1><<<ceil_div(rows, kWavesPerWg), kThreads, lds, s>>>(W, b, a_in, a_out, rows, cols);
-    }
+                               int rows, int cols, bool stream_weights, hipStream_t s) {
+    if (stream_weights) fwd_gemv<true>(W, b, a_in, a_out, rows, cols, s);
+    else fwd_gemv<false>(W, b, a_in, a_out, rows, cols, s);
     return hipGetLastError();
 }
 

@@ -1001,12 +1001,13 @@ lf_status lf_forward(lf_net* net, const void* x1, void* hip_stream) {
         net->fwd_done = true;
         return LF_OK;
     }
+    const bool single = single_sample_path(net->N, net->B, net->dt), stream_weights = single && weights_exceed_cache(net);
     for (int l = 2; l <= net->L; ++l) {
-        if (single_sample_path(net->N, net->B, net->dt)) {
+        if (single) {
             LF_HIP(net, lf::launch_fwd_gemv_f32(static_cast<const float*>(net->w[l - 2]), net->b[l - 2],
                                                 static_cast<const float*>(net->a_ptr(l - 1)),
                                                 static_cast<float*>(net->a_ptr(l)), net->width(l),
-                                                net->width(l - 1), s));
+                                                net->width(l - 1), stream_weights, s));
         } else if (net->gemm.forward == lf::GEMM_DIRECT) {
             LF_HIP(net, lf::launch_forward_direct(net->w[l - 2], net->b[l - 2], net->a_ptr(l - 1), net->a_ptr(l),
                                                   net->width(l), net->width(l - 1), net->B, bf, s));

@@ -15,9 +15,9 @@ namespace lf {
 // Row blocks the transposed GEMV of eq. (bp2) is split into (its partial buffer is [P][cols]).
 int chain_partial_blocks(int rows);
 
-// eqs. (z),(a): a_out = sigma(W a_in + b)
+// eqs. (z),(a): a_out = sigma(W a_in + b); stream_weights: W is not worth keeping in the caches
 hipError_t launch_fwd_gemv_f32(const float* W, const float* b, const float* a_in, float* a_out,
-                               int rows, int cols, hipStream_t s);
+                               int rows, int cols, bool stream_weights, hipStream_t s);
 // eq. (bp2): delta_l = (W_next^T delta_next) (.) a_l (1 - a_l); W_next is rows x cols, delta_next has rows
 // entries, delta_l and a_l cols; partial: [chain_partial_blocks(rows)][cols]
 hipError_t launch_chain_gemvT_f32(const float* W_next, const float* delta_next, const float* a_l,

@@ -183,7 +183,8 @@ __device__ __forceinline__ void contract(v4f (&acc)[MT][NT], float* lds, const v
     v4f* const lp = reinterpret_cast<v4f*>(lds) + (threadIdx.x >> 6) * (OP::kLdsVecs + OQ::kLdsVecs);
     v4f* const lq = lp + OP::kLdsVecs;
     const int units = ceil_div(K, Unit<T>::Q), pairs = ceil_div(units, 2);
-    // (a QC operand goes through LDS by pairs; without one, a wave that has the contraction to itself ends with its last unit)
+    // A QC operand goes through LDS by pairs; without one, a wave that has the contraction to itself ends with its last unit
+    // (gradients, fp32, us a layer, pairs / units: N = 4096, B = 8 22.0 / 18.2;  N = 1500, B = 100 13.3 / 12.6).
     const int nu = P_IC && W == 1 ? units : (w < pairs ? 2 * ((pairs - w + W - 1) / W) : 0);
     // (units past the last one start at K or beyond and load zeros)
     auto q_of = [&](int j) { return (((j >> 1) * W + w) * 2 + (j & 1)) * Unit<T>::Q; };
