@@ -607,55 +607,81 @@ TileShape chain_tile(int B, int n_out, bool bf16, bool chain) {
     return best;
 }
 
-// The chain product of a few samples is the reading of W_next, by columns: a tile's workgroup walks a strip of it, 32 nt (bf16)
-// or 64 nt (fp32) bytes wide, down all its rows.  Whole tiles alone make too few workgroups to keep memory busy (N = 4096,
-// B = 8, bf16: 128 of 64-byte strips, 2.1 TB/s), so their contraction is split over workgroups that meet in memory, which
-// costs about 2 us, and the strips become wider.  us a layer of a backward pass (weights and gradients from memory), unsplit
-// -> split (mt, nt, splits):
-//   bf16  B = 8: N = 1024 7.3 -> 6.9 (1, 2, 4);  2048 10.5 -> 8.4 (1, 2, 4);  3072 15.7 -> 13.1 (1, 4, 2);  4096 27.8 -> 23.4 (1, 4, 2);
-//         6144 52 -> 43, 8192 80 -> 71 (1, 4, 2);  B = 32: N = 1536 9.1 -> 7.8, 2048 10.6 -> 8.7 (2, 2, 4);  3072 15.0 -> 14.5,
-//         6144 57 -> 45 (2, 4, 2);  B = 64: N = 4096 30.8 -> 25.6 (4, 4, 4);  5200 55 -> 45, 8192 86 -> 78 (4, 4, 2)
-//   fp32  B = 8: N = 1024 7.7 -> 7.0 (1, 2, 4);  2048 12.1 -> 11.3, 3072 27 -> 21, 4096 37 -> 33 (1, 4, 4);  6144 73 -> 68 (1, 4, 2);
-//         B = 32: N = 3072 28 -> 24, 4096 41 -> 37 (2, 4, 4);  6144 79 -> 70 (2, 4, 2);  B = 64: N = 4096 53 -> 49 (2, 4, 2);
-//         5200 84 -> 79 (4, 4, 2)
-// Below 1024 rows or columns the meeting costs more than it brings (N = 512, 768: 20 to 30 % slower), in between (bf16 B = 24
-// at N = 2600, fp32 B = 32 at N = 2048) nothing is gained, and longer minibatches have tiles enough.  Three row blocks whose
-// 32 x 64 tiles are one a compute unit stay with those: a quarter of every 64 x 64 tile would be padding.
-TileShape chain_shape(int B, int n_l, int n_next, bool bf16) {
-    TileShape t{0, 0, 1};
-    const int rows = ceil_div(B, 16);
-    auto groups = [&](int mt, int nt) { return ceil_div(rows, mt) * ceil_div(n_l, 16 * nt); };
-    auto most = [&](int mt, int nt) { return groups(mt, nt) * 4 <= kSplitWorkgroups ? 4 : 2; };
-    if (std::min(n_l, n_next) >= 1024) {
-        if (bf16) {
-            if (rows <= 2 && n_l <= 2048) t = {rows, 2, 4};
-            else if (rows == 1 || (rows == 2 && n_l >= 3072)) t = {rows, 4, 2};
-            else if (rows > 2 && rows <= 4 && n_l >= 4096 && !(rows == 3 && groups(2, 4) == 256)) t = {4, 4, most(4, 4)};
-        } else {
-            if (rows == 1) t = n_l < 2048 ? TileShape{1, 2, 4} : TileShape{1, 4, most(1, 4)};
-            else if (rows == 2 && n_l >= 3072) t = {2, 4, most(2, 4)};
-            else if (rows > 2 && rows <= 4 && n_l >= 3072) t = n_l <= 4096 ? TileShape{2, 4, 2} : TileShape{4, 4, 2};
-        }
-    }
-    if (t.splits == 1 || groups(t.mt, t.nt) * t.splits > kSplitWorkgroups) return chain_tile(B, n_l, bf16, true);
-    return t;
-}
-size_t chain_scratch(int B, int n_l, int n_next, bool bf16) {  // floats: arrival counters, then the partial tiles
-    const TileShape t = chain_shape(B, n_l, n_next, bf16);
-    if (t.splits == 1) return 0;
-    return kSplitWorkgroups + (size_t)ceil_div(B, 16 * t.mt) * ceil_div(n_l, 16 * t.nt) * t.splits * (16 * t.mt) * (16 * t.nt);
-}
-
 // How nabla_w of a layer is cut: 64 x 64 a wave where that gives at least four waves per compute unit; 32 x 32 a wave
 // below; and where even those leave SIMDs idle and the minibatch is long enough to divide, 32 x 32 a workgroup whose
 // waves share the samples.  Backward, us a layer, 64 / 32 / 32 split: fp32, N = 2048, B = 64: 14.3 / 18.5 / 31; N = 1024,
 // B = 64: 11.1 / 8.8 / 10.7; N = 512, B = 128: 14 / 7.3 / 6.2, B = 512: 39 / 17 / 10; bf16, N = 1024, B = 256: 10.9 / 8.4 / 12.
 enum GradKind { GRAD_WAVE_64, GRAD_WAVE_32, GRAD_SPLIT_32 };
 
-GradKind grad_kind(const GradStep& g, int B, bool bf16) {
-    if ((long)ceil_div(g.n_l, 64) * ceil_div(g.n_prev, 64) >= 1024) return GRAD_WAVE_64;
-    if ((long)ceil_div(g.n_l, 32) * ceil_div(g.n_prev, 32) < 1024 && B > (bf16 ? 96 : 48)) return GRAD_SPLIT_32;
+GradKind grad_kind(int n_l, int n_prev, int B, bool bf16) {
+    if ((long)ceil_div(n_l, 64) * ceil_div(n_prev, 64) >= 1024) return GRAD_WAVE_64;
+    if ((long)ceil_div(n_l, 32) * ceil_div(n_prev, 32) < 1024 && B > (bf16 ? 96 : 48)) return GRAD_SPLIT_32;
     return GRAD_WAVE_32;
+}
+
+// The chain product of a few samples is the reading of W_next, by columns: a tile's workgroup walks a strip of it, 32 nt (bf16)
+// or 64 nt (fp32) bytes wide, down all its rows.  Whole tiles alone make too few workgroups to keep memory busy (N = 4096,
+// B = 8, bf16: 128 of 64-byte strips, 2.1 TB/s), so their contraction is split over workgroups that meet in memory, which
+// costs about 2 us, and the strips become wider.  Backward, us a layer, whole tiles -> split (mt, nt, splits), weights in the
+// cache (140 MB of them) | from memory (1.2 GB):
+//   bf16  B = 8: N = 1024 7.0 -> 6.6, 1536 8.2 -> 7.4, 2048 10.0 -> 8.0 | 11.8 -> 8.1 (1, 2, 4);  2056 10.7 -> 9.5 | 12.2 -> 10.0,
+//         2304 10.3 -> 9.2 | 13.1 -> 10.4 (1, 4, 4);  2560 12.1 -> 10.9 | 15.6 -> 13.2, 3072 14.9 -> 12.8 | 19.8 -> 16.1, 4096 18.6 -> 18.4 |
+//         26.9 -> 22.6, 8192 57 -> 57 | 73 -> 66 (1, 4, 2);  four splits there: 10.4 | 12.2, 14.0 | 14.5, 20.9 | 22.1;
+//         B = 32: N = 1536 8.3 -> 7.6, 2048 10.1 -> 8.6 | 12.5 -> 9.0 (2, 2, 4);  3072 14.2 -> 14.3 | 20.0 -> 18.1, 4096 22.2 -> 19.1 |
+//         28.1 -> 24.5, 6144 35 -> 35 | 51 -> 43 (2, 4, 2);  B = 64: N = 3072 15.0 -> 14.5 | 21.3 -> 18.0, 4096 23.0 -> 22.7 | 29.6 -> 25.8
+//         (2, 4, 2);  4104 26.3 -> 25.6 | 35.2 -> 32.1, 8192 63 -> 62 | 81 -> 74 (4, 4, 2);  B = 40: 8128 72 -> 70 | 86 -> 82, 8192 62 -> 61 | 79 -> 73
+//   fp32  B = 8: N = 1024 6.9 -> 6.4, 1536 9.1 -> 8.1 | 10.9 -> 8.4 (1, 2, 4);  2304 11.4 -> 10.8 | 14.8 -> 12.9, 3072 16.9 -> 16.2 | 22.5 -> 17.6
+//         (1, 4, 4);  6144 45 -> 44 | 62 -> 57 (1, 4, 2);  B = 32: N = 3072 20.2 -> 21.6 | 26.0 -> 23.0, 3584 25.0 -> 24.4 | 31.4 -> 26.4 (2, 4, 4);
+//         4096 30.3 -> 28.2 | 37.2 -> 33.1 (four splits: 31.0 | 34.5), 6144 53 -> 53 | 75 -> 66 (2, 4, 2);  B = 64: N = 4096 40.3 -> 36.9 |
+//         50.4 -> 46.4 (2, 4, 2);  4104 44.1 -> 44.4 | 56.1 -> 51.2 (4, 4, 2)
+// Nothing is gained, or little, below 1024 rows or columns (the meeting: N = 512, 768 20 to 30 % slower), for 17 .. 32 samples
+// between the ranges below (bf16 N = 2176 -1 | +7 %), and by longer minibatches, which have tiles enough.  fp32, 33 samples and
+// more: 4 x 4 blocks take the matrix cores as long as two of 2 x 4, and what their strips gain is lost where the gradients' matrix
+// instructions beside them set the pace (B = 64, N = 4608: 45.5 -> 49.0 | 59.4 -> 58.5; B = 40: 43.4 -> 42.5 | 57.6 -> 50.0, 5632 59 -> 61 | 74 -> 74).
+TileShape split_shape(int rows, int n_l, bool bf16) {
+    if (bf16) {
+        if (rows <= 2 && n_l <= 2048) return {rows, 2, 4};
+        if (rows == 1) return {1, 4, n_l <= 2304 ? 4 : 2};
+        if (rows == 2 && n_l >= 3072) return {2, 4, 2};
+        if (rows <= 4 && n_l >= 3072) return n_l <= 4096 ? TileShape{2, 4, 2} : TileShape{4, 4, 2};
+    } else {
+        if (rows == 1) return n_l <= 1984 ? TileShape{1, 2, 4} : TileShape{1, 4, n_l <= 4096 ? 4 : 2};
+        if (rows == 2 && n_l >= 3072) return {2, 4, n_l <= 3584 ? 4 : 2};
+        if (rows <= 4 && n_l >= 3072 && n_l <= 4096) return {2, 4, 2};
+        if (rows <= 4 && n_l > 4096 && n_l <= (rows == 3 ? 5200 : 4352)) return {4, 4, 2};
+    }
+    return {0, 0, 1};
+}
+
+// Workgroups of a chain product in the grid.
+int chain_blocks(const TileShape& t, int B, int n_l) {
+    return ceil_div(ceil_div(n_l, 16 * t.nt), 8) * 8 * ceil_div(B, 16 * t.mt) * t.splits;
+}
+
+TileShape chain_shape(int B, int n_l, int n_next, bool bf16) {
+    const TileShape whole = chain_tile(B, n_l, bf16, true);
+    const TileShape t = std::min(n_l, n_next) < 1024 ? TileShape{0, 0, 1} : split_shape(ceil_div(B, 16), n_l, bf16);
+    if (t.splits == 1 || ceil_div(B, 16 * t.mt) * ceil_div(n_l, 16 * t.nt) * t.splits > kSplitWorkgroups) return whole;
+    if (n_next >= 2 * n_l) return t;
+    // A contraction that is short beside the width is not worth the meeting.  us a pair of layers, whole -> split: bf16, B = 64, 1024
+    // rows x 4096 columns 25.4 -> 30.0, 2048 x 4096 37.1 -> 37.5, 3072 x 4096 49.6 -> 47.8;  B = 8, 1024 x 4096 22.0 -> 22.9, 2048 x 4096
+    // 33.4 -> 31.7, 2048 x 8192 59.5 -> 59.6, 4096 x 8192 87 -> 84;  fp32, B = 8, 1024 x 4096 28.8 -> 29.3, 2048 x 4096 41.4 -> 40.2.
+    if (n_next < n_l && (n_next < 1536 || (B <= 32 ? 2 * n_next < n_l : 3 * n_next < 2 * n_l))) return whole;
+    // Beside 32 x 32 gradients (of the layer with these weights) three workgroups are resident on a compute unit, four of the fp32
+    // ones with the fewest registers; where the splits make it more, or one more than whole tiles would, that turn costs more
+    // than they bring: bf16, B = 8: N = 1152 (two) 7.2 -> 6.7, 1280 (three, for two) 8.9 -> 9.3 with the descent step, 1536 (three) 8.2 ->
+    // 7.4, 1600 (four) 7.9 -> 9.4, 1920 9.6 -> 10.5;  fp32: 1152 6.9 -> 6.7, 1216 6.8 -> 7.6, 1536 9.1 -> 8.1, 1600 9.0 -> 10.6, 1920 10.2 -> 13.5.
+    if (grad_kind(n_next, n_l, B, bf16) != GRAD_WAVE_64) {
+        const int grads = ceil_div(n_next, 64) * ceil_div(n_l, 64), resident = !bf16 && t.mt == 1 && t.nt == 4 ? 4 : 3;
+        const int turns = ceil_div(chain_blocks(t, B, n_l) + grads, 256);
+        if (turns > resident || turns > ceil_div(chain_blocks(whole, B, n_l) + grads, 256)) return whole;
+    }
+    return t;
+}
+size_t chain_scratch(int B, int n_l, int n_next, bool bf16) {  // floats: arrival counters, then the partial tiles
+    const TileShape t = chain_shape(B, n_l, n_next, bf16);
+    if (t.splits == 1) return 0;
+    return kSplitWorkgroups + (size_t)ceil_div(B, 16 * t.mt) * ceil_div(n_l, 16 * t.nt) * t.splits * (16 * t.mt) * (16 * t.nt);
 }
 
 // What the direct kernels take for a layer of a bf16 net in us, for the choice between them and the wide-net kernels
@@ -683,8 +709,7 @@ double forward_us(int n_out, int n_in, int B) {
     return 2.8 + 0.915 * chain_us(B, n_out, n_in, false) * (n_in % 64 ? 1.34 : 1.0) + 0.06 * 2e-6 * n_out * n_in;
 }
 double grad_us(int n_l, int n_prev, int B) {
-    const GradStep g{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, n_l, n_prev};
-    const int gt = grad_kind(g, B, true) == GRAD_WAVE_64 ? 4 : 2;
+    const int gt = grad_kind(n_l, n_prev, B, true) == GRAD_WAVE_64 ? 4 : 2;
     const double waves = (double)ceil_div(n_l, 16 * gt) * ceil_div(n_prev, 16 * gt);
     const double wave = 2.0 * ceil_div(B, 64) * 35 * 2 * gt / 2400.0;                // units of 32 samples come in pairs
     return 1.58 * turns(waves, 1024, 0.4) * 4 * wave * (n_prev % 64 ? 1.24 : 1.0) + 0.442e-6 * n_l * n_prev;
@@ -757,7 +782,8 @@ hipError_t launch_forward_direct(const void* W, const float* bias, const void* A
 hipError_t launch_backward_step(const ChainStep* c, const GradStep* grads, int ngrads, int B, bool bf16, float sgd_eta,
                                 hipStream_t s) {
     using namespace direct;
-    if (ngrads == 2 && grad_kind(grads[0], B, bf16) != grad_kind(grads[1], B, bf16)) {
+    auto kind_of = [&](const GradStep& g) { return grad_kind(g.n_l, g.n_prev, B, bf16); };
+    if (ngrads == 2 && kind_of(grads[0]) != kind_of(grads[1])) {
         const hipError_t e = launch_backward_step(c, grads, 1, B, bf16, sgd_eta, s);
         return e != hipSuccess ? e : launch_backward_step(nullptr, grads + 1, 1, B, bf16, sgd_eta, s);
     }
@@ -778,9 +804,9 @@ hipError_t launch_backward_step(const ChainStep* c, const GradStep* grads, int n
         g.tiles_n = ceil_div(c->n_l, 16 * t.nt);
         g.splits = t.splits;
         g.scratch = c->scratch;
-        g.chain_blocks = ceil_div(g.tiles_n, 8) * 8 * g.tiles_m * g.splits;
+        g.chain_blocks = chain_blocks(t, B, c->n_l);
     }
-    const GradKind kind = ngrads > 0 ? grad_kind(grads[0], B, bf16) : GRAD_WAVE_32;
+    const GradKind kind = ngrads > 0 ? kind_of(grads[0]) : GRAD_WAVE_32;
     const bool split = kind == GRAD_SPLIT_32;
     const int gt = kind == GRAD_WAVE_64 ? 4 : 2;
     for (int i = 0; i < ngrads; ++i) {

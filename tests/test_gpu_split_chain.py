@@ -15,14 +15,19 @@ def _tensors(g):
 
 @pytest.mark.parametrize("widths,B,dtype", [
     ((1024,) * 4, 8, "bf16"),               # 16 x 32 tiles, four splits: the narrowest
-    ((1288, 1032, 2048, 1024), 24, "bf16"),  # 32 x 32, four splits; ragged tiles and contractions
+    ((1288, 1032, 2048, 1024), 24, "bf16"),  # 32 x 32, four splits; ragged tiles and contractions; a whole step above it
+    ((2184,) * 3, 16, "bf16"),              # 16 x 64, four splits
     ((2600,) * 3, 16, "bf16"),              # 16 x 64, two splits
     ((3080,) * 3, 19, "bf16"),              # 32 x 64, two splits
-    ((4096,) * 4, 64, "bf16"),              # 64 x 64, four splits, all of 256 workgroups
+    ((3080,) * 3, 41, "bf16"),              # the same for three row blocks
+    ((4096,) * 4, 64, "bf16"),              # 32 x 64, two splits, all of 256 workgroups
     ((4104,) * 3, 33, "bf16"),              # 64 x 64, two splits
-    ((1024, 1028, 1500, 1024), 2, "f32"),   # 16 x 32, four splits
+    ((8192,) * 3, 40, "bf16"),              # 64 x 64, two splits, all of 256 workgroups, a row block past the minibatch
+    ((1024, 1028, 1040, 1024), 2, "f32"),   # 16 x 32, four splits
+    ((1024, 1028, 1500, 1024), 2, "f32"),   # whole steps: a turn more, a contraction shorter than the width
     ((2052,) * 3, 16, "f32"),               # 16 x 64, four splits
     ((3076,) * 3, 30, "f32"),               # 32 x 64, four splits
+    ((3588,) * 3, 30, "f32"),               # 32 x 64, two splits
     ((4100, 3072, 4100), 37, "f32"),        # 32 x 64, two splits, a ragged second row block
     ((4100,) * 3, 64, "f32"),               # 64 x 64, two splits
     ((1020, 1024, 1024, 2048, 512), 16, "f32"),   # split and whole steps in one net

@@ -1,5 +1,7 @@
 """Which kernels a net's passes launch, and which nets lf_backward_leapfrog_noalloc serves, from the calls the library makes
 on the host (no kernel runs)."""
+import re
+
 import pytest
 
 from tests import host_hip
@@ -61,7 +63,7 @@ def test_nets_served_without_allocation(program, N, B, dtype, want):
 
 
 @pytest.mark.parametrize("N,B,dtype,mt,nt", [
-    (8192, 40, "bf16", 2, 4), (9216, 32, "bf16", 2, 4),        # one turn of the compute units
+    (9216, 32, "bf16", 2, 4),                                  # one turn of the compute units
     (8256, 33, "bf16", 4, 4), (9216, 48, "bf16", 4, 4),        # 4 x 4 blocks, one of them past the minibatch: still one turn
     (16384, 48, "f32", 4, 4),
 ])
@@ -70,6 +72,44 @@ def test_tile_of_a_direct_product(program, N, B, dtype, mt, nt):
     type_ = {"f32": "f", "bf16": "DF16b"}[dtype]
     assert len(forward) == 3 and all(f"k_forward_tileI{type_}Li{mt}ELi{nt}E" in name for name in forward)
     assert sum(f"k_backward_stepI{type_}Li{mt}ELi{nt}E" in name for name in backward) == 2
+
+
+def test_tile_of_a_direct_forward_product_in_one_turn(program):
+    forward, _, _ = _routes(program, [8192] * 4, 40, "bf16", LF_GEMM_BIG="0")
+    assert len(forward) == 3 and all("k_forward_tileIDF16bLi2ELi4E" in name for name in forward)
+
+
+@pytest.mark.parametrize("widths,B,dtype,want", [
+    # (tile in 16 x 16 blocks, split over workgroups) of the chain steps, top layer first
+    ([1536] * 4, 8, "bf16", [(1, 2, True)] * 2), ([2048] * 4, 32, "bf16", [(2, 2, True)] * 2),
+    ([1536] * 4, 8, "f32", [(1, 2, True)] * 2), ([3072] * 4, 30, "f32", [(2, 4, True)] * 2),
+    # the launch's workgroups would be a turn more
+    ([1280] * 4, 8, "bf16", [(1, 2, False)] * 2), ([1600] * 4, 8, "bf16", [(1, 2, False)] * 2),
+    ([1920] * 4, 24, "bf16", [(1, 2, False)] * 2),
+    ([1280] * 4, 8, "f32", [(1, 1, False)] * 2), ([1920] * 4, 16, "f32", [(1, 1, False)] * 2),
+    # contractions that are short beside the width, and long ones
+    ([2048, 4096, 1024, 4096, 2048], 64, "bf16", [(2, 2, False), (1, 2, False), (2, 2, False)]),
+    ([2048, 4096, 3072, 4096, 2048], 64, "bf16", [(2, 2, False), (2, 4, True), (2, 4, True)]),
+    ([1024, 8192, 2048, 8192], 8, "bf16", [(1, 2, True), (1, 2, False)]),
+    ([1024, 4096, 1024, 4096], 8, "f32", [(1, 2, True), (1, 1, False)]),
+    ([1536, 2048, 1536, 2048], 8, "f32", [(1, 1, False), (1, 4, True)]),
+    ([2048, 4096, 2048, 4096], 8, "bf16", [(1, 2, True), (1, 4, True)]),
+    # a width is cut as its neighbours are
+    *[([n] * 3, B, "bf16", [(4, 4, True)]) for n in (4104, 8128, 8136, 8192) for B in (33, 40, 48, 64)],
+    *[([n] * 3, 64, "bf16", [(2, 4, True)]) for n in (3072, 4088, 4096)],
+    *[([n] * 3, 8, "bf16", [(1, 4, True)]) for n in (2056, 3072, 8192)],
+    # where the gradients beside it set the pace
+    ([4608] * 3, 64, "f32", [(2, 4, False)]), ([4608] * 3, 40, "f32", [(4, 4, True)]), ([5632] * 3, 40, "f32", [(2, 4, False)]),
+])
+def test_chain_steps_are_split_where_that_pays(program, widths, B, dtype, want):
+    _, backward, _ = _routes(program, widths, B, dtype, LF_GEMM_BIG="0")
+    steps = [name for name in backward if "k_backward_step" in name][:len(want)]
+    type_ = {"f32": "f", "bf16": "DF16b"}[dtype]
+    got = []
+    for name in steps:
+        mt, nt, split = re.search(rf"k_backward_stepI{type_}Li(\d)ELi(\d)ELi\dELb[01]ELb([01])E", name).groups()
+        got.append((int(mt), int(nt), split == "1"))
+    assert got == want
 
 
 # us a layer, (direct, wide-net kernels), measured at L = 6 .. 8, k = 4: the choice is to be the faster side
