@@ -44,34 +44,50 @@ __global__ __launch_bounds__(kThreads) void k_fwd_gemv(const float* __restrict__
     for (int r = 0; r < R; ++r) acc[r] = 0.0f;
 
     constexpr int U = R == 2 ? 4 : 8;                    // float4 loads in flight per lane = R*U
-    int v = lane;
-    for (; v + (U - 1) * kWave < nvec; v += U * kWave) {
-        v4f w[U][R];
+    v4f w[U][R];
+    auto request = [&](int u, int v) {
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int r = 0; r < R; ++r) w[u][r] = NT ? __builtin_nontemporal_load(&wrow[r][v + u * kWave]) : wrow[r][v + u * kWave];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const v4f a = s_a[v + u * kWave];
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                acc[r] = fmaf(w[u][r].x, a.x, acc[r]);
-                acc[r] = fmaf(w[u][r].y, a.y, acc[r]);
-                acc[r] = fmaf(w[u][r].z, a.z, acc[r]);
-                acc[r] = fmaf(w[u][r].w, a.w, acc[r]);
-            }
-        }
-    }
-    for (; v < nvec; v += kWave) {
+        for (int r = 0; r < R; ++r) w[u][r] = NT ? __builtin_nontemporal_load(&wrow[r][v]) : wrow[r][v];
+    };
+    auto add = [&](int u, int v) {
         const v4f a = s_a[v];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const v4f w = wrow[r][v];
-            acc[r] = fmaf(w.x, a.x, acc[r]);
-            acc[r] = fmaf(w.y, a.y, acc[r]);
-            acc[r] = fmaf(w.z, a.z, acc[r]);
-            acc[r] = fmaf(w.w, a.w, acc[r]);
+            acc[r] = fmaf(w[u][r].x, a.x, acc[r]);
+            acc[r] = fmaf(w[u][r].y, a.y, acc[r]);
+            acc[r] = fmaf(w[u][r].z, a.z, acc[r]);
+            acc[r] = fmaf(w[u][r].w, a.w, acc[r]);
+        }
+    };
+    int v = lane, left = nvec;                           // this lane's vector; vectors of the row from lane 0's on
+#pragma unroll 1
+    for (; left >= U * kWave; left -= U * kWave, v += U * kWave) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) request(u, v + u * kWave);
+#pragma unroll
+        for (int u = 0; u < U; ++u) add(u, v + u * kWave);
+    }
+    // What is left of the row, U - 1 whole steps and a part of one at most: requested at once as well (U/2, U/4, .. 1 steps, then the
+    // part), but for a step or two, which short rows end with sooner (widths 64-8192-64-8192-64 3.9 us a layer, 4.1 that way).
+    // One step after the other, us a layer: N = 8000, L = 3 53 -> 50, 14000, L = 2 155 -> 142; non-temporal 46 -> 43, 126 -> 118.
+    if (left > 2 * kWave) {
+        const int steps = left / kWave;
+        auto rest = [&](auto each) {
+#pragma unroll
+            for (int h = U / 2; h >= 1; h /= 2)
+                if (steps & h) {
+#pragma unroll
+                    for (int u = 0; u < h; ++u) each(U - 2 * h + u, v + ((steps & (U - 2 * h)) + u) * kWave);
+                }
+            if (lane < left % kWave) each(U - 1, v + steps * kWave);
+        };
+        rest(request);
+        rest(add);
+    } else {
+#pragma unroll 1
+        for (; v < nvec; v += kWave) {
+            request(0, v);
+            add(0, v);
         }
     }
 #pragma unroll
@@ -257,7 +273,8 @@ int chain_partial_blocks(int rows) { return ceil_div(rows, kWavesPerWg * chain_r
 
 // Rows a wave: one where the matrix is large or small, two in between (as few waves as fill the chip, as many bytes in flight).
 // Weights that exceed the cache are read with non-temporal loads.  Forward pass, us, four rows a wave / one / one, non-temporal:
-// N = 4100, L = 6 83 / 74 / 66;  N = 5000, L = 12 265 / 225 / 206;  N = 8192, L = 12 649 / 544 / 490 (6.0 TB/s).
+// N = 4100, L = 6 81 / 74 / 66;  N = 5000, L = 6 120 / 98 / 89;  N = 8192, L = 12 649 / 544 / 490 (6.0 TB/s);  L = 2, N = 12288
+// 110 / 101 / 88, 16384 (two workgroups a compute unit, for the 64 KB of a^{l-1} that each holds) 182 / 201 / 163.
 template <bool NT>
 static void fwd_gemv(const float* W, const float* b, const float* a_in, float* a_out, int rows, int cols, hipStream_t s) {
     const size_t lds = (size_t)cols * sizeof(float), elems = (size_t)rows * cols;

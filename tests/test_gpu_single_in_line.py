@@ -41,3 +41,22 @@ def test_gradients_beside_the_chain_match_the_streams_and_the_oracle(widths):
         for sched, k in ((P.LF_SCHED_AUTO, 1), (P.LF_SCHED_AUTO, L - 1), (P.LF_SCHED_STREAMS, L - 1)):
             assert all(np.array_equal(a, b) for a, b in zip(want, run(sched, k, eta))), (sched, k, eta)
     g.close()
+
+
+@pytest.mark.parametrize("widths", [
+    (2300, 8, 4092, 68, 1020, 4),      # a row a wave: what is left of a row 63, 2, 7 x 64 + 63, 17, 3 x 64 + 63 vectors of four
+    (3000, 2504, 3008, 2560, 2048),    # two rows a wave: 3 x 64 + 46, 64 + 50, 3 x 64 - 16, 2 x 64
+    (5000, 4100, 4612),                # a row a wave: 3 x 64 + 34, 1, after whole turns
+])
+def test_forward_rows_of_any_length_plain_and_non_temporal(monkeypatch, widths):
+    """How a load is cached changes no value."""
+    net = make_net(len(widths), widths, 1, dtype="f32", seed=sum(widths), cache=False)
+    bits = []
+    for stream in ("1", "0"):
+        monkeypatch.setenv("LF_PERSISTENT_STREAM_WEIGHTS", stream)
+        g = run_gpu(net, 1)
+        rep = check_against_oracle(net, g)
+        log(f"forward rows {widths}, streamed {stream}: worst {rep['worst']:.2e}")
+        bits.append([to_np(g.activation(l)).view(np.uint32).copy() for l in range(2, len(widths) + 1)])
+        g.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*bits))
