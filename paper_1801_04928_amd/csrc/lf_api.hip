@@ -236,15 +236,18 @@ struct lf_net {
 
 namespace {
 
-// Whether a single-sample fp32 net's weights are far too many to stay in the device's 256 MB cache from the forward
-// to the backward pass and from one pass to the next (then they are read with non-temporal loads).  Measured: 4.2 GB
-// of weights gain 7 % forward and 2 % backward, 268 MB lose 10 % (part of them still hits), 130 MB lose a third; the
-// line is drawn at twice the cache.  LF_PERSISTENT_STREAM_WEIGHTS=0/1 overrides.
-bool weights_exceed_cache(const lf_net* net) {
+// Whether a single-sample fp32 net's weights are too many to stay in the device's 256 MB cache from the forward to the
+// backward pass and from one pass to the next (then they are read with non-temporal loads).  The persistent kernels: 4.2 GB
+// of weights gain 7 % forward and 2 % backward, 268 MB lose 10 % (part of them still hits), 130 MB lose a third; the line
+// is drawn at twice the cache.  The forward product of the other kernels, us a layer of a pass with gradients / with the
+// descent step, plain -> non-temporal: 274 MB (N = 6000, L = 3) 67 -> 70 / 85 -> 89;  286 (5000, 4) 57 -> 57 / 67 -> 70;  308 (9000, 2)
+// 135 -> 132 / 182 -> 161;  320 (4100, 6) 42.2 -> 43.5 / 51.5 -> 51.9;  351 (9600, 2) 136 -> 128 / 210 -> 177;  411 (6000, 4) 74 -> 75 /
+// 102 -> 97: the line is drawn at 300.  LF_PERSISTENT_STREAM_WEIGHTS=0/1 overrides.
+bool weights_exceed_cache(const lf_net* net, bool persistent) {
     if (const char* e = std::getenv("LF_PERSISTENT_STREAM_WEIGHTS")) return e[0] == '1';
     size_t bytes = 0;
     for (int l = 2; l <= net->L; ++l) bytes += (size_t)net->width(l) * (size_t)net->width(l - 1) * sizeof(float);
-    return bytes > (size_t)512 << 20;
+    return bytes > (size_t)(persistent ? 512 : 300) << 20;
 }
 
 
@@ -452,7 +455,7 @@ lf_status prepare_persistent(lf_net* net, hipStream_t s) {
             probe.n_in = net->width(1); probe.n_out = net->width(net->L);
             probe.G = net->p_groups; probe.RPG = net->p_rpg;
             probe.GB = net->p_bgroups; probe.TPR = net->p_tpr; probe.RS = net->p_rs;
-            probe.stream_weights = weights_exceed_cache(net) ? 1 : 0;
+            probe.stream_weights = weights_exceed_cache(net, true) ? 1 : 0;
             int occ_f = 0, occ_b = 0, occ_bf = 0;
             LF_HIP(net, lf::persistent_resident_per_cu(probe, &occ_f, &occ_b, &occ_bf));
             if (cus <= 0 || net->p_groups > occ_f * cus || net->p_bgroups + 1 > occ_b * cus)
@@ -508,7 +511,7 @@ lf::PersistArgs persist_args(lf_net* net, const void* y, int k) {
     A.GW = net->p_workers;
     A.k = k < net->p_workers ? k : net->p_workers;   // never more partitions than worker workgroups
     A.sgd_eta = net->sgd_eta;
-    A.stream_weights = weights_exceed_cache(net) ? 1 : 0;
+    A.stream_weights = weights_exceed_cache(net, true) ? 1 : 0;
     A.spread = net->p_spread;
     A.fused = net->sched == LF_SCHED_FUSED ? 1 : 0;
     A.no_grads = (net->debug_flags & LF_DEBUG_CHAIN_ONLY) ? 1 : 0;
@@ -1001,7 +1004,8 @@ lf_status lf_forward(lf_net* net, const void* x1, void* hip_stream) {
         net->fwd_done = true;
         return LF_OK;
     }
-    const bool single = single_sample_path(net->N, net->B, net->dt), stream_weights = single && weights_exceed_cache(net);
+    const bool single = single_sample_path(net->N, net->B, net->dt);
+    const bool stream_weights = single && weights_exceed_cache(net, false);
     for (int l = 2; l <= net->L; ++l) {
         if (single) {
             LF_HIP(net, lf::launch_fwd_gemv_f32(static_cast<const float*>(net->w[l - 2]), net->b[l - 2],

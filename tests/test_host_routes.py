@@ -112,6 +112,15 @@ def test_chain_steps_are_split_where_that_pays(program, widths, B, dtype, want):
     assert got == want
 
 
+@pytest.mark.parametrize("widths,rows,streamed", [
+    ([6000] * 3, 1, False), ([5000] * 4, 1, False), ([9000] * 2, 1, True), ([9600] * 2, 1, True),      # 275, 286, 309, 352 MB
+    ([3000, 3004] * 4, 2, False), ([3000, 3004] * 6, 2, True),
+])
+def test_weights_beyond_the_cache_are_streamed_by_the_forward_product(program, widths, rows, streamed):
+    forward, _, _ = _routes(program, widths, 1, "f32", k=1)
+    assert forward and all(f"k_fwd_gemvILi{rows}ELb{int(streamed)}E" in name for name in forward)
+
+
 # us a layer, (direct, wide-net kernels), measured at L = 6 .. 8, k = 4: the choice is to be the faster side
 @pytest.mark.parametrize("N,B,forward,backward", [
     (256, 32768, (51, 26), (263, 537)), (1024, 512, (6.4, 16.8), (11.8, 28.3)), (1024, 4096, (27, 34), (69, 82)),
