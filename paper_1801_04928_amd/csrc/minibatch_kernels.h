@@ -619,25 +619,28 @@ GradKind grad_kind(int n_l, int n_prev, int B, bool bf16) {
     return GRAD_WAVE_32;
 }
 
-// The chain product of a few samples is the reading of W_next, by columns: a tile's workgroup walks a strip of it, 32 nt (bf16)
-// or 64 nt (fp32) bytes wide, down all its rows.  Whole tiles alone make too few workgroups to keep memory busy (N = 4096,
-// B = 8, bf16: 128 of 64-byte strips, 2.1 TB/s), so their contraction is split over workgroups that meet in memory, which
-// costs about 2 us, and the strips become wider.  Backward, us a layer, whole tiles -> split (mt, nt, splits), weights in the
-// cache (140 MB of them) | from memory (1.2 GB):
-//   bf16  B = 8: N = 1024 7.0 -> 6.6, 1536 8.2 -> 7.4, 2048 10.0 -> 8.0 | 11.8 -> 8.1 (1, 2, 4);  2056 10.7 -> 9.5 | 12.2 -> 10.0,
-//         2304 10.3 -> 9.2 | 13.1 -> 10.4 (1, 4, 4);  2560 12.1 -> 10.9 | 15.6 -> 13.2, 3072 14.9 -> 12.8 | 19.8 -> 16.1, 4096 18.6 -> 18.4 |
-//         26.9 -> 22.6, 8192 57 -> 57 | 73 -> 66 (1, 4, 2);  four splits there: 10.4 | 12.2, 14.0 | 14.5, 20.9 | 22.1;
-//         B = 32: N = 1536 8.3 -> 7.6, 2048 10.1 -> 8.6 | 12.5 -> 9.0 (2, 2, 4);  3072 14.2 -> 14.3 | 20.0 -> 18.1, 4096 22.2 -> 19.1 |
-//         28.1 -> 24.5, 6144 35 -> 35 | 51 -> 43 (2, 4, 2);  B = 64: N = 3072 15.0 -> 14.5 | 21.3 -> 18.0, 4096 23.0 -> 22.7 | 29.6 -> 25.8
-//         (2, 4, 2);  4104 26.3 -> 25.6 | 35.2 -> 32.1, 8192 63 -> 62 | 81 -> 74 (4, 4, 2);  B = 40: 8128 72 -> 70 | 86 -> 82, 8192 62 -> 61 | 79 -> 73
-//   fp32  B = 8: N = 1024 6.9 -> 6.4, 1536 9.1 -> 8.1 | 10.9 -> 8.4 (1, 2, 4);  2304 11.4 -> 10.8 | 14.8 -> 12.9, 3072 16.9 -> 16.2 | 22.5 -> 17.6
-//         (1, 4, 4);  6144 45 -> 44 | 62 -> 57 (1, 4, 2);  B = 32: N = 3072 20.2 -> 21.6 | 26.0 -> 23.0, 3584 25.0 -> 24.4 | 31.4 -> 26.4 (2, 4, 4);
-//         4096 30.3 -> 28.2 | 37.2 -> 33.1 (four splits: 31.0 | 34.5), 6144 53 -> 53 | 75 -> 66 (2, 4, 2);  B = 64: N = 4096 40.3 -> 36.9 |
-//         50.4 -> 46.4 (2, 4, 2);  4104 44.1 -> 44.4 | 56.1 -> 51.2 (4, 4, 2)
-// Nothing is gained, or little, below 1024 rows or columns (the meeting: N = 512, 768 20 to 30 % slower), for 17 .. 32 samples
-// between the ranges below (bf16 N = 2176 -1 | +7 %), and by longer minibatches, which have tiles enough.  fp32, 33 samples and
-// more: 4 x 4 blocks take the matrix cores as long as two of 2 x 4, and what their strips gain is lost where the gradients' matrix
-// instructions beside them set the pace (B = 64, N = 4608: 45.5 -> 49.0 | 59.4 -> 58.5; B = 40: 43.4 -> 42.5 | 57.6 -> 50.0, 5632 59 -> 61 | 74 -> 74).
+// The chain product of a few samples is the reading of W_next, by columns: a tile's workgroup walks a strip of it, 32 nt
+// (bf16) or 64 nt (fp32) bytes wide, down all its rows.  Whole tiles alone make too few workgroups to keep memory busy (N =
+// 4096, B = 8, bf16: 128 of 64-byte strips, 2.1 TB/s), so their contraction is split over workgroups that meet in memory,
+// which costs about 2 us, and the strips become wider.  Backward, us a layer, whole tiles -> split (mt, nt, splits),
+// weights in the cache (140 MB of them) | from memory (1.2 GB):
+//   bf16  B = 8: N = 1024 7.0 -> 6.6, 1536 8.2 -> 7.4, 2048 10.0 -> 8.0 | 11.8 -> 8.1 (1, 2, 4);  2056 10.7 -> 9.5 | 12.2
+//         -> 10.0, 2304 10.3 -> 9.2 | 13.1 -> 10.4 (1, 4, 4);  2560 12.1 -> 10.9 | 15.6 -> 13.2, 3072 14.9 -> 12.8 | 19.8
+//         -> 16.1, 4096 18.6 -> 18.4 | 26.9 -> 22.6, 8192 57 -> 57 | 73 -> 66 (1, 4, 2);  four splits there: 10.4 | 12.2,
+//         14.0 | 14.5, 20.9 | 22.1; B = 32: N = 1536 8.3 -> 7.6, 2048 10.1 -> 8.6 | 12.5 -> 9.0 (2, 2, 4);  3072 14.2 ->
+//         14.3 | 20.0 -> 18.1, 4096 22.2 -> 19.1 | 28.1 -> 24.5, 6144 35 -> 35 | 51 -> 43 (2, 4, 2);  B = 64: N = 3072 15.0
+//         -> 14.5 | 21.3 -> 18.0, 4096 23.0 -> 22.7 | 29.6 -> 25.8 (2, 4, 2);  4104 26.3 -> 25.6 | 35.2 -> 32.1, 8192 63 ->
+//         62 | 81 -> 74 (4, 4, 2);  B = 40: 8128 72 -> 70 | 86 -> 82, 8192 62 -> 61 | 79 -> 73
+//   fp32  B = 8: N = 1024 6.9 -> 6.4, 1536 9.1 -> 8.1 | 10.9 -> 8.4 (1, 2, 4);  2304 11.4 -> 10.8 | 14.8 -> 12.9, 3072 16.9
+//         -> 16.2 | 22.5 -> 17.6 (1, 4, 4);  6144 45 -> 44 | 62 -> 57 (1, 4, 2);  B = 32: N = 3072 20.2 -> 21.6 | 26.0 ->
+//         23.0, 3584 25.0 -> 24.4 | 31.4 -> 26.4 (2, 4, 4); 4096 30.3 -> 28.2 | 37.2 -> 33.1 (four splits: 31.0 | 34.5),
+//         6144 53 -> 53 | 75 -> 66 (2, 4, 2);  B = 64: N = 4096 40.3 -> 36.9 | 50.4 -> 46.4 (2, 4, 2);  4104 44.1 -> 44.4 |
+//         56.1 -> 51.2 (4, 4, 2)
+// Nothing is gained, or little, below 1024 rows or columns (the meeting: N = 512, 768 20 to 30 % slower), for 17 .. 32
+// samples between the ranges below (bf16 N = 2176 -1 | +7 %), and by longer minibatches, which have tiles enough.  fp32, 33
+// samples and more: 4 x 4 blocks take the matrix cores as long as two of 2 x 4, and what their strips gain is lost where
+// the gradients' matrix instructions beside them set the pace (B = 64, N = 4608: 45.5 -> 49.0 | 59.4 -> 58.5; B = 40: 43.4
+// -> 42.5 | 57.6 -> 50.0, 5632 59 -> 61 | 74 -> 74).
 TileShape split_shape(int rows, int n_l, bool bf16) {
     if (bf16) {
         if (rows <= 2 && n_l <= 2048) return {rows, 2, 4};
@@ -663,14 +666,16 @@ TileShape chain_shape(int B, int n_l, int n_next, bool bf16) {
     const TileShape t = std::min(n_l, n_next) < 1024 ? TileShape{0, 0, 1} : split_shape(ceil_div(B, 16), n_l, bf16);
     if (t.splits == 1 || ceil_div(B, 16 * t.mt) * ceil_div(n_l, 16 * t.nt) * t.splits > kSplitWorkgroups) return whole;
     if (n_next >= 2 * n_l) return t;
-    // A contraction that is short beside the width is not worth the meeting.  us a pair of layers, whole -> split: bf16, B = 64, 1024
-    // rows x 4096 columns 25.4 -> 30.0, 2048 x 4096 37.1 -> 37.5, 3072 x 4096 49.6 -> 47.8;  B = 8, 1024 x 4096 22.0 -> 22.9, 2048 x 4096
-    // 33.4 -> 31.7, 2048 x 8192 59.5 -> 59.6, 4096 x 8192 87 -> 84;  fp32, B = 8, 1024 x 4096 28.8 -> 29.3, 2048 x 4096 41.4 -> 40.2.
+    // A contraction that is short beside the width is not worth the meeting.  us a pair of layers, whole -> split: bf16, B
+    // = 64, 1024 rows x 4096 columns 25.4 -> 30.0, 2048 x 4096 37.1 -> 37.5, 3072 x 4096 49.6 -> 47.8;  B = 8, 1024 x 4096
+    // 22.0 -> 22.9, 2048 x 4096 33.4 -> 31.7, 2048 x 8192 59.5 -> 59.6, 4096 x 8192 87 -> 84;  fp32, B = 8, 1024 x 4096
+    // 28.8 -> 29.3, 2048 x 4096 41.4 -> 40.2.
     if (n_next < n_l && (n_next < 1536 || (B <= 32 ? 2 * n_next < n_l : 3 * n_next < 2 * n_l))) return whole;
-    // Beside 32 x 32 gradients (of the layer with these weights) three workgroups are resident on a compute unit, four of the fp32
-    // ones with the fewest registers; where the splits make it more, or one more than whole tiles would, that turn costs more
-    // than they bring: bf16, B = 8: N = 1152 (two) 7.2 -> 6.7, 1280 (three, for two) 8.9 -> 9.3 with the descent step, 1536 (three) 8.2 ->
-    // 7.4, 1600 (four) 7.9 -> 9.4, 1920 9.6 -> 10.5;  fp32: 1152 6.9 -> 6.7, 1216 6.8 -> 7.6, 1536 9.1 -> 8.1, 1600 9.0 -> 10.6, 1920 10.2 -> 13.5.
+    // Beside 32 x 32 gradients (of the layer with these weights) three workgroups are resident on a compute unit, four of
+    // the fp32 ones with the fewest registers; where the splits make it more, or one more than whole tiles would, that turn
+    // costs more than they bring: bf16, B = 8: N = 1152 (two) 7.2 -> 6.7, 1280 (three, for two) 8.9 -> 9.3 with the descent
+    // step, 1536 (three) 8.2 -> 7.4, 1600 (four) 7.9 -> 9.4, 1920 9.6 -> 10.5;  fp32: 1152 6.9 -> 6.7, 1216 6.8 -> 7.6,
+    // 1536 9.1 -> 8.1, 1600 9.0 -> 10.6, 1920 10.2 -> 13.5.
     if (grad_kind(n_next, n_l, B, bf16) != GRAD_WAVE_64) {
         const int grads = ceil_div(n_next, 64) * ceil_div(n_l, 64), resident = !bf16 && t.mt == 1 && t.nt == 4 ? 4 : 3;
         const int turns = ceil_div(chain_blocks(t, B, n_l) + grads, 256);
@@ -744,14 +749,19 @@ hipError_t launch_step(const StepArgs& g, hipStream_t s) {
 
 template <typename T, int GT, bool GSPLIT>
 hipError_t step_any(StepArgs g, TileShape t, hipStream_t s) {
-    if (t.splits > 1) {                                                    // (the shapes of chain_shape)
-        if (t.mt == 4) return launch_step<T, 4, 4, GT, GSPLIT, true>(g, s);
-        if (t.mt == 2 && t.nt == 4) return launch_step<T, 2, 4, GT, GSPLIT, true>(g, s);
-        if (t.mt == 1 && t.nt == 4) return launch_step<T, 1, 4, GT, GSPLIT, true>(g, s);
-        if constexpr (sizeof(T) == 2)
-            if (t.mt == 2) return launch_step<T, 2, 2, GT, GSPLIT, true>(g, s);
-        return launch_step<T, 1, 2, GT, GSPLIT, true>(g, s);
+    // The shapes of split_shape.  Gradients whose waves share the samples are fp32 ones of more than 48 samples there,
+    // which ride beside a chain step of other widths than their own (the descent step's).
+    if constexpr (!GSPLIT || sizeof(T) == 4) {
+        if (t.splits > 1 && t.mt == 4) return launch_step<T, 4, 4, GT, GSPLIT, true>(g, s);
+        if (t.splits > 1 && t.mt == 2 && t.nt == 4) return launch_step<T, 2, 4, GT, GSPLIT, true>(g, s);
     }
+    if constexpr (!GSPLIT) {
+        if (t.splits > 1 && t.nt == 4) return launch_step<T, 1, 4, GT, GSPLIT, true>(g, s);
+        if constexpr (sizeof(T) == 2)
+            if (t.splits > 1 && t.mt == 2) return launch_step<T, 2, 2, GT, GSPLIT, true>(g, s);
+        if (t.splits > 1) return launch_step<T, 1, 2, GT, GSPLIT, true>(g, s);
+    }
+    if (t.splits > 1) return hipErrorInvalidValue;
     if (t.mt == 4 && t.nt == 4) return launch_step<T, 4, 4, GT, GSPLIT>(g, s);
     if (t.mt == 2 && t.nt == 4) return launch_step<T, 2, 4, GT, GSPLIT>(g, s);
     if (t.mt == 2 && t.nt == 2) return launch_step<T, 2, 2, GT, GSPLIT>(g, s);

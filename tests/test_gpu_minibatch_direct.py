@@ -14,7 +14,8 @@ def _tensors(g):
 
 
 # of the nets below: those that lf_backward_leapfrog_noalloc is not published to serve
-BEYOND_NOALLOC = [((3, 2056), 130), ((3, 4104), 64), ((3, 2056), 400), ((3, 3080), 200)]
+BEYOND_NOALLOC = [((3, 2056), 130), ((3, 4104), 64), ((3, 2056), 400), ((3, 3080), 200), ((64, 3076, 3076, 260), 64),
+                  ((64, 4100, 4100, 200), 52)]
 
 
 @pytest.mark.parametrize("shape,B,dtype", [
@@ -36,6 +37,8 @@ BEYOND_NOALLOC = [((3, 2056), 130), ((3, 4104), 64), ((3, 2056), 400), ((3, 3080
     ((3, 2048), 128, "bf16"),         # tiles of 32 x 32, all full; gradients 64 x 64 a wave
     ((520, 1000, 1500, 1500, 700, 264), 100, "f32"),   # layers whose gradients are cut in different ways, the last two too
     ((520, 1000, 1504, 1504, 704, 264), 100, "bf16"),
+    ((64, 3076, 3076, 260), 64, "f32"),        # descent step: gradients whose waves share the samples beside a split chain step,
+    ((64, 4100, 4100, 200), 52, "f32"),        # of 32 x 64 and of 64 x 64 tiles
 ])
 def test_direct_kernels_match_oracle_with_the_same_bits_from_every_schedule(monkeypatch, shape, B, dtype):
     import paper_1801_04928_amd as P

@@ -6,15 +6,20 @@ import pytest
 
 from tests import host_hip
 
-# argv: widths, B, dtype, k.  Prints the kernels of a forward pass, of a backward pass, and the status of the
+# argv: widths, B, dtype, k, and "sgd" for the descent step.  Prints the kernels of a forward pass, of a backward pass, and the status of the
 # no-alloc backward pass.
 MAIN = r"""
 #include <sstream>
-int main(int, char** argv) {
+int main(int argc, char** argv) {
     std::vector<int> n;
     std::stringstream widths(argv[1]);
     for (std::string w; std::getline(widths, w, '-');) n.push_back(std::atoi(w.c_str()));
     lf_net* net = make(n, std::atoi(argv[2]), argv[3][0] == 'b' ? LF_BF16 : LF_F32, LF_SCHED_AUTO);
+    if (argc > 5) {                                       // the descent step
+        std::vector<float*> masters(n.size(), (float*)some_input);
+        if (argv[3][0] == 'b') CHECK(lf_set_master_weights(net, masters.data()) == LF_OK);
+        CHECK(lf_set_sgd(net, 0.125f) == LF_OK);
+    }
     auto print = [&](const char* what) {
         for (const std::string& s : launched) std::printf("%s %s\n", what, s.c_str());
         launched.clear();
@@ -35,8 +40,8 @@ def program(tmp_path_factory):
     return host_hip.build(tmp_path_factory.mktemp("routes"), MAIN)
 
 
-def _routes(program, widths, B, dtype, k=2, **env):
-    out = host_hip.run(program, "-".join(map(str, widths)), B, dtype, k, **env).splitlines()
+def _routes(program, widths, B, dtype, k=2, sgd=False, **env):
+    out = host_hip.run(program, "-".join(map(str, widths)), B, dtype, k, *(["sgd"] if sgd else []), **env).splitlines()
     pick = lambda what: [line.split(" ", 1)[1] for line in out if line.startswith(what + " ")]  # noqa: E731
     return pick("forward"), pick("backward"), int(pick("noalloc")[0])
 
@@ -110,6 +115,17 @@ def test_chain_steps_are_split_where_that_pays(program, widths, B, dtype, want):
         mt, nt, split = re.search(rf"k_backward_stepI{type_}Li(\d)ELi(\d)ELi\dELb[01]ELb([01])E", name).groups()
         got.append((int(mt), int(nt), split == "1"))
     assert got == want
+
+
+@pytest.mark.parametrize("widths,B,dtype,want", [
+    ((64, 3076, 3076, 260), 64, "f32", "IfLi2ELi4ELi2ELb1ELb1E"), ((64, 4100, 4100, 200), 52, "f32", "IfLi4ELi4ELi2ELb1ELb1E"),
+    ((264, 1024, 1024, 260), 32, "f32", "IfLi1ELi1ELi2ELb0ELb0E"), ((64, 3072, 3072, 256), 64, "bf16", "IDF16bLi2ELi4ELi2ELb0ELb1E"),
+    ((64, 1024, 1024, 256), 8, "bf16", "IDF16bLi1ELi2ELi2ELb0ELb1E"),
+])
+def test_descent_step_beside_a_chain_step_of_other_widths(program, widths, B, dtype, want):
+    """The last chain step, beside which layer 4's descent step rides."""
+    _, backward, _ = _routes(program, widths, B, dtype, sgd=True, LF_GEMM_BIG="0")
+    assert f"k_backward_step{want}" in [name for name in backward if "k_backward_step" in name][1]
 
 
 @pytest.mark.parametrize("widths,rows,streamed", [
