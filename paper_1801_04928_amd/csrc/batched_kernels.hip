@@ -732,7 +732,7 @@ static int chain_splits(int n_out, int K, int B, int kernel, int target) {
 
 // What the wide-net kernels take for a layer, as direct::forward_us and backward_us.  Forward: turns of 256 compute
 // units, a k-tile at a time, and the split's second pass over its partial sums.  Backward: the chain and the workers'
-// streams side by side have a floor of 18 us a layer, to which come the partial sums, the turns of 96 resident
+// streams side by side have a floor of 20 us a layer, to which come the partial sums, the turns of 96 resident
 // workgroups through the samples, and the gradient stores.
 static double wide_forward_us(int n_out, int n_in, int B) {
     const int s = chain_splits(n_out, n_in, B, GEMM_BIG, kSplitTarget);
@@ -743,9 +743,9 @@ static double wide_forward_us(int n_out, int n_in, int B) {
 static double wide_backward_us(int n_l, int n_prev, int B, bool chain) {
     const int s = chain ? chain_splits(n_prev, n_l, B, GEMM_BIG, kChainSplitTarget) : 1;
     const double tiles = (double)ceil_div(n_l, big::TM) * ceil_div(n_prev, big::TN);
-    return 18.0 + (s > 1 ? 0.172 * 4e-6 * s * B * n_prev : 0.0) +
-           0.758 * direct::turns(tiles, kStreamGroups, 1.0) * ceil_div(B, big::TK) +
-           0.624e-6 * n_l * n_prev * (n_prev % kStreamAlign ? 1.31 : 1.0) + 0.993 * 2e-6 * B * n_prev;
+    return 20.5 + (s > 1 ? 0.155 * 4e-6 * s * B * n_prev : 0.0) +
+           0.715 * direct::turns(tiles, kStreamGroups, 1.0) * ceil_div(B, big::TK) +
+           0.686e-6 * n_l * n_prev * (n_prev % kStreamAlign ? 1.31 : 1.0) + 0.54 * 2e-6 * B * n_prev;
 }
 
 // Which kernels a minibatch net takes, decided once per net from its widths n[0 .. L-1] and its storage type.
@@ -755,14 +755,16 @@ static double wide_backward_us(int n_l, int n_prev, int B, bool chain) {
 // outputs or a long contraction that traffic decides; with few the wide kernels' second pass, their events and their
 // whole tiles of 256 samples do.  Neither N nor B nor a number of tiles alone says which is faster, because turns of the
 // chip are whole numbers: the two estimates above are compared, summed over the layers, forward and backward each for
-// itself.  Their constants are fitted to 230 uniform nets, N = 256 .. 16384, B = 1 .. 32768; the choice is within 4 % of
-// the faster kernels on 96 % of them and within 15 % on all.  us a layer, direct / wide, k = 4:
+// itself.  The forward constants are fitted to 230 uniform nets, N = 256 .. 16384, B = 1 .. 32768, L = 6 .. 8, the backward ones
+// to 557, N = 512 .. 16384, B = 2 .. 2048, L = 6 and 16; the choice is within 4 % of the faster kernels on 97 % of the
+// latter, forward and backward, and within 20 % on all but two (backward, L = 16, N = 5120, B = 128 and 192: 28 and 21 %, with
+// weights that come from memory, which the estimates do not know of).  us a layer, direct / wide, k = 4:
 //   forward   N = 2048: B = 1024 17 / 31, 2048 39 / 37, 4096 80 / 52;  N = 3072: B = 1024 33 / 55, 2048 85 / 71;
 //             N = 4096: B = 256 17 / 38, 512 28 / 38, 1024 59 / 50, 4096 293 / 120;  N = 5120: B = 256 41 / 52, 768 73 / 75, 2048 230 / 139;
 //             N = 6144: B = 128 36 / 42, 256 50 / 58, 640 85 / 85;  N = 8192: B = 64 37 / 38, 256 66 / 56, 512 108 / 79
-//   backward  N = 1536: B = 768 31 / 34, 2048 76 / 54;  N = 2048: B = 1024 35 / 41, 2048 77 / 60;  N = 3072: B = 512 42 / 45, 768 62 / 49;
-//             N = 4096: B = 256 42 / 43, 512 72 / 53, 4096 537 / 249;  N = 5120: B = 128 39 / 44, 256 62 / 54;
-//             N = 6144: B = 64 49 / 50, 128 62 / 57, 512 146 / 100;  N = 8192: B = 64 74 / 78, 128 100 / 84, 512 258 / 146
+//   backward  N = 1536: B = 768 31 / 35, 2048 75 / 57;  N = 2048: B = 1024 34 / 44, 2048 72 / 63;  N = 3072: B = 512 42 / 46, 768 60 / 52;
+//             N = 4096: B = 256 40 / 47, 512 65 / 57, 4096 537 / 249;  N = 5120: B = 128 38 / 45, 256 63 / 53;
+//             N = 6144: B = 64 45 / 51, 128 63 / 56, 512 146 / 103;  N = 7168: B = 96 69 / 73;  N = 8192: B = 64 71 / 80, 128 103 / 85, 512 256 / 146
 // The streamed gradient product stores single columns, 32 neighbouring ones of a row at a time: where rows of nabla_w are
 // no whole 128-byte lines (n_prev not a multiple of 32) every store is two partial lines, and the layer takes the
 // kernel with a workgroup per tile, whose epilogue stores 512 bytes of a row at a time.  Backward, us a layer, streamed /

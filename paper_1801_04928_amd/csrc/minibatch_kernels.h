@@ -699,28 +699,30 @@ double turns(double jobs, int units, double part) {
 // A chain-side product: the busiest XCD's tiles over its 32 compute units, a tile's units at the rate of the L2s, or at
 // the rate at which memory feeds an XCD's L2 (3 cycles for each 16 operand rows that its 32 tiles of a turn read between
 // them: from B = 2048 on every tile brings rows of its own).  With nothing beside it a second turn, once begun, takes
-// as long as the first.
+// as long as the first.  (The meeting of a split one is in backward_us's constants.)
 double chain_us(int B, int n_out, int K, bool chain) {
-    const TileShape t = chain_tile(B, n_out, true, chain);
+    const TileShape t = chain ? chain_shape(B, n_out, K, true) : chain_tile(B, n_out, true, false);
     const int tm = ceil_div(B, 16 * t.mt), tn = ceil_div(n_out, 16 * t.nt);
     const double rows = std::min(tm, 32) * t.mt + std::max(1.0, 32.0 / tm) * t.nt;
     const double cycles = std::max((double)tile_cycles(t, true), 3.0 * rows);
-    double n = turns((double)ceil_div(tn, 8) * tm, 32, 0.76);
+    double n = turns((double)ceil_div(tn, 8) * tm * t.splits, 32, 0.76);
     if (!chain && n > 1.0 && n < 2.0) n = 2.0;
-    return n * cycles * ceil_div(K, 32) / 2400.0;
+    return n * cycles * ceil_div(K, 32) / t.splits / 2400.0;
 }
 // (rows that are no whole 128-byte lines cost forward operands a third more, gradients a quarter)
 double forward_us(int n_out, int n_in, int B) {
     return 2.8 + 0.915 * chain_us(B, n_out, n_in, false) * (n_in % 64 ? 1.34 : 1.0) + 0.06 * 2e-6 * n_out * n_in;
 }
 double grad_us(int n_l, int n_prev, int B) {
-    const int gt = grad_kind(n_l, n_prev, B, true) == GRAD_WAVE_64 ? 4 : 2;
+    const GradKind kind = grad_kind(n_l, n_prev, B, true);
+    const int gt = kind == GRAD_WAVE_64 ? 4 : 2;
     const double waves = (double)ceil_div(n_l, 16 * gt) * ceil_div(n_prev, 16 * gt);
-    const double wave = 2.0 * ceil_div(B, 64) * 35 * 2 * gt / 2400.0;                // units of 32 samples come in pairs
-    return 1.58 * turns(waves, 1024, 0.4) * 4 * wave * (n_prev % 64 ? 1.24 : 1.0) + 0.442e-6 * n_l * n_prev;
+    const double units = kind == GRAD_SPLIT_32 ? 2 * ceil_div(B, 64) : ceil_div(B, 32);    // (in pairs where waves share them)
+    const double wave = units * 35 * 2 * gt / 2400.0;
+    return 1.18 * turns(waves, 1024, 0.4) * 4 * wave * (n_prev % 64 ? 1.24 : 1.0) + 0.521e-6 * n_l * n_prev;
 }
 double backward_us(int n_l, int n_prev, int B, bool chain) {    // gradients of layer l, and the chain step below it
-    return 4.2 + grad_us(n_l, n_prev, B) + (chain ? 0.437 * chain_us(B, n_prev, n_l, true) : 0.0);
+    return 3.09 + grad_us(n_l, n_prev, B) + (chain ? 0.918 * chain_us(B, n_prev, n_l, true) : 0.0);
 }
 
 template <typename T, int MT, int NT>

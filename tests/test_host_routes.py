@@ -151,6 +151,7 @@ def test_weights_beyond_the_cache_are_streamed_by_the_forward_product(program, w
     (7168, 256, (57, 67), (120, 92)), (8192, 32, (31, 36), (70, 75)), (8192, 192, (67, 49), (118, 89)),
     (8192, 512, (108, 78), (258, 148)), (10240, 128, (97, 79), (157, 115)), (12288, 384, (216, 166), (444, 256)),
     (16384, 8, (99, 139), (259, 261)), (16384, 256, (238, 179), (595, 312)),
+    (6144, 128, (35, 44), (63, 56)), (6656, 80, (32, 40), (59, 64)), (7168, 96, (35, 45), (69, 73)),
 ])
 def test_bf16_nets_take_the_faster_kernels(program, N, B, forward, backward):
     """(sides within 6 % of each other are as good; L = 6)"""
