@@ -506,7 +506,7 @@ def test_minibatch_bf16_half_tile_kernel_deeper_split(monkeypatch, target):
 @pytest.mark.parametrize("widths,B,dtype,k,big", [
     ((260, 1028, 516, 2052, 64), 1, "f32", 2, None),     # single sample: every matrix ragged, rows-per-wave 4 and 8
     ((1000, 4100, 300, 4100), 1, "f32", 3, None),        # rows-per-wave 16 on a 4100 x 300 and a 300 x 4100 matrix
-    ((4100, 4100, 8), 1, "f32", 1, None),                # four rows per wave forward; an 8 x 4100 last layer
+    ((4100, 4100, 8), 1, "f32", 1, None),                # an 8 x 4100 last layer
     ((8, 4), 1, "f32", 1, None),                         # one tiny weight layer
     ((264, 520, 136, 392), 70, "f32", 2, None),          # minibatch fp32 MFMA, ragged in every dimension
     ((136, 1032, 264), 300, "f32", 1, None),             # several row tiles

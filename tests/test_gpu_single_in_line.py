@@ -10,10 +10,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("widths", [
-    (4, 8),                                    # no chain step
+    (4, 8),                                    # the persistent kernels' shape: no chain step
+    (4100, 8), (8, 4100),                      # outside it, and no chain step
     (260, 4, 516),                             # one chain step, less than a row block
     (4100, 4100, 4100),                        # beyond the persistent kernels' width
-    (8, 2052, 260, 4096, 12, 1000, 4, 256),    # 4, 8 and 16 rows a wave in one net; strips and rows that end inside a block
+    (8, 2052, 260, 4096, 12, 1000, 4, 256),    # chain steps of 4 and 16 rows a wave; strips and rows that end inside a block
+    (8, 260, 2052, 1000, 12, 256),             # of 8 rows a wave, with the gradients or the descent step beside them
     (84, 996, 6348, 1364, 88),
 ])
 def test_gradients_beside_the_chain_match_the_streams_and_the_oracle(widths):
