@@ -132,8 +132,8 @@ lf_status lf_create(lf_net** out, int L, int N, int B, lf_dtype dt, lf_cost cost
  * widths).  n: HOST array of L entries, n[l-1] = neurons of layer l, read during the call only.  The
  * persistent kernels take a net whose layers 2..L-1 have one width and whose first and last layer are no
  * wider than that (an input and an output of their own sizes around equal hidden layers); any other net runs
- * the stream schedule (LF_SCHED_PERSISTENT is then LF_EUNSUPPORTED, LF_SCHED_AUTO picks streams).  With all
- * n[l-1] equal this is lf_create. */
+ * kernels that take one layer each (LF_SCHED_PERSISTENT is then LF_EUNSUPPORTED; LF_SCHED_AUTO enqueues a single
+ * sample's on the caller's stream alone).  With all n[l-1] equal this is lf_create. */
 size_t lf_workspace_bytes_widths(int L, const int* n, int B, lf_dtype dt);
 lf_status lf_create_widths(lf_net** out, int L, const int* n, int B, lf_dtype dt, lf_cost cost,
                            void* workspace, size_t workspace_bytes);
@@ -208,7 +208,8 @@ lf_status lf_backward_leapfrog(lf_net* net, const void* y, int k, void* hip_stre
  * allocates nothing, on the device or through any library: it enqueues the chain and gradient kernels of
  * layer L, L-1, ..., 2 in that order on hip_stream alone, and the scratch of the chain
  * products (row-block partial sums at B = 1, split-K partials of a wide minibatch net) is a static device array inside
- * the library instead of the caller's workspace.  Same arguments, same checks, same results bit for bit as
+ * the library instead of the caller's workspace.  (The kernels that serve the other minibatch nets keep what little they
+ * need, for few samples and wide layers, in the workspace.)  Same arguments, same checks, same results bit for bit as
  * lf_backward_leapfrog with LF_SCHED_STREAMS (k only names the worker a layer would belong to; the gradients do
  * not depend on it).  lf_forward must have run (with LF_SCHED_STREAMS it allocates nothing either).
  * Limits: the chain scratch that the net's shape is charged for must fit lf_noalloc_scratch_limit() bytes -- 8 MiB:

@@ -64,7 +64,8 @@ GemmPlan gemm_plan(const int* n, int L, int B, bool bf16);
 size_t split_workspace_floats(int n_out, int B, bool bf16);
 // Floats of chain scratch that lf_backward_leapfrog_noalloc charges a minibatch net of L layers of n[0 .. L-1] neurons for.
 // This is the published limit of that call and does not follow the choice of kernels, which may change from one version
-// to the next (the direct kernels use no scratch at all): the split-K partials of 128 x 128 tiles split to at most 512
+// to the next (the direct kernels use none of this scratch: the partial tiles of their split chain steps are in the
+// handle's workspace, in this call too): the split-K partials of 128 x 128 tiles split to at most 512
 // workgroups, or, for wide bf16 nets, those of 256 x 256 tiles split to at most 128 where they are fewer; and never
 // less than what the plan's kernels do use.
 size_t noalloc_scratch_floats(const int* n, int L, int B, bool bf16, const GemmPlan& plan);

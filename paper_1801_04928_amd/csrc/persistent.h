@@ -7,7 +7,7 @@ namespace lf {
 
 constexpr int kMaxGroups = 256;          // chain workgroups of a persistent kernel (one per compute unit)
 constexpr int kMaxRowsPerGroup = 256;    // rows one forward workgroup may own
-constexpr int kMaxPersistentN = 4096;    // wider nets take the stream schedule
+constexpr int kMaxPersistentN = 4096;    // wider nets take the kernels that do one layer each
 constexpr int kMaxPersistentDepth = 1025; // deeper nets too (the per-layer pointer tables live in LDS)
 constexpr int kMaxRowSplit = 4;          // row blocks a backward column strip may be split into
 constexpr int kMaxLaunchGroups = 1024;   // workgroups of one launch (chain + gradient workers)

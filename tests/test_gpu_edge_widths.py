@@ -86,7 +86,7 @@ def test_auto_takes_the_persistent_kernels_for_such_a_net():
 
 
 def test_shapes_the_persistent_kernels_refuse():
-    """A hidden layer of another width, or an input or output wider than the hidden layers: stream schedule."""
+    """A hidden layer of another width, or an input or output wider than the hidden layers: the stream schedule's kernels."""
     import paper_1801_04928_amd as P
     for widths in ([64, 256, 128, 256, 32], [512, 256, 256, 32], [64, 256, 256, 512]):
         g = P.LeapfrogNet(len(widths), widths, 1, "f32")

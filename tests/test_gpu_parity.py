@@ -713,7 +713,7 @@ def test_single_sample_wider_than_the_gemv_kernels_takes_the_matrix_kernels():
 @pytest.mark.parametrize("L,sched", [(1025, "persistent"), (1030, "auto")])
 def test_deepest_nets(L, sched):
     """L = 1025 is the deepest net of the persistent kernels (their per-layer pointer tables live in LDS); deeper
-    nets take the stream schedule.  delta vanishes by about 4x per layer, so below the top 60 layers the
+    nets take the stream schedule's kernels.  delta vanishes by about 4x per layer, so below the top 60 layers the
     gradients are subnormal or zero and are compared absolutely; the activations are compared at every layer."""
     import paper_1801_04928_amd as P
     N = 16

@@ -1,6 +1,6 @@
 """GPU tests of the schedules beside leapfrogging and of the persistent launch's guarantees: the on-chain
 fusion (LF_SCHED_FUSED), the chain alone (LF_DEBUG_CHAIN_ONLY), two handles taking turns on one stream, and
-an LF_SCHED_AUTO handle that loses a persistent pass and moves to the stream schedule."""
+an LF_SCHED_AUTO handle that loses a persistent pass and moves to the stream schedule's kernels."""
 import numpy as np
 import pytest
 
@@ -137,7 +137,7 @@ def test_two_persistent_handles_take_turns_on_one_stream():
 
 def test_auto_handle_moves_to_streams_after_a_lost_persistent_pass(monkeypatch):
     """An LF_SCHED_AUTO handle whose persistent pass gives up a wait (forced from the host: a spin limit of one
-    poll) reports LF_EHIP once and then runs on the stream schedule; its results match the oracle."""
+    poll) reports LF_EHIP once and then runs the stream schedule's kernels in line; its results match the oracle."""
     import torch
     import paper_1801_04928_amd as P
     monkeypatch.setenv("LF_PERSISTENT_SPIN_LIMIT", "1")
