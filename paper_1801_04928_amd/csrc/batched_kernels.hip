@@ -732,7 +732,7 @@ static int chain_splits(int n_out, int K, int B, int kernel, int target) {
 
 // What the wide-net kernels take for a layer, as direct::forward_us and backward_us.  Forward: turns of 256 compute
 // units, a k-tile at a time, and the split's second pass over its partial sums.  Backward: the chain and the workers'
-// streams side by side have a floor of 20 us a layer, to which come the partial sums, the turns of 96 resident
+// streams side by side have a floor of 22 us a layer, to which come the partial sums, the turns of 96 resident
 // workgroups through the samples, and the gradient stores.
 static double wide_forward_us(int n_out, int n_in, int B) {
     const int s = chain_splits(n_out, n_in, B, GEMM_BIG, kSplitTarget);
@@ -743,9 +743,9 @@ static double wide_forward_us(int n_out, int n_in, int B) {
 static double wide_backward_us(int n_l, int n_prev, int B, bool chain) {
     const int s = chain ? chain_splits(n_prev, n_l, B, GEMM_BIG, kChainSplitTarget) : 1;
     const double tiles = (double)ceil_div(n_l, big::TM) * ceil_div(n_prev, big::TN);
-    return 20.5 + (s > 1 ? 0.155 * 4e-6 * s * B * n_prev : 0.0) +
-           0.715 * direct::turns(tiles, kStreamGroups, 1.0) * ceil_div(B, big::TK) +
-           0.686e-6 * n_l * n_prev * (n_prev % kStreamAlign ? 1.31 : 1.0) + 0.54 * 2e-6 * B * n_prev;
+    return 22.0 + (s > 1 ? 0.155 * 4e-6 * s * B * n_prev : 0.0) +
+           0.706 * direct::turns(tiles, kStreamGroups, 1.0) * ceil_div(B, big::TK) +
+           0.643e-6 * n_l * n_prev * (n_prev % kStreamAlign ? 1.31 : 1.0) + 0.54 * 2e-6 * B * n_prev;
 }
 
 // Which kernels a minibatch net takes, decided once per net from its widths n[0 .. L-1] and its storage type.
@@ -756,9 +756,10 @@ static double wide_backward_us(int n_l, int n_prev, int B, bool chain) {
 // whole tiles of 256 samples do.  Neither N nor B nor a number of tiles alone says which is faster, because turns of the
 // chip are whole numbers: the two estimates above are compared, summed over the layers, forward and backward each for
 // itself.  The forward constants are fitted to 230 uniform nets, N = 256 .. 16384, B = 1 .. 32768, L = 6 .. 8, the backward ones
-// to 557, N = 512 .. 16384, B = 2 .. 2048, L = 6 and 16; the choice is within 4 % of the faster kernels on 97 % of the
-// latter, forward and backward, and within 20 % on all but two (backward, L = 16, N = 5120, B = 128 and 192: 28 and 21 %, with
-// weights that come from memory, which the estimates do not know of).  us a layer, direct / wide, k = 4:
+// to 856, N = 512 .. 16384, B = 2 .. 2048, L = 6, 8 and 16.  On the latter the choice is within 4 % of the faster kernels
+// for 97 % backward, 94 % forward; the worst are L = 16, N = 5120, B = 128 backward (28 %: its weights come from memory, which
+// the estimates do not know of) and N = 8120, B = 128 forward (39 %: rows of no whole lines).  us a layer, direct / wide,
+// k = 4:
 //   forward   N = 2048: B = 1024 17 / 31, 2048 39 / 37, 4096 80 / 52;  N = 3072: B = 1024 33 / 55, 2048 85 / 71;
 //             N = 4096: B = 256 17 / 38, 512 28 / 38, 1024 59 / 50, 4096 293 / 120;  N = 5120: B = 256 41 / 52, 768 73 / 75, 2048 230 / 139;
 //             N = 6144: B = 128 36 / 42, 256 50 / 58, 640 85 / 85;  N = 8192: B = 64 37 / 38, 256 66 / 56, 512 108 / 79
