@@ -112,6 +112,7 @@ def test_tile_with_a_row_block_past_the_minibatch(dtype):
     ((4, 256), 32768, 2),                 # wide-net forward, direct backward
     ((4, 4104), 304, 2),                  # wide-net backward with a workgroup per gradient tile (rows of no whole lines)
     ((2048, 4104, 2080, 2048), 1024, 2),  # streamed and per-tile gradients in one net
+    ((3, 8120), 8, 2),                    # a handful of samples, rows of gradients that are no whole 64-byte pieces
 ])
 def test_plans_that_mix_direct_and_wide_kernels_match_oracle(shape, B, k):
     import torch
