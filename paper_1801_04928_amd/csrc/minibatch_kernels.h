@@ -719,10 +719,11 @@ double grad_us(int n_l, int n_prev, int B) {
     const double waves = (double)ceil_div(n_l, 16 * gt) * ceil_div(n_prev, 16 * gt);
     const double units = kind == GRAD_SPLIT_32 ? 2 * ceil_div(B, 64) : ceil_div(B, 32);    // (in pairs where waves share them)
     const double wave = units * 35 * 2 * gt / 2400.0;
-    // stores; half as much again and more where rows are no whole 64-byte pieces and a layer's gradients exceed 200 MB (the cache
-    // does not put the pieces together: B = 40, N = 8120 109, 8128 72 us a layer;  N = 6200, B = 128 73, 6144 63)
-    const double stores = 0.512e-6 * n_l * n_prev, pieces = n_prev % 16 && (double)n_l * n_prev > 50e6 ? 0.5e-6 * n_l * n_prev : 0.0;
-    return 1.27 * turns(waves, 1024, 0.4) * 4 * wave * (n_prev % 64 ? 1.24 : 1.0) + stores + pieces;
+    // the stores, twice as long where rows are no whole 64-byte pieces and a layer's gradients exceed 200 MB (the cache does not
+    // put the pieces together then: B = 40, N = 8120 109, 8128 72 us a layer)
+    const bool pieces = n_prev % 16 && (double)n_l * n_prev > 50e6;
+    const double stores = (pieces ? 1.012e-6 : 0.512e-6) * n_l * n_prev;
+    return 1.27 * turns(waves, 1024, 0.4) * 4 * wave * (n_prev % 64 ? 1.24 : 1.0) + stores;
 }
 double backward_us(int n_l, int n_prev, int B, bool chain) {    // gradients of layer l, and the chain step below it
     return 3.08 + grad_us(n_l, n_prev, B) + (chain ? 0.878 * chain_us(B, n_prev, n_l, true) : 0.0);
