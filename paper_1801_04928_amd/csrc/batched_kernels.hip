@@ -8,6 +8,7 @@
 // grads: P = D (IC), Q = A_prev (IC).  Accumulation is fp32 in the MFMA accumulators, in an order fixed
 // by (N, B) alone, so results do not depend on k or on the launch.
 #include "lf_internal.h"
+#include "cluster_kernels.h"
 #include "minibatch_kernels.h"
 
 namespace lf {

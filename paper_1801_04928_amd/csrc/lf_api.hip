@@ -74,6 +74,8 @@ struct Layout {
     size_t abort_off;
     size_t counts_off;               // per-workgroup launch counts: 3 x kMaxLaunchGroups words
     size_t reads_off, reads_words;   // [L-1][kMaxGroups] tagged words: chain workgroup g has finished reading w^l
+    lf::ClusterPlan cluster;             // small minibatch nets: exchanged words and state of the kernels that walk all layers
+    size_t cluster_words_off, cluster_state_off;
     size_t total;
 };
 
@@ -176,6 +178,13 @@ Layout make_layout(int L, const int* n, int B, lf_dtype dt) {
         y.reads_words = M * lf::kMaxGroups;
         y.reads_off = off; off += align_up(y.reads_words * 8);
     }
+    if (!single_sample_path(N, B, dt)) {
+        y.cluster = lf::cluster_plan(n, L, B, dt == LF_BF16);
+        if (y.cluster.forward || y.cluster.backward) {
+            y.cluster_words_off = off; off += align_up(y.cluster.words * 8);
+            y.cluster_state_off = off; off += align_up(y.cluster.state_words * 4);
+        }
+    }
     y.total = off;
     return y;
 }
@@ -212,6 +221,7 @@ struct lf_net {
     std::vector<hipEvent_t> ev_delta;  // index l-2
     std::vector<hipEvent_t> ev_done;   // per worker stream
     std::string err;
+    bool cluster_ready;                // the state of the small nets' kernels has been prepared
     // persistent path
     unsigned debug_flags;              // LF_DEBUG_*
     bool p_ready, p_tables_dirty;
@@ -563,7 +573,7 @@ lf::GradStep grad_step(const lf_net* net, int l) {              // (bp3), (bp4),
     const int i = l - 2;
     const bool sgd = net->sgd_eta != 0.0f, bf = net->dt == LF_BF16;
     lf::GradStep g{net->d_ptr(l), net->dbf_ptr(l), net->a_ptr(l - 1), net->gw[i], net->gb[i], nullptr,
-                   net->width(l), net->width(l - 1)};
+                   net->width(l), net->width(l - 1), net->lay.cluster.backward ? net->lay.cluster.grad_kind : -1};
     if (sgd) {
         g.w = bf ? net->w32[i] : static_cast<float*>(const_cast<void*>(net->w[i]));
         g.b = const_cast<float*>(net->b[i]);
@@ -680,6 +690,27 @@ lf_status check_backward_call(lf_net* net, const void* y, int k) {
     return LF_OK;
 }
 
+// What the small nets' kernels work on.  Their state is prepared in front of a handle's first pass; a pass that is being
+// captured before that brings its own preparation along.
+lf_status cluster_pass(lf_net* net, const void* y, hipStream_t s, lf::ClusterPass* p) {
+    const Layout& lay = net->lay;
+    *p = lf::ClusterPass{};
+    p->plan = lay.cluster;
+    p->L = net->L; p->B = net->B; p->n = net->n.data(); p->bf16 = net->dt == LF_BF16;
+    p->x = net->x1; p->y = y; p->scale = net->cost_scale;
+    p->w = net->w.data(); p->b = net->b.data();
+    p->a = net->ws + lay.a_off; p->a_stride = lay.a_stride;
+    p->d = net->ws + lay.d_off; p->d_stride = lay.d_stride;
+    p->d_bf = net->ws + lay.dbf_off; p->d_bf_stride = lay.dbf_stride;
+    p->words = reinterpret_cast<unsigned long long*>(net->ws + lay.cluster_words_off);
+    p->state = reinterpret_cast<unsigned*>(net->ws + lay.cluster_state_off);
+    if (!net->cluster_ready) {
+        LF_HIP(net, lf::launch_cluster_state(p->plan, p->state, p->words, s));
+        net->cluster_ready = !is_capturing(s);
+    }
+    return LF_OK;
+}
+
 // The stream realisation of the schedule.  The chain runs on s; `partial` / `raw` are the scratch of its
 // products (the row-block partial sums of the single-sample step, the split-K partials of the minibatch
 // products).  in_line: layer l's gradient kernels follow delta^l on s itself (the sequential pass; also the
@@ -696,7 +727,14 @@ lf_status backward_streams(lf_net* net, const void* y, int k, hipStream_t s, flo
     lf_status st = LF_OK;
     for (int l = L; l >= 2; --l) {
         // the chain: (bp1) at L, (bp2) below
-        if (l == L) {
+        if (net->lay.cluster.backward) {                // all of it in one launch
+            lf::ClusterPass p;
+            if (l == L) {
+                st = cluster_pass(net, y, s, &p);
+                if (st != LF_OK) return st;
+                LF_HIP(net, lf::launch_cluster_chain(p, s));
+            }
+        } else if (l == L) {
             LF_HIP(net, lf::launch_output_error(net->a_ptr(L), y, net->d_ptr(L), net->dbf_ptr(L),
                                                 (size_t)B * net->width(L), bf, net->cost_scale, chain_counters(net),
                                                 lf::chain_counters(), s));
@@ -762,6 +800,26 @@ lf_status backward_steps(lf_net* net, const void* y, hipStream_t s) {
         int n = 0;
         for (int l = std::min(L, 1 + lag); l >= 2; --l) last[n++] = grad_step(net, l);
         LF_HIP(net, lf::launch_backward_step(nullptr, last, n, B, bf, net->sgd_eta, s));
+    }
+    net->bwd_done = !chain_only;
+    if (sgd) net->stepped = true;
+    return LF_OK;
+}
+
+// The small minibatch nets: the chain in one launch, the gradients of all layers in another.
+lf_status backward_cluster(lf_net* net, const void* y, hipStream_t s) {
+    const bool sgd = net->sgd_eta != 0.0f, chain_only = (net->debug_flags & LF_DEBUG_CHAIN_ONLY) != 0;
+    lf::ClusterPass p;
+    const lf_status st = cluster_pass(net, y, s, &p);
+    if (st != LF_OK) return st;
+    LF_HIP(net, lf::launch_cluster_chain(p, s));
+    if (!chain_only) {
+        lf::GradStep grads[lf::kGradLayers];
+        for (int l = net->L; l >= 2;) {
+            int n = 0;
+            for (; n < lf::kGradLayers && l >= 2; --l) grads[n++] = grad_step(net, l);
+            LF_HIP(net, lf::launch_all_gradients(grads, n, net->B, net->dt == LF_BF16, net->sgd_eta, s));
+        }
     }
     net->bwd_done = !chain_only;
     if (sgd) net->stepped = true;
@@ -860,6 +918,7 @@ lf_status lf_create_widths(lf_net** out, int L, const int* n, int B, lf_dtype dt
     net->have_master = false;
     net->gemm = lf::gemm_plan(n, L, B, dt == LF_BF16);
     net->debug_flags = 0; net->p_failed_over = false; net->p_fused_ok = false;
+    net->cluster_ready = false;
     net->p_ready = false; net->p_tables_dirty = true; net->p_groups = net->p_rpg = net->p_bgroups = net->p_tpr = 0; net->p_workers = 0;
     net->p_abort_host = nullptr; net->p_abort_dev_view = nullptr;
     net->err = "no error";
@@ -1006,6 +1065,14 @@ lf_status lf_forward(lf_net* net, const void* x1, void* hip_stream) {
         net->fwd_done = true;
         return LF_OK;
     }
+    if (net->lay.cluster.forward) {
+        lf::ClusterPass p;
+        st0 = cluster_pass(net, nullptr, s, &p);
+        if (st0 != LF_OK) return st0;
+        LF_HIP(net, lf::launch_cluster_forward(p, s));
+        net->fwd_done = true;
+        return LF_OK;
+    }
     const bool single = single_sample_path(net->N, net->B, net->dt);
     const bool stream_weights = single && weights_exceed_cache(net, false);
     for (int l = 2; l <= net->L; ++l) {
@@ -1056,6 +1123,7 @@ lf_status lf_backward_leapfrog(lf_net* net, const void* y, int k, void* hip_stre
         if (st == LF_OK) net->bwd_done = true;
         return st;
     }
+    if (net->sched == LF_SCHED_AUTO && net->lay.cluster.backward) return backward_cluster(net, y, s);
     if (net->sched == LF_SCHED_AUTO && direct_minibatch(net)) return backward_steps(net, y, s);
     // Left to the library, a single sample outside the persistent kernels' shapes has its gradients in line as well: its
     // kernels are bound by memory or by their launches, and a worker's stream costs an event, a wait on another queue and a
@@ -1089,6 +1157,7 @@ lf_status lf_backward_leapfrog_noalloc(lf_net* net, const void* y, int k, void* 
     st = static_scratch_of_current_device(net, &area);
     if (st != LF_OK) return st;
     net->bwd_done = false;
+    if (net->lay.cluster.backward) return backward_cluster(net, y, static_cast<hipStream_t>(hip_stream));
     if (direct_minibatch(net)) return backward_steps(net, y, static_cast<hipStream_t>(hip_stream));
     // every word of the scratch a pass reads it has written before (the chain's partial sums are stored
     // whole, then summed): nothing needs clearing between calls

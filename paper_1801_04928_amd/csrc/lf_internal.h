@@ -104,13 +104,55 @@ struct ChainStep {      // eq. (bp2): delta^l from delta^{l+1} (as launch_chain_
 };                      // when the first chain step of a pass starts, and again when a step has ended
 int chain_counters();
 size_t direct_chain_scratch_floats(int n_l, int n_next, int B, bool bf16);
+// Time of the tiles of a forward or chain product with a B x n_out result, as the choice of its tiles prices it, in us.
+double direct_product_us(int B, int n_out, int K, bool bf16, bool chain);
 struct GradStep {       // eqs. (bp3), (bp4) of one layer (as launch_grad_gemm)
     const float* D; const void* D_bf; const void* A_prev; float* w; float* b; void* w_bf;
     int n_l, n_prev;
+    int kind = -1;          // how nabla_w is cut (a GradKind of minibatch_kernels.h), -1: as the layer's shape has it
 };
 // One launch that takes a chain step (or none: NULL) and the gradients of up to two layers, none of which depends on
-// another.  What a product's sums look like depends on its shape, B and the type alone, not on what it is launched with.
+// another.  What a product's sums look like depends on its shape, B, the type and `kind` alone, not on what it is launched with.
 hipError_t launch_backward_step(const ChainStep* chain, const GradStep* grads, int ngrads, int B, bool bf16,
                                 float sgd_eta, hipStream_t s);
+
+// The gradients of up to kGradLayers layers, all of one kind, in one launch (none depends on another); and the kind that such a
+// launch takes for all layers of a net.
+constexpr int kGradLayers = 64;
+hipError_t launch_all_gradients(const GradStep* grads, int count, int B, bool bf16, float sgd_eta, hipStream_t s);
+int grad_kind_of_all(const int* n, int L, int B, bool bf16);
+
+// ---- minibatch path: small nets (cluster_kernels.hip) -----------------------------------------------
+
+constexpr int kClusterLayers = 64;      // steps of one launch
+struct ClusterPlan {
+    bool forward, backward;             // whether the net's passes take these kernels
+    int grad_kind;                      // GradStep::kind of the net's layers, backward
+    int clusters, per_cluster;          // clusters; workgroups of one
+    int expected;                       // workgroups that make a cluster complete
+    int S, ST;                          // samples of a slice; slices of a cluster
+    int units;                          // units of the widest layer
+    int nap;                            // pause before the first poll, in units of 64 cycles
+    size_t words;                       // exchanged words
+    int state_words;
+};
+// The plan of a net of L layers of n[0 .. L-1] neurons (decided once per net).
+ClusterPlan cluster_plan(const int* n, int L, int B, bool bf16);
+struct ClusterPass {
+    ClusterPlan plan;
+    int L, B; const int* n; bool bf16;
+    const void* x; const void* y; float scale;
+    const void* const* w; const float* const* b;    // index l - 2
+    char* a; size_t a_stride;           // a^l at a + (l - 2) a_stride
+    char* d; size_t d_stride;           // delta^l, fp32
+    char* d_bf; size_t d_bf_stride;     // its bfloat16 copy
+    unsigned long long* words; unsigned* state;
+};
+// Clears the words and the state: in front of a handle's first launch.
+hipError_t launch_cluster_state(const ClusterPlan& plan, unsigned* state, unsigned long long* words, hipStream_t s);
+// a^2 .. a^L
+hipError_t launch_cluster_forward(const ClusterPass& p, hipStream_t s);
+// delta^L .. delta^2
+hipError_t launch_cluster_chain(const ClusterPass& p, hipStream_t s);
 
 }  // namespace lf

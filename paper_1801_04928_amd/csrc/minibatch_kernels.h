@@ -576,6 +576,34 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_backward_step(const StepArgs
     else bias_block(j, x - j.tile_blocks, g.B, g.sgd_eta, lds);
 }
 
+// The gradients of several layers, none of which depends on another.
+struct AllGradArgs {
+    struct Layer { const void* D_op; const float* D; const void* A_prev; float* w; float* b; void* w_bf; int n_l, n_prev; };
+    Layer layer[kGradLayers];
+    int first[kGradLayers + 1];         // workgroups of the layers before
+    int layers, B;
+    float sgd_eta;
+};
+
+template <typename T, int GT, bool GSPLIT>
+__global__ __launch_bounds__(64 * kWaves, 2) void k_all_gradients(const AllGradArgs g) {
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    const int lane = threadIdx.x & 63;
+    const int at = __builtin_popcountll(__ballot(lane < g.layers && (int)blockIdx.x >= g.first[lane])) - 1;
+    const AllGradArgs::Layer& in = g.layer[at];
+    GradJob j;
+    j.D_op = in.D_op; j.D = in.D; j.A_prev = in.A_prev; j.w = in.w; j.b = in.b; j.w_bf = in.w_bf;
+    j.n_l = in.n_l; j.n_prev = in.n_prev;
+    j.d_bytes = (unsigned)(g.B * in.n_l) * (unsigned)sizeof(T);
+    j.a_bytes = (unsigned)(g.B * in.n_prev) * (unsigned)sizeof(T);
+    constexpr int tm = GSPLIT ? 16 * GT : 2 * 16 * GT, tn = GSPLIT ? 16 * GT : kWaves / 2 * 16 * GT;
+    j.tiles_x = ceil_div(in.n_prev, tn);
+    j.tile_blocks = j.tiles_x * ceil_div(in.n_l, tm);
+    const int x = (int)blockIdx.x - g.first[at];
+    if (x < j.tile_blocks) grad_block<T, GT, GSPLIT>(j, x, g.B, g.sgd_eta, lds);
+    else bias_block(j, x - j.tile_blocks, g.B, g.sgd_eta, lds);
+}
+
 bool fits_buffer(unsigned long long bytes) { return bytes < 0xFFFFFFF0ull; }
 
 // Tile of a chain-side product, in 16 x 16 blocks.  A compute unit works through ceil(tiles / 256) of them; a tile
@@ -776,8 +804,57 @@ hipError_t step_any(StepArgs g, TileShape t, hipStream_t s) {
     return launch_step<T, 1, 2, GT, GSPLIT>(g, s);
 }
 
+template <typename T, int GT, bool GSPLIT>
+hipError_t launch_gradients_of(AllGradArgs& g, hipStream_t s) {
+    const int tm = GSPLIT ? 16 * GT : 2 * 16 * GT, tn = GSPLIT ? 16 * GT : kWaves / 2 * 16 * GT;
+    for (int i = 0; i < g.layers; ++i)
+        g.first[i + 1] = g.first[i] + ceil_div(g.layer[i].n_prev, tn) * ceil_div(g.layer[i].n_l, tm) + ceil_div(g.layer[i].n_l, 32);
+    k_all_gradients<T, GT, GSPLIT><<<g.first[g.layers], 64 * kWaves, lds_bytes(0, GT), s>>>(g);
+    return hipGetLastError();
+}
+
 }  // namespace
 }  // namespace direct
+
+double direct_product_us(int B, int n_out, int K, bool bf16, bool chain) {
+    using namespace direct;
+    const TileShape t = chain_tile(B, n_out, bf16, chain);
+    const long tiles = (long)ceil_div(B, 16 * t.mt) * ceil_div(n_out, 16 * t.nt);
+    return (double)((tiles + 255) / 256 * tile_cycles(t, bf16)) * ceil_div(K, bf16 ? 32 : 16) / 2400.0;
+}
+
+hipError_t launch_all_gradients(const GradStep* grads, int count, int B, bool bf16, float sgd_eta, hipStream_t s) {
+    using namespace direct;
+    if (count < 1 || count > kGradLayers) return hipErrorInvalidValue;
+    AllGradArgs g{};
+    g.layers = count;
+    g.B = B; g.sgd_eta = sgd_eta;
+    for (int i = 0; i < count; ++i) {
+        const GradStep& in = grads[i];
+        const unsigned long long es = bf16 ? 2 : 4;
+        if (in.kind != grads[0].kind || !fits_buffer(es * B * in.n_l) || !fits_buffer(es * B * in.n_prev)) return hipErrorInvalidValue;
+        g.layer[i] = {bf16 ? in.D_bf : static_cast<const void*>(in.D), in.D, in.A_prev, in.w, in.b, in.w_bf, in.n_l, in.n_prev};
+    }
+    switch (grads[0].kind) {
+        case GRAD_WAVE_64: return bf16 ? launch_gradients_of<__bf16, 4, false>(g, s) : launch_gradients_of<float, 4, false>(g, s);
+        case GRAD_WAVE_32: return bf16 ? launch_gradients_of<__bf16, 2, false>(g, s) : launch_gradients_of<float, 2, false>(g, s);
+        case GRAD_SPLIT_32: return bf16 ? launch_gradients_of<__bf16, 2, true>(g, s) : launch_gradients_of<float, 2, true>(g, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+// As grad_kind, for the tiles of all layers.  us a backward pass, 64 / 32 / 32 split, the chain included: fp32, L = 16, N = 512, B =
+// 128 74 / 71 / 78;  N = 256, B = 128 43 / 40 / 40;  N = 128, B = 512 59 / 39 / 34;  N = 64, B = 512 53 / 33 / 25;  L = 6, N = 256, B =
+// 512 59 / 39 / 35;  bf16, L = 16, N = 512, B = 128 58 / 57 / 71.
+int grad_kind_of_all(const int* n, int L, int B, bool bf16) {
+    using namespace direct;
+    long tiles64 = 0, tiles32 = 0;
+    for (int i = 1; i < L; ++i) {
+        tiles64 += (long)ceil_div(n[i], 64) * ceil_div(n[i - 1], 64);
+        tiles32 += (long)ceil_div(n[i], 32) * ceil_div(n[i - 1], 32);
+    }
+    return tiles64 >= 1024 ? GRAD_WAVE_64 : tiles32 < 1024 && B > (bf16 ? 96 : 48) ? GRAD_SPLIT_32 : GRAD_WAVE_32;
+}
 
 int chain_counters() { return direct::kSplitWorkgroups; }
 size_t direct_chain_scratch_floats(int n_l, int n_next, int B, bool bf16) { return direct::chain_scratch(B, n_l, n_next, bf16); }
@@ -798,7 +875,7 @@ hipError_t launch_forward_direct(const void* W, const float* bias, const void* A
 hipError_t launch_backward_step(const ChainStep* c, const GradStep* grads, int ngrads, int B, bool bf16, float sgd_eta,
                                 hipStream_t s) {
     using namespace direct;
-    auto kind_of = [&](const GradStep& g) { return grad_kind(g.n_l, g.n_prev, B, bf16); };
+    auto kind_of = [&](const GradStep& g) { return g.kind >= 0 ? (GradKind)g.kind : grad_kind(g.n_l, g.n_prev, B, bf16); };
     if (ngrads == 2 && kind_of(grads[0]) != kind_of(grads[1])) {
         const hipError_t e = launch_backward_step(c, grads, 1, B, bf16, sgd_eta, s);
         return e != hipSuccess ? e : launch_backward_step(nullptr, grads + 1, 1, B, bf16, sgd_eta, s);
