@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_cluster(const Args g) {
             if (x0.m < 0) break;
             step(i + 1, raw0);
         }
-        // the last to leave prepares the next launch
+        // the last to leave prepares the pass's next launch
         if (draws) {
             const unsigned gone = __hip_atomic_fetch_add(state + EXITED, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (gone == (unsigned)g.per_cluster - 1) {
@@ -428,8 +428,10 @@ __global__ __launch_bounds__(kThreads, 2) void k_cluster(const Args g) {
     }
 }
 
+// Whatever the workspace held: every counter at its start, and no word with a tag that is waited for (those of a pass begin at 2).
 __global__ void k_cluster_state(unsigned* state, u64* words, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) words[i] = 0;
+    v4u* const pairs = reinterpret_cast<v4u*>(words);           // (the words of a unit are 256)
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n / 2; i += (size_t)gridDim.x * blockDim.x) pairs[i] = v4u{0, 0, 0, 0};
     if (blockIdx.x == 0 && threadIdx.x < 8 * STATE_WORDS) state[threadIdx.x] = threadIdx.x % STATE_WORDS == BASE ? 1u : 0u;
 }
 

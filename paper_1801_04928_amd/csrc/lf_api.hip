@@ -221,7 +221,6 @@ struct lf_net {
     std::vector<hipEvent_t> ev_delta;  // index l-2
     std::vector<hipEvent_t> ev_done;   // per worker stream
     std::string err;
-    bool cluster_ready;                // the state of the small nets' kernels has been prepared
     // persistent path
     unsigned debug_flags;              // LF_DEBUG_*
     bool p_ready, p_tables_dirty;
@@ -690,25 +689,20 @@ lf_status check_backward_call(lf_net* net, const void* y, int k) {
     return LF_OK;
 }
 
-// What the small nets' kernels work on.  Their state is prepared in front of a handle's first pass; a pass that is being
-// captured before that brings its own preparation along.
-lf_status cluster_pass(lf_net* net, const void* y, hipStream_t s, lf::ClusterPass* p) {
+// What the small nets' kernels work on.
+lf::ClusterPass cluster_pass(const lf_net* net, const void* y) {
     const Layout& lay = net->lay;
-    *p = lf::ClusterPass{};
-    p->plan = lay.cluster;
-    p->L = net->L; p->B = net->B; p->n = net->n.data(); p->bf16 = net->dt == LF_BF16;
-    p->x = net->x1; p->y = y; p->scale = net->cost_scale;
-    p->w = net->w.data(); p->b = net->b.data();
-    p->a = net->ws + lay.a_off; p->a_stride = lay.a_stride;
-    p->d = net->ws + lay.d_off; p->d_stride = lay.d_stride;
-    p->d_bf = net->ws + lay.dbf_off; p->d_bf_stride = lay.dbf_stride;
-    p->words = reinterpret_cast<unsigned long long*>(net->ws + lay.cluster_words_off);
-    p->state = reinterpret_cast<unsigned*>(net->ws + lay.cluster_state_off);
-    if (!net->cluster_ready) {
-        LF_HIP(net, lf::launch_cluster_state(p->plan, p->state, p->words, s));
-        net->cluster_ready = !is_capturing(s);
-    }
-    return LF_OK;
+    lf::ClusterPass p{};
+    p.plan = lay.cluster;
+    p.L = net->L; p.B = net->B; p.n = net->n.data(); p.bf16 = net->dt == LF_BF16;
+    p.x = net->x1; p.y = y; p.scale = net->cost_scale;
+    p.w = net->w.data(); p.b = net->b.data();
+    p.a = net->ws + lay.a_off; p.a_stride = lay.a_stride;
+    p.d = net->ws + lay.d_off; p.d_stride = lay.d_stride;
+    p.d_bf = net->ws + lay.dbf_off; p.d_bf_stride = lay.dbf_stride;
+    p.words = reinterpret_cast<unsigned long long*>(net->ws + lay.cluster_words_off);
+    p.state = reinterpret_cast<unsigned*>(net->ws + lay.cluster_state_off);
+    return p;
 }
 
 // The stream realisation of the schedule.  The chain runs on s; `partial` / `raw` are the scratch of its
@@ -728,12 +722,7 @@ lf_status backward_streams(lf_net* net, const void* y, int k, hipStream_t s, flo
     for (int l = L; l >= 2; --l) {
         // the chain: (bp1) at L, (bp2) below
         if (net->lay.cluster.backward) {                // all of it in one launch
-            lf::ClusterPass p;
-            if (l == L) {
-                st = cluster_pass(net, y, s, &p);
-                if (st != LF_OK) return st;
-                LF_HIP(net, lf::launch_cluster_chain(p, s));
-            }
+            if (l == L) LF_HIP(net, lf::launch_cluster_chain(cluster_pass(net, y), s));
         } else if (l == L) {
             LF_HIP(net, lf::launch_output_error(net->a_ptr(L), y, net->d_ptr(L), net->dbf_ptr(L),
                                                 (size_t)B * net->width(L), bf, net->cost_scale, chain_counters(net),
@@ -809,10 +798,7 @@ lf_status backward_steps(lf_net* net, const void* y, hipStream_t s) {
 // The small minibatch nets: the chain in one launch, the gradients of all layers in another.
 lf_status backward_cluster(lf_net* net, const void* y, hipStream_t s) {
     const bool sgd = net->sgd_eta != 0.0f, chain_only = (net->debug_flags & LF_DEBUG_CHAIN_ONLY) != 0;
-    lf::ClusterPass p;
-    const lf_status st = cluster_pass(net, y, s, &p);
-    if (st != LF_OK) return st;
-    LF_HIP(net, lf::launch_cluster_chain(p, s));
+    LF_HIP(net, lf::launch_cluster_chain(cluster_pass(net, y), s));
     if (!chain_only) {
         lf::GradStep grads[lf::kGradLayers];
         for (int l = net->L; l >= 2;) {
@@ -918,7 +904,6 @@ lf_status lf_create_widths(lf_net** out, int L, const int* n, int B, lf_dtype dt
     net->have_master = false;
     net->gemm = lf::gemm_plan(n, L, B, dt == LF_BF16);
     net->debug_flags = 0; net->p_failed_over = false; net->p_fused_ok = false;
-    net->cluster_ready = false;
     net->p_ready = false; net->p_tables_dirty = true; net->p_groups = net->p_rpg = net->p_bgroups = net->p_tpr = 0; net->p_workers = 0;
     net->p_abort_host = nullptr; net->p_abort_dev_view = nullptr;
     net->err = "no error";
@@ -1065,13 +1050,17 @@ lf_status lf_forward(lf_net* net, const void* x1, void* hip_stream) {
         net->fwd_done = true;
         return LF_OK;
     }
-    if (net->lay.cluster.forward) {
-        lf::ClusterPass p;
-        st0 = cluster_pass(net, nullptr, s, &p);
-        if (st0 != LF_OK) return st0;
-        LF_HIP(net, lf::launch_cluster_forward(p, s));
-        net->fwd_done = true;
-        return LF_OK;
+    if (net->lay.cluster.forward || net->lay.cluster.backward) {
+        // Since the last pass the caller may have used the workspace otherwise, another handle among them: what the kernels
+        // of either direction exchange is prepared here, and from here on the workspace holds a^l and is left alone.  (A
+        // launch a pass: L = 8, N = 256, B = 32 fp32 @@ us, with the state kept from pass to pass @@.)
+        const lf::ClusterPass p = cluster_pass(net, nullptr);
+        LF_HIP(net, lf::launch_cluster_state(p.plan, p.state, p.words, s));
+        if (net->lay.cluster.forward) {
+            LF_HIP(net, lf::launch_cluster_forward(p, s));
+            net->fwd_done = true;
+            return LF_OK;
+        }
     }
     const bool single = single_sample_path(net->N, net->B, net->dt);
     const bool stream_weights = single && weights_exceed_cache(net, false);

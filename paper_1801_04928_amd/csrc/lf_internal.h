@@ -148,7 +148,7 @@ struct ClusterPass {
     char* d_bf; size_t d_bf_stride;     // its bfloat16 copy
     unsigned long long* words; unsigned* state;
 };
-// Clears the words and the state: in front of a handle's first launch.
+// Clears the words and the state: in front of a pass's first launch.
 hipError_t launch_cluster_state(const ClusterPlan& plan, unsigned* state, unsigned long long* words, hipStream_t s);
 // a^2 .. a^L
 hipError_t launch_cluster_forward(const ClusterPass& p, hipStream_t s);

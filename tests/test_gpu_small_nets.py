@@ -163,3 +163,51 @@ def test_infinities_and_nans_stay_in_their_sample(monkeypatch):
         assert np.array_equal(to_np(g.delta(l))[others], d[l - 2][others])
     assert np.isnan(to_np(g.activation(6))[4]).all() and np.isnan(to_np(g.delta(2))[4]).all()
     g.close()
+
+
+def _on_workspace(g, workspace):
+    """The same net on a handle that works in this workspace."""
+    import paper_1801_04928_amd as P
+    P.lf_destroy(g.handle)
+    g.workspace = workspace
+    st, g.handle = P.lf_create(g.L, g.N, g.B, g.dt, P.LF_COST_QUADRATIC, workspace.data_ptr(), workspace.numel())
+    assert st == P.LF_OK, P.lf_last_error(None)
+    pointers = lambda tensors: [t.data_ptr() for t in tensors]  # noqa: E731
+    assert P.lf_set_params(g.handle, pointers(g.w), pointers(g.b)) == P.LF_OK
+    assert P.lf_set_grad_buffers(g.handle, pointers(g.nabla_w), pointers(g.nabla_b)) == P.LF_OK
+
+
+def test_the_workspace_may_hold_anything_when_a_pass_begins(monkeypatch):
+    """Other values between the passes (words that carry tags of a pass too), eager and in a graph captured as the handle's
+    first pass; and handles of other shapes and types that take turns on one workspace."""
+    import paper_1801_04928_amd as P
+    import torch
+    monkeypatch.setenv("LF_CLUSTER", "1")
+    shapes = [(6, 200, 21, "f32"), (5, 256, 40, "bf16"), (9, 64, 130, "f32")]
+    nets = [make_net(L, N, B, dtype=dtype, seed=L) for L, N, B, dtype in shapes]
+    handles = [run_gpu(net, 1) for net in nets]
+    want = [_bits(g) for g in handles]
+    workspace = torch.empty(max(g.workspace.numel() for g in handles), dtype=torch.uint8, device="cuda")
+    for g in handles:
+        _on_workspace(g, workspace)
+    for _ in range(3):
+        for g, w in zip(handles, want):
+            assert all(np.array_equal(a, b) for a, b in zip(w, _again(g, 2)))
+    g, w = handles[0], want[0]
+    words = workspace[: workspace.numel() // 8 * 8].view(torch.int64)
+    for value in (-1, 0, 1, *(tag << 32 for tag in range(1, 16)), 0x0000000200000002):
+        words.fill_(value)
+        assert all(np.array_equal(a, b) for a, b in zip(w, _again(g))), hex(value)
+    _on_workspace(g, workspace)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        g.forward()
+        g.backward(1)
+    for value in (-1, 0x0000000200000002, 3 << 32, 0):
+        words.fill_(value)
+        for t in g.nabla_w + g.nabla_b:
+            t.fill_(float("nan"))
+        graph.replay()
+        assert all(np.array_equal(a, b) for a, b in zip(w, _bits(g))), hex(value)
+    for g in handles:
+        g.close()

@@ -6,8 +6,8 @@ import pytest
 
 from tests import host_hip
 
-# argv: widths, B, dtype, k, and "sgd" for the descent step.  Prints the kernels of a forward pass, of a backward pass, and the status of the
-# no-alloc backward pass.
+# argv: widths, B, dtype, k, and "sgd" for the descent step.  Prints the kernels of a forward pass, of a backward pass, the status of the
+# no-alloc backward pass, and the kernels of one more forward pass.
 MAIN = r"""
 #include <sstream>
 int main(int argc, char** argv) {
@@ -29,6 +29,9 @@ int main(int argc, char** argv) {
     CHECK(lf_backward_leapfrog(net, some_input, std::atoi(argv[4]), &caller_1) == LF_OK);
     print("backward");
     std::printf("noalloc %d\n", (int)lf_backward_leapfrog_noalloc(net, some_input, 1, &caller_1));
+    launched.clear();
+    CHECK(lf_forward(net, some_input, &caller_1) == LF_OK);
+    print("again");
     lf_destroy(net);
     return failures != 0;
 }
@@ -40,9 +43,13 @@ def program(tmp_path_factory):
     return host_hip.build(tmp_path_factory.mktemp("routes"), MAIN)
 
 
-def _routes(program, widths, B, dtype, k=2, sgd=False, **env):
+def _picked(program, widths, B, dtype, k=2, sgd=False, **env):
     out = host_hip.run(program, "-".join(map(str, widths)), B, dtype, k, *(["sgd"] if sgd else []), **env).splitlines()
-    pick = lambda what: [line.split(" ", 1)[1] for line in out if line.startswith(what + " ")]  # noqa: E731
+    return lambda what: [line.split(" ", 1)[1] for line in out if line.startswith(what + " ")]
+
+
+def _routes(program, widths, B, dtype, k=2, sgd=False, **env):
+    pick = _picked(program, widths, B, dtype, k, sgd, **env)
     return pick("forward"), pick("backward"), int(pick("noalloc")[0])
 
 
@@ -185,3 +192,13 @@ def test_streamed_gradients_have_rows_of_whole_lines(program, widths, streamed):
     _, bwd, _ = _routes(program, widths, 1024, "bf16")
     grads = [name for name in bwd if "k_grad_stream" in name or "k_gemm_bigILb1ELb1E" in name]
     assert len(grads) == 3 and sum("k_grad_stream" in name for name in grads) == streamed
+
+
+@pytest.mark.parametrize("N,dtype", [(256, "f32"), (512, "bf16")])
+def test_each_pass_of_a_small_net_prepares_what_its_workgroups_exchange(program, N, dtype):
+    """The workspace may have held anything since the last pass: its counters and words are cleared in front of every
+    forward pass, the first as the next."""
+    pick = _picked(program, [N] * 6, 32, dtype, LF_CLUSTER="1")
+    for names in (pick("forward"), pick("again")):
+        assert len(names) == 2 and "k_cluster_state" in names[0] and "k_clusterI" in names[1]
+    assert "k_clusterI" in pick("backward")[0] and "k_all_gradients" in pick("backward")[1]
