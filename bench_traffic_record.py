@@ -34,7 +34,7 @@ def counter(path, name):
 
 
 PERSISTENT_SOURCES = ("persistent_kernels.hip", "persistent.h", "persistent_partition.h", "device_helpers.h")
-MINIBATCH_SOURCES = ("batched_kernels.hip", "minibatch_kernels.h", "b1_kernels.hip", "lf_internal.h", "device_helpers.h")
+MINIBATCH_SOURCES = ("batched_kernels.hip", "minibatch_kernels.h", "cluster_kernels.h", "b1_kernels.hip", "lf_internal.h", "device_helpers.h")
 
 
 def source_hash(names):

@@ -49,6 +49,11 @@
  *     the wait (after seconds, not a hang).  An LF_SCHED_AUTO handle then moves to the stream
  *     schedule for good and works again from the next lf_forward; a handle set to
  *     LF_SCHED_PERSISTENT or LF_SCHED_FUSED stays failed (destroy it).
+ *   - The workgroups of the kernels that serve small minibatch nets (LF_SCHED_AUTO) wait for each other as well, but
+ *     only for ones that are running: nothing has to be resident at once, and such passes may overlap with anything.  Their
+ *     waits are bounded all the same.  If one gives up, the pass applies no descent step, the next call on the handle returns
+ *     LF_EHIP, and the handle, whatever its schedule, takes the kernels of one launch per layer from the next lf_forward.
+ *     (A handle whose first pass was recorded into a graph has no means of saying so: its activations are NaN then.)
  *   - Shape limits: N a multiple of 4 (fp32) or 8 (bf16) so rows stay 16-byte
  *     aligned; 2 <= L <= 4096; 1 <= B; 1 <= k <= L-1.
  *   - Layers of different widths (lf_create_widths): section 2 fixes N neurons per

@@ -24,7 +24,8 @@
 //              arrived they are resident, and walk on in steps of their count (fixed shares: one task each per layer).  Where
 //              they have not after a while (other work holds the compute units) those that run draw every further number
 //              from the counter, in order: the lowest unfinished task is then always some running workgroup's current one.
-//              The placement (cluster = workgroup index mod 8) decides the speed only.
+//              The placement (cluster = workgroup index mod 8) decides the speed only.  Waits are bounded all the same: one that gives up
+//              makes its values NaN and raises a word that the gradients' launch (no descent step then) and the host look at.
 //   sums       in an order fixed by the shape alone.
 #pragma once
 #include "lf_internal.h"
@@ -43,7 +44,7 @@ constexpr int kThreads = 64 * 2 * kWaves;       // the computing waves, then tho
 constexpr int kTasks = 8;                       // numbers of tasks kept in LDS
 constexpr int kRedRow = 80;                     // floats between the rows of the waves' partial tiles in LDS
 constexpr unsigned kOutside = 0xFFFFFFF0u;      // an offset past the end of every buffer: loads zeros
-constexpr unsigned kPatience = 1u << 23;        // polls a wave spends in vain in all (seconds); then its values are NaN: no wait is endless
+constexpr unsigned kPatience = 1u << 23;        // polls a wave spends in vain in all (seconds): no wait is endless
 constexpr int kDevice = 16;                     // device scope of a buffer access
 constexpr unsigned kArrivalPolls = 256;         // how long the workgroups of a cluster wait for each other's arrival
 
@@ -53,8 +54,8 @@ template <> struct Shape<__bf16> { static constexpr int Q = 32, M = 2; };
 
 __host__ __device__ constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-// Words of the state block of a cluster.
-enum { ARRIVED = 0, DECISION = 1, EXITED = 2, BASE = 3, STATE_WORDS = 32 };
+// Words of the state block of a cluster.  (LOST: of the first block, for the whole pass)
+enum { ARRIVED = 0, DECISION = 1, EXITED = 2, BASE = 3, LOST = 4, STATE_WORDS = 32 };
 enum { UNDECIDED = 0, TOGETHER = 1, IN_ORDER = 2 };
 
 struct Args {
@@ -72,6 +73,9 @@ struct Args {
     const char* act; long act_step;             // backward: a^l
     u64* words;                                 // [2][slices][units][256]
     unsigned* state;                            // [clusters][STATE_WORDS]
+    unsigned patience;
+    int layer;                                  // of the first step
+    int* lost_host;                             // pinned word, or null
     const void* w[kClusterLayers];
     const float* b[kClusterLayers];
     int n[kClusterLayers + 1];                  // n[m]: contraction of step m; n[m + 1]: its outputs
@@ -80,6 +84,9 @@ struct Args {
 __device__ __forceinline__ unsigned load_state(const unsigned* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+// Where a wait gave up (site 4 of the handle's abort word).
+__device__ __forceinline__ int abort_code(int l, int workgroup) { return (4 << 24) | (l << 10) | (workgroup & 0x3ff); }
 
 // Where output neuron c of a tile lies in a wave's partial tile: row `row` (of 4 M), lane 16 * group + sample.
 template <typename T, bool BWD> __device__ __forceinline__ void place_of(int c, int* row, int* group) {
@@ -294,7 +301,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_cluster(const Args g) {
 
     // ---- the waves that compute: units 4 s + wave of the contraction
     const __amdgpu_buffer_rsrc_t words = make_buffer(g.words, 2u * (unsigned)slices_all * (unsigned)g.units * 2048u);
-    unsigned patience = kPatience;
+    unsigned patience = g.patience;
     __syncthreads();                                                        // the next numbers
     __syncthreads();                                                        // the first weights
     Task x = task(0);
@@ -380,11 +387,15 @@ __global__ __launch_bounds__(kThreads, 2) void k_cluster(const Args g) {
                     xs[s] = v4u{y[s][0][0], y[s][0][2], y[s][1][0], y[s][1][2]};
                 }
                 if (__all(bad == 0u)) break;
-                if (patience == 0) {
+                if (patience == 0) {                                        // the pass is lost: NaN, and both words say so
                     xs[0][0] = 0x7fc07fc0u;
+                    __hip_atomic_store(g.state + LOST, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (g.lost_host)
+                        __hip_atomic_store(g.lost_host, abort_code(BWD ? g.layer - x.m : g.layer + x.m, (int)blockIdx.x), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_SYSTEM);
                     break;
                 }
-                --patience;
+                if ((--patience & 255u) == 0 && load_state(g.state + LOST)) patience = 0;
                 __builtin_amdgcn_s_sleep(1);
                 asm volatile("" ::: "memory");
             }
@@ -466,6 +477,8 @@ hipError_t run(const ClusterPass& p, hipStream_t s) {
         for (int i = 0; i <= g.layers; ++i) g.n[i] = BWD ? p.n[p.L - 1 - from - i] : p.n[from + i];
         for (int i = 0; i < g.layers; ++i) widest = std::max(widest, g.n[i]);
         g.words = p.words; g.state = p.state;
+        g.patience = p.plan.patience; g.lost_host = p.lost_host;
+        g.layer = BWD ? p.L - 1 - from : from + 2;
         for (int i = 0; i < g.layers; ++i) {
             const int l = BWD ? p.L - 1 - from - i : from + i + 2;      // the layer whose a^l or delta^l step i forms
             g.w[i] = p.w[(BWD ? l + 1 : l) - 2];
@@ -499,6 +512,8 @@ hipError_t run(const ClusterPass& p, hipStream_t s) {
 }  // namespace
 }  // namespace cluster
 
+const unsigned* cluster_lost(const unsigned* state) { return state + cluster::LOST; }
+
 ClusterPlan cluster_plan(const int* n, int L, int B, bool bf16) {
     using namespace cluster;
     ClusterPlan p{};
@@ -520,6 +535,9 @@ ClusterPlan cluster_plan(const int* n, int L, int B, bool bf16) {
     // LF_CLUSTER_INCOMPLETE=1: no cluster is ever complete, so that its workgroups draw every task (the tests' way there)
     const char* incomplete = std::getenv("LF_CLUSTER_INCOMPLETE");
     p.expected = p.per_cluster + (incomplete && incomplete[0] == '1' ? 1 : 0);
+    // LF_CLUSTER_SPIN_LIMIT: polls before a wait gives up; 0 makes the first one that finds nothing fail (the tests' way there)
+    const char* limit = std::getenv("LF_CLUSTER_SPIN_LIMIT");
+    p.patience = limit ? (unsigned)std::strtoul(limit, nullptr, 10) : kPatience;
     // A poll that finds nothing costs a round trip, and its lines are taken from the writers: the first one is sent when the
     // words are about due.  us a layer forward, pauses of 0, 2, 4, 8, 14, 18 x 64 cycles: fp32 N = 64 1.19, 1.20, 1.20;
     // N = 256, B = 32 1.94, 1.77, 1.71, 1.83 (8);  N = 512, B = 16 3.20 (8), 3.00 (14), 3.09 (18);  bf16 N = 256, B = 32 1.69,

@@ -47,6 +47,14 @@ struct SharedWorkers {
 std::list<SharedWorkers> g_shared_workers;
 std::mutex g_shared_workers_mutex;
 
+// Pinned words for the handles whose kernels wait for each other: a page of the process's, kept until it ends, because making
+// pinned memory is most of a small net's first pass (L = 8, N = 256, B = 32 fp32 69 us; 107 with a block of its own).  The
+// word given back first is the next to be given out.
+constexpr int kAbortWords = 1024;
+int* g_abort_words;
+int g_abort_free[kAbortWords], g_abort_first, g_abort_count;        // a ring of the words that are free
+std::mutex g_abort_words_mutex;
+
 constexpr size_t kAlign = 256;
 constexpr int kMaxL = 4096;
 constexpr int kMaxWorkerStreams = 32;   // workers beyond this share streams (worker j -> stream j mod 32)
@@ -230,6 +238,7 @@ struct lf_net {
     unsigned p_spin_limit;             // polls before a bounded wait gives up
     int* p_abort_host;                 // pinned, mapped; the kernels raise it when a wait gives up
     int* p_abort_dev_view;             // the same word as the device addresses it
+    bool p_abort_asked;                // a pass of the small nets' kernels has had its chance to make it
     std::vector<const void*> p_tables;
 
     void* a_ptr(int l) const {         // l = 1..L
@@ -384,9 +393,66 @@ bool use_persistent(const lf_net* net) {
 }
 
 
-// A persistent kernel whose wait gave up has raised the pinned abort word.
+// The pinned word that a kernel whose wait gave up raises.
+lf_status ensure_abort_word(lf_net* net) {
+    if (net->p_abort_host) return LF_OK;
+    int* word = nullptr;
+    {
+        std::lock_guard<std::mutex> lock(g_abort_words_mutex);
+        if (!g_abort_words) {
+            void* h = nullptr;
+            LF_HIP(net, hipHostMalloc(&h, kAbortWords * sizeof(int), hipHostMallocMapped | hipHostMallocPortable));
+            g_abort_words = static_cast<int*>(h);
+            for (int i = 0; i < kAbortWords; ++i) g_abort_free[i] = i;
+            g_abort_count = kAbortWords;
+        }
+        if (g_abort_count > 0) {
+            word = g_abort_words + g_abort_free[g_abort_first];
+            g_abort_first = (g_abort_first + 1) % kAbortWords;
+            --g_abort_count;
+        }
+    }
+    if (!word) {                        // more handles than that: one of its own
+        void* h = nullptr;
+        LF_HIP(net, hipHostMalloc(&h, sizeof(int), hipHostMallocMapped));
+        word = static_cast<int*>(h);
+    }
+    *word = 0;
+    net->p_abort_host = word;
+    void* d = nullptr;
+    LF_HIP(net, hipHostGetDevicePointer(&d, word, 0));
+    net->p_abort_dev_view = static_cast<int*>(d);
+    return LF_OK;
+}
+
+void release_abort_word(lf_net* net) {
+    if (!net->p_abort_host) return;
+    std::lock_guard<std::mutex> lock(g_abort_words_mutex);
+    if (g_abort_words && net->p_abort_host >= g_abort_words && net->p_abort_host < g_abort_words + kAbortWords)
+        g_abort_free[(g_abort_first + g_abort_count++) % kAbortWords] = (int)(net->p_abort_host - g_abort_words);
+    else
+        (void)hipHostFree(net->p_abort_host);
+}
+
+// The small nets' kernels do without it where a handle's first pass is a captured one: allocating is no part of a capture, nor of
+// a later pass.  (A lost pass then shows in its NaNs alone.)
+lf_status small_net_abort_word(lf_net* net, hipStream_t s) {
+    if (net->p_abort_asked) return LF_OK;
+    net->p_abort_asked = true;
+    return is_capturing(s) ? LF_OK : ensure_abort_word(net);
+}
+
 lf_status check_abort(lf_net* net) {
     const int code = net->p_abort_host ? *reinterpret_cast<volatile int*>(net->p_abort_host) : 0;
+    if (code >> 24 == 4) {
+        // The small nets' kernels, which need nothing to be resident and so should not come here; the handle does without them.
+        *reinterpret_cast<volatile int*>(net->p_abort_host) = 0;
+        net->lay.cluster.forward = net->lay.cluster.backward = false;
+        net->fwd_done = net->bwd_done = false;
+        return fail(net, LF_EHIP, "a small net's kernel gave up waiting for its peers (layer " + std::to_string((code >> 10) & 0x3fff) +
+                                      ", workgroup " + std::to_string(code & 0x3ff) +
+                                      "); results are invalid; the handle takes a launch a layer from now on (run lf_forward again)");
+    }
     if (code) {
         static const char* const site[] = {"partial-sum wait", "forward gather", "chain gather", "gradient wait"};
         std::string msg = std::string("a persistent kernel gave up waiting for its peers (") + site[(code >> 24) & 3] +
@@ -474,15 +540,8 @@ lf_status prepare_persistent(lf_net* net, hipStream_t s) {
             if (net->p_workers > occ_b * cus - net->p_bgroups) net->p_workers = occ_b * cus - net->p_bgroups;
             net->p_fused_ok = net->p_bgroups <= occ_bf * cus;
         }
-        if (!net->p_abort_host) {
-            void* h = nullptr;
-            LF_HIP(net, hipHostMalloc(&h, sizeof(int), hipHostMallocMapped));
-            net->p_abort_host = static_cast<int*>(h);
-            *net->p_abort_host = 0;
-            void* d = nullptr;
-            LF_HIP(net, hipHostGetDevicePointer(&d, h, 0));
-            net->p_abort_dev_view = static_cast<int*>(d);
-        }
+        const lf_status st = ensure_abort_word(net);
+        if (st != LF_OK) return st;
         // tagged words start as tag 0 (never a valid tag); the abort word as 0
         LF_HIP(net, lf::launch_fill_u64(net->ws + net->lay.dll_off, net->lay.ll_words, 0ull, s));
         LF_HIP(net, lf::launch_fill_u64(net->ws + net->lay.all_off, net->lay.ll_words, 0ull, s));
@@ -572,13 +631,26 @@ lf::GradStep grad_step(const lf_net* net, int l) {              // (bp3), (bp4),
     const int i = l - 2;
     const bool sgd = net->sgd_eta != 0.0f, bf = net->dt == LF_BF16;
     lf::GradStep g{net->d_ptr(l), net->dbf_ptr(l), net->a_ptr(l - 1), net->gw[i], net->gb[i], nullptr,
-                   net->width(l), net->width(l - 1), net->lay.cluster.backward ? net->lay.cluster.grad_kind : -1};
+                   net->width(l), net->width(l - 1)};
     if (sgd) {
         g.w = bf ? net->w32[i] : static_cast<float*>(const_cast<void*>(net->w[i]));
         g.b = const_cast<float*>(net->b[i]);
         g.w_bf = bf ? const_cast<void*>(net->w[i]) : nullptr;
     }
     return g;
+}
+
+unsigned* cluster_state(const lf_net* net) { return reinterpret_cast<unsigned*>(net->ws + net->lay.cluster_state_off); }
+
+// (bp3),(bp4) of layers l, l-1, .. of a small net (as many as a launch takes, or `most`), in one launch.  Returns their number.
+lf_status enqueue_small_grads(lf_net* net, int l, int most, hipStream_t s, int* taken) {
+    lf::GradStep grads[lf::kGradLayers];
+    int n = 0;
+    for (; n < std::min(lf::kGradLayers, most) && l - n >= 2; ++n) grads[n] = grad_step(net, l - n);
+    LF_HIP(net, lf::launch_all_gradients(grads, n, net->lay.cluster.grad_kind, net->B, net->dt == LF_BF16, net->sgd_eta,
+                                         lf::cluster_lost(cluster_state(net)), s));
+    *taken = n;
+    return LF_OK;
 }
 
 // (bp3),(bp4) of layer l on stream s; with the descent step fused in, applied to w^l and b^l in place.
@@ -591,6 +663,9 @@ lf_status enqueue_grads(lf_net* net, int l, hipStream_t s, bool whole_chip = tru
     if (single_sample_path(net->N, net->B, net->dt)) {
         LF_HIP(net, lf::launch_grad_outer_f32(net->d_ptr(l), static_cast<const float*>(net->a_ptr(l - 1)),
                                               out_w, out_b, net->width(l), net->width(l - 1), net->sgd_eta, s));
+    } else if (net->lay.cluster.backward) {
+        int one;
+        return enqueue_small_grads(net, l, 1, s, &one);
     } else if (net->gemm.grad == lf::GEMM_DIRECT) {
         const lf::GradStep g = grad_step(net, l);
         LF_HIP(net, lf::launch_backward_step(nullptr, &g, 1, net->B, bf, net->sgd_eta, s));
@@ -701,7 +776,8 @@ lf::ClusterPass cluster_pass(const lf_net* net, const void* y) {
     p.d = net->ws + lay.d_off; p.d_stride = lay.d_stride;
     p.d_bf = net->ws + lay.dbf_off; p.d_bf_stride = lay.dbf_stride;
     p.words = reinterpret_cast<unsigned long long*>(net->ws + lay.cluster_words_off);
-    p.state = reinterpret_cast<unsigned*>(net->ws + lay.cluster_state_off);
+    p.state = cluster_state(net);
+    p.lost_host = net->p_abort_dev_view;
     return p;
 }
 
@@ -799,13 +875,9 @@ lf_status backward_steps(lf_net* net, const void* y, hipStream_t s) {
 lf_status backward_cluster(lf_net* net, const void* y, hipStream_t s) {
     const bool sgd = net->sgd_eta != 0.0f, chain_only = (net->debug_flags & LF_DEBUG_CHAIN_ONLY) != 0;
     LF_HIP(net, lf::launch_cluster_chain(cluster_pass(net, y), s));
-    if (!chain_only) {
-        lf::GradStep grads[lf::kGradLayers];
-        for (int l = net->L; l >= 2;) {
-            int n = 0;
-            for (; n < lf::kGradLayers && l >= 2; --l) grads[n++] = grad_step(net, l);
-            LF_HIP(net, lf::launch_all_gradients(grads, n, net->B, net->dt == LF_BF16, net->sgd_eta, s));
-        }
+    for (int l = net->L, n = 0; !chain_only && l >= 2; l -= n) {
+        const lf_status st = enqueue_small_grads(net, l, net->L, s, &n);
+        if (st != LF_OK) return st;
     }
     net->bwd_done = !chain_only;
     if (sgd) net->stepped = true;
@@ -905,7 +977,7 @@ lf_status lf_create_widths(lf_net** out, int L, const int* n, int B, lf_dtype dt
     net->gemm = lf::gemm_plan(n, L, B, dt == LF_BF16);
     net->debug_flags = 0; net->p_failed_over = false; net->p_fused_ok = false;
     net->p_ready = false; net->p_tables_dirty = true; net->p_groups = net->p_rpg = net->p_bgroups = net->p_tpr = 0; net->p_workers = 0;
-    net->p_abort_host = nullptr; net->p_abort_dev_view = nullptr;
+    net->p_abort_host = nullptr; net->p_abort_dev_view = nullptr; net->p_abort_asked = false;
     net->err = "no error";
     try {
         net->n.assign(n, n + L);
@@ -1054,6 +1126,8 @@ lf_status lf_forward(lf_net* net, const void* x1, void* hip_stream) {
         // Since the last pass the caller may have used the workspace otherwise, another handle among them: what the kernels
         // of either direction exchange is prepared here, and from here on the workspace holds a^l and is left alone.  (A
         // launch a pass: L = 8, N = 256, B = 32 fp32 39.4 us, 37.7 with the state kept from pass to pass.)
+        st0 = net->sched == LF_SCHED_STREAMS ? LF_OK : small_net_abort_word(net, s);    // (with that schedule this call allocates nothing)
+        if (st0 != LF_OK) return st0;
         const lf::ClusterPass p = cluster_pass(net, nullptr);
         LF_HIP(net, lf::launch_cluster_state(p.plan, p.state, p.words, s));
         if (net->lay.cluster.forward) {
@@ -1112,6 +1186,8 @@ lf_status lf_backward_leapfrog(lf_net* net, const void* y, int k, void* hip_stre
         if (st == LF_OK) net->bwd_done = true;
         return st;
     }
+    st = net->lay.cluster.backward ? small_net_abort_word(net, s) : LF_OK;
+    if (st != LF_OK) return st;
     if (net->sched == LF_SCHED_AUTO && net->lay.cluster.backward) return backward_cluster(net, y, s);
     if (net->sched == LF_SCHED_AUTO && direct_minibatch(net)) return backward_steps(net, y, s);
     // Left to the library, a single sample outside the persistent kernels' shapes has its gradients in line as well: its
@@ -1146,6 +1222,8 @@ lf_status lf_backward_leapfrog_noalloc(lf_net* net, const void* y, int k, void* 
     st = static_scratch_of_current_device(net, &area);
     if (st != LF_OK) return st;
     net->bwd_done = false;
+    st = check_abort(net);
+    if (st != LF_OK) return st;
     if (net->lay.cluster.backward) return backward_cluster(net, y, static_cast<hipStream_t>(hip_stream));
     if (direct_minibatch(net)) return backward_steps(net, y, static_cast<hipStream_t>(hip_stream));
     // every word of the scratch a pass reads it has written before (the chain's partial sums are stored
@@ -1193,7 +1271,7 @@ void lf_destroy(lf_net* net) {
     release_worker_streams(net);
     for (hipEvent_t e : net->ev_delta) (void)hipEventDestroy(e);
     for (hipEvent_t e : net->ev_done) (void)hipEventDestroy(e);
-    if (net->p_abort_host) (void)hipHostFree(net->p_abort_host);
+    release_abort_word(net);
     delete net;
 }
 

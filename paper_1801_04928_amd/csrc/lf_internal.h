@@ -109,30 +109,31 @@ double direct_product_us(int B, int n_out, int K, bool bf16, bool chain);
 struct GradStep {       // eqs. (bp3), (bp4) of one layer (as launch_grad_gemm)
     const float* D; const void* D_bf; const void* A_prev; float* w; float* b; void* w_bf;
     int n_l, n_prev;
-    int kind = -1;          // how nabla_w is cut (a GradKind of minibatch_kernels.h), -1: as the layer's shape has it
 };
 // One launch that takes a chain step (or none: NULL) and the gradients of up to two layers, none of which depends on
-// another.  What a product's sums look like depends on its shape, B, the type and `kind` alone, not on what it is launched with.
+// another.  What a product's sums look like depends on its shape, B and the type alone, not on what it is launched with.
 hipError_t launch_backward_step(const ChainStep* chain, const GradStep* grads, int ngrads, int B, bool bf16,
                                 float sgd_eta, hipStream_t s);
 
-// The gradients of up to kGradLayers layers, all of one kind, in one launch (none depends on another); and the kind that such a
-// launch takes for all layers of a net.
+// The gradients of up to kGradLayers layers in one launch (none depends on another), all cut in one way (kind: a GradKind of
+// minibatch_kernels.h); and the kind that all layers of a net take.  *lost != 0: no descent step.
 constexpr int kGradLayers = 64;
-hipError_t launch_all_gradients(const GradStep* grads, int count, int B, bool bf16, float sgd_eta, hipStream_t s);
+hipError_t launch_all_gradients(const GradStep* grads, int count, int kind, int B, bool bf16, float sgd_eta, const unsigned* lost,
+                                hipStream_t s);
 int grad_kind_of_all(const int* n, int L, int B, bool bf16);
 
-// ---- minibatch path: small nets (cluster_kernels.hip) -----------------------------------------------
+// ---- minibatch path: small nets (cluster_kernels.h) -------------------------------------------------
 
 constexpr int kClusterLayers = 64;      // steps of one launch
 struct ClusterPlan {
     bool forward, backward;             // whether the net's passes take these kernels
-    int grad_kind;                      // GradStep::kind of the net's layers, backward
+    int grad_kind;                      // how the gradients of all layers are cut, backward
     int clusters, per_cluster;          // clusters; workgroups of one
     int expected;                       // workgroups that make a cluster complete
     int S, ST;                          // samples of a slice; slices of a cluster
     int units;                          // units of the widest layer
     int nap;                            // pause before the first poll, in units of 64 cycles
+    unsigned patience;                  // polls before a wait gives up
     size_t words;                       // exchanged words
     int state_words;
 };
@@ -147,7 +148,10 @@ struct ClusterPass {
     char* d; size_t d_stride;           // delta^l, fp32
     char* d_bf; size_t d_bf_stride;     // its bfloat16 copy
     unsigned long long* words; unsigned* state;
+    int* lost_host;                     // pinned word that a wait which gives up raises, as the device addresses it, or null
 };
+// The device's word, in the state: raised by a wait of this pass that gave up.
+const unsigned* cluster_lost(const unsigned* state);
 // Clears the words and the state: in front of a pass's first launch.
 hipError_t launch_cluster_state(const ClusterPlan& plan, unsigned* state, unsigned long long* words, hipStream_t s);
 // a^2 .. a^L

@@ -583,11 +583,13 @@ struct AllGradArgs {
     int first[kGradLayers + 1];         // workgroups of the layers before
     int layers, B;
     float sgd_eta;
+    const unsigned* lost;               // != 0: what the step would apply is not to be trusted
 };
 
 template <typename T, int GT, bool GSPLIT>
 __global__ __launch_bounds__(64 * kWaves, 2) void k_all_gradients(const AllGradArgs g) {
     extern __shared__ __attribute__((aligned(16))) float lds[];
+    if (g.sgd_eta != 0.0f && *g.lost) return;
     const int lane = threadIdx.x & 63;
     const int at = __builtin_popcountll(__ballot(lane < g.layers && (int)blockIdx.x >= g.first[lane])) - 1;
     const AllGradArgs::Layer& in = g.layer[at];
@@ -823,19 +825,20 @@ double direct_product_us(int B, int n_out, int K, bool bf16, bool chain) {
     return (double)((tiles + 255) / 256 * tile_cycles(t, bf16)) * ceil_div(K, bf16 ? 32 : 16) / 2400.0;
 }
 
-hipError_t launch_all_gradients(const GradStep* grads, int count, int B, bool bf16, float sgd_eta, hipStream_t s) {
+hipError_t launch_all_gradients(const GradStep* grads, int count, int kind, int B, bool bf16, float sgd_eta, const unsigned* lost,
+                                hipStream_t s) {
     using namespace direct;
     if (count < 1 || count > kGradLayers) return hipErrorInvalidValue;
     AllGradArgs g{};
     g.layers = count;
-    g.B = B; g.sgd_eta = sgd_eta;
+    g.B = B; g.sgd_eta = sgd_eta; g.lost = lost;
     for (int i = 0; i < count; ++i) {
         const GradStep& in = grads[i];
         const unsigned long long es = bf16 ? 2 : 4;
-        if (in.kind != grads[0].kind || !fits_buffer(es * B * in.n_l) || !fits_buffer(es * B * in.n_prev)) return hipErrorInvalidValue;
+        if (!fits_buffer(es * B * in.n_l) || !fits_buffer(es * B * in.n_prev)) return hipErrorInvalidValue;
         g.layer[i] = {bf16 ? in.D_bf : static_cast<const void*>(in.D), in.D, in.A_prev, in.w, in.b, in.w_bf, in.n_l, in.n_prev};
     }
-    switch (grads[0].kind) {
+    switch (kind) {
         case GRAD_WAVE_64: return bf16 ? launch_gradients_of<__bf16, 4, false>(g, s) : launch_gradients_of<float, 4, false>(g, s);
         case GRAD_WAVE_32: return bf16 ? launch_gradients_of<__bf16, 2, false>(g, s) : launch_gradients_of<float, 2, false>(g, s);
         case GRAD_SPLIT_32: return bf16 ? launch_gradients_of<__bf16, 2, true>(g, s) : launch_gradients_of<float, 2, true>(g, s);
@@ -875,7 +878,7 @@ hipError_t launch_forward_direct(const void* W, const float* bias, const void* A
 hipError_t launch_backward_step(const ChainStep* c, const GradStep* grads, int ngrads, int B, bool bf16, float sgd_eta,
                                 hipStream_t s) {
     using namespace direct;
-    auto kind_of = [&](const GradStep& g) { return g.kind >= 0 ? (GradKind)g.kind : grad_kind(g.n_l, g.n_prev, B, bf16); };
+    auto kind_of = [&](const GradStep& g) { return grad_kind(g.n_l, g.n_prev, B, bf16); };
     if (ngrads == 2 && kind_of(grads[0]) != kind_of(grads[1])) {
         const hipError_t e = launch_backward_step(c, grads, 1, B, bf16, sgd_eta, s);
         return e != hipSuccess ? e : launch_backward_step(nullptr, grads + 1, 1, B, bf16, sgd_eta, s);

@@ -211,3 +211,37 @@ def test_the_workspace_may_hold_anything_when_a_pass_begins(monkeypatch):
         assert all(np.array_equal(a, b) for a, b in zip(w, _bits(g))), hex(value)
     for g in handles:
         g.close()
+
+
+@pytest.mark.parametrize("sched", ["AUTO", "STREAMS"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_wait_that_gives_up_is_reported_and_takes_no_step(monkeypatch, dtype, sched):
+    """No poll is repeated, and workgroups that draw their tasks are ahead of others' results: some wait gives up at once (the kernels
+    end normally).  The descent step leaves the weights alone, the next call says so, and the handle's later passes are right."""
+    import paper_1801_04928_amd as P
+    import torch
+    monkeypatch.setenv("LF_CLUSTER", "1")
+    monkeypatch.setenv("LF_CLUSTER_SPIN_LIMIT", "0")
+    monkeypatch.setenv("LF_CLUSTER_INCOMPLETE", "1")
+    net = make_net(8, 256, 128, dtype=dtype, seed=6)
+    g = P.LeapfrogNet(8, 256, 128, dtype)
+    g.load(net)
+    g.set_schedule(getattr(P, "LF_SCHED_" + sched))
+    g.set_sgd(0.125)
+    before = [t.clone() for t in g.w + g.b + (g.master_w or [])]
+    g.forward()
+    g.backward(2)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(before, g.w + g.b + (g.master_w or [])))
+    with pytest.raises(P.LfError) as e:
+        g.forward()
+    assert e.value.status == P.LF_EHIP and "gave up" in str(e.value)
+    with pytest.raises(P.LfError) as e:
+        g.backward(1)
+    assert e.value.status == P.LF_ESTATE
+    g.set_sgd(0.0)
+    g.forward()
+    g.backward(2)
+    torch.cuda.synchronize()
+    check_against_oracle(net, g)
+    g.close()
