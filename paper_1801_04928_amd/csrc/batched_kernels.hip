@@ -780,7 +780,7 @@ static double wide_backward_us(int n_l, int n_prev, int B, bool chain) {
 // pass against 8.0 ms with every kernel spread over the whole chip.  (The split does not depend on k: the
 // gradients must be the same bits for every k.  A sequential pass, k = 1, would be faster with four splits.)
 // Overrides for tests and A/B runs, read when the plan is made:
-// LF_GEMM_BIG=0/1 forces the direct / wide-net kernels; LF_GEMM_CHAIN_TILE = "big" or "half" picks the wide-net
+// LF_GEMM_BIG=0/1 forces the direct / wide-net kernels (also where a small net would take those of cluster_kernels.h); LF_GEMM_CHAIN_TILE = "big" or "half" picks the wide-net
 // kernel of the forward and chain products, LF_GEMM_GRAD_TILE = "stream", "big" or "half" that of the gradient
 // product of every layer; LF_GEMM_SPLIT_TARGET = workgroups the split of a chain-side product aims at (both products),
 // LF_GEMM_CHAIN_SPLIT_TARGET = the same for the backward chain product alone; LF_GEMM_STREAM_GROUPS = resident

@@ -548,6 +548,7 @@ ClusterPlan cluster_plan(const int* n, int L, int B, bool bf16) {
         p.forward = p.backward = e[0] == '1';   // (a tuning knob, read whenever a layout is made: the same for all of a handle)
         return p;
     }
+    if (std::getenv("LF_GEMM_BIG")) return p;   // (which of the other kernels to take has been asked for)
     // What these kernels and those of one launch a layer take, in us.  Fitted to uniform nets of L = 3 .. 12, N = 64 .. 512
     // (fp32) and 64 .. 1024 (bf16), B = 2 .. 1024.  us a pass forward / backward, a launch a layer -> one launch, L = 12:
     //   fp32  N = 64, B = 32 30 -> 15 / 44 -> 19;  N = 256, B = 2 32 -> 20 / 46 -> 26, B = 128 34 -> 21 / 50 -> 33, B = 512 43 -> 36 /

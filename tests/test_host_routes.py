@@ -204,6 +204,15 @@ def test_each_pass_of_a_small_net_prepares_what_its_workgroups_exchange(program,
     assert "k_clusterI" in pick("backward")[0] and "k_all_gradients" in pick("backward")[1]
 
 
+@pytest.mark.parametrize("choice,kernels", [("0", ("k_forward_tile", "k_backward_step")), ("1", ("k_gemm_big", "k_gemm_big"))])
+def test_the_forced_choice_of_kernels_holds_for_small_nets(program, choice, kernels):
+    forward, backward, noalloc = _routes(program, [256] * 8, 32, "bf16", LF_GEMM_BIG=choice)
+    for names, kernel in zip((forward, backward), kernels):
+        assert any(kernel in name for name in names)
+        assert not any("k_cluster" in name or "k_all_gradients" in name for name in names)
+    assert noalloc == OK
+
+
 # argv: how the lost pass is found out.  A wait of a small net's kernels that gave up has raised the pinned word.
 LOST = r"""
 int main(int, char** argv) {
