@@ -627,30 +627,22 @@ lf::ChainStep chain_step(const lf_net* net, int l) {            // delta^l from 
 unsigned* chain_counters(const lf_net* net) {
     return direct_minibatch(net) && net->lay.direct_splits ? reinterpret_cast<unsigned*>(net->raw()) : nullptr;
 }
+unsigned* cluster_state(const lf_net* net) { return reinterpret_cast<unsigned*>(net->ws + net->lay.cluster_state_off); }
 lf::GradStep grad_step(const lf_net* net, int l) {              // (bp3), (bp4), or the descent step, of layer l
     const int i = l - 2;
     const bool sgd = net->sgd_eta != 0.0f, bf = net->dt == LF_BF16;
     lf::GradStep g{net->d_ptr(l), net->dbf_ptr(l), net->a_ptr(l - 1), net->gw[i], net->gb[i], nullptr,
                    net->width(l), net->width(l - 1)};
+    if (net->lay.cluster.backward) {
+        g.kind = net->lay.cluster.grad_kind;
+        g.lost = lf::cluster_lost(cluster_state(net));
+    }
     if (sgd) {
         g.w = bf ? net->w32[i] : static_cast<float*>(const_cast<void*>(net->w[i]));
         g.b = const_cast<float*>(net->b[i]);
         g.w_bf = bf ? const_cast<void*>(net->w[i]) : nullptr;
     }
     return g;
-}
-
-unsigned* cluster_state(const lf_net* net) { return reinterpret_cast<unsigned*>(net->ws + net->lay.cluster_state_off); }
-
-// (bp3),(bp4) of layers l, l-1, .. of a small net (as many as a launch takes, or `most`), in one launch.  Returns their number.
-lf_status enqueue_small_grads(lf_net* net, int l, int most, hipStream_t s, int* taken) {
-    lf::GradStep grads[lf::kGradLayers];
-    int n = 0;
-    for (; n < std::min(lf::kGradLayers, most) && l - n >= 2; ++n) grads[n] = grad_step(net, l - n);
-    LF_HIP(net, lf::launch_all_gradients(grads, n, net->lay.cluster.grad_kind, net->B, net->dt == LF_BF16, net->sgd_eta,
-                                         lf::cluster_lost(cluster_state(net)), s));
-    *taken = n;
-    return LF_OK;
 }
 
 // (bp3),(bp4) of layer l on stream s; with the descent step fused in, applied to w^l and b^l in place.
@@ -663,10 +655,7 @@ lf_status enqueue_grads(lf_net* net, int l, hipStream_t s, bool whole_chip = tru
     if (single_sample_path(net->N, net->B, net->dt)) {
         LF_HIP(net, lf::launch_grad_outer_f32(net->d_ptr(l), static_cast<const float*>(net->a_ptr(l - 1)),
                                               out_w, out_b, net->width(l), net->width(l - 1), net->sgd_eta, s));
-    } else if (net->lay.cluster.backward) {
-        int one;
-        return enqueue_small_grads(net, l, 1, s, &one);
-    } else if (net->gemm.grad == lf::GEMM_DIRECT) {
+    } else if (net->gemm.grad == lf::GEMM_DIRECT || net->lay.cluster.backward) {
         const lf::GradStep g = grad_step(net, l);
         LF_HIP(net, lf::launch_backward_step(nullptr, &g, 1, net->B, bf, net->sgd_eta, s));
     } else {
@@ -875,9 +864,13 @@ lf_status backward_steps(lf_net* net, const void* y, hipStream_t s) {
 lf_status backward_cluster(lf_net* net, const void* y, hipStream_t s) {
     const bool sgd = net->sgd_eta != 0.0f, chain_only = (net->debug_flags & LF_DEBUG_CHAIN_ONLY) != 0;
     LF_HIP(net, lf::launch_cluster_chain(cluster_pass(net, y), s));
-    for (int l = net->L, n = 0; !chain_only && l >= 2; l -= n) {
-        const lf_status st = enqueue_small_grads(net, l, net->L, s, &n);
-        if (st != LF_OK) return st;
+    if (!chain_only) {
+        lf::GradStep grads[lf::kGradLayers];
+        for (int l = net->L; l >= 2;) {
+            int n = 0;
+            for (; n < lf::kGradLayers && l >= 2; --l) grads[n++] = grad_step(net, l);
+            LF_HIP(net, lf::launch_all_gradients(grads, n, net->B, net->dt == LF_BF16, net->sgd_eta, s));
+        }
     }
     net->bwd_done = !chain_only;
     if (sgd) net->stepped = true;

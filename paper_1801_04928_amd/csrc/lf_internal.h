@@ -109,17 +109,18 @@ double direct_product_us(int B, int n_out, int K, bool bf16, bool chain);
 struct GradStep {       // eqs. (bp3), (bp4) of one layer (as launch_grad_gemm)
     const float* D; const void* D_bf; const void* A_prev; float* w; float* b; void* w_bf;
     int n_l, n_prev;
+    int kind = -1;                  // how nabla_w is cut (a GradKind of minibatch_kernels.h), -1: as the layer's shape has it
+    const unsigned* lost = nullptr; // a word of the device's, or none: while it is not 0 no descent step is taken
 };
 // One launch that takes a chain step (or none: NULL) and the gradients of up to two layers, none of which depends on
-// another.  What a product's sums look like depends on its shape, B and the type alone, not on what it is launched with.
+// another.  What a product's sums look like depends on its shape, B, the type and `kind` alone, not on what it is launched with.
 hipError_t launch_backward_step(const ChainStep* chain, const GradStep* grads, int ngrads, int B, bool bf16,
                                 float sgd_eta, hipStream_t s);
 
-// The gradients of up to kGradLayers layers in one launch (none depends on another), all cut in one way (kind: a GradKind of
-// minibatch_kernels.h); and the kind that all layers of a net take.  *lost != 0: no descent step.
+// The gradients of up to kGradLayers layers, all of one kind and with one `lost`, in one launch (none depends on another); and the kind
+// that such a launch takes for all layers of a net.
 constexpr int kGradLayers = 64;
-hipError_t launch_all_gradients(const GradStep* grads, int count, int kind, int B, bool bf16, float sgd_eta, const unsigned* lost,
-                                hipStream_t s);
+hipError_t launch_all_gradients(const GradStep* grads, int count, int B, bool bf16, float sgd_eta, hipStream_t s);
 int grad_kind_of_all(const int* n, int L, int B, bool bf16);
 
 // ---- minibatch path: small nets (cluster_kernels.h) -------------------------------------------------

@@ -412,6 +412,7 @@ struct GradJob {                    // (bp3), (bp4) of one layer
     unsigned d_bytes, a_bytes;
     int n_l, n_prev;
     int tiles_x, tile_blocks, blocks;   // workgroups: tile_blocks for nabla_w, the rest for nabla_b
+    const unsigned* lost;               // none, or != 0 there: what a descent step would apply is not to be trusted
 };
 struct StepArgs {
     // the chain: delta^l from delta^{l+1}
@@ -448,7 +449,8 @@ __device__ __forceinline__ void bias_block(const GradJob& g, int x, int B, float
         s = lds[c];
 #pragma unroll
         for (int q = 1; q < 8; ++q) s += lds[q * 32 + c];
-        g.b[j] = sgd_eta != 0.0f ? fmaf(-sgd_eta, s, g.b[j]) : s;
+        if (sgd_eta == 0.0f) g.b[j] = s;
+        else if (!g.lost || *g.lost == 0) g.b[j] = fmaf(-sgd_eta, s, g.b[j]);
     }
 }
 
@@ -477,6 +479,7 @@ __device__ __forceinline__ void put_grads(const GradJob& g, float sgd_eta, At at
         old[r] = *(const __attribute__((address_space(1))) vf*)(
             g.w + (size_t)min(m, g.n_l - 1) * g.n_prev + min(n, g.n_prev - N));
     }
+    if (g.lost && *g.lost) return;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         int m, n;
@@ -583,19 +586,18 @@ struct AllGradArgs {
     int first[kGradLayers + 1];         // workgroups of the layers before
     int layers, B;
     float sgd_eta;
-    const unsigned* lost;               // != 0: what the step would apply is not to be trusted
+    const unsigned* lost;
 };
 
 template <typename T, int GT, bool GSPLIT>
 __global__ __launch_bounds__(64 * kWaves, 2) void k_all_gradients(const AllGradArgs g) {
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    if (g.sgd_eta != 0.0f && *g.lost) return;
     const int lane = threadIdx.x & 63;
     const int at = __builtin_popcountll(__ballot(lane < g.layers && (int)blockIdx.x >= g.first[lane])) - 1;
     const AllGradArgs::Layer& in = g.layer[at];
     GradJob j;
     j.D_op = in.D_op; j.D = in.D; j.A_prev = in.A_prev; j.w = in.w; j.b = in.b; j.w_bf = in.w_bf;
-    j.n_l = in.n_l; j.n_prev = in.n_prev;
+    j.n_l = in.n_l; j.n_prev = in.n_prev; j.lost = g.lost;
     j.d_bytes = (unsigned)(g.B * in.n_l) * (unsigned)sizeof(T);
     j.a_bytes = (unsigned)(g.B * in.n_prev) * (unsigned)sizeof(T);
     constexpr int tm = GSPLIT ? 16 * GT : 2 * 16 * GT, tn = GSPLIT ? 16 * GT : kWaves / 2 * 16 * GT;
@@ -825,20 +827,19 @@ double direct_product_us(int B, int n_out, int K, bool bf16, bool chain) {
     return (double)((tiles + 255) / 256 * tile_cycles(t, bf16)) * ceil_div(K, bf16 ? 32 : 16) / 2400.0;
 }
 
-hipError_t launch_all_gradients(const GradStep* grads, int count, int kind, int B, bool bf16, float sgd_eta, const unsigned* lost,
-                                hipStream_t s) {
+hipError_t launch_all_gradients(const GradStep* grads, int count, int B, bool bf16, float sgd_eta, hipStream_t s) {
     using namespace direct;
     if (count < 1 || count > kGradLayers) return hipErrorInvalidValue;
     AllGradArgs g{};
     g.layers = count;
-    g.B = B; g.sgd_eta = sgd_eta; g.lost = lost;
+    g.B = B; g.sgd_eta = sgd_eta; g.lost = grads[0].lost;
     for (int i = 0; i < count; ++i) {
         const GradStep& in = grads[i];
         const unsigned long long es = bf16 ? 2 : 4;
-        if (!fits_buffer(es * B * in.n_l) || !fits_buffer(es * B * in.n_prev)) return hipErrorInvalidValue;
+        if (in.kind != grads[0].kind || !fits_buffer(es * B * in.n_l) || !fits_buffer(es * B * in.n_prev)) return hipErrorInvalidValue;
         g.layer[i] = {bf16 ? in.D_bf : static_cast<const void*>(in.D), in.D, in.A_prev, in.w, in.b, in.w_bf, in.n_l, in.n_prev};
     }
-    switch (kind) {
+    switch (grads[0].kind) {
         case GRAD_WAVE_64: return bf16 ? launch_gradients_of<__bf16, 4, false>(g, s) : launch_gradients_of<float, 4, false>(g, s);
         case GRAD_WAVE_32: return bf16 ? launch_gradients_of<__bf16, 2, false>(g, s) : launch_gradients_of<float, 2, false>(g, s);
         case GRAD_SPLIT_32: return bf16 ? launch_gradients_of<__bf16, 2, true>(g, s) : launch_gradients_of<float, 2, true>(g, s);
@@ -878,7 +879,7 @@ hipError_t launch_forward_direct(const void* W, const float* bias, const void* A
 hipError_t launch_backward_step(const ChainStep* c, const GradStep* grads, int ngrads, int B, bool bf16, float sgd_eta,
                                 hipStream_t s) {
     using namespace direct;
-    auto kind_of = [&](const GradStep& g) { return grad_kind(g.n_l, g.n_prev, B, bf16); };
+    auto kind_of = [&](const GradStep& g) { return g.kind >= 0 ? (GradKind)g.kind : grad_kind(g.n_l, g.n_prev, B, bf16); };
     if (ngrads == 2 && kind_of(grads[0]) != kind_of(grads[1])) {
         const hipError_t e = launch_backward_step(c, grads, 1, B, bf16, sgd_eta, s);
         return e != hipSuccess ? e : launch_backward_step(nullptr, grads + 1, 1, B, bf16, sgd_eta, s);
@@ -911,7 +912,7 @@ hipError_t launch_backward_step(const ChainStep* c, const GradStep* grads, int n
         const unsigned long long db = es * B * in.n_l, ab = es * B * in.n_prev;
         if (!fits_buffer(db) || !fits_buffer(ab)) return hipErrorInvalidValue;
         j.D_op = bf16 ? in.D_bf : static_cast<const void*>(in.D);
-        j.D = in.D; j.A_prev = in.A_prev; j.w = in.w; j.b = in.b; j.w_bf = in.w_bf;
+        j.D = in.D; j.A_prev = in.A_prev; j.w = in.w; j.b = in.b; j.w_bf = in.w_bf; j.lost = in.lost;
         j.d_bytes = (unsigned)db; j.a_bytes = (unsigned)ab;
         j.n_l = in.n_l; j.n_prev = in.n_prev;
         const int tm = split ? 16 * gt : 2 * 16 * gt, tn = split ? 16 * gt : kWaves / 2 * 16 * gt;
