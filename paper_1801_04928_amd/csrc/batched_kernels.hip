@@ -828,6 +828,18 @@ GemmPlan gemm_plan(const int* n, int L, int B, bool bf16) {
     return p;
 }
 
+double layer_launches_us(const int* n, int L, int B, bool bf16, bool backward) {
+    const GemmPlan plan = gemm_plan(n, L, B, bf16);
+    const bool wide = (backward ? plan.chain : plan.forward) != GEMM_DIRECT;
+    double us = backward ? 1.8 : 0.0;
+    for (int l = 2; l <= L; ++l) {
+        const int n_l = n[l - 1], n_prev = n[l - 2];
+        if (wide) us += backward ? wide_backward_us(n_l, n_prev, B, l > 2) : wide_forward_us(n_l, n_prev, B);
+        else us += backward ? direct::small_backward_us(n_l, n_prev, B, bf16, l > 2) : direct::small_forward_us(n_l, n_prev, B, bf16);
+    }
+    return backward ? us : std::max(us, 3.0 + 2.5 * (L - 1));      // (2.5: what the host takes to launch one)
+}
+
 size_t split_workspace_floats(int n_out, int B, bool bf16) {             // enough for any plan
     return bf16 ? (size_t)16 * B * n_out : 0;                            // no plan splits more than 16 ways
 }

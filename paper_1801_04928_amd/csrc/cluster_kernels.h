@@ -446,21 +446,29 @@ __global__ void k_cluster_state(unsigned* state, u64* words, size_t n) {
     if (blockIdx.x == 0 && threadIdx.x < 8 * STATE_WORDS) state[threadIdx.x] = threadIdx.x % STATE_WORDS == BASE ? 1u : 0u;
 }
 
+// Units of the contraction that each wave of a kernel takes, where the widest one of a launch has this many units.
+int units_a_wave(int units) {
+    const int ku = ceil_div(units, kWaves);
+    return ku <= 4 ? ku : ku <= 6 ? 6 : 8;
+}
+
 template <typename T, bool BWD>
 hipError_t launch_steps(const Args& g, int widest_contraction, hipStream_t s) {
-    const int ku = ceil_div(ceil_div(widest_contraction, Shape<T>::Q), kWaves);
     const int grid = g.per_cluster * 8;         // (workgroup x goes to XCD x mod 8)
     auto launch = [&](auto kernel, int KU) -> hipError_t {
         kernel<<<grid, kThreads, 2 * 4096 * Shape<T>::M * KU, s>>>(g);
         return hipGetLastError();
     };
-    if (ku <= 1) return launch(k_cluster<T, BWD, 1>, 1);
-    if (ku <= 2) return launch(k_cluster<T, BWD, 2>, 2);
-    if (ku <= 3) return launch(k_cluster<T, BWD, 3>, 3);
-    if (ku <= 4) return launch(k_cluster<T, BWD, 4>, 4);
-    if (ku <= 6) return launch(k_cluster<T, BWD, 6>, 6);
-    if (ku <= 8) return launch(k_cluster<T, BWD, 8>, 8);
-    return hipErrorInvalidValue;
+    const int units = ceil_div(widest_contraction, Shape<T>::Q);
+    if (units > 8 * kWaves) return hipErrorInvalidValue;
+    switch (units_a_wave(units)) {
+        case 1: return launch(k_cluster<T, BWD, 1>, 1);
+        case 2: return launch(k_cluster<T, BWD, 2>, 2);
+        case 3: return launch(k_cluster<T, BWD, 3>, 3);
+        case 4: return launch(k_cluster<T, BWD, 4>, 4);
+        case 6: return launch(k_cluster<T, BWD, 6>, 6);
+        default: return launch(k_cluster<T, BWD, 8>, 8);
+    }
 }
 
 // The launches of a direction: at most kClusterLayers steps each.
@@ -509,6 +517,34 @@ hipError_t run(const ClusterPass& p, hipStream_t s) {
     return hipSuccess;
 }
 
+// What a direction's launches take, in us: `start` a launch, and a step for each layer.  Every task of a launch moves and multiplies
+// the units of the launch's widest contraction, whatever its own layer's (`unit`, from a least of `least` on), finds its place among the
+// slices (`slice` each), and where workgroups have one task or none it also waits for its own layer's words (`wait` an index); two
+// turns of tasks take the time of `pair` steps, more of them a step each.  The first step of the chain forms delta^L from a^L and y
+// (`top` an index).
+struct StepPrices { double start, least, base, unit, slice, wait, pair, top; };
+constexpr StepPrices kForwardPrices[] = {{5.5, 0.915, 0.62, 0.178, 0.0094, 0.0011, 1.67, 0.0}, {5.5, 1.035, 0.62, 0.236, 0.0094, 0.0007, 1.96, 0.0}};
+constexpr StepPrices kChainPrices[] = {{8.7, 0.825, 0.56, 0.197, 0.0061, 0.0, 1.55, 0.0102}, {9.0, 0.985, 0.673, 0.212, 0.0096, 0.0, 1.55, 0.0102}};
+double steps_us(const ClusterPlan& p, const int* n, int L, bool bf16, bool backward) {
+    const StepPrices& c = (backward ? kChainPrices : kForwardPrices)[bf16];
+    const int Q = bf16 ? 32 : 16, all = backward ? L - 2 : L - 1;
+    auto width = [&](int i) { return backward ? n[L - 1 - i] : n[i]; };         // contraction of step i, outputs of step i - 1
+    double us = c.top * width(0);
+    for (int from = 0; from < all; from += kClusterLayers) {
+        const int to = std::min(all, from + kClusterLayers);
+        int widest = 0;
+        for (int i = from; i < to; ++i) widest = std::max(widest, width(i));
+        const double step = std::max(c.least, c.base + c.unit * units_a_wave(ceil_div(widest, Q))) + c.slice * p.ST;
+        us += c.start;
+        for (int i = from; i < to; ++i) {
+            const double turns = (double)p.ST * ceil_div(width(i + 1), Q) / p.per_cluster, one = step + c.wait * width(i);
+            us += turns <= 1.0 ? one : std::max(one, std::max(c.pair, turns) * step);
+        }
+    }
+    return us;
+}
+constexpr double kPrepare = 1.8;                // us of the launch that prepares the words
+
 }  // namespace
 }  // namespace cluster
 
@@ -549,35 +585,23 @@ ClusterPlan cluster_plan(const int* n, int L, int B, bool bf16) {
         return p;
     }
     if (std::getenv("LF_GEMM_BIG")) return p;   // (which of the other kernels to take has been asked for)
-    // What these kernels and those of one launch a layer take, in us.  Fitted to uniform nets of L = 3 .. 12, N = 64 .. 512
-    // (fp32) and 64 .. 1024 (bf16), B = 2 .. 1024.  us a pass forward / backward, a launch a layer -> one launch, L = 12:
-    //   fp32  N = 64, B = 32 30 -> 15 / 44 -> 19;  N = 256, B = 2 32 -> 20 / 46 -> 26, B = 128 34 -> 21 / 50 -> 33, B = 512 43 -> 36 /
-    //         84 -> 57, B = 1024 58 -> 66 / 117 -> 102;  N = 384, B = 32 36 -> 28 / 49 -> 35, B = 512 62 -> 60 / 96 -> 104;  N = 512,
-    //         B = 32 40 -> 36 / 53 -> 45, B = 128 41 -> 36 / 68 -> 56, B = 256 52 -> 53 / 93 -> 87, B = 512 67 -> 96 / 109 -> 160
-    //   bf16  N = 128, B = 32 32 -> 16 / 45 -> 21;  N = 256, B = 256 34 -> 18 / 49 -> 33;  N = 512, B = 32 34 -> 25 / 50 -> 36, B = 256
-    //         40 -> 27 / 68 -> 47, B = 512 47 -> 45 / 84 -> 77, B = 1024 63 -> 81;  N = 768, B = 32 36 -> 34 / 53 -> 50, B = 160 44 -> 52 /
-    //         91 -> 78;  N = 1024, B = 32 38 -> 47 / 74 -> 67, B = 256 55 -> 65 / 93 -> 123
-    // and what few layers make of the set-up, L = 5: fp32 N = 64 13 -> 8 / 21 -> 13, N = 256 13 -> 11 / 20 -> 16, N = 512 14 -> 15 / 20 -> 25.
-    double here_f = 4.5, here_b = 9.5, there_f = 2.5, there_b = 4.0;
-    const double a = bf16 ? (B <= 64 ? 0.55 : B < 256 ? 1.1 : B < 384 ? 1.4 : 1.65) : (B <= 128 ? 1.0 : B < 256 ? 1.2 : B < 384 ? 1.5 : 1.85);
-    auto step = [&](int K, int N) {             // tasks of a layer over the cluster's compute units
-        const double one = bf16 ? 0.85 + 0.0016 * K + 0.0015 * std::max(0, K - 384) : 0.75 + 0.0026 * K + 0.0026 * std::max(0, K - 256);
-        const double turns = (double)p.ST * ceil_div(N, Q) / 32.0, turn = bf16 ? 0.75 + 0.0019 * K : 0.85 + 0.0023 * K;
-        return turns <= 1.0 ? one : std::max(one, std::max(2.0, turns) * turn);
-    };
-    for (int i = 1; i < L; ++i) {
-        const int K = n[i - 1], N = n[i];
-        const double grads = (double)K * N * (4.0 / 3e6 + 2.0 * B / (bf16 ? 150e6 : 70e6));
-        here_f += step(K, N);
-        there_f += 2.4 + a * direct_product_us(B, N, K, bf16, false);
-        here_b += grads;
-        there_b += 3.2 + 0.6 * grads + 0.003 * B;
-        if (i > 1) here_b += 1.17 * step(N, K);
-        there_b += a * direct_product_us(B, K, N, bf16, true);
-    }
-    // (the line is drawn where these kernels gain a twelfth: so far apart are the estimates of either side)
-    p.forward = 1.09 * here_f < there_f;
-    p.backward = 1.09 * here_b < there_b;
+    // What these kernels and those of one launch a layer take: fitted to 1700 uniform nets, L = 5 .. 64, N = 8 .. 512 (fp32) and 8 .. 1024
+    // (bf16), B = 2 .. 32640, and 800 of unequal widths, within 5 to 8 % (root mean square) a side.  By the choice 17 of these nets take more
+    // than 2 % longer than by a launch a layer, and 17 more than 10 % longer than by the better side; those it sends here gain 1.5 times.  us a pass forward / backward, a launch a layer -> here (the preparation with the forward pass), L = 8:
+    //   fp32  N = 64, B = 32 19 -> 12 / 29 -> 15, B = 8192 145 -> 90 / 400 -> 128;  N = 256, B = 32 21 -> 17 / 31 -> 21, B = 300 27 -> 22 /
+    //         43 -> 36, B = 512 29 -> 27 / 55 -> 42, B = 1024 37 -> 47 / 75 -> 70, B = 4096 114 -> 187 / 234 -> 265;  N = 384, B = 32 23 -> 20 /
+    //         32 -> 28, B = 256 30 -> 28 / 46 -> 48, B = 512 39 -> 43 / 60 -> 72;  N = 512, B = 32 25 -> 28 / 33 -> 37, B = 256 34 -> 38 / 60 -> 67
+    //   bf16  N = 256, B = 32 21 -> 15 / 31 -> 19, B = 512 24 -> 16 / 40 -> 28, B = 2048 42 -> 44 / 121 -> 80, B = 8192 114 -> 205 / 414 -> 324;
+    //         N = 512, B = 32 22 -> 19 / 32 -> 29, B = 256 26 -> 20 / 45 -> 40, B = 384 30 -> 27 / 43 -> 57;  N = 768, B = 32 23 -> 27 / 33 -> 42, B =
+    //         128 27 -> 27 / 52 -> 46, B = 256 35 -> 37 / 60 -> 70;  N = 1024, B = 32 24 -> 35 / 47 -> 52
+    //   one layer of 512 among 64 (fp32) B = 32 20 -> 22 / 30 -> 24, B = 512 23 -> 28 / 50 -> 32;  64 and 1024 in turn (bf16) B = 32 22 -> 24 /
+    //   37 -> 39, B = 512 31 -> 49 / 47 -> 70;  784, six of 256, 16 (bf16) B = 32 21 -> 22 / 31 -> 18
+    // and what few layers make of the start, L = 5: fp32 N = 64, B = 32 12 -> 10 / 18 -> 13, N = 512 14 -> 17 / 20 -> 24.
+    const double forward = steps_us(p, n, L, bf16, false);
+    const double backward = steps_us(p, n, L, bf16, true) + all_gradients_us(n, L, B, bf16);
+    p.forward = forward + kPrepare < layer_launches_us(n, L, B, bf16, false);
+    p.backward = backward + (p.forward ? 0.0 : kPrepare) < layer_launches_us(n, L, B, bf16, true);
+    p.forward = p.forward && p.backward;        // (the other kernels' descent step would not know of a lost forward pass)
     return p;
 }
 

@@ -753,7 +753,10 @@ lf_status check_backward_call(lf_net* net, const void* y, int k) {
     return LF_OK;
 }
 
-// What the small nets' kernels work on.
+// What the small nets' kernels work on.  Since the last pass the caller may have used the workspace otherwise, another handle among
+// them, so what the kernels exchange there is prepared by a launch in front of the pass's first (L = 8, N = 256, B = 32 fp32
+// 39.2 us a pass, 37.6 with the state kept from pass to pass, whatever is cleared: the launch is what it costs).  From the forward to
+// the backward pass the workspace holds a^l and is left alone.
 lf::ClusterPass cluster_pass(const lf_net* net, const void* y) {
     const Layout& lay = net->lay;
     lf::ClusterPass p{};
@@ -768,6 +771,13 @@ lf::ClusterPass cluster_pass(const lf_net* net, const void* y) {
     p.state = cluster_state(net);
     p.lost_host = net->p_abort_dev_view;
     return p;
+}
+
+lf_status cluster_chain(lf_net* net, const void* y, hipStream_t s) {
+    const lf::ClusterPass p = cluster_pass(net, y);
+    if (!net->lay.cluster.forward) LF_HIP(net, lf::launch_cluster_state(p.plan, p.state, p.words, s));
+    LF_HIP(net, lf::launch_cluster_chain(p, s));
+    return LF_OK;
 }
 
 // The stream realisation of the schedule.  The chain runs on s; `partial` / `raw` are the scratch of its
@@ -787,7 +797,8 @@ lf_status backward_streams(lf_net* net, const void* y, int k, hipStream_t s, flo
     for (int l = L; l >= 2; --l) {
         // the chain: (bp1) at L, (bp2) below
         if (net->lay.cluster.backward) {                // all of it in one launch
-            if (l == L) LF_HIP(net, lf::launch_cluster_chain(cluster_pass(net, y), s));
+            st = l == L ? cluster_chain(net, y, s) : LF_OK;
+            if (st != LF_OK) return st;
         } else if (l == L) {
             LF_HIP(net, lf::launch_output_error(net->a_ptr(L), y, net->d_ptr(L), net->dbf_ptr(L),
                                                 (size_t)B * net->width(L), bf, net->cost_scale, chain_counters(net),
@@ -863,7 +874,8 @@ lf_status backward_steps(lf_net* net, const void* y, hipStream_t s) {
 // The small minibatch nets: the chain in one launch, the gradients of all layers in another.
 lf_status backward_cluster(lf_net* net, const void* y, hipStream_t s) {
     const bool sgd = net->sgd_eta != 0.0f, chain_only = (net->debug_flags & LF_DEBUG_CHAIN_ONLY) != 0;
-    LF_HIP(net, lf::launch_cluster_chain(cluster_pass(net, y), s));
+    const lf_status st = cluster_chain(net, y, s);
+    if (st != LF_OK) return st;
     if (!chain_only) {
         lf::GradStep grads[lf::kGradLayers];
         for (int l = net->L; l >= 2;) {
@@ -1115,19 +1127,14 @@ lf_status lf_forward(lf_net* net, const void* x1, void* hip_stream) {
         net->fwd_done = true;
         return LF_OK;
     }
-    if (net->lay.cluster.forward || net->lay.cluster.backward) {
-        // Since the last pass the caller may have used the workspace otherwise, another handle among them: what the kernels
-        // of either direction exchange is prepared here, and from here on the workspace holds a^l and is left alone.  (A
-        // launch a pass: L = 8, N = 256, B = 32 fp32 39.4 us, 37.7 with the state kept from pass to pass.)
+    if (net->lay.cluster.forward) {
         st0 = net->sched == LF_SCHED_STREAMS ? LF_OK : small_net_abort_word(net, s);    // (with that schedule this call allocates nothing)
         if (st0 != LF_OK) return st0;
         const lf::ClusterPass p = cluster_pass(net, nullptr);
         LF_HIP(net, lf::launch_cluster_state(p.plan, p.state, p.words, s));
-        if (net->lay.cluster.forward) {
-            LF_HIP(net, lf::launch_cluster_forward(p, s));
-            net->fwd_done = true;
-            return LF_OK;
-        }
+        LF_HIP(net, lf::launch_cluster_forward(p, s));
+        net->fwd_done = true;
+        return LF_OK;
     }
     const bool single = single_sample_path(net->N, net->B, net->dt);
     const bool stream_weights = single && weights_exceed_cache(net, false);

@@ -104,8 +104,6 @@ struct ChainStep {      // eq. (bp2): delta^l from delta^{l+1} (as launch_chain_
 };                      // when the first chain step of a pass starts, and again when a step has ended
 int chain_counters();
 size_t direct_chain_scratch_floats(int n_l, int n_next, int B, bool bf16);
-// Time of the tiles of a forward or chain product with a B x n_out result, as the choice of its tiles prices it, in us.
-double direct_product_us(int B, int n_out, int K, bool bf16, bool chain);
 struct GradStep {       // eqs. (bp3), (bp4) of one layer (as launch_grad_gemm)
     const float* D; const void* D_bf; const void* A_prev; float* w; float* b; void* w_bf;
     int n_l, n_prev;
@@ -122,6 +120,10 @@ hipError_t launch_backward_step(const ChainStep* chain, const GradStep* grads, i
 constexpr int kGradLayers = 64;
 hipError_t launch_all_gradients(const GradStep* grads, int count, int B, bool bf16, float sgd_eta, hipStream_t s);
 int grad_kind_of_all(const int* n, int L, int B, bool bf16);
+// For the choice of the kernels that walk all layers (cluster_plan), in us: such a gradients' launch, beyond its start; and a direction of
+// a net of widths up to 1024 by a launch a layer.
+double all_gradients_us(const int* n, int L, int B, bool bf16);
+double layer_launches_us(const int* n, int L, int B, bool bf16, bool backward);
 
 // ---- minibatch path: small nets (cluster_kernels.h) -------------------------------------------------
 

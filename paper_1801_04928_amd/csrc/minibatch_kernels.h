@@ -761,6 +761,39 @@ double backward_us(int n_l, int n_prev, int B, bool chain) {    // gradients of 
     return 3.08 + grad_us(n_l, n_prev, B) + (chain ? 0.878 * chain_us(B, n_prev, n_l, true) : 0.0);
 }
 
+// The same for nets of widths up to 1024, fp32 too, against which the kernels that walk all layers in one launch are set
+// (cluster_plan, where the measurements are).  A chain-side product takes as many turns as the busiest XCD's tiles make on its 32
+// compute units (whole columns of tiles go to an XCD); a turn is the units of a tile, dearer by `part` where rows are no whole lines,
+// and what larger tiles take to start and end.
+struct SmallProduct { double turns, tile; };
+SmallProduct small_product(int B, int n_out, int K, bool bf16, bool chain, double unit, double part, double block) {
+    const TileShape t = chain_tile(B, n_out, bf16, chain);
+    const double jobs = (double)ceil_div(ceil_div(n_out, 16 * t.nt), 8) * ceil_div(B, 16 * t.mt);
+    const double us = (double)tile_cycles(t, bf16) * ceil_div(K, bf16 ? 32 : 16) / 2400.0;
+    const bool lines = (chain ? n_out : K) % (bf16 ? 64 : 32) == 0;
+    return {std::max(1.0, jobs / 32), unit * us * (lines ? 1.0 : part) + block * (t.mt + t.nt - 2)};
+}
+double small_forward_us(int n_out, int n_in, int B, bool bf16) {
+    const SmallProduct p = bf16 ? small_product(B, n_out, n_in, bf16, false, 0.62, 1.5, 0.35) : small_product(B, n_out, n_in, bf16, false, 0.886, 1.25, 0.506);
+    return (bf16 ? 2.8 : 2.63) + p.tile + (p.turns - 1.0) * (0.35 + (bf16 ? 0.8 : 0.69) * p.tile) + (bf16 ? 1.65e-6 : 3.52e-6) * B * n_out;
+}
+// The units of the samples that one wave of a gradient tile walks (in pairs), and the waves, in 1024.
+struct SmallGrads { double units, waves; };
+SmallGrads small_grads(GradKind kind, int n_l, int n_prev, int B, bool bf16) {
+    const int edge = kind == GRAD_WAVE_64 ? 64 : 32, q = bf16 ? 32 : 16;
+    return {2.0 * ceil_div(B, kind == GRAD_SPLIT_32 ? 2 * kWaves * q : 2 * q),
+            (double)ceil_div(n_l, edge) * ceil_div(n_prev, edge) * (kind == GRAD_SPLIT_32 ? kWaves : 1) / 1024.0};
+}
+double small_backward_us(int n_l, int n_prev, int B, bool bf16, bool chain) {      // as backward_us
+    const GradKind kind = grad_kind(n_l, n_prev, B, bf16);
+    const SmallGrads g = small_grads(kind, n_l, n_prev, B, bf16);
+    const double unit = (bf16 ? 0.222 * g.waves : 0.048 + 0.108 * g.waves) * (kind == GRAD_SPLIT_32 ? (bf16 ? 2.14 : 2.49) : 1.0);
+    const double us = (bf16 ? 3.33 : 3.55) + g.units * unit + (bf16 ? 1.63e-6 : 2.9e-6) * n_l * n_prev + (bf16 ? 2.9e-3 : 3.55e-3) * B;
+    if (!chain) return us;
+    const SmallProduct p = bf16 ? small_product(B, n_prev, n_l, bf16, true, 0.284, 2.47, 0.294) : small_product(B, n_prev, n_l, bf16, true, 0.26, 3.0, 0.12);
+    return us + p.tile * (1.0 + (p.turns - 1.0) * (bf16 ? 3.9 : 1.85));
+}
+
 template <typename T, int MT, int NT>
 hipError_t launch_forward(const ForwardArgs& g, hipStream_t s) {
     k_forward_tile<T, MT, NT><<<ceil_div(g.tiles_n, 8) * 8 * g.tiles_m, 64 * kWaves, lds_bytes(MT + NT, NT), s>>>(g);
@@ -820,13 +853,6 @@ hipError_t launch_gradients_of(AllGradArgs& g, hipStream_t s) {
 }  // namespace
 }  // namespace direct
 
-double direct_product_us(int B, int n_out, int K, bool bf16, bool chain) {
-    using namespace direct;
-    const TileShape t = chain_tile(B, n_out, bf16, chain);
-    const long tiles = (long)ceil_div(B, 16 * t.mt) * ceil_div(n_out, 16 * t.nt);
-    return (double)((tiles + 255) / 256 * tile_cycles(t, bf16)) * ceil_div(K, bf16 ? 32 : 16) / 2400.0;
-}
-
 hipError_t launch_all_gradients(const GradStep* grads, int count, int B, bool bf16, float sgd_eta, hipStream_t s) {
     using namespace direct;
     if (count < 1 || count > kGradLayers) return hipErrorInvalidValue;
@@ -858,6 +884,21 @@ int grad_kind_of_all(const int* n, int L, int B, bool bf16) {
         tiles32 += (long)ceil_div(n[i], 32) * ceil_div(n[i - 1], 32);
     }
     return tiles64 >= 1024 ? GRAD_WAVE_64 : tiles32 < 1024 && B > (bf16 ? 96 : 48) ? GRAD_SPLIT_32 : GRAD_WAVE_32;
+}
+
+double all_gradients_us(const int* n, int L, int B, bool bf16) {
+    using namespace direct;
+    const GradKind kind = (GradKind)grad_kind_of_all(n, L, B, bf16);
+    double waves = 0.0, entries = 0.0, units = 0.0;
+    for (int i = 1; i < L; ++i) {
+        const SmallGrads g = small_grads(kind, n[i], n[i - 1], B, bf16);
+        units = g.units;
+        waves += g.waves;
+        entries += (double)n[i] * n[i - 1];
+    }
+    const double unit = kind == GRAD_SPLIT_32 ? (bf16 ? 1.13 : 0.80) * waves : kind == GRAD_WAVE_64 ? (bf16 ? 1.97 : 0.71) + waves
+                                              : (bf16 ? 0.21 + 0.81 * waves : 0.46 + 0.37 * waves);
+    return units * unit + (bf16 ? 1.2e-6 : 3.1e-6) * entries + (bf16 ? 5.7e-3 : 5.6e-3) * B;
 }
 
 int chain_counters() { return direct::kSplitWorkgroups; }

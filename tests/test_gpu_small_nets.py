@@ -245,3 +245,32 @@ def test_a_wait_that_gives_up_is_reported_and_takes_no_step(monkeypatch, dtype, 
     torch.cuda.synchronize()
     check_against_oracle(net, g)
     g.close()
+
+
+@pytest.mark.parametrize("widths,B,dtype", [
+    ((256,) * 8, 32, "f32"), ((64, 64, 64, 64, 512, 64, 64, 64), 32, "f32"), ((784,) + (256,) * 6 + (16,), 32, "bf16")])
+def test_small_nets_as_they_are_chosen(widths, B, dtype):
+    """No choice forced: nets whose two directions, and nets whose chain alone, take these kernels, from any workspace, eager and replayed."""
+    import torch
+    net = make_net(len(widths), widths, B, dtype=dtype, seed=B)
+    g = run_gpu(net, 1)
+    check_against_oracle(net, g)
+    want = _bits(g)
+    for k in (1, 3):
+        g.workspace.fill_(255)
+        assert all(np.array_equal(a, b) for a, b in zip(want, _again(g, k))), k
+    for _ in range(2):                 # backward passes of one forward pass
+        g.backward(1)
+        assert all(np.array_equal(a, b) for a, b in zip(want, _bits(g)))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        g.forward()
+        g.backward(1)
+    for _ in range(3):
+        g.workspace.fill_(255)
+        for t in g.nabla_w + g.nabla_b:
+            t.fill_(float("nan"))
+        graph.replay()
+        assert all(np.array_equal(a, b) for a, b in zip(want, _bits(g)))
+        assert all(np.array_equal(a, b) for a, b in zip(want, _again(g)))
+    g.close()

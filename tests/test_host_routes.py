@@ -204,6 +204,40 @@ def test_each_pass_of_a_small_net_prepares_what_its_workgroups_exchange(program,
     assert "k_clusterI" in pick("backward")[0] and "k_all_gradients" in pick("backward")[1]
 
 
+# us a pass forward / backward, measured: by a launch a layer, and by one for all (the forward pass with its preparation)
+@pytest.mark.parametrize("widths,B,dtype,layers,one", [
+    ([64] * 8, 32, "f32", (19, 29), (12, 15)), ([256] * 8, 32, "f32", (21, 31), (17, 21)), ([256] * 8, 300, "f32", (27, 43), (22, 36)),
+    ([256] * 8, 1024, "f32", (37, 75), (47, 70)), ([256] * 8, 4096, "f32", (114, 234), (187, 265)), ([512] * 10, 128, "f32", (34, 57), (34, 47)),
+    ([512] * 8, 256, "f32", (34, 60), (38, 67)), ([512] * 8, 1024, "f32", (62, 112), (124, 226)), ([384] * 8, 512, "f32", (39, 60), (43, 72)),
+    ([64] * 16, 4096, "f32", (117, 416), (80, 101)), ([64] * 8, 16384, "f32", (247, 748), (232, 293)),
+    ([256] * 8, 64, "bf16", (21, 31), (15, 20)), ([512] * 8, 64, "bf16", (22, 32), (19, 30)), ([512] * 16, 256, "bf16", (55, 91), (36, 56)),
+    ([512] * 5, 384, "bf16", (17, 26), (19, 44)), ([704] * 5, 384, "bf16", (23, 38), (26, 70)), ([704] * 8, 384, "bf16", (40, 66), (41, 88)),
+    ([768] * 16, 64, "bf16", (49, 72), (46, 70)), ([768] * 16, 65, "bf16", (49, 81), (46, 70)), ([896] * 16, 128, "bf16", (62, 152), (57, 90)),
+    ([1024] * 8, 32, "bf16", (24, 47), (35, 52)), ([1024] * 8, 256, "bf16", (35, 59), (46, 90)), ([256] * 5, 32640, "bf16", (106, 947), (866, 1243)),
+    ([128] * 16, 4096, "bf16", (132, 467), (83, 145)),
+    # unequal widths: the widest contraction of a launch decides what each of its steps takes
+    ([64] * 4 + [512] + [64] * 3, 512, "f32", (23, 50), (28, 32)), ([512] + [64] * 7, 512, "f32", (21, 48), (23, 19)),
+    ([64] * 7 + [512], 32, "f32", (20, 30), (15, 28)), ([64, 512] * 4, 512, "f32", (31, 54), (45, 54)), ([300, 44, 76, 512, 308], 448, "f32", (17, 33), (25, 47)),
+    ([64, 1024] * 4, 512, "bf16", (31, 47), (49, 70)), ([784] + [256] * 6 + [16], 32, "bf16", (21, 31), (22, 18)),
+    ([64] * 4 + [512] + [64] * 3, 32, "f32", (20, 30), (22, 24)), ([192] * 5 + [848, 192], 1030, "bf16", (34, 56), (45, 92)), ([160, 56, 56, 136, 832], 10, "bf16", (13, 19), (12, 28)),
+])
+def test_small_nets_take_the_faster_kernels(program, widths, B, dtype, layers, one):
+    """The choice is no more than 4 % off the best of: a launch a layer, one for the chain alone (and its preparation), one a direction."""
+    forward, backward, _ = _routes(program, widths, B, dtype)
+    here = [any("k_clusterI" in name for name in names) for names in (forward, backward)]
+    assert any("k_all_gradients" in name for name in backward) == here[1]
+    times = {(False, False): sum(layers), (False, True): layers[0] + one[1] + 1.8, (True, True): sum(one)}
+    assert times[tuple(here)] <= 1.04 * min(times.values()), (here, times)
+    prepared = sum("k_cluster_state" in name for name in forward), sum("k_cluster_state" in name for name in backward)
+    assert prepared == (here[0], here[1] and not here[0])
+
+
+@pytest.mark.parametrize("widths,dtype", [([64] * 4, "f32"), ([516] + [64] * 9, "f32"), ([64] * 9 + [1032], "bf16")])
+def test_few_layers_and_wide_ones_take_a_launch_a_layer(program, widths, dtype):
+    forward, backward, _ = _routes(program, widths, 32, dtype)
+    assert not any("k_cluster" in name for name in forward + backward)
+
+
 @pytest.mark.parametrize("choice,kernels", [("0", ("k_forward_tile", "k_backward_step")), ("1", ("k_gemm_big", "k_gemm_big"))])
 def test_the_forced_choice_of_kernels_holds_for_small_nets(program, choice, kernels):
     forward, backward, noalloc = _routes(program, [256] * 8, 32, "bf16", LF_GEMM_BIG=choice)
