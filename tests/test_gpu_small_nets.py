@@ -63,8 +63,8 @@ def test_small_nets_match_oracle_with_the_same_bits_from_every_schedule(monkeypa
         t.fill_(float("nan"))
     g.forward()
     st = P.lf_backward_leapfrog_noalloc(g.handle, g.y.data_ptr(), 1, g.torch.cuda.current_stream().cuda_stream)
-    if st == P.LF_OK:                  # (its limit does not follow the choice of kernels)
-        assert all(np.array_equal(a, b) for a, b in zip(want, _bits(g)))
+    assert st == P.LF_OK, P.lf_last_error(g.handle)
+    assert all(np.array_equal(a, b) for a, b in zip(want, _bits(g)))
     g.close()
     # no cluster is ever complete: its workgroups draw their tasks in order
     monkeypatch.setenv("LF_CLUSTER_INCOMPLETE", "1")
@@ -115,6 +115,62 @@ def test_descent_step_of_a_small_net(monkeypatch, widths, B, dtype):
             exact = o.astype(np.float64) - 0.125 * d.astype(np.float64)
             assert np.array_equal(to_np(t), exact.astype(np.float32).reshape(o.shape))
     g.close()
+
+
+def test_bf16_weights_follow_their_masters(monkeypatch):
+    """The weights that the next pass multiplies with are the stepped masters, rounded to nearest even: three steps in a row, each from
+    the gradients of a net that starts with the same weights."""
+    import paper_1801_04928_amd as P
+    import torch
+    monkeypatch.setenv("LF_CLUSTER", "1")
+    L, N, B = 6, 520, 100
+    net = make_net(L, N, B, dtype="bf16", seed=4)
+    g, fresh = P.LeapfrogNet(L, N, B, "bf16"), P.LeapfrogNet(L, N, B, "bf16")
+    for h in (g, fresh):
+        h.load(net)
+        h.set_sgd(0.125)
+    tensors = lambda h: h.w + h.master_w + h.b  # noqa: E731
+    for _ in range(3):
+        before = [t.clone() for t in tensors(g)]
+        for a, b in zip(tensors(fresh), before):
+            a.copy_(b)
+        fresh.set_sgd(0.0)
+        fresh.forward()
+        fresh.backward(1)
+        g.forward()
+        g.backward(1)
+        torch.cuda.synchronize()
+        for w, m, old, d in zip(g.w, g.master_w, before[L - 1:], fresh.nabla_w):
+            exact = old.double() - 0.125 * d.double()          # (eta is a power of two: one rounding)
+            assert torch.equal(m, exact.float()) and torch.equal(w, m.to(torch.bfloat16)) and not torch.equal(m, old)
+    fresh.close()
+    g.close()
+
+
+def test_passes_of_several_nets_overlap(monkeypatch):
+    """Nets that fill the compute units, each on a stream of its own, pass after pass without a wait between: their workgroups are not
+    all resident at once, and nothing of one shows in another."""
+    import torch
+    monkeypatch.setenv("LF_CLUSTER", "1")
+    shapes = [(8, 512, 128, "f32"), (8, 1024, 128, "bf16"), (8, 512, 300, "f32"), (12, 256, 512, "f32")]
+    nets = [make_net(L, N, B, dtype=dtype, seed=L + B) for L, N, B, dtype in shapes]
+    handles = [run_gpu(net, 1) for net in nets]
+    want = [_bits(g) for g in handles]
+    streams = [torch.cuda.Stream() for _ in handles]
+    for g in handles:
+        for t in g.nabla_w + g.nabla_b:
+            t.fill_(float("nan"))
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for g, stream in zip(handles, streams):
+            with torch.cuda.stream(stream):
+                g.forward()
+                g.backward(1)
+    torch.cuda.synchronize()
+    for g, w in zip(handles, want):
+        assert all(np.array_equal(a, b) for a, b in zip(w, _bits(g)))
+        g.grads(2)                     # (raises where a wait has given up)
+        g.close()
 
 
 def test_replays_of_a_captured_pass_beside_eager_ones(monkeypatch):
