@@ -50,7 +50,7 @@
  *     schedule for good and works again from the next lf_forward; a handle set to
  *     LF_SCHED_PERSISTENT or LF_SCHED_FUSED stays failed (destroy it).
  *   - The workgroups of the kernels that serve small minibatch nets (LF_SCHED_AUTO) wait for each other as well, but
- *     only for ones that are running: nothing has to be resident at once, and such passes may overlap with anything.  Their
+ *     only for ones that are running: nothing has to be resident at once, and such passes may overlap with other work.  Their
  *     waits are bounded all the same.  If one gives up, the pass applies no descent step, the next call on the handle returns
  *     LF_EHIP, and the handle, whatever its schedule, takes the kernels of one launch per layer from the next lf_forward.
  *     (A handle whose first pass was recorded into a graph has no means of saying so: its activations are NaN then.)
@@ -92,9 +92,13 @@ typedef enum { LF_COST_QUADRATIC = 0, LF_COST_INT_RANGE = 0x7fffffff } lf_cost;
 typedef enum {
     LF_SCHED_AUTO = 0,        /* the library picks: persistent where supported; for most minibatch nets one launch per
                                  layer on the caller's stream, in which the gradients of layer l+1 ride beside the
-                                 chain step delta^{l+1} -> delta^l; for a single sample outside the persistent
+                                 chain step delta^{l+1} -> delta^l; for small minibatch nets (five layers and more, up to
+                                 512 neurons in fp32, 1024 in bf16, where it is estimated to pay) one launch for the chain
+                                 through all layers and one for all gradients; for a single sample outside the persistent
                                  kernels' shapes every kernel in line on the caller's stream; else streams */
-    LF_SCHED_STREAMS = 1,     /* chain on the caller's stream, k worker streams fed by per-layer events */
+    LF_SCHED_STREAMS = 1,     /* chain on the caller's stream, k worker streams fed by per-layer events (the chain of a small
+                                 minibatch net, as LF_SCHED_AUTO has it, is one launch in front of the first of these: its
+                                 workers start when the chain has ended) */
     LF_SCHED_PERSISTENT = 2,  /* one persistent kernel, k workgroup partitions fed by per-layer ready flags */
     LF_SCHED_REDUNDANT = 3,   /* Algorithm 1 as printed, for comparison: the parent (the caller's stream) walks
                                  the top k layers, then each of k worker streams walks its OWN delta chain down
@@ -128,8 +132,12 @@ size_t lf_workspace_bytes(int L, int N, int B, lf_dtype dt);
 
 /* Create a handle.  `workspace` is caller-owned device memory of at least
  * lf_workspace_bytes() bytes, 256-byte aligned; its contents need not be
- * initialised.  Pure host work: touches no device.  LF_EINVAL on a bad shape,
- * null/misaligned/small workspace. */
+ * initialised.  From lf_forward to the end of the backward passes that follow it
+ * belongs to the handle; what it holds when a forward pass begins does not matter,
+ * so in between the caller, another handle included, may use it (not where the
+ * passes run the persistent kernels: those keep what their workgroups exchange there
+ * from the first pass to lf_destroy).  Pure host work: touches no device.  LF_EINVAL
+ * on a bad shape, null/misaligned/small workspace. */
 lf_status lf_create(lf_net** out, int L, int N, int B, lf_dtype dt, lf_cost cost,
                     void* workspace, size_t workspace_bytes);
 
@@ -211,10 +219,10 @@ lf_status lf_backward_leapfrog(lf_net* net, const void* y, int k, void* hip_stre
  * first call, tight serving loops, harnesses that forbid hipMalloc.  (lf_backward_leapfrog may create worker
  * streams and events, or pinned memory, the first time a handle runs with a new k or schedule.)  This call
  * allocates nothing, on the device or through any library: it enqueues the chain and gradient kernels of
- * layer L, L-1, ..., 2 in that order on hip_stream alone, and the scratch of the chain
+ * layer L, L-1, ..., 2 in that order (a small minibatch net's: the chain, then the gradients) on hip_stream alone, and the scratch of the chain
  * products (row-block partial sums at B = 1, split-K partials of a wide minibatch net) is a static device array inside
  * the library instead of the caller's workspace.  (The kernels that serve the other minibatch nets keep what little they
- * need, for few samples and wide layers, in the workspace.)  Same arguments, same checks, same results bit for bit as
+ * need, for few samples and wide layers and for small nets, in the workspace.)  Same arguments, same checks, same results bit for bit as
  * lf_backward_leapfrog with LF_SCHED_STREAMS (k only names the worker a layer would belong to; the gradients do
  * not depend on it).  lf_forward must have run (with LF_SCHED_STREAMS it allocates nothing either).
  * Limits: the chain scratch that the net's shape is charged for must fit lf_noalloc_scratch_limit() bytes -- 8 MiB:

@@ -5,7 +5,8 @@
 // exchange inside that XCD's L2 (0.6 us among 16 workgroups, 1.0 to 1.2 among XCDs), not by a kernel boundary (2.5 to 3.5 us
 // with the first requests behind it).  The price is that every cluster reads all the weights, which is why wide nets take the
 // kernels of minibatch_kernels.h.  us a layer, a launch a layer -> here: fp32 forward N = 64 2.7 -> 0.9, N = 256 3.0 -> 1.4, N = 512
-// 3.6 -> 2.7; the pass with gradients, L = 16, N = 64, B = 8 107 -> 40 us, N = 256, B = 32 112 -> 60, bf16 N = 512, B = 256 147 -> 93.
+// 3.6 -> 2.7; the pass with gradients, L = 16, N = 64, B = 8 96 -> 41 us, N = 256, B = 32 112 -> 62, bf16 N = 512, B = 256 147 -> 96 (with
+// the 1.8 us of the launch that prepares the exchange).
 // What bounds it: a step is a chain of latencies (poll 400 cycles, matrix instructions 32 per 4 indices and wave, the waves'
 // sum through LDS, sigma, store), and from N = 384 on what a compute unit takes in, weights and words at 40 bytes a cycle.
 //
@@ -556,7 +557,7 @@ ClusterPlan cluster_plan(const int* n, int L, int B, bool bf16) {
     const int Q = bf16 ? 32 : 16;
     int widest = 0;
     for (int i = 0; i < L; ++i) widest = std::max(widest, n[i]);
-    // (what fewer layers would gain is less than 6 us a pass: L = 4, N = 64 10 -> 7 / 17 -> 12 us, N = 512 11 -> 12 / 15 -> 20)
+    // (what fewer layers would gain is less than 6 us a pass: L = 4, N = 64 10 -> 9 / 17 -> 12 us, N = 512 11 -> 14 / 15 -> 20)
     if (L < 5 || widest > 8 * kWaves * Q) return p;
     p.clusters = std::min(8, B);
     p.ST = ceil_div(B, 16 * p.clusters);
