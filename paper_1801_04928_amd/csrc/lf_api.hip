@@ -418,7 +418,7 @@ lf_status ensure_abort_word(lf_net* net) {
         word = static_cast<int*>(h);
     }
     *word = 0;
-    net->p_abort_host = word;
+    net->p_abort_host = word;           // (whatever comes next, lf_destroy gives it back)
     void* d = nullptr;
     LF_HIP(net, hipHostGetDevicePointer(&d, word, 0));
     net->p_abort_dev_view = static_cast<int*>(d);
@@ -434,12 +434,12 @@ void release_abort_word(lf_net* net) {
         (void)hipHostFree(net->p_abort_host);
 }
 
-// The small nets' kernels do without it where a handle's first pass is a captured one: allocating is no part of a capture, nor of
-// a later pass.  (A lost pass then shows in its NaNs alone.)
-lf_status small_net_abort_word(lf_net* net, hipStream_t s) {
-    if (net->p_abort_asked) return LF_OK;
+// The small nets' kernels do without it where a handle's first pass is a captured one (allocating is no part of a capture, nor of
+// a later pass) or there is no pinned memory to be had.  (A lost pass then shows in its NaNs alone.)
+void small_net_abort_word(lf_net* net, hipStream_t s) {
+    if (net->p_abort_asked) return;
     net->p_abort_asked = true;
-    return is_capturing(s) ? LF_OK : ensure_abort_word(net);
+    if (!is_capturing(s) && ensure_abort_word(net) != LF_OK) (void)hipGetLastError();
 }
 
 lf_status check_abort(lf_net* net) {
@@ -1128,8 +1128,7 @@ lf_status lf_forward(lf_net* net, const void* x1, void* hip_stream) {
         return LF_OK;
     }
     if (net->lay.cluster.forward) {
-        st0 = net->sched == LF_SCHED_STREAMS ? LF_OK : small_net_abort_word(net, s);    // (with that schedule this call allocates nothing)
-        if (st0 != LF_OK) return st0;
+        if (net->sched != LF_SCHED_STREAMS) small_net_abort_word(net, s);       // (with that schedule this call allocates nothing)
         const lf::ClusterPass p = cluster_pass(net, nullptr);
         LF_HIP(net, lf::launch_cluster_state(p.plan, p.state, p.words, s));
         LF_HIP(net, lf::launch_cluster_forward(p, s));
@@ -1186,8 +1185,7 @@ lf_status lf_backward_leapfrog(lf_net* net, const void* y, int k, void* hip_stre
         if (st == LF_OK) net->bwd_done = true;
         return st;
     }
-    st = net->lay.cluster.backward ? small_net_abort_word(net, s) : LF_OK;
-    if (st != LF_OK) return st;
+    if (net->lay.cluster.backward) small_net_abort_word(net, s);
     if (net->sched == LF_SCHED_AUTO && net->lay.cluster.backward) return backward_cluster(net, y, s);
     if (net->sched == LF_SCHED_AUTO && direct_minibatch(net)) return backward_steps(net, y, s);
     // Left to the library, a single sample outside the persistent kernels' shapes has its gradients in line as well: its

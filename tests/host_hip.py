@@ -20,6 +20,8 @@ struct dim3 { unsigned x, y, z; };
 static std::set<stream_t> used, live;
 static int created;                                  // streams, events and pinned blocks
 static void* pinned;                                 // the last of these
+static bool no_pinned_memory;
+static void* pinned_word;                            // the last that the device asked for
 static bool capturing;
 static uintptr_t next_handle = 0x1000;
 static int caller_1, caller_2, caller_3;
@@ -56,9 +58,9 @@ int hipDeviceGetAttribute(int* v, int, int) { *v = 256; return 0; }
 int hipGetLastError() { return 0; }
 const char* hipGetErrorString(int) { return "error"; }
 int hipGetSymbolAddress(void** p, const void*) { *p = (void*)0x100000; return 0; }
-int hipHostMalloc(void** p, size_t n, unsigned) { ++created; *p = pinned = calloc(1, n); return 0; }
+int hipHostMalloc(void** p, size_t n, unsigned) { if (no_pinned_memory) return 2; ++created; *p = pinned = calloc(1, n); return 0; }
 int hipHostFree(void* p) { free(p); return 0; }
-int hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return 0; }
+int hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = pinned_word = h; return 0; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 0; return 0; }
 }
 static int failures;

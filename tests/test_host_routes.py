@@ -280,3 +280,45 @@ int main(int, char** argv) {
 def test_a_small_net_that_lost_a_pass_says_so_and_does_without_these_kernels(tmp_path, by):
     out = host_hip.run(host_hip.build(tmp_path, LOST), by, LF_CLUSTER="1")
     assert "layer 3, workgroup 7" in out and "run lf_forward again" in out
+
+
+# Every handle has a pinned word of its own, from one page for 1024 of them, and gives it back; without pinned memory the passes
+# of small nets run all the same.
+WORDS = r"""
+#include <algorithm>
+int main() {
+    std::vector<lf_net*> nets;
+    std::vector<void*> words;
+    auto add = [&]() {
+        nets.push_back(make({64, 64, 64, 64, 64, 64}, 8, LF_F32, LF_SCHED_AUTO));
+        pinned_word = nullptr;
+        CHECK(lf_forward(nets.back(), some_input, &caller_1) == LF_OK);
+        CHECK(pinned_word != nullptr && std::find(words.begin(), words.end(), pinned_word) == words.end());
+        words.push_back(pinned_word);
+    };
+    for (int i = 0; i < 1030; ++i) add();
+    CHECK(created == 1 + 6);
+    for (int i = 0; i < 500; ++i) {                       // the ones in the middle go
+        lf_destroy(nets[100]);
+        nets.erase(nets.begin() + 100);
+        words.erase(words.begin() + 100);
+    }
+    for (int i = 0; i < 500; ++i) add();
+    CHECK(created == 1 + 6);
+    for (lf_net* net : nets) lf_destroy(net);
+    nets.clear(); words.clear();
+    for (int i = 0; i < 1024; ++i) add();
+    CHECK(created == 1 + 6);
+    no_pinned_memory = true;
+    lf_net* net = make({64, 64, 64, 64, 64, 64}, 8, LF_F32, LF_SCHED_AUTO);
+    CHECK(lf_forward(net, some_input, &caller_1) == LF_OK);
+    CHECK(lf_backward_leapfrog(net, some_input, 1, &caller_1) == LF_OK);
+    lf_destroy(net);
+    for (lf_net* n : nets) lf_destroy(n);
+    return failures != 0;
+}
+"""
+
+
+def test_handles_share_a_page_of_pinned_words(tmp_path):
+    host_hip.run(host_hip.build(tmp_path, WORDS), LF_CLUSTER="1")
