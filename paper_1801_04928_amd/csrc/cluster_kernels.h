@@ -544,7 +544,7 @@ double steps_us(const ClusterPlan& p, const int* n, int L, bool bf16, bool backw
     }
     return us;
 }
-constexpr double kPrepare = 1.8;                // us of the launch that prepares the words
+constexpr double kPrepare = 1.8;                // us of the launch that prepares the words (and up to half of one a MB)
 
 }  // namespace
 }  // namespace cluster
@@ -588,7 +588,8 @@ ClusterPlan cluster_plan(const int* n, int L, int B, bool bf16) {
     if (std::getenv("LF_GEMM_BIG")) return p;   // (which of the other kernels to take has been asked for)
     // What these kernels and those of one launch a layer take: fitted to 1700 uniform nets, L = 5 .. 64, N = 8 .. 512 (fp32) and 8 .. 1024
     // (bf16), B = 2 .. 32640, and 800 of unequal widths, within 5 to 8 % (root mean square) a side.  By the choice 17 of these nets take more
-    // than 2 % longer than by a launch a layer, and 17 more than 10 % longer than by the better side; those it sends here gain 1.5 times.  us a pass forward / backward, a launch a layer -> here (the preparation with the forward pass), L = 8:
+    // than 2 % longer than by a launch a layer, and 17 more than 10 % longer than by the better side; those it sends here gain 1.5 times.
+    // us a pass forward / backward, a launch a layer -> here (the preparation with the forward pass), L = 8:
     //   fp32  N = 64, B = 32 19 -> 12 / 29 -> 15, B = 8192 145 -> 90 / 400 -> 128;  N = 256, B = 32 21 -> 17 / 31 -> 21, B = 300 27 -> 22 /
     //         43 -> 36, B = 512 29 -> 27 / 55 -> 42, B = 1024 37 -> 47 / 75 -> 70, B = 4096 114 -> 187 / 234 -> 265;  N = 384, B = 32 23 -> 20 /
     //         32 -> 28, B = 256 30 -> 28 / 46 -> 48, B = 512 39 -> 43 / 60 -> 72;  N = 512, B = 32 25 -> 28 / 33 -> 37, B = 256 34 -> 38 / 60 -> 67

@@ -755,8 +755,8 @@ lf_status check_backward_call(lf_net* net, const void* y, int k) {
 
 // What the small nets' kernels work on.  Since the last pass the caller may have used the workspace otherwise, another handle among
 // them, so what the kernels exchange there is prepared by a launch in front of the pass's first (L = 8, N = 256, B = 32 fp32
-// 39.2 us a pass, 37.6 with the state kept from pass to pass, whatever is cleared: the launch is what it costs).  From the forward to
-// the backward pass the workspace holds a^l and is left alone.
+// 39.2 us a pass, 37.6 with the state kept from pass to pass and 39.1 with nothing cleared: the launch is what it costs).  From the
+// forward to the backward pass the workspace holds a^l and is left alone.
 lf::ClusterPass cluster_pass(const lf_net* net, const void* y) {
     const Layout& lay = net->lay;
     lf::ClusterPass p{};
